@@ -220,6 +220,7 @@ hipError_t launch_fwd_generic(const Problem& p, const void* q, const void* k, co
                               const float* wk, const float* wv, const float* bias, void* out,
                               float* lse, hipStream_t st)
 {
+    if (wk && m32_supported(p)) return launch_fwd_m32(p, q, k, v, wk, wv, bias, out, lse, st);
     SLIDE_DISPATCH(launch_fwd_t, p, q, k, v, wk, wv, bias, out, lse, st);
 }
 
@@ -649,6 +650,8 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
         const bool streaming = half_ws && fwd_ring_enabled() && bwd_pixel_ring_supported(p, aligned16({dq}));
         e = launch_bwd_pixel_mfma(p, dout, q, k, v, wk, wv, bias, dq, attn_ws, dl_ws, half_ws, image_ws,
                                   dkdv_image_ws, streaming, st);
+    } else if (m32_supported(p)) {
+        e = launch_bwd_pixel_m32(p, dout, q, k, v, wk, wv, bias, dq, attn_ws, dl_ws, st);
     } else {
         if (few_pixels(p)) {
             dim3 grid8((unsigned)((p.plane() * 8 + 255) / 256), (unsigned)p.heads, (unsigned)p.B);

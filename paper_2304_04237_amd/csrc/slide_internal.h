@@ -70,6 +70,14 @@ hipError_t launch_bwd_generic(const Problem& p, const void* dout, const void* q,
                               void* dq, void* dk, void* dv, float* dwk, float* dwv, float* dbias,
                               void* workspace, hipStream_t st);
 
+// ---- float32 on the matrix cores (slide_mfma32.hip): ksize 3 or 5, any head size, layout and dtype
+bool m32_supported(const Problem& p);
+hipError_t launch_fwd_m32(const Problem& p, const void* q, const void* k, const void* v, const float* wk,
+                          const float* wv, const float* bias, void* out, float* lse, hipStream_t st);
+hipError_t launch_bwd_pixel_m32(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
+                                const float* wk, const float* wv, const float* bias, void* dq, float* a_ws,
+                                float* dl_ws, hipStream_t st);
+
 // forward of heads narrower than 32 channels (bf16, ksize 3, H * W % 8 == 0) through the
 // matrix-core kernels on copies padded to 32 channels per head (p32: the padded problem)
 bool fwd_padded_problem(const Problem& p, Problem& p32);

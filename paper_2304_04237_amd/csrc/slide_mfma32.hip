@@ -1,0 +1,439 @@
+// Float32 Slide Attention on the matrix cores of gfx950, windows of 3 and 5: every head size,
+// width, layout and element type; products, sums and results in float32 like the general kernels
+// of slide_generic.hip, which state the same operator one multiply-add at a time.
+//
+// What bounds these kernels is the learned-kernel contraction, k^2 shifts by k^2 taps per channel
+// and pixel.  v_mfma_f32_4x4x1_16b_f32 with a broadcast left operand (cbsz = 4) is an outer product of
+// four weights with 64 lanes: D[r][lane] += A[4 * abid + r] * B[lane], 256 float32 multiply-adds in
+// 8 cycles (measured 8.4 at 4 waves per SIMD; 143 TFLOP/s).  A lane is a pixel, a register of A
+// holds 64 weights, so the weights come as one coalesced LDS read per 64 of them instead of one
+// scalar load per multiply-add, which is what held the general kernels at 4.6 TFLOP/s.  Of the k^2
+// shifts of a channel k^2 - 1 (8 or 24, a multiple of four) go through the matrix cores and the
+// last one is a vector multiply-add, so no matrix row is padding.
+#include "slide_internal.h"
+#include "slide_device.h"
+#include <utility>
+
+namespace slide {
+namespace m32 {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+template <int KS> struct Dim {
+    static constexpr int S = KS * KS, R = KS / 2;
+    static constexpr int SM = S - 1, SB = SM / 4;           // shifts on the matrix cores, blocks of four of them
+    // the weights of four channels lie in LDS as they do in memory, [channel][shift][tap]; lane l of
+    // operand register j holds weight (tap, channel, shift < SM) number 64 j + l of UT taps
+    static constexpr int UT = KS == 3 ? 3 : 1, UNIT = UT * 4 * SM, WV = (UNIT + 63) / 64;
+    static constexpr int LASTV = (4 * S + 63) / 64;         // registers of the last shift's weights, [tap][channel]
+    static constexpr int QUAD_W = 4 * S * S;
+};
+
+template <int ABID>
+__device__ __forceinline__ f4 outer(float a, float b, f4 c)
+{
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, ABID, 0);
+}
+template <typename F, int... i>
+__device__ __forceinline__ void unroll_over(F&& f, std::integer_sequence<int, i...>)
+{
+    (f(std::integral_constant<int, i>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F&& f) { unroll_over(f, std::make_integer_sequence<int, N>{}); }
+// acc[SB] += A[block FIRST + sb] (outer) b, A in registers of 16 blocks
+template <int FIRST, int SB, int NV>
+__device__ __forceinline__ void outer_blocks(const float (&wv)[NV], float b, f4 (&acc)[SB])
+{
+    unroll<SB>([&](auto i) {
+        constexpr int blk = FIRST + decltype(i)::value;
+        acc[decltype(i)::value] = outer<blk % 16>(wv[blk / 16], b, acc[decltype(i)::value]);
+    });
+}
+__device__ __forceinline__ float lane_of(float x, int lane)
+{
+    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), lane));
+}
+
+// what is derived from x, y and v is formed after this point (keeps the compiler from reading every
+// tap and weight of a channel ahead of the first product)
+template <int N>
+__device__ __forceinline__ void pin(int& x, int& y, float (&v)[N])
+{
+    asm volatile("" : "+v"(x), "+v"(y));
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
+}
+
+// How a plane is cut: column strips of TW (the last one narrower), each flattened row by row and
+// cut into runs of PX pixels, so that nearly every lane has a pixel whatever the map's width.  A run
+// touches NR - 2R rows; LDS holds those rows and the halo, RP = TW + 2R pixels each.
+struct Cut { int TW, ns, runs, NR, RP, npx; };
+
+static Cut plan_cut(int H, int W, int PX, int R, int max_tw)
+{
+    Cut c;
+    c.ns = (W + max_tw - 1) / max_tw;
+    c.TW = (W + c.ns - 1) / c.ns;
+    c.ns = (W + c.TW - 1) / c.TW;
+    c.runs = (int)(((long)H * c.TW + PX - 1) / PX);
+    const int narrow = W - (c.ns - 1) * c.TW;               // the last strip: its runs touch the most rows
+    int rows = (PX - 2) / narrow + 2;
+    if (rows > H) rows = H;
+    c.NR = rows + 2 * R;
+    c.RP = c.TW + 2 * R;
+    c.npx = c.NR * c.RP;
+    return c;
+}
+
+struct PixelArgs {
+    const void* q; const void* k; const void* v; const void* dout;
+    const float* wk; const float* wv; const float* bias;
+    void* out;                  // forward: out; backward: dq
+    float* lse;                 // forward, may be null
+    float* a_ws; float* dl_ws;  // backward: [B, heads, S, H, W]
+    int H, W, C, d;
+    long sc, sp;                // element (b, c, pixel) at b*C*H*W + c*sc + pixel*sp
+    float idw, scale;
+    Cut cut;
+};
+
+// One run of PX = 64 * PG pixels of one head: waves = PG pixel groups x CG channel groups.
+// CQ quads of channels are staged per step (CG waves take CQ / CG of them each); their halo tile
+// lies in LDS as [quad][pixel][4 channels], so a tap is one 16-byte read for four channels (the
+// LDS moves 190 B per cycle and CU that way, 82 in 4-byte reads, measured).  The next step's
+// elements are fetched into registers while the current one is multiplied.  MI355X, against one
+// thread per pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: forward 335 -> 65
+// us, backward 503 -> 94 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 428 us; one
+// 14x14 map of 2 heads, forward: 18.9 -> 10.4 us.
+template <typename T, int KS, int PG, int CG, int CQ, bool BWD>
+__global__ void __launch_bounds__(64 * PG * CG, CG > 1 ? 2 : (KS == 3 ? 4 : 2))
+pixel32_kernel(const PixelArgs a)
+{
+    using D = Dim<KS>;
+    constexpr int S = D::S, SM = D::SM, SB = D::SB, R = D::R;
+    constexpr int NT = 64 * PG * CG, PX = 64 * PG;
+    constexpr int EW = 256, TG = NT / EW, QPT = CQ / TG;    // staging: EW pixels wide, TG quad groups, QPT quads per thread
+    constexpr int NI = 2;                                   // pixels per thread fetched ahead
+    constexpr int NW = (CQ * 4 * S * S + NT - 1) / NT;      // weights per thread
+    constexpr bool AHEAD_W = NW <= 24;
+    static_assert(NT % EW == 0 && CQ % TG == 0 && CQ % CG == 0, "");
+
+    extern __shared__ __align__(16) float smem_raw[];
+    float* const smem = smem_raw;                           // (through a pointer: 16-byte accesses keep their alignment)
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int pg = wave % PG, cg = wave / PG;
+    const int H = a.H, W = a.W, d = a.d;
+    const int m = blockIdx.y, b = blockIdx.z;
+    const long HW = (long)H * W;
+    const int strip = blockIdx.x / a.cut.runs, run = blockIdx.x - strip * a.cut.runs;
+    const int j0 = strip * a.cut.TW;
+    const int tw = min(a.cut.TW, W - j0);
+    const int n0 = run * PX;
+    if (n0 >= H * tw) return;
+    const int npx = a.cut.npx, RP = a.cut.RP;
+    const int row0 = n0 / tw - R;                           // first staged row of the map (may be negative)
+    float* tile = smem;                                     // [CQ][npx][4]
+    float* wl = smem + CQ * npx * 4;                        // [CQ][QUAD_W]
+    float* xl = wl + CQ * D::QUAD_W;                        // [CQ][PX][4]
+
+    // this lane's pixel
+    const int n = n0 + pg * 64 + lane;
+    const bool live = n < H * tw;
+    const int nn = live ? n : H * tw - 1;
+    const int ti = nn / tw, tj = nn - ti * tw;
+    const long pix = (long)ti * W + j0 + tj;
+    const int at = ((ti - row0 - R) * RP + tj) * 4;         // its upper left tap in a tile plane
+
+    const long item = (long)b * a.C * HW + (long)m * d * a.sc;
+    // staging: pixels e = (tid % EW) + i * EW of the tile
+    const int e0 = tid % EW, tg = tid / EW;
+    auto tile_pixel = [&](int e, bool& in) -> long {
+        const int rr = e / RP, xx = e - rr * RP;
+        const int y = row0 + rr, x = j0 + xx - R;
+        in = e < npx && y >= 0 && y < H && x >= 0 && x < W;
+        return in ? ((long)y * W + x) * a.sp : 0;
+    };
+    bool in[NI]; long off[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) off[i] = tile_pixel(e0 + i * EW, in[i]);
+    const int pe = tid % PX, peg = tid / PX;                // staging of x: pixel pe, quads peg, peg + CG, ...
+    long xoff;
+    {
+        const int nx = min(n0 + pe, H * tw - 1);
+        const int xi = nx / tw;
+        xoff = ((long)xi * W + j0 + nx - xi * tw) * a.sp;
+    }
+
+    // channels c..c+3 of the head (past d: the last one again, their weights are zeros)
+    auto load4 = [&](const T* base, long o, int c) -> f4 {
+        f4 r;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = Elem<T>::load(base + o + (long)min(c + u, d - 1) * a.sc);
+        return r;
+    };
+    // this lane's weights (float offsets from a quad's weights, for the operand registers above)
+    int woff[D::WV], loff[D::LASTV];
+#pragma unroll
+    for (int j = 0; j < D::WV; ++j) {
+        const int f = min(j * 64 + lane, D::UNIT - 1);
+        const int tt = f / (4 * SM), r = f - tt * (4 * SM), e = r / SM;
+        woff[j] = e * (S * S) + (r - e * SM) * S + tt;
+    }
+#pragma unroll
+    for (int j = 0; j < D::LASTV; ++j) {
+        const int f = min(j * 64 + lane, 4 * S - 1);
+        loff[j] = (f & 3) * (S * S) + SM * S + (f >> 2);
+    }
+
+    // runs `body(quad, offset of the quad's tile, of its weights, x of this lane)` over this wave's quads
+    auto phase = [&](const void* yp, const void* xp, const float* w, auto&& body) {
+        const T* yb = (const T*)yp + item;
+        const T* xb = xp ? (const T*)xp + item : nullptr;
+        const float* wb = w + (long)m * d * S * S;
+        f4 yr[NI][QPT], xr[CQ / CG];
+        float wr[AHEAD_W ? NW : 1];
+        auto fetch = [&](int c0) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int u = 0; u < QPT; ++u) yr[i][u] = load4(yb, off[i], c0 + 4 * (tg + u * TG));
+            if (xb)
+#pragma unroll
+                for (int u = 0; u < CQ / CG; ++u) xr[u] = load4(xb, xoff, c0 + 4 * (peg + u * CG));
+            if (AHEAD_W)
+#pragma unroll
+                for (int u = 0; u < NW; ++u) {
+                    const int idx = tid + u * NT;
+                    wr[u] = (idx < CQ * 4 * S * S && c0 * S * S + idx < d * S * S) ? wb[c0 * S * S + idx] : 0.0f;
+                }
+        };
+        fetch(0);
+        for (int c0 = 0; c0 < d; c0 += 4 * CQ) {
+            __syncthreads();                                // the step before is no longer read
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int u = 0; u < QPT; ++u)
+                    if (e0 + i * EW < npx) *(f4*)(tile + ((tg + u * TG) * npx + e0 + i * EW) * 4) = in[i] ? yr[i][u] : f4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int e = e0 + NI * EW; e < npx; e += EW) {   // (maps of a few columns, wide windows)
+                bool ok;
+                const long o = tile_pixel(e, ok);
+#pragma unroll
+                for (int u = 0; u < QPT; ++u)
+                    *(f4*)(tile + ((tg + u * TG) * npx + e) * 4) = ok ? load4(yb, o, c0 + 4 * (tg + u * TG)) : f4{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+            if (xb)
+#pragma unroll
+                for (int u = 0; u < CQ / CG; ++u) *(f4*)(xl + ((peg + u * CG) * PX + pe) * 4) = xr[u];
+            if (AHEAD_W) {
+#pragma unroll
+                for (int u = 0; u < NW; ++u)
+                    if (tid + u * NT < CQ * 4 * S * S) wl[tid + u * NT] = wr[u];
+            } else {
+#pragma unroll 4
+                for (int idx = tid; idx < CQ * 4 * S * S; idx += NT)
+                    wl[idx] = c0 * S * S + idx < d * S * S ? wb[c0 * S * S + idx] : 0.0f;
+            }
+            if (a.idw != 0.0f) {                            // the fixed shift path of the two-branch form
+                __syncthreads();
+                for (int i = tid; i < min(CQ * 4, d - c0) * S; i += NT) wl[(i / S) * (S * S) + (i % S) * (S + 1)] += a.idw;
+            }
+            __syncthreads();
+            if (c0 + 4 * CQ < d) fetch(c0 + 4 * CQ);
+#pragma unroll 1
+            for (int u = cg; u < CQ; u += CG) {
+                if (c0 + 4 * u >= d) break;
+                body(c0 + 4 * u, u * npx * 4 + at, CQ * npx * 4 + u * D::QUAD_W, xl + (u * PX + pg * 64 + lane) * 4);
+            }
+        }
+    };
+
+    // sums over shifts: acc[s] += sum over channels and taps of W[c,s,t] x[c] y[c,t]
+    auto contract = [&](const void* yp, const void* xp, const float* w, float (&sum)[S]) {
+        f4 acc[SB];
+        float last = 0.0f;
+#pragma unroll
+        for (int i = 0; i < SB; ++i) acc[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        phase(yp, xp, w, [&](int, int yo, int wo, const float* xq) {
+            const f4 x = *(const f4*)xq;
+            float wv[D::WV], wlast[D::LASTV];
+#pragma unroll
+            for (int j = 0; j < D::LASTV; ++j) wlast[j] = smem[wo + loff[j]];
+            unroll<S>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if (t % KS == 0) pin(yo, wo, wlast);        // (one window row in registers at a time)
+                if (t % D::UT == 0)
+#pragma unroll
+                    for (int j = 0; j < D::WV; ++j) wv[j] = smem[wo + woff[j] + t];
+                const f4 yt = *(const f4*)(smem + yo + ((t / KS) * RP + t % KS) * 4);
+                unroll<4>([&](auto ec) {
+                    constexpr int e = decltype(ec)::value;
+                    const float g = x[e] * yt[e];
+                    outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, g, acc);
+                    last = fmaf(lane_of(wlast[(4 * t + e) / 64], (4 * t + e) % 64), g, last);
+                });
+                asm volatile("" : "+v"(last));
+                if (t % KS == KS - 1) __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+#pragma unroll
+        for (int s = 0; s < SM; ++s) sum[s] = acc[s / 4][s % 4];
+        sum[SM] = last;
+        if (CG > 1) {                                       // the channel groups' shares, added in a fixed order
+            float* red = smem;                              // [CG][S][PX]
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < S; ++s) red[(cg * S + s) * PX + pg * 64 + lane] = sum[s];
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                sum[s] = 0.0f;
+#pragma unroll
+                for (int c = 0; c < CG; ++c) sum[s] += red[(c * S + s) * PX + pg * 64 + lane];
+                asm volatile("" : "+v"(sum[s]) :: "memory");
+            }
+            // (the next phase starts with a barrier before it writes LDS)
+        }
+    };
+    // out[c] = f * sum over shifts of p[s] * (sum over taps of W[c,s,t] y[c,t])
+    auto expand = [&](const void* yp, const float* w, const float (&p)[S], float f) {
+        T* ob = (T*)a.out + item + pix * a.sp;
+        phase(yp, nullptr, w, [&](int c, int yo, int wo, const float*) {
+            f4 acc[4][SB];
+            float last[4];
+            float wv[D::WV], wlast[D::LASTV];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                last[e] = 0.0f;
+#pragma unroll
+                for (int i = 0; i < SB; ++i) acc[e][i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+#pragma unroll
+            for (int j = 0; j < D::LASTV; ++j) wlast[j] = smem[wo + loff[j]];
+            unroll<S>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if (t % KS == 0) pin(yo, wo, wlast);        // (one window row in registers at a time)
+                if (t % D::UT == 0)
+#pragma unroll
+                    for (int j = 0; j < D::WV; ++j) wv[j] = smem[wo + woff[j] + t];
+                const f4 yt = *(const f4*)(smem + yo + ((t / KS) * RP + t % KS) * 4);
+                unroll<4>([&](auto ec) {
+                    constexpr int e = decltype(ec)::value;
+                    outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, yt[e], acc[e]);
+                    last[e] = fmaf(lane_of(wlast[(4 * t + e) / 64], (4 * t + e) % 64), yt[e], last[e]);
+                });
+                asm volatile("" : "+v"(last[0]), "+v"(last[1]), "+v"(last[2]), "+v"(last[3]));
+                if (t % KS == KS - 1) __builtin_amdgcn_sched_barrier(0);
+            });
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float o = p[SM] * last[e];
+#pragma unroll
+                for (int s = 0; s < SM; ++s) o = fmaf(p[s], acc[e][s / 4][s % 4], o);
+                if (live && c + e < d) Elem<T>::store(ob + (long)(c + e) * a.sc, f * o);
+            }
+        });
+    };
+
+    float p[S];
+    contract(a.k, a.q, a.wk, p);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        p[s] = fmaf(a.scale, p[s], a.bias ? a.bias[m * S + s] : 0.0f);
+        mx = fmaxf(mx, p[s]);
+    }
+    float den = 0.0f;
+#pragma unroll
+    for (int s = 0; s < S; ++s) { p[s] = expf(p[s] - mx); den += p[s]; }
+    const float inv = 1.0f / den;
+#pragma unroll
+    for (int s = 0; s < S; ++s) p[s] *= inv;
+    if (!BWD) {
+        if (a.lse && live && cg == 0) a.lse[((long)b * (a.C / d) + m) * HW + pix] = mx + logf(den);
+        expand(a.v, a.wv, p, 1.0f);
+    } else {
+        float da[S];
+        contract(a.v, a.dout, a.wv, da);
+        float dsum = 0.0f;
+#pragma unroll
+        for (int s = 0; s < S; ++s) dsum = fmaf(p[s], da[s], dsum);
+        const long ws = ((long)b * (a.C / d) + m) * S * HW + pix;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            da[s] = p[s] * (da[s] - dsum);
+            if (live && cg == 0) {
+                a.a_ws[ws + (long)s * HW] = p[s];
+                a.dl_ws[ws + (long)s * HW] = da[s];
+            }
+        }
+        expand(a.k, a.wk, da, a.scale);
+    }
+}
+
+template <typename T, int KS, int PG, int CG, int CQ, bool BWD>
+static hipError_t launch_pixel(const Problem& p, PixelArgs& a, hipStream_t st)
+{
+    using D = Dim<KS>;
+    constexpr int PX = 64 * PG;
+    a.cut = plan_cut(p.H, p.W, PX, D::R, 64 - 2 * D::R);
+    size_t lds = (size_t)CQ * (a.cut.npx * 4 + D::QUAD_W + PX * 4) * sizeof(float);
+    const size_t red = CG > 1 ? (size_t)CG * D::S * PX * sizeof(float) : 0;
+    if (lds < red) lds = red;
+    static LdsOptIn opt_in;
+    hipError_t e = opt_in.ensure({(const void*)pixel32_kernel<T, KS, PG, CG, CQ, BWD>}, 160 * 1024);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)(a.cut.ns * a.cut.runs), (unsigned)p.heads, (unsigned)p.B);
+    hipLaunchKernelGGL((pixel32_kernel<T, KS, PG, CG, CQ, BWD>), grid, dim3(64 * PG * CG), lds, st, a);
+    return hipGetLastError();
+}
+
+template <typename T, int KS, bool BWD>
+static hipError_t launch_pixel_t(const Problem& p, PixelArgs& a, hipStream_t st)
+{
+    // blocks of 256 pixels where those give every compute unit two; else 64 pixels whose channels
+    // eight waves share
+    const long blocks = (p.plane() + 255) / 256 * p.heads * p.B;
+    if (blocks >= 512) return launch_pixel<T, KS, 4, 1, KS == 3 ? 2 : 1, BWD>(p, a, st);
+    return launch_pixel<T, KS, 1, 8, 8, BWD>(p, a, st);
+}
+
+static PixelArgs pixel_args(const Problem& p, const void* q, const void* k, const void* v, const float* wk,
+                            const float* wv, const float* bias, void* out)
+{
+    PixelArgs a{};
+    a.q = q; a.k = k; a.v = v; a.wk = wk; a.wv = wv; a.bias = bias; a.out = out;
+    a.H = p.H; a.W = p.W; a.C = p.C; a.d = p.d();
+    a.sc = p.nhwc ? 1 : p.plane(); a.sp = p.nhwc ? p.C : 1;
+    a.idw = p.two_branch ? 1.0f : 0.0f;
+    a.scale = 1.0f / sqrtf((float)p.d());
+    return a;
+}
+
+}  // namespace m32
+
+bool m32_supported(const Problem& p) { return p.ksize == 3 || p.ksize == 5; }
+
+hipError_t launch_fwd_m32(const Problem& p, const void* q, const void* k, const void* v, const float* wk,
+                          const float* wv, const float* bias, void* out, float* lse, hipStream_t st)
+{
+    m32::PixelArgs a = m32::pixel_args(p, q, k, v, wk, wv, bias, out);
+    a.lse = lse;
+    if (p.dtype == 0)
+        return p.ksize == 3 ? m32::launch_pixel_t<float, 3, false>(p, a, st) : m32::launch_pixel_t<float, 5, false>(p, a, st);
+    return p.ksize == 3 ? m32::launch_pixel_t<bf16_bits, 3, false>(p, a, st) : m32::launch_pixel_t<bf16_bits, 5, false>(p, a, st);
+}
+
+hipError_t launch_bwd_pixel_m32(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
+                                const float* wk, const float* wv, const float* bias, void* dq, float* a_ws,
+                                float* dl_ws, hipStream_t st)
+{
+    m32::PixelArgs a = m32::pixel_args(p, q, k, v, wk, wv, bias, dq);
+    a.dout = dout; a.a_ws = a_ws; a.dl_ws = dl_ws;
+    if (p.dtype == 0)
+        return p.ksize == 3 ? m32::launch_pixel_t<float, 3, true>(p, a, st) : m32::launch_pixel_t<float, 5, true>(p, a, st);
+    return p.ksize == 3 ? m32::launch_pixel_t<bf16_bits, 3, true>(p, a, st) : m32::launch_pixel_t<bf16_bits, 5, true>(p, a, st);
+}
+
+}  // namespace slide

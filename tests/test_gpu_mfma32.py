@@ -1,0 +1,85 @@
+"""The float32 matrix-core kernels (windows of 3 and 5): forward, log of the softmax denominator and
+all six gradients against the CPU oracle where their tiling can go wrong: maps of one and two
+columns (runs of pixels that touch hundreds of rows), runs that end inside a row, several column
+strips with a narrower last one, head sizes that are no multiple of four or of a staged step, both
+block shapes (few pixels: channels shared between waves), both layouts, both element types.
+
+Tolerances: float32 1e-5 of the largest entry (the operator's); bfloat16 activations 2e-2 of
+max(1, largest entry) for the rounded outputs, and 1e-5 for the kernel and bias gradients, which
+stay float32 from exact inputs."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2304_04237_amd as sa
+from paper_2304_04237_amd import synth
+from oracle import slide_oracle as oracle
+
+pytestmark = pytest.mark.gpu
+
+GRAD_NAMES = "dq dk dv dwk dwv dbias".split()
+
+SHAPES = [
+    # B, H, W, C, heads, ksize, dtype, channels-last
+    (1, 5, 1, 6, 1, 3, "f32", False), (1, 300, 1, 4, 1, 5, "f32", False), (2, 150, 2, 9, 3, 3, "f32", False),
+    (1, 1, 1, 1, 1, 3, "f32", False), (2, 1, 70, 8, 1, 5, "f32", False), (1, 14, 14, 64, 2, 3, "f32", False),
+    (1, 9, 125, 40, 1, 3, "f32", False), (1, 9, 121, 20, 1, 5, "f32", True), (2, 13, 63, 33, 1, 3, "f32", False),
+    (2, 13, 61, 64, 2, 5, "f32", False), (64, 33, 62, 8, 1, 3, "f32", False), (40, 33, 29, 12, 1, 5, "f32", True),
+    (40, 33, 29, 14, 2, 3, "f32", True), (4, 63, 63, 24, 1, 3, "f32", False), (40, 200, 125, 4, 1, 3, "f32", False), (33, 61, 31, 16, 2, 5, "f32", False),
+    (40, 30, 27, 24, 2, 5, "bf16", False), (1, 28, 28, 64, 2, 5, "bf16", False), (2, 17, 19, 64, 1, 3, "bf16", True),
+    (64, 40, 67, 40, 1, 3, "bf16", False),
+]
+
+
+def _check(name, got, want, tol, floor):
+    got = got.detach().double().cpu().numpy()
+    assert got.shape == want.shape, name
+    err = float(np.abs(got - want).max())
+    bound = tol * max(floor, float(np.abs(want).max()))
+    assert err <= bound, "%s: max abs err %.3e > %.3e" % (name, err, bound)
+
+
+@pytest.mark.parametrize("two_branch", [False, True])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_against_oracle(shape, two_branch):
+    B, H, W, C, heads, ks, dtype, last = shape
+    print("float32 matrix-core case", shape, two_branch, flush=True)
+    dev = torch.device("cuda:0")
+    dd = synth.make_inputs(B, H, W, C, heads, ks, dtype, seed=300 + H + W + C, with_dout=True)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    lay = (lambda t: t.permute(0, 2, 3, 1).contiguous()) if last else (lambda t: t)
+    back = (lambda t: t.permute(0, 3, 1, 2)) if last else (lambda t: t)
+    q, k, v, do = (lay(dd[n].to(dev).to(tdt)) for n in ("q", "k", "v", "dout"))
+    bias = dd["bias"].to(dev)
+    wk_l, wv_l = dd["wk_learned"].to(dev), dd["wv_learned"].to(dev)
+    wk, wv = sa.slide_reparam(wk_l), sa.slide_reparam(wv_l)
+    lse = torch.full((B, heads, H, W), float("nan"), dtype=torch.float32, device=dev)
+    if last:
+        out = sa.slide_attn_fwd_nhwc(q, k, v, wk, wv, bias, heads, ks, lse=lse)
+        w = (wk_l, wv_l) if two_branch else (wk, wv)
+        grads = sa.slide_attn_bwd_nhwc(do, q, k, v, *w, bias, heads, ks, two_branch=two_branch)
+    elif two_branch:
+        out = sa.slide_attn_fwd_two_branch(q, k, v, wk_l, wv_l, bias, heads, ks, lse=lse)
+        grads = sa.slide_attn_bwd_two_branch(do, q, k, v, wk_l, wv_l, bias, heads, ks)
+    else:
+        out = sa.slide_attn_fwd(q, k, v, wk, wv, bias, heads, ks, lse=lse)
+        grads = sa.slide_attn_bwd(do, q, k, v, wk, wv, bias, heads, ks)
+    torch.cuda.synchronize()
+    n = {x: dd[x].double().numpy() for x in ("q", "k", "v", "dout", "bias")}
+    wkn, wvn = wk.double().cpu().numpy(), wv.double().cpu().numpy()
+    ref, ref_lse = oracle.fwd(n["q"], n["k"], n["v"], wkn, wvn, n["bias"], heads, ks, return_lse=True)
+    refg = oracle.bwd(n["dout"], n["q"], n["k"], n["v"], wkn, wvn, n["bias"], heads, ks)
+    exact = dtype == "f32"
+    # planar bf16: window 3 with heads of up to 32 channels, and the forward of window 5 with heads of 32,
+    # run on the half-precision kernels
+    half = not exact and ks == 3 and not last and C // heads <= 32
+    half_fwd = half or (not exact and ks == 5 and not last and C // heads == 32)
+    _check("out", back(out), ref, 1e-5 if exact else 2e-2, 0.0 if exact else 1.0)
+    _check("lse", lse, ref_lse, 1e-5 if not half_fwd else 2e-2, 1.0)
+    for name, got, want in zip(GRAD_NAMES, grads, refg):
+        param = name in ("dwk", "dwv", "dbias")
+        got = got if param else back(got)
+        if exact or (param and not half):
+            _check(name, got, want, 1e-5, 0.0)
+        else:
+            _check(name, got, want, 2e-2, 1.0)
