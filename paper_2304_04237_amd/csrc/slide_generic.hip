@@ -514,10 +514,9 @@ hipError_t launch_bwd_dw_reduce(const float* partial, float* dwk, float* dwv, lo
 static size_t bwd_partial_bytes(const Problem& p)
 {
     size_t part = (size_t)dw_chunks(p) * 2 * (size_t)p.C * p.S() * p.S() * sizeof(float);
-    if (bwd_dw_mfma_supported(p)) {
-        const size_t part2 = bwd_dw_mfma_partial_floats(p) * sizeof(float);
-        if (part2 > part) part = part2;
-    }
+    const size_t floats[] = {bwd_dw_mfma_supported(p) ? bwd_dw_mfma_partial_floats(p) : 0, bwd_dw_m32_partial_floats(p)};
+    for (size_t f : floats)
+        if (f * sizeof(float) > part) part = f * sizeof(float);
     return (part + 15) & ~(size_t)15;
 }
 
@@ -632,12 +631,13 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
                                void* dq, void* dk, void* dv, float* dwk, float* dwv, float* dbias,
                                void* workspace, hipStream_t st)
 {
+    constexpr bool M32 = KS == 3 || KS == 5;    // the general kernels serve the other windows
     const int S = p.S();
     const size_t per = (size_t)p.B * p.heads * S * (size_t)p.plane();
     float* attn_ws = (float*)workspace;
     float* dl_ws = attn_ws + per;
     float* partial = dl_ws + per;
-    dim3 grid((unsigned)((p.plane() + 255) / 256), (unsigned)p.heads, (unsigned)p.B);
+    [[maybe_unused]] dim3 grid((unsigned)((p.plane() + 255) / 256), (unsigned)p.heads, (unsigned)p.B);
     const bool fast = bwd_dkdv_mfma_supported(p) && aligned16({dout, q, k, v, workspace});
     // when all three kernels are matrix-core kernels a and dl cross the workspace as halves
     // (in the first half of the same two regions)
@@ -650,7 +650,7 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
         const bool streaming = half_ws && fwd_ring_enabled() && bwd_pixel_ring_supported(p, aligned16({dq}));
         e = launch_bwd_pixel_mfma(p, dout, q, k, v, wk, wv, bias, dq, attn_ws, dl_ws, half_ws, image_ws,
                                   dkdv_image_ws, streaming, st);
-    } else if (m32_supported(p)) {
+    } else if constexpr (M32) {
         e = launch_bwd_pixel_m32(p, dout, q, k, v, wk, wv, bias, dq, attn_ws, dl_ws, st);
     } else {
         if (few_pixels(p)) {
@@ -672,6 +672,8 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
             e = launch_bwd_dkdv_ring(p, dout, q, attn_ws, dl_ws, dk, dv, image_ws, st);
         else
             e = launch_bwd_dkdv_mfma(p, dout, q, wk, wv, attn_ws, dl_ws, half_ws, dk, dv, image_ws, st);
+    } else if constexpr (M32) {
+        e = launch_bwd_dkdv_m32(p, dout, q, wk, wv, attn_ws, dl_ws, dk, dv, st);
     } else {
         if (few_pixels(p)) {
             dim3 grid8((unsigned)((p.plane() * 8 + 255) / 256), (unsigned)p.heads, (unsigned)p.B);
@@ -689,22 +691,26 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
         // kernel and bias gradients on the matrix cores
         return launch_bwd_dw_mfma(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
     }
-    const int n_chunks = dw_chunks(p);
-    const long n_items = (long)p.B * p.plane();
-    const long per_chunk = (n_items + n_chunks - 1) / n_chunks;
-    hipLaunchKernelGGL((bwd_dw_partial_kernel<T, KS>), dim3((unsigned)(p.C * S), (unsigned)n_chunks),
-                       dim3(256), 0, st,
-                       (const T*)dout, (const T*)q, (const T*)k, (const T*)v, attn_ws, dl_ws,
-                       partial, p.B, p.H, p.W, p.C, p.heads, per_chunk);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const long side = (long)p.C * S * S;
-    e = launch_bwd_dw_reduce(partial, dwk, dwv, side, n_chunks, nullptr, nullptr, 0, p.accumulate, st);
-    if (e != hipSuccess) return e;
-    if (dbias)
-        hipLaunchKernelGGL(bwd_dbias_kernel, dim3((unsigned)(p.heads * S)), dim3(256), 0, st,
-                           dl_ws, dbias, p.B, p.plane(), p.heads, S, p.accumulate);
-    return hipGetLastError();
+    if constexpr (M32) {
+        return launch_bwd_dw_m32(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
+    } else {
+        const int n_chunks = dw_chunks(p);
+        const long n_items = (long)p.B * p.plane();
+        const long per_chunk = (n_items + n_chunks - 1) / n_chunks;
+        hipLaunchKernelGGL((bwd_dw_partial_kernel<T, KS>), dim3((unsigned)(p.C * S), (unsigned)n_chunks),
+                           dim3(256), 0, st,
+                           (const T*)dout, (const T*)q, (const T*)k, (const T*)v, attn_ws, dl_ws,
+                           partial, p.B, p.H, p.W, p.C, p.heads, per_chunk);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const long side = (long)p.C * S * S;
+        e = launch_bwd_dw_reduce(partial, dwk, dwv, side, n_chunks, nullptr, nullptr, 0, p.accumulate, st);
+        if (e != hipSuccess) return e;
+        if (dbias)
+            hipLaunchKernelGGL(bwd_dbias_kernel, dim3((unsigned)(p.heads * S)), dim3(256), 0, st,
+                               dl_ws, dbias, p.B, p.plane(), p.heads, S, p.accumulate);
+        return hipGetLastError();
+    }
 }
 
 int bwd_variant(const Problem& p, bool all_aligned16)

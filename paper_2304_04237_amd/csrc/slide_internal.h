@@ -77,6 +77,13 @@ hipError_t launch_fwd_m32(const Problem& p, const void* q, const void* k, const 
 hipError_t launch_bwd_pixel_m32(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
                                 const float* wk, const float* wv, const float* bias, void* dq, float* a_ws,
                                 float* dl_ws, hipStream_t st);
+// (slide_mfma32_bwd.hip) key and value gradients; kernel and bias gradients with their reduction
+hipError_t launch_bwd_dkdv_m32(const Problem& p, const void* dout, const void* q, const float* wk, const float* wv,
+                               const float* attn_ws, const float* dl_ws, void* dk, void* dv, hipStream_t st);
+size_t bwd_dw_m32_partial_floats(const Problem& p);
+hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
+                             const float* attn_ws, const float* dl_ws, float* partial, float* dwk, float* dwv,
+                             float* dbias, hipStream_t st);
 
 // forward of heads narrower than 32 channels (bf16, ksize 3, H * W % 8 == 0) through the
 // matrix-core kernels on copies padded to 32 channels per head (p32: the padded problem)

@@ -10,81 +10,10 @@
 // scalar load per multiply-add, which is what held the general kernels at 4.6 TFLOP/s.  Of the k^2
 // shifts of a channel k^2 - 1 (8 or 24, a multiple of four) go through the matrix cores and the
 // last one is a vector multiply-add, so no matrix row is padding.
-#include "slide_internal.h"
-#include "slide_device.h"
-#include <utility>
+#include "slide_mfma32.h"
 
 namespace slide {
 namespace m32 {
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-template <int KS> struct Dim {
-    static constexpr int S = KS * KS, R = KS / 2;
-    static constexpr int SM = S - 1, SB = SM / 4;           // shifts on the matrix cores, blocks of four of them
-    // the weights of four channels lie in LDS as they do in memory, [channel][shift][tap]; lane l of
-    // operand register j holds weight (tap, channel, shift < SM) number 64 j + l of UT taps
-    static constexpr int UT = KS == 3 ? 3 : 1, UNIT = UT * 4 * SM, WV = (UNIT + 63) / 64;
-    static constexpr int LASTV = (4 * S + 63) / 64;         // registers of the last shift's weights, [tap][channel]
-    static constexpr int QUAD_W = 4 * S * S;
-};
-
-template <int ABID>
-__device__ __forceinline__ f4 outer(float a, float b, f4 c)
-{
-    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, ABID, 0);
-}
-template <typename F, int... i>
-__device__ __forceinline__ void unroll_over(F&& f, std::integer_sequence<int, i...>)
-{
-    (f(std::integral_constant<int, i>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void unroll(F&& f) { unroll_over(f, std::make_integer_sequence<int, N>{}); }
-// acc[SB] += A[block FIRST + sb] (outer) b, A in registers of 16 blocks
-template <int FIRST, int SB, int NV>
-__device__ __forceinline__ void outer_blocks(const float (&wv)[NV], float b, f4 (&acc)[SB])
-{
-    unroll<SB>([&](auto i) {
-        constexpr int blk = FIRST + decltype(i)::value;
-        acc[decltype(i)::value] = outer<blk % 16>(wv[blk / 16], b, acc[decltype(i)::value]);
-    });
-}
-__device__ __forceinline__ float lane_of(float x, int lane)
-{
-    return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), lane));
-}
-
-// what is derived from x, y and v is formed after this point (keeps the compiler from reading every
-// tap and weight of a channel ahead of the first product)
-template <int N>
-__device__ __forceinline__ void pin(int& x, int& y, float (&v)[N])
-{
-    asm volatile("" : "+v"(x), "+v"(y));
-#pragma unroll
-    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
-}
-
-// How a plane is cut: column strips of TW (the last one narrower), each flattened row by row and
-// cut into runs of PX pixels, so that nearly every lane has a pixel whatever the map's width.  A run
-// touches NR - 2R rows; LDS holds those rows and the halo, RP = TW + 2R pixels each.
-struct Cut { int TW, ns, runs, NR, RP, npx; };
-
-static Cut plan_cut(int H, int W, int PX, int R, int max_tw)
-{
-    Cut c;
-    c.ns = (W + max_tw - 1) / max_tw;
-    c.TW = (W + c.ns - 1) / c.ns;
-    c.ns = (W + c.TW - 1) / c.TW;
-    c.runs = (int)(((long)H * c.TW + PX - 1) / PX);
-    const int narrow = W - (c.ns - 1) * c.TW;               // the last strip: its runs touch the most rows
-    int rows = (PX - 2) / narrow + 2;
-    if (rows > H) rows = H;
-    c.NR = rows + 2 * R;
-    c.RP = c.TW + 2 * R;
-    c.npx = c.NR * c.RP;
-    return c;
-}
 
 struct PixelArgs {
     const void* q; const void* k; const void* v; const void* dout;

@@ -1,0 +1,618 @@
+// Float32 key, value, kernel and bias gradients on the matrix cores of gfx950, windows of 3 and 5:
+// every head size, width and element type; products, sums and results in float32 like the
+// general kernels of slide_generic.hip.  Both kernels are bound by the learned-kernel contraction and
+// run it as outer products of four weights with 64 lanes (slide_mfma32.hip says how).
+#include "slide_mfma32.h"
+
+namespace slide {
+namespace m32 {
+
+// ---- key and value gradients
+//   dk[c,y] = scale * sum_t q[c, y - off(t)] * sum_s wk[c,s,t] dl[s, y - off(t)]
+//   dv[c,y] =         sum_t dO[c, y - off(t)] * sum_s wv[c,s,t] a[s, y - off(t)]
+struct DkdvArgs {
+    const void* x[2];           // q, dO
+    const float* w[2];          // wk, wv
+    const float* p[2];          // dl, a: [B, heads, S, H, W]
+    void* out[2];               // dk, dv
+    float f[2];                 // logit scale, 1
+    int H, W, C, d;
+    float idw;
+    Cut cut;
+};
+
+// One run of PX = 64 * PG pixels of one head and side: waves = PG pixel groups x CG channel groups.
+// A lane is a pixel y; for one tap after the other it holds the S values of a (or dl) at
+// y - off(t), and the matrix cores form the sums over s for four channels at a time (rows = channels,
+// K = s: no padding), which are then multiplied with the four channels of dO (or q) at y - off(t).
+// LDS holds a (or dl) of the run's rows and halo as planes, NQ quads of channels of dO (or q) as
+// [quad][pixel][4] and their kernels.  A tap costs S 4-byte LDS reads per lane whatever the number of
+// quads, so NQ is as large as two blocks per compute unit allow.  MI355X, against one thread per
+// pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: 846 -> 65 us; bf16, 5x5, B=64,
+// 28x28, C=128, 4 heads: 4855 -> 368 us.
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+    typedef f4 Raw;
+    static __device__ __forceinline__ Raw load(const float* b, long o, long sc, int c, int d)
+    {
+        Raw r;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r[u] = b[o + (long)min(c + u, d - 1) * sc];
+        return r;
+    }
+    static __device__ __forceinline__ f4 value(Raw r) { return r; }
+    static __device__ __forceinline__ Raw zero() { return f4{0.0f, 0.0f, 0.0f, 0.0f}; }
+};
+template <> struct Quad<bf16_bits> {
+    typedef uint32_t Raw __attribute__((ext_vector_type(2)));
+    static __device__ __forceinline__ Raw load(const bf16_bits* b, long o, long sc, int c, int d)
+    {
+        uint32_t h[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) h[u] = b[o + (long)min(c + u, d - 1) * sc];
+        return Raw{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+    }
+    static __device__ __forceinline__ f4 value(Raw r)
+    {
+        return f4{__uint_as_float(r[0] << 16), __uint_as_float(r[0] & 0xffff0000u),
+                  __uint_as_float(r[1] << 16), __uint_as_float(r[1] & 0xffff0000u)};
+    }
+    static __device__ __forceinline__ Raw zero() { return Raw{0u, 0u}; }
+};
+
+template <typename T, int KS, int PG, int CG, int NQ>
+__global__ void __launch_bounds__(64 * PG * CG, 2)
+dkdv32_kernel(const DkdvArgs a)
+{
+    using D = Dim<KS>;
+    using Raw = typename Quad<T>::Raw;
+    constexpr int S = D::S, R = D::R;
+    constexpr int NT = 64 * PG * CG, PX = 64 * PG;
+    constexpr int NW = NQ / CG;                             // quads per wave
+    constexpr int WR = (4 * S + 63) / 64;                   // operand registers of one quad and tap
+    static_assert(NQ % CG == 0, "");
+
+    extern __shared__ __align__(16) float smem_raw[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int pg = wave % PG, cg = wave / PG;
+    const int H = a.H, W = a.W, d = a.d;
+    const int m = blockIdx.y, side = blockIdx.x & 1, b = blockIdx.z;
+    const long HW = (long)H * W;
+    const int strip = (blockIdx.x >> 1) / a.cut.runs, run = (blockIdx.x >> 1) - strip * a.cut.runs;
+    const int j0 = strip * a.cut.TW;
+    const int tw = min(a.cut.TW, W - j0);
+    const int n0 = run * PX;
+    if (n0 >= H * tw) return;
+    const int npx = a.cut.npx, RP = a.cut.RP;
+    const int row0 = n0 / tw - R;
+    Raw* xl = (Raw*)smem_raw;                               // [NQ][npx]
+    float* pl = (float*)(xl + NQ * npx);                    // [S][npx]
+    float* wl = pl + S * npx;                               // [NQ][QUAD_W]
+
+    const int n = n0 + pg * 64 + lane;
+    const bool live = n < H * tw;
+    const int nn = live ? n : H * tw - 1;
+    const int ti = nn / tw, tj = nn - ti * tw;
+    const long pix = (long)ti * W + j0 + tj;
+    const int at = (ti - row0) * RP + tj + R;               // its own place in a tile plane
+    const long item = ((long)b * a.C + (long)m * d) * HW;
+    const T* xb = (const T*)a.x[side] + item;
+    const float* pb = a.p[side] + ((long)b * (a.C / d) + m) * S * HW;
+    const float* wb = a.w[side] + (long)m * d * S * S;
+    T* ob = (T*)a.out[side] + item + pix;
+    const float f = a.f[side];
+
+    auto tile_pixel = [&](int e, bool& in) -> long {
+        const int rr = e / RP, xx = e - rr * RP;
+        const int y = row0 + rr, x = j0 + xx - R;
+        in = y >= 0 && y < H && x >= 0 && x < W;
+        return in ? (long)y * W + x : 0;
+    };
+    for (int e = tid; e < npx; e += NT) {
+        bool in;
+        const long o = tile_pixel(e, in);
+        float v[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) v[s] = pb[(long)s * HW + o];
+#pragma unroll
+        for (int s = 0; s < S; ++s) pl[s * npx + e] = in ? v[s] : 0.0f;
+    }
+    int woff[WR];                                           // lane l: channel l & 3, shift l >> 2
+#pragma unroll
+    for (int j = 0; j < WR; ++j) {
+        const int l = min(j * 64 + lane, 4 * S - 1);
+        woff[j] = (l & 3) * (S * S) + (l >> 2) * S;
+    }
+
+    for (int c0 = 0; c0 < d; c0 += 4 * NQ) {
+        if (c0 > 0) __syncthreads();                        // the step before is no longer read
+        for (int e = tid; e < npx; e += NT) {
+            bool in;
+            const long o = tile_pixel(e, in);
+            Raw v[NQ];
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) v[u] = Quad<T>::load(xb, o, HW, c0 + 4 * u, d);
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) xl[u * npx + e] = in ? v[u] : Quad<T>::zero();
+        }
+        const int nw = min(4 * NQ, d - c0) * S * S;
+#pragma unroll 4
+        for (int idx = tid; idx < NQ * D::QUAD_W; idx += NT) {
+            float w = idx < nw ? wb[(long)c0 * S * S + idx] : 0.0f;
+            // the fixed shift path of the two-branch form: shift t reads tap t
+            if (a.idw != 0.0f && idx % (S * S) % (S + 1) == 0) w += a.idw;
+            wl[idx] = w;
+        }
+        __syncthreads();
+
+        f4 acc[NW];
+#pragma unroll
+        for (int u = 0; u < NW; ++u) acc[u] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        float p[S], pn[S];
+        int src = at + R * RP + R;                          // y - off(0)
+#pragma unroll
+        for (int s = 0; s < S; ++s) p[s] = pl[s * npx + src];
+#pragma unroll 1
+        for (int t = 0; t < S; ++t) {
+            const int next = t + 1 < S ? (((t + 1) % KS) ? src - 1 : src - RP + (KS - 1)) : src;
+#pragma unroll
+            for (int s = 0; s < S; ++s) pn[s] = pl[s * npx + next];
+#pragma unroll
+            for (int u = 0; u < NW; ++u) {
+                const int qd = cg + u * CG;
+                float wv[WR];
+#pragma unroll
+                for (int j = 0; j < WR; ++j) wv[j] = wl[qd * D::QUAD_W + woff[j] + t];
+                const f4 x = Quad<T>::value(xl[qd * npx + src]);
+                f4 ck = {0.0f, 0.0f, 0.0f, 0.0f};
+                unroll<S>([&](auto sc) {
+                    constexpr int s = decltype(sc)::value;
+                    ck = outer<s % 16>(wv[s / 16], p[s], ck);
+                });
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[u][e] = fmaf(ck[e], x[e], acc[u][e]);
+            }
+            src = next;
+#pragma unroll
+            for (int s = 0; s < S; ++s) p[s] = pn[s];
+        }
+        if (live) {
+#pragma unroll
+            for (int u = 0; u < NW; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int c = c0 + 4 * (cg + u * CG) + e;
+                    if (c < d) Elem<T>::store(ob + (long)c * HW, f * acc[u][e]);
+                }
+        }
+    }
+}
+
+template <typename T, int KS, int PG, int CG, int NQ>
+static size_t dkdv_lds(const Cut& c)
+{
+    return (size_t)c.npx * (NQ * sizeof(typename Quad<T>::Raw) + Dim<KS>::S * sizeof(float)) + (size_t)NQ * Dim<KS>::QUAD_W * sizeof(float);
+}
+template <typename T, int KS, int PG, int CG, int NQ>
+static hipError_t launch_dkdv(const Problem& p, DkdvArgs& a, hipStream_t st)
+{
+    static LdsOptIn opt_in;
+    hipError_t e = opt_in.ensure({(const void*)dkdv32_kernel<T, KS, PG, CG, NQ>}, 160 * 1024);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)(2 * a.cut.ns * a.cut.runs), (unsigned)p.heads, (unsigned)p.B);
+    const size_t lds = dkdv_lds<T, KS, PG, CG, NQ>(a.cut);
+    hipLaunchKernelGGL((dkdv32_kernel<T, KS, PG, CG, NQ>), grid, dim3(64 * PG * CG), lds, st, a);
+    return hipGetLastError();
+}
+template <typename T, int KS>
+static hipError_t launch_dkdv_t(const Problem& p, DkdvArgs& a, hipStream_t st)
+{
+    // blocks of 256 pixels where those give every compute unit two and two fit its LDS (maps of a
+    // few columns have tall runs with much halo); else 64 pixels whose channels four waves share
+    constexpr int NQ = KS == 3 ? (sizeof(T) == 2 ? 8 : 4) : (sizeof(T) == 2 ? 2 : 1);
+    const long blocks = (p.plane() + 255) / 256 * p.heads * 2 * p.B;
+    a.cut = plan_cut(p.H, p.W, 256, Dim<KS>::R, 64 - 2 * Dim<KS>::R);
+    if (blocks >= 512 && dkdv_lds<T, KS, 4, 1, NQ>(a.cut) <= 80 * 1024) return launch_dkdv<T, KS, 4, 1, NQ>(p, a, st);
+    a.cut = plan_cut(p.H, p.W, 64, Dim<KS>::R, 64 - 2 * Dim<KS>::R);
+    return launch_dkdv<T, KS, 1, 4, (KS == 3 ? 8 : 4)>(p, a, st);
+}
+
+// ---- kernel and bias gradients
+//   dwk[c,s,t] = scale * sum over items and pixels y of dl[s,y] * q[c,y] * k[c, y + off(t)]
+//   dwv[c,s,t] =                                        a[s,y] * dO[c,y] * v[c, y + off(t)]
+//   dbias[s]   =                                       dl[s,y]
+struct DwArgs {
+    const void* y[2]; const void* x[2];     // k, v; q, dO
+    const float* p[2];                      // dl, a: [B, heads, S, H, W]
+    float* partial;                         // [chunks][2][C][S][S]
+    float* bias_partial;                    // [chunks][heads][S]
+    float f[2];
+    int H, W, C, d, heads;
+    int TR, TC, ntr, ntc;                   // tiles of TR rows and TC columns
+    long tiles;                             // all of them, over the batch
+    int chunks;
+    int KST, QST;                           // floats per channel of the y and x tiles in LDS
+};
+
+constexpr int DW_CH = 32;                   // channels per block
+constexpr int DW_ZEROS = 160;               // as many as the taps of a quad span: 4 * 36 + 8
+
+template <typename T> struct Vec4;
+template <> struct Vec4<float> {
+    static __device__ __forceinline__ f4 load(const float* p) { return *(const f4*)p; }
+};
+template <> struct Vec4<bf16_bits> {
+    static __device__ __forceinline__ f4 load(const bf16_bits* p) { return Quad<bf16_bits>::value(*(const Quad<bf16_bits>::Raw*)p); }
+};
+
+// One block sums 32 channels of a head and one side over its chunk of tiles.  A lane is a channel, its
+// half of the wave one of two walkers over the tile's quads of four pixels; per pixel the products
+// x * y of the taps are formed once and the matrix cores multiply them with S - 1 shifts' dl (or a),
+// four rows at a time, broadcast inside a half (cbsz = 3); the last shift is a vector
+// multiply-add.  The S^2 sums of a channel stay in registers: all 81 of a 3x3 window in
+// each of the four waves, which share the pixels; with a 5x5 window a wave holds six taps and the
+// four waves see the same pixels (tap 24 is dealt out by blocks of shifts).  MI355X, against one block
+// per channel and shift (slide_generic.hip) and a launch of its own for dbias: float32, 3x3, B=32,
+// 56x56, C=64, 2 heads: 598 -> 100 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: 6875 -> 226 us; bf16, 3x3,
+// B=128, 28x28, C=128, 4 heads: 1854 -> 160 us.
+template <typename T, int KS, bool VEC>
+__global__ void __launch_bounds__(256, 2)
+dw32_kernel(const DwArgs a)
+{
+    using D = Dim<KS>;
+    constexpr int S = D::S, SM = D::SM, SB = D::SB, R = D::R;
+    constexpr int ROLES = KS == 3 ? 1 : 4, NTAP = KS == 3 ? 9 : 6;
+    constexpr bool EXTRA = KS == 5;                         // tap 24: two blocks of shifts in each of waves 0..2
+    constexpr int WALK = 8 / ROLES;
+    constexpr int AR = 4 * SM / 32;                         // registers of the four pixels' shifts
+    constexpr int AQ = 4 * SM + 1;                          // floats per quad in LDS (odd: the quads' writes spread over the banks)
+
+    extern __shared__ __align__(16) float smem_raw[];
+    float* const smem = smem_raw;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int role = wave % ROLES, half = lane >> 5, ch = lane & 31;
+    const int walker = (wave / ROLES) * 2 + half;
+    const int H = a.H, W = a.W, d = a.d, TR = a.TR, TC = a.TC;
+    // blocks of one chunk are neighbours: they read the same a (or dl)
+    const int m = blockIdx.y, side = blockIdx.x & 1;
+    const int ncb = (d + DW_CH - 1) / DW_CH;
+    const int chunk = (blockIdx.x >> 1) / ncb, cb = (blockIdx.x >> 1) - chunk * ncb;
+    const long HW = (long)H * W;
+    const int RS = TC + 2 * R;
+    float* yl = smem;                                       // [32][KST]: [TR + 2R][RS]
+    float* xl = yl + DW_CH * a.KST;                         // [32][QST]: [TR][TC]
+    float* ll = xl + DW_CH * a.QST;                         // last shift [quad][4]; 32 * (KST + QST) is a multiple of 4
+    float* zl = ll + TR * TC;                               // [DW_ZEROS] zeros
+    float* al = zl + DW_ZEROS;                              // [quad][AQ]: pixel x shift
+    const T* yb = (const T*)a.y[side];
+    const T* xb = (const T*)a.x[side];
+    const float* pb = a.p[side];
+
+    f4 acc[NTAP][SB];
+    float last[NTAP];
+#pragma unroll
+    for (int i = 0; i < NTAP; ++i) {
+        last[i] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < SB; ++s) acc[i][s] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    f4 xacc[2] = {f4{0.0f, 0.0f, 0.0f, 0.0f}, f4{0.0f, 0.0f, 0.0f, 0.0f}};
+    float xlast = 0.0f;
+    float bsum[AR], blast = 0.0f;
+#pragma unroll
+    for (int j = 0; j < AR; ++j) bsum[j] = 0.0f;
+    int toff[NTAP];
+#pragma unroll
+    for (int i = 0; i < NTAP; ++i) {
+        const int t = role * NTAP + i;
+        toff[i] = (t / KS) * RS + t % KS;
+    }
+
+    if (tid < DW_ZEROS) zl[tid] = 0.0f;
+    // staging: eight lanes per channel, one column quad each
+    const int sch = tid >> 3, sq = tid & 7;
+    const bool sc_live = cb * DW_CH + sch < d;
+    const long chan = (long)m * d + min(cb * DW_CH + sch, d - 1);
+
+    const long t0 = a.tiles * chunk / a.chunks, t1 = a.tiles * (chunk + 1) / a.chunks;
+    for (long tile = t0; tile < t1; ++tile) {
+        const long b = tile / (a.ntr * a.ntc);
+        const int tr_ = (int)(tile - b * (a.ntr * a.ntc));
+        const int ty = tr_ / a.ntc, tx = tr_ - ty * a.ntc;
+        const int y0 = ty * TR, x0 = tx * TC;
+        const int th = min(TR, H - y0), tw = min(TC, W - x0);
+        const int qpr = (tw + 3) >> 2, nq = th * qpr;
+        __syncthreads();                                    // the tile before is no longer read
+        {
+            const T* yc = yb + (b * a.C + chan) * HW;
+            const T* xc = xb + (b * a.C + chan) * HW;
+            auto quad4 = [&](const T* base, int y, int x, bool ok) -> f4 {  // pixels x..x+3 of row y, zero outside the map
+                f4 r = {0.0f, 0.0f, 0.0f, 0.0f};
+                if (VEC) {
+                    if (ok) r = Vec4<T>::load(base + (long)y * W + x);      // (W % 4 == 0: a quad is whole)
+                } else {
+                    const long row = ok ? (long)y * W : 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool in = ok && x + e < W;
+                        const float v = Elem<T>::load(base + (in ? row + x + e : 0));
+                        r[e] = in ? v : 0.0f;
+                    }
+                }
+                return r;
+            };
+            constexpr int NB = 6;
+            for (int r0 = 0; r0 < th + 2 * R; r0 += NB) {
+                f4 v[NB];
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    const int y = y0 + r0 + i - R;
+                    v[i] = quad4(yc, y, x0 + 4 * sq, sc_live && sq < qpr && r0 + i < th + 2 * R && y >= 0 && y < H);
+                }
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    if (sq < qpr && r0 + i < th + 2 * R) {
+                        float* o = yl + sch * a.KST + (r0 + i) * RS + R + 4 * sq;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = v[i][e];
+                    }
+            }
+            for (int r0 = 0; r0 < th; r0 += NB) {
+                f4 v[NB];
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    v[i] = quad4(xc, y0 + r0 + i, x0 + 4 * sq, sc_live && sq < qpr && r0 + i < th);
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    if (sq < qpr && r0 + i < th) {
+                        float* o = xl + sch * a.QST + (r0 + i) * TC + 4 * sq;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = v[i][e];
+                    }
+            }
+            // the R columns on each side of the tile's 4 * qpr
+            constexpr int HL = 2 * R, RPI = 8 / HL;
+            for (int r = sq / HL; r < th + 2 * R; r += RPI) {
+                const int h = sq % HL;
+                const int y = y0 + r - R;
+                const int col = h < R ? h : 4 * qpr + h;    // column of the LDS row
+                const int x = x0 + col - R;
+                const bool in = sc_live && y >= 0 && y < H && x >= 0 && x < W;
+                const float v = Elem<T>::load(yc + (in ? (long)y * W + x : 0));
+                yl[sch * a.KST + r * RS + col] = in ? v : 0.0f;
+            }
+            const float* pc = pb + (b * a.heads + m) * S * HW;
+            const int np = S * th;
+            for (int i0 = 0; i0 < np; i0 += 32) {
+                const int i = i0 + sch;
+                const int s = i / th, r = i - s * th;
+                if (i < np && sq < qpr) {
+                    const float* g = pc + (long)s * HW + (long)(y0 + r) * W + x0 + 4 * sq;
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = 4 * sq + e < tw ? g[e] : 0.0f;
+                    const int q = r * qpr + sq;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (s < SM) al[q * AQ + e * SM + s] = v[e];
+                        else ll[q * 4 + e] = v[e];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+
+        const uint32_t inv = (65536u + qpr - 1) / qpr;      // qi / qpr for qi < 256 (qpr <= 8)
+        for (int q0 = 0; q0 < nq; q0 += WALK) {
+            const int qi = min(q0 + walker, nq - 1);
+            const bool mine = q0 + walker < nq;
+            const int row = (int)((qi * inv) >> 16), qx = qi - row * qpr;
+            const int live = mine ? min(4, tw - 4 * qx) : 0;    // pixels of the quad
+            // (products of pixels that are none must be zeros also where a neighbour is infinite: rows that
+            // are no whole quads are masked, a walker past the last quad reads zeros)
+            const float* yq = VEC && !mine ? zl : yl + ch * a.KST + row * RS + 4 * qx;
+            const float* xq = VEC && !mine ? zl : xl + ch * a.QST + row * TC + 4 * qx;
+            float A[AR];
+#pragma unroll
+            for (int j = 0; j < AR; ++j) {
+                const float v = al[qi * AQ + j * 32 + ch];
+                A[j] = mine ? v : 0.0f;
+                bsum[j] += A[j];
+            }
+            f4 L = *(const f4*)(ll + qi * 4);
+            if (!mine) L = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            blast += ch < 4 ? L[ch & 3] : 0.0f;
+            float A2 = 0.0f;
+            if (EXTRA) {
+                const float v = al[qi * AQ + (ch >> 3) * SM + min(role * 8, SM - 8) + (ch & 7)];
+                A2 = mine ? v : 0.0f;
+            }
+            float x[4], y[NTAP][4], ye[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = xq[e];
+            if (KS == 3) {
+                float w[3][6];
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) w[r][c] = yq[r * RS + c];
+#pragma unroll
+                for (int i = 0; i < NTAP; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[i][e] = w[(i / 3) % 3][i % 3 + e];
+            } else {
+#pragma unroll
+                for (int i = 0; i < NTAP; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[i][e] = yq[toff[i] + e];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ye[e] = yq[4 * RS + 4 + e];
+            }
+            unroll<4>([&](auto ec) {
+                constexpr int e = decltype(ec)::value;
+                unroll<NTAP>([&](auto ic) {
+                    constexpr int i = decltype(ic)::value;
+                    float g = x[e] * y[i][e];
+                    if (!VEC) g = e < live ? g : 0.0f;
+                    unroll<SB>([&](auto sc) {
+                        constexpr int blk = e * SB + decltype(sc)::value;
+                        acc[i][decltype(sc)::value] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[blk / 8], g, acc[i][decltype(sc)::value], 3, blk % 8, 0);
+                    });
+                    last[i] = fmaf(L[e], g, last[i]);
+                });
+                if (EXTRA) {
+                    float g = x[e] * ye[e];
+                    if (!VEC) g = e < live ? g : 0.0f;
+                    xacc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, g, xacc[0], 3, e * 2, 0);
+                    xacc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, g, xacc[1], 3, e * 2 + 1, 0);
+                    xlast = fmaf(L[e], g, xlast);
+                }
+            });
+        }
+    }
+
+    // the two walkers of a wave, then (3x3) the four waves in order, through LDS [channel][s][t]
+    float* red = smem;                                      // [32][S * S]
+    const float f = a.f[side];
+    auto fold = [&](float v) { return v + __shfl_xor(v, 32); };
+    __syncthreads();
+#pragma unroll 1
+    for (int w = 0; w < (KS == 3 ? 4 : 1); ++w) {
+        if (KS == 5 || wave == w) {
+            auto put = [&](int s, int t, float v) {
+                v = fold(v);
+                if (half == 0) {
+                    float* o = red + ch * (S * S) + s * S + t;
+                    *o = (KS == 3 && w > 0) ? *o + v : v;
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < NTAP; ++i) {
+#pragma unroll
+                for (int s = 0; s < SM; ++s) put(s, role * NTAP + i, acc[i][s / 4][s % 4]);
+                put(SM, role * NTAP + i, last[i]);
+            }
+            if (EXTRA) {
+                if (role < 3) {
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) put(role * 8 + s, 24, xacc[s / 4][s % 4]);
+                } else {
+                    put(SM, 24, xlast);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    const int nch = min(DW_CH, d - cb * DW_CH);
+    float* out = a.partial + (((long)chunk * 2 + side) * a.C + (long)m * d + cb * DW_CH) * S * S;
+    for (int i = tid; i < nch * S * S; i += 256) out[i] = f * red[i];
+
+    if (side == 0 && cb == 0 && a.bias_partial) {
+        __syncthreads();
+        // [wave][half][pixel x shift], then the last shift's four pixels
+        constexpr int BW = 4 * SM + 4;
+        float* bl = smem + (wave * 2 + half) * BW;
+#pragma unroll
+        for (int j = 0; j < AR; ++j) bl[j * 32 + ch] = bsum[j];
+        if (ch < 4) bl[4 * SM + ch] = blast;
+        __syncthreads();
+        if (tid < S) {
+            float sum = 0.0f;
+            for (int w = 0; w < (KS == 3 ? 8 : 2); ++w)     // (5x5: the waves saw the same pixels)
+                for (int e = 0; e < 4; ++e) sum += smem[w * BW + (tid < SM ? e * SM + tid : 4 * SM + e)];
+            a.bias_partial[((long)chunk * a.heads + m) * S + tid] = sum;
+        }
+    }
+}
+
+struct DwPlan { int TR, TC, ntr, ntc, KST, QST, chunks; long tiles; size_t lds; };
+
+static DwPlan plan_dw(const Problem& p)
+{
+    const int S = p.S(), R = p.ksize / 2;
+    DwPlan t;
+    t.ntc = (p.W + 31) / 32;
+    t.TC = ((p.W + t.ntc - 1) / t.ntc + 3) & ~3;            // <= 32: eight staging lanes, one quad each
+    t.ntc = (p.W + t.TC - 1) / t.TC;
+    auto lds = [&](int TR) {
+        t.KST = ((TR + 2 * R) * (t.TC + 2 * R)) | 1;        // odd: 32 channels, 32 banks
+        t.QST = (TR * t.TC) | 1;
+        const size_t tile = (size_t)DW_CH * (t.KST + t.QST) + (size_t)TR * t.TC + DW_ZEROS + (size_t)TR * (t.TC / 4) * (4 * (S - 1) + 1);
+        const size_t red = (size_t)DW_CH * S * S;
+        return (tile > red ? tile : red) * sizeof(float);
+    };
+    int TR = 16;
+    while (TR > 1 && lds(TR) > 80 * 1024) --TR;             // two blocks per compute unit
+    t.ntr = (p.H + TR - 1) / TR;
+    t.TR = (p.H + t.ntr - 1) / t.ntr;
+    t.ntr = (p.H + t.TR - 1) / t.TR;
+    t.lds = lds(t.TR);
+    t.tiles = (long)p.B * t.ntr * t.ntc;
+    const long jobs = 2L * p.heads * ((p.d() + DW_CH - 1) / DW_CH);
+    long n = (2 * MAX_CU_PLANNED + jobs - 1) / jobs;
+    if (n > t.tiles) n = t.tiles;
+    t.chunks = (int)n;
+    return t;
+}
+
+template <typename T, int KS, bool VEC>
+static hipError_t launch_dw(const Problem& p, const DwArgs& a, const DwPlan& t, hipStream_t st)
+{
+    static LdsOptIn opt_in;
+    hipError_t e = opt_in.ensure({(const void*)dw32_kernel<T, KS, VEC>}, 160 * 1024);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)(2 * t.chunks * ((p.d() + DW_CH - 1) / DW_CH)), (unsigned)p.heads);
+    hipLaunchKernelGGL((dw32_kernel<T, KS, VEC>), grid, dim3(256), t.lds, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace m32
+
+size_t bwd_dw_m32_partial_floats(const Problem& p)
+{
+    if (!m32_supported(p)) return 0;
+    const m32::DwPlan t = m32::plan_dw(p);
+    return (size_t)t.chunks * (2 * (size_t)p.C * p.S() * p.S() + (size_t)p.heads * p.S());
+}
+
+hipError_t launch_bwd_dkdv_m32(const Problem& p, const void* dout, const void* q, const float* wk, const float* wv,
+                               const float* attn_ws, const float* dl_ws, void* dk, void* dv, hipStream_t st)
+{
+    m32::DkdvArgs a{};
+    a.x[0] = q; a.x[1] = dout; a.w[0] = wk; a.w[1] = wv; a.p[0] = dl_ws; a.p[1] = attn_ws;
+    a.out[0] = dk; a.out[1] = dv; a.f[0] = p.logit_scale(); a.f[1] = 1.0f;
+    a.H = p.H; a.W = p.W; a.C = p.C; a.d = p.d();
+    a.idw = p.two_branch ? 1.0f : 0.0f;
+    if (p.dtype == 0)
+        return p.ksize == 3 ? m32::launch_dkdv_t<float, 3>(p, a, st) : m32::launch_dkdv_t<float, 5>(p, a, st);
+    return p.ksize == 3 ? m32::launch_dkdv_t<bf16_bits, 3>(p, a, st) : m32::launch_dkdv_t<bf16_bits, 5>(p, a, st);
+}
+
+hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
+                             const float* attn_ws, const float* dl_ws, float* partial, float* dwk, float* dwv,
+                             float* dbias, hipStream_t st)
+{
+    const m32::DwPlan t = m32::plan_dw(p);
+    const long side = (long)p.C * p.S() * p.S();
+    m32::DwArgs a{};
+    a.y[0] = k; a.y[1] = v; a.x[0] = q; a.x[1] = dout; a.p[0] = dl_ws; a.p[1] = attn_ws;
+    a.partial = partial;
+    a.bias_partial = dbias ? partial + (size_t)t.chunks * 2 * side : nullptr;
+    a.f[0] = p.logit_scale(); a.f[1] = 1.0f;
+    a.H = p.H; a.W = p.W; a.C = p.C; a.d = p.d(); a.heads = p.heads;
+    a.TR = t.TR; a.TC = t.TC; a.ntr = t.ntr; a.ntc = t.ntc; a.tiles = t.tiles; a.chunks = t.chunks;
+    a.KST = t.KST; a.QST = t.QST;
+    // whole quads by one load where every row starts at one
+    const size_t quad = p.dtype == 0 ? 16 : 8;
+    bool vec = p.W % 4 == 0;
+    for (const void* x : {k, v, q, dout}) vec = vec && (uintptr_t)x % quad == 0;
+    hipError_t e;
+#define SLIDE_DW(T, KS) (vec ? m32::launch_dw<T, KS, true>(p, a, t, st) : m32::launch_dw<T, KS, false>(p, a, t, st))
+    if (p.dtype == 0) e = p.ksize == 3 ? SLIDE_DW(float, 3) : SLIDE_DW(float, 5);
+    else              e = p.ksize == 3 ? SLIDE_DW(bf16_bits, 3) : SLIDE_DW(bf16_bits, 5);
+#undef SLIDE_DW
+    if (e != hipSuccess) return e;
+    return launch_bwd_dw_reduce(partial, dwk, dwv, side, t.chunks, a.bias_partial, dbias, p.heads * p.S(), p.accumulate, st);
+}
+
+}  // namespace slide

@@ -1,0 +1,95 @@
+"""Key, value, kernel and bias gradients of the float32 matrix-core kernels against the CPU oracle where
+their tiling can go wrong: rows that are whole quads of pixels and rows that are not, tiles of rows and
+columns with smaller last ones, fewer quads than walkers, blocks that sum several tiles, heads of more
+than one block of 32 channels and of fewer than one quad, bfloat16 with a window of 3 on widths
+that keep float32 attention weights, pointers that are not aligned to a quad, sums that continue.
+
+Tolerances: float32 1e-5 of the largest entry (the operator's); bfloat16 activations 2e-2 of
+max(1, largest entry) for the rounded gradients.  Kernel and bias gradients of bfloat16 inputs: 1e-5
+where the per-pixel part is float32 too, 2e-2 of max(1, largest) after the half-precision one."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2304_04237_amd as sa
+from paper_2304_04237_amd import synth
+from oracle import slide_oracle as oracle
+
+pytestmark = pytest.mark.gpu
+
+GRAD_NAMES = "dq dk dv dwk dwv dbias".split()
+
+SHAPES = [
+    # B, H, W, C, heads, ksize, dtype
+    (1, 1, 1, 1, 1, 5, "f32"), (1, 2, 3, 2, 1, 5, "f32"), (1, 1, 4, 3, 1, 3, "f32"), (3, 17, 33, 3, 1, 3, "f32"),
+    (2, 9, 64, 34, 1, 3, "f32"), (2, 9, 66, 34, 1, 5, "f32"), (1, 21, 36, 66, 2, 5, "f32"), (2, 11, 101, 65, 1, 3, "f32"),
+    (130, 16, 28, 8, 1, 3, "f32"), (70, 13, 14, 5, 1, 5, "f32"), (70, 12, 20, 8, 2, 5, "bf16"),
+    (1, 300, 2, 4, 1, 5, "f32"), (40, 30, 30, 32, 4, 3, "f32"),
+    (3, 28, 28, 64, 2, 3, "bf16"), (2, 15, 27, 32, 1, 3, "bf16"), (2, 28, 28, 64, 1, 5, "bf16"), (2, 20, 44, 64, 1, 3, "bf16"),
+]
+
+
+def _check(name, got, want, tol, floor):
+    got = got.detach().double().cpu().numpy()
+    assert got.shape == want.shape, name
+    err = float(np.abs(got - want).max())
+    bound = tol * max(floor, float(np.abs(want).max()))
+    assert err <= bound, "%s: max abs err %.3e > %.3e" % (name, err, bound)
+
+
+def _shifted(t, elements):
+    """The same values `elements` past an aligned address."""
+    buf = torch.empty(t.numel() + elements, dtype=t.dtype, device=t.device)
+    out = buf[elements:].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+def _inputs(shape, seed):
+    B, H, W, C, heads, ks, dtype = shape
+    dev = torch.device("cuda:0")
+    dd = synth.make_inputs(B, H, W, C, heads, ks, dtype, seed=seed, with_dout=True)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    acts = [dd[n].to(dev).to(tdt) for n in ("dout", "q", "k", "v")]
+    wk, wv = (sa.slide_reparam(dd[n].to(dev)) for n in ("wk_learned", "wv_learned"))
+    return acts, wk, wv, dd["bias"].to(dev)
+
+
+def _oracle(acts, wk, wv, bias, heads, ks):
+    n = [x.double().cpu().numpy() for x in (*acts, wk, wv, bias)]
+    return oracle.bwd(*n, heads, ks)
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_against_oracle(shape, shift):
+    heads, ks, dtype = shape[4:]
+    print("float32 matrix-core gradients", shape, shift, flush=True)
+    acts, wk, wv, bias = _inputs(shape, 500 + sum(shape[1:4]))
+    grads = sa.slide_attn_bwd(*(_shifted(a, shift) for a in acts), wk, wv, bias, heads, ks)
+    # the same again, added to what is there
+    twice = [torch.full_like(g, 3.0) for g in grads]
+    sa.slide_attn_bwd_two_branch(*acts, wk, wv, bias, heads, ks, outputs=twice, accumulate=True)
+    torch.cuda.synchronize()
+    half = dtype == "bf16" and ks == 3 and shape[3] // heads == 32
+    for name, got, want in zip(GRAD_NAMES, grads, _oracle(acts, wk, wv, bias, heads, ks)):
+        if dtype == "f32" or (name in ("dwk", "dwv", "dbias") and not half):
+            _check(name, got, want, 1e-5, 0.0)
+        else:
+            _check(name, got, want, 2e-2, 1.0)
+    # (the fixed shift path changes a and dl, so the sums are compared with a second run of that form)
+    again = sa.slide_attn_bwd_two_branch(*acts, wk, wv, bias, heads, ks)
+    for name, a, b in list(zip(GRAD_NAMES, twice, again))[3:]:
+        assert torch.equal(a, b + 3.0), name
+
+
+@pytest.mark.parametrize("W", [20, 21, 33])
+def test_infinite_value_reaches_no_other_tap(W):
+    """An infinite v in the last column: the kernel gradient of a tap that never reads that column stays finite."""
+    heads, ks = 1, 3
+    acts, wk, wv, bias = _inputs((1, 6, W, 8, heads, ks, "f32"), 77)
+    acts[3][:, :, :, -1] = float("inf")
+    dwv = sa.slide_attn_bwd(*acts, wk, wv, bias, heads, ks)[4]
+    left = dwv.view(8, 9, 3, 3)[:, :, :, 0]
+    assert torch.isfinite(left).all()
+    assert not torch.isfinite(dwv.view(8, 9, 3, 3)[:, :, :, 1]).any()
