@@ -32,9 +32,9 @@ struct PixelArgs {
 // lies in LDS as [quad][pixel][4 channels], so a tap is one 16-byte read for four channels (the
 // LDS moves 190 B per cycle and CU that way, 82 in 4-byte reads, measured).  The next step's
 // elements are fetched into registers while the current one is multiplied.  MI355X, against one
-// thread per pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: forward 335 -> 65
-// us, backward 503 -> 94 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 428 us; one
-// 14x14 map of 2 heads, forward: 18.9 -> 10.4 us.
+// thread per pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: forward 335 -> 50
+// us, backward 503 -> 77 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 337 us; one
+// 14x14 map of 2 heads, forward: 18.9 -> 9.4 us.
 template <typename T, int KS, int PG, int CG, int CQ, bool BWD>
 __global__ void __launch_bounds__(64 * PG * CG, CG > 1 ? 2 : (KS == 3 ? 4 : 2))
 pixel32_kernel(const PixelArgs a)
@@ -50,7 +50,7 @@ pixel32_kernel(const PixelArgs a)
 
     extern __shared__ __align__(16) float smem_raw[];
     float* const smem = smem_raw;                           // (through a pointer: 16-byte accesses keep their alignment)
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int pg = wave % PG, cg = wave / PG;
     const int H = a.H, W = a.W, d = a.d;
     const int m = blockIdx.y, b = blockIdx.z;
@@ -66,6 +66,7 @@ pixel32_kernel(const PixelArgs a)
     float* wl = smem + CQ * npx * 4;                        // [CQ][QUAD_W]
     float* xl = wl + CQ * D::QUAD_W;                        // [CQ][PX][4]
 
+    const bool wave_live = n0 + pg * 64 < H * tw;           // (the last run's waves past the strip only stage)
     // this lane's pixel
     const int n = n0 + pg * 64 + lane;
     const bool live = n < H * tw;
@@ -171,7 +172,7 @@ pixel32_kernel(const PixelArgs a)
             __syncthreads();
             if (c0 + 4 * CQ < d) fetch(c0 + 4 * CQ);
 #pragma unroll 1
-            for (int u = cg; u < CQ; u += CG) {
+            for (int u = cg; u < CQ && wave_live; u += CG) {
                 if (c0 + 4 * u >= d) break;
                 body(c0 + 4 * u, u * npx * 4 + at, CQ * npx * 4 + u * D::QUAD_W, xl + (u * PX + pg * 64 + lane) * 4);
             }
@@ -196,14 +197,20 @@ pixel32_kernel(const PixelArgs a)
 #pragma unroll
                     for (int j = 0; j < D::WV; ++j) wv[j] = smem[wo + woff[j] + t];
                 const f4 yt = *(const f4*)(smem + yo + ((t / KS) * RP + t % KS) * 4);
+                // (vector work first, then the matrix instructions back to back: between two of them a
+                // vector instruction costs the issue of about one more, measured)
+                const f4 g = x * yt;
                 unroll<4>([&](auto ec) {
                     constexpr int e = decltype(ec)::value;
-                    const float g = x[e] * yt[e];
-                    outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, g, acc);
-                    last = fmaf(lane_of(wlast[(4 * t + e) / 64], (4 * t + e) % 64), g, last);
+                    last = fmaf(lane_of(wlast[(4 * t + e) / 64], (4 * t + e) % 64), g[e], last);
                 });
                 asm volatile("" : "+v"(last));
-                if (t % KS == KS - 1) __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_sched_barrier(0);
+                unroll<4>([&](auto ec) {
+                    constexpr int e = decltype(ec)::value;
+                    outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, g[e], acc);
+                });
+                __builtin_amdgcn_sched_barrier(0);
             });
         });
 #pragma unroll
@@ -249,11 +256,15 @@ pixel32_kernel(const PixelArgs a)
                 const f4 yt = *(const f4*)(smem + yo + ((t / KS) * RP + t % KS) * 4);
                 unroll<4>([&](auto ec) {
                     constexpr int e = decltype(ec)::value;
-                    outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, yt[e], acc[e]);
                     last[e] = fmaf(lane_of(wlast[(4 * t + e) / 64], (4 * t + e) % 64), yt[e], last[e]);
                 });
                 asm volatile("" : "+v"(last[0]), "+v"(last[1]), "+v"(last[2]), "+v"(last[3]));
-                if (t % KS == KS - 1) __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_sched_barrier(0);
+                unroll<4>([&](auto ec) {
+                    constexpr int e = decltype(ec)::value;
+                    outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, yt[e], acc[e]);
+                });
+                __builtin_amdgcn_sched_barrier(0);
             });
 #pragma unroll
             for (int e = 0; e < 4; ++e) {

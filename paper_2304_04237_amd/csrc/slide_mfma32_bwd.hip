@@ -25,11 +25,12 @@ struct DkdvArgs {
 // A lane is a pixel y; for one tap after the other it holds the S values of a (or dl) at
 // y - off(t), and the matrix cores form the sums over s for four channels at a time (rows = channels,
 // K = s: no padding), which are then multiplied with the four channels of dO (or q) at y - off(t).
-// LDS holds a (or dl) of the run's rows and halo as planes, NQ quads of channels of dO (or q) as
+// LDS holds a (or dl) of the run's rows and halo as [pixel][s], NQ quads of channels of dO (or q) as
 // [quad][pixel][4] and their kernels.  A tap costs S 4-byte LDS reads per lane whatever the number of
 // quads, so NQ is as large as two blocks per compute unit allow.  MI355X, against one thread per
-// pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: 846 -> 65 us; bf16, 5x5, B=64,
-// 28x28, C=128, 4 heads: 4855 -> 368 us.
+// pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: 846 -> 49 us; bf16, 5x5, B=64,
+// 28x28, C=128, 4 heads: 4855 -> 289 us (368 with a (or dl) as planes, a step's elements loaded when it
+// begins and idle waves computing).
 template <typename T> struct Quad;
 template <> struct Quad<float> {
     typedef f4 Raw;
@@ -40,6 +41,7 @@ template <> struct Quad<float> {
         for (int u = 0; u < 4; ++u) r[u] = b[o + (long)min(c + u, d - 1) * sc];
         return r;
     }
+    static __device__ __forceinline__ Raw pack(const float (&e)[4]) { return f4{e[0], e[1], e[2], e[3]}; }
     static __device__ __forceinline__ f4 value(Raw r) { return r; }
     static __device__ __forceinline__ Raw zero() { return f4{0.0f, 0.0f, 0.0f, 0.0f}; }
 };
@@ -47,10 +49,14 @@ template <> struct Quad<bf16_bits> {
     typedef uint32_t Raw __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ Raw load(const bf16_bits* b, long o, long sc, int c, int d)
     {
-        uint32_t h[4];
+        bf16_bits e[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) h[u] = b[o + (long)min(c + u, d - 1) * sc];
-        return Raw{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+        for (int u = 0; u < 4; ++u) e[u] = b[o + (long)min(c + u, d - 1) * sc];
+        return pack(e);
+    }
+    static __device__ __forceinline__ Raw pack(const bf16_bits (&e)[4])
+    {
+        return Raw{e[0] | ((uint32_t)e[1] << 16), e[2] | ((uint32_t)e[3] << 16)};
     }
     static __device__ __forceinline__ f4 value(Raw r)
     {
@@ -73,7 +79,7 @@ dkdv32_kernel(const DkdvArgs a)
     static_assert(NQ % CG == 0, "");
 
     extern __shared__ __align__(16) float smem_raw[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int pg = wave % PG, cg = wave / PG;
     const int H = a.H, W = a.W, d = a.d;
     const int m = blockIdx.y, side = blockIdx.x & 1, b = blockIdx.z;
@@ -86,7 +92,7 @@ dkdv32_kernel(const DkdvArgs a)
     const int npx = a.cut.npx, RP = a.cut.RP;
     const int row0 = n0 / tw - R;
     Raw* xl = (Raw*)smem_raw;                               // [NQ][npx]
-    float* pl = (float*)(xl + NQ * npx);                    // [S][npx]
+    float* pl = (float*)(xl + NQ * npx);                    // [npx][S]: S is odd, lanes read without conflicts and a tap's S values are one address
     float* wl = pl + S * npx;                               // [NQ][QUAD_W]
 
     const int n = n0 + pg * 64 + lane;
@@ -108,42 +114,77 @@ dkdv32_kernel(const DkdvArgs a)
         in = y >= 0 && y < H && x >= 0 && x < W;
         return in ? (long)y * W + x : 0;
     };
-    for (int e = tid; e < npx; e += NT) {
-        bool in;
-        const long o = tile_pixel(e, in);
-        float v[S];
-#pragma unroll
-        for (int s = 0; s < S; ++s) v[s] = pb[(long)s * HW + o];
-#pragma unroll
-        for (int s = 0; s < S; ++s) pl[s * npx + e] = in ? v[s] : 0.0f;
-    }
     int woff[WR];                                           // lane l: channel l & 3, shift l >> 2
 #pragma unroll
     for (int j = 0; j < WR; ++j) {
         const int l = min(j * 64 + lane, 4 * S - 1);
         woff[j] = (l & 3) * (S * S) + (l >> 2) * S;
     }
+    const bool wave_live = n0 + pg * 64 < H * tw;           // (the last run's waves past the strip only stage)
+
+    // the quads and kernels of a step, fetched while the step before is multiplied
+    constexpr int NI = 2;                                   // pixels per thread fetched ahead
+    constexpr int NWT = (NQ * D::QUAD_W + NT - 1) / NT;     // weights per thread
+    constexpr bool AHEAD_W = NWT <= 24;
+    bool in[NI]; long off[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        off[i] = tile_pixel(min(tid + i * NT, npx - 1), in[i]);
+    }
+    Raw xr[NI][NQ];
+    float wr[AHEAD_W ? NWT : 1];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) xr[i][u] = Quad<T>::load(xb, off[i], HW, c0 + 4 * u, d);
+        if (AHEAD_W)
+#pragma unroll
+            for (int u = 0; u < NWT; ++u) {
+                const int idx = tid + u * NT;
+                wr[u] = (idx < NQ * D::QUAD_W && c0 * S * S + idx < d * S * S) ? wb[(long)c0 * S * S + idx] : 0.0f;
+            }
+    };
+    fetch(0);
+    for (int e = tid; e < npx; e += NT) {
+        bool ok;
+        const long o = tile_pixel(e, ok);
+        float v[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) v[s] = pb[(long)s * HW + o];
+#pragma unroll
+        for (int s = 0; s < S; ++s) pl[e * S + s] = ok ? v[s] : 0.0f;
+    }
 
     for (int c0 = 0; c0 < d; c0 += 4 * NQ) {
         if (c0 > 0) __syncthreads();                        // the step before is no longer read
-        for (int e = tid; e < npx; e += NT) {
-            bool in;
-            const long o = tile_pixel(e, in);
-            Raw v[NQ];
 #pragma unroll
-            for (int u = 0; u < NQ; ++u) v[u] = Quad<T>::load(xb, o, HW, c0 + 4 * u, d);
+        for (int i = 0; i < NI; ++i)
+            if (tid + i * NT < npx)
 #pragma unroll
-            for (int u = 0; u < NQ; ++u) xl[u * npx + e] = in ? v[u] : Quad<T>::zero();
+                for (int u = 0; u < NQ; ++u) xl[u * npx + tid + i * NT] = in[i] ? xr[i][u] : Quad<T>::zero();
+        for (int e = tid + NI * NT; e < npx; e += NT) {     // (maps of a few columns, wide windows)
+            bool ok;
+            const long o = tile_pixel(e, ok);
+#pragma unroll
+            for (int u = 0; u < NQ; ++u) xl[u * npx + e] = ok ? Quad<T>::load(xb, o, HW, c0 + 4 * u, d) : Quad<T>::zero();
         }
-        const int nw = min(4 * NQ, d - c0) * S * S;
+        if (AHEAD_W) {
+#pragma unroll
+            for (int u = 0; u < NWT; ++u)
+                if (tid + u * NT < NQ * D::QUAD_W) wl[tid + u * NT] = wr[u];
+        } else {
 #pragma unroll 4
-        for (int idx = tid; idx < NQ * D::QUAD_W; idx += NT) {
-            float w = idx < nw ? wb[(long)c0 * S * S + idx] : 0.0f;
-            // the fixed shift path of the two-branch form: shift t reads tap t
-            if (a.idw != 0.0f && idx % (S * S) % (S + 1) == 0) w += a.idw;
-            wl[idx] = w;
+            for (int idx = tid; idx < NQ * D::QUAD_W; idx += NT)
+                wl[idx] = c0 * S * S + idx < d * S * S ? wb[(long)c0 * S * S + idx] : 0.0f;
+        }
+        if (a.idw != 0.0f) {                                // the fixed shift path of the two-branch form: shift t reads tap t
+            __syncthreads();
+            for (int i = tid; i < min(NQ * 4, d - c0) * S; i += NT) wl[(i / S) * (S * S) + (i % S) * (S + 1)] += a.idw;
         }
         __syncthreads();
+        if (c0 + 4 * NQ < d) fetch(c0 + 4 * NQ);
+        if (!wave_live) continue;
 
         f4 acc[NW];
 #pragma unroll
@@ -151,12 +192,12 @@ dkdv32_kernel(const DkdvArgs a)
         float p[S], pn[S];
         int src = at + R * RP + R;                          // y - off(0)
 #pragma unroll
-        for (int s = 0; s < S; ++s) p[s] = pl[s * npx + src];
+        for (int s = 0; s < S; ++s) p[s] = pl[src * S + s];
 #pragma unroll 1
         for (int t = 0; t < S; ++t) {
             const int next = t + 1 < S ? (((t + 1) % KS) ? src - 1 : src - RP + (KS - 1)) : src;
 #pragma unroll
-            for (int s = 0; s < S; ++s) pn[s] = pl[s * npx + next];
+            for (int s = 0; s < S; ++s) pn[s] = pl[next * S + s];
 #pragma unroll
             for (int u = 0; u < NW; ++u) {
                 const int qd = cg + u * CG;
@@ -237,12 +278,19 @@ struct DwArgs {
 constexpr int DW_CH = 32;                   // channels per block
 constexpr int DW_ZEROS = 160;               // as many as the taps of a quad span: 4 * 36 + 8
 
-template <typename T> struct Vec4;
-template <> struct Vec4<float> {
-    static __device__ __forceinline__ f4 load(const float* p) { return *(const f4*)p; }
-};
-template <> struct Vec4<bf16_bits> {
-    static __device__ __forceinline__ f4 load(const bf16_bits* p) { return Quad<bf16_bits>::value(*(const Quad<bf16_bits>::Raw*)p); }
+constexpr int dw_max_rows(int ks) { return ks == 3 ? 8 : 6; }   // rows of a tile at most
+
+// pixels x..x+3 of row y, zeros outside the map and where !ok; VEC: W % 4 == 0, a quad is one load
+template <typename T, bool VEC> struct Row4 {
+    using Raw = typename Quad<T>::Raw;
+    static __device__ __forceinline__ Raw load(const T* base, int y, int x, int W, bool ok)
+    {
+        if (VEC) return ok ? *(const Raw*)(base + (long)y * W + x) : Quad<T>::zero();
+        T e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = ok && x + u < W ? base[(long)y * W + x + u] : T(0);
+        return Quad<T>::pack(e);
+    }
 };
 
 // One block sums 32 channels of a head and one side over its chunk of tiles.  A lane is a channel, its
@@ -253,8 +301,9 @@ template <> struct Vec4<bf16_bits> {
 // each of the four waves, which share the pixels; with a 5x5 window a wave holds six taps and the
 // four waves see the same pixels (tap 24 is dealt out by blocks of shifts).  MI355X, against one block
 // per channel and shift (slide_generic.hip) and a launch of its own for dbias: float32, 3x3, B=32,
-// 56x56, C=64, 2 heads: 598 -> 100 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: 6875 -> 226 us; bf16, 3x3,
-// B=128, 28x28, C=128, 4 heads: 1854 -> 160 us.
+// 56x56, C=64, 2 heads: 598 -> 59 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: 6875 -> 174 us; bf16, 3x3,
+// B=128, 28x28, C=128, 4 heads: 1854 -> 86 us (160 with each tile loaded when its turn comes and the waves'
+// sums added one wave after the other, 101 with vector and matrix instructions mixed).
 template <typename T, int KS, bool VEC>
 __global__ void __launch_bounds__(256, 2)
 dw32_kernel(const DwArgs a)
@@ -269,7 +318,7 @@ dw32_kernel(const DwArgs a)
 
     extern __shared__ __align__(16) float smem_raw[];
     float* const smem = smem_raw;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int role = wave % ROLES, half = lane >> 5, ch = lane & 31;
     const int walker = (wave / ROLES) * 2 + half;
     const int H = a.H, W = a.W, d = a.d, TR = a.TR, TC = a.TC;
@@ -314,93 +363,124 @@ dw32_kernel(const DwArgs a)
     const bool sc_live = cb * DW_CH + sch < d;
     const long chan = (long)m * d + min(cb * DW_CH + sch, d - 1);
 
-    const long t0 = a.tiles * chunk / a.chunks, t1 = a.tiles * (chunk + 1) / a.chunks;
-    for (long tile = t0; tile < t1; ++tile) {
-        const long b = tile / (a.ntr * a.ntc);
-        const int tr_ = (int)(tile - b * (a.ntr * a.ntc));
-        const int ty = tr_ / a.ntc, tx = tr_ - ty * a.ntc;
-        const int y0 = ty * TR, x0 = tx * TC;
-        const int th = min(TR, H - y0), tw = min(TC, W - x0);
-        const int qpr = (tw + 3) >> 2, nq = th * qpr;
-        __syncthreads();                                    // the tile before is no longer read
-        {
-            const T* yc = yb + (b * a.C + chan) * HW;
-            const T* xc = xb + (b * a.C + chan) * HW;
-            auto quad4 = [&](const T* base, int y, int x, bool ok) -> f4 {  // pixels x..x+3 of row y, zero outside the map
-                f4 r = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (VEC) {
-                    if (ok) r = Vec4<T>::load(base + (long)y * W + x);      // (W % 4 == 0: a quad is whole)
-                } else {
-                    const long row = ok ? (long)y * W : 0;
+    // a tile's elements on their way from memory to LDS.  With a 3x3 window there are registers left to
+    // fetch the next tile while this one is multiplied.
+    constexpr bool AHEAD = KS == 3;
+    constexpr int MAX_TR = dw_max_rows(KS);
+    constexpr int YR = MAX_TR + 2 * R, XR = MAX_TR;   // rows of y and x
+    constexpr int HL = 2 * R, RPI = 8 / HL, HR = (YR + RPI - 1) / RPI;      // halo columns; rows of them per step, steps
+    constexpr int PR = (S * MAX_TR + 31) / 32;           // rows of dl (or a): 32 at a time
+    using Raw = typename Quad<T>::Raw;
+    Raw yv[YR], xv[XR];
+    T hv[HR];
+    f4 pv[PR];
+    struct Where { long b; int y0, x0, th, tw, qpr; };
+    auto locate = [&](long tile) -> Where {
+        Where w;
+        w.b = tile / (a.ntr * a.ntc);
+        const int r = (int)(tile - w.b * (a.ntr * a.ntc));
+        const int ty = r / a.ntc, tx = r - ty * a.ntc;
+        w.y0 = ty * TR; w.x0 = tx * TC;
+        w.th = min(TR, H - w.y0); w.tw = min(TC, W - w.x0);
+        w.qpr = (w.tw + 3) >> 2;
+        return w;
+    };
+    auto fetch_y = [&](const Where& w) {
+        const T* yc = yb + (w.b * a.C + chan) * HW;
+        const int x = w.x0 + 4 * sq;
+        const bool col = sc_live && sq < w.qpr;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const bool in = ok && x + e < W;
-                        const float v = Elem<T>::load(base + (in ? row + x + e : 0));
-                        r[e] = in ? v : 0.0f;
-                    }
+        for (int i = 0; i < YR; ++i) {
+            const int y = w.y0 + i - R;
+            yv[i] = Row4<T, VEC>::load(yc, y, x, W, col && i < w.th + 2 * R && y >= 0 && y < H);
+        }
+        // the R columns on each side of the tile's 4 * qpr
+#pragma unroll
+        for (int i = 0; i < HR; ++i) {
+            const int rr = sq / HL + i * RPI, h = sq % HL;
+            const int y = w.y0 + rr - R, xx = w.x0 + (h < R ? h - R : 4 * w.qpr + h - R);
+            const bool in = sc_live && rr < w.th + 2 * R && y >= 0 && y < H && xx >= 0 && xx < W;
+            hv[i] = in ? yc[(long)y * W + xx] : T(0);
+        }
+    };
+    auto fetch_x = [&](const Where& w) {
+        const T* xc = xb + (w.b * a.C + chan) * HW;
+        const int x = w.x0 + 4 * sq;
+        const bool col = sc_live && sq < w.qpr;
+#pragma unroll
+        for (int i = 0; i < XR; ++i) xv[i] = Row4<T, VEC>::load(xc, w.y0 + i, x, W, col && i < w.th);
+        const float* pc = pb + (w.b * a.heads + m) * S * HW;
+        const uint32_t inv = (65536u + w.th - 1) / w.th;
+#pragma unroll
+        for (int i = 0; i < PR; ++i) {
+            const int n = i * 32 + sch;
+            const int sh = (int)((n * inv) >> 16), rr = n - sh * w.th;
+            pv[i] = Row4<float, VEC>::load(pc + (long)min(sh, SM) * HW, w.y0 + rr, x, W, n < S * w.th && sq < w.qpr);
+        }
+    };
+    auto put_y = [&](const Where& w) {
+        if (sq < w.qpr) {
+#pragma unroll
+            for (int i = 0; i < YR; ++i)
+                if (i < w.th + 2 * R) {
+                    float* o = yl + sch * a.KST + i * RS + R + 4 * sq;
+                    const f4 v = Quad<T>::value(yv[i]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = v[e];
                 }
-                return r;
-            };
-            constexpr int NB = 6;
-            for (int r0 = 0; r0 < th + 2 * R; r0 += NB) {
-                f4 v[NB];
+        }
 #pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    const int y = y0 + r0 + i - R;
-                    v[i] = quad4(yc, y, x0 + 4 * sq, sc_live && sq < qpr && r0 + i < th + 2 * R && y >= 0 && y < H);
-                }
+        for (int i = 0; i < HR; ++i) {
+            const int rr = sq / HL + i * RPI, h = sq % HL;
+            if (rr < w.th + 2 * R) yl[sch * a.KST + rr * RS + (h < R ? h : 4 * w.qpr + h)] = Elem<T>::load(&hv[i]);
+        }
+    };
+    auto put_x = [&](const Where& w) {
+        if (sq >= w.qpr) return;
 #pragma unroll
-                for (int i = 0; i < NB; ++i)
-                    if (sq < qpr && r0 + i < th + 2 * R) {
-                        float* o = yl + sch * a.KST + (r0 + i) * RS + R + 4 * sq;
+        for (int i = 0; i < XR; ++i)
+            if (i < w.th) {
+                float* o = xl + sch * a.QST + i * TC + 4 * sq;
+                const f4 v = Quad<T>::value(xv[i]);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = v[i][e];
-                    }
+                for (int e = 0; e < 4; ++e) o[e] = v[e];
             }
-            for (int r0 = 0; r0 < th; r0 += NB) {
-                f4 v[NB];
+        const uint32_t inv = (65536u + w.th - 1) / w.th;
 #pragma unroll
-                for (int i = 0; i < NB; ++i)
-                    v[i] = quad4(xc, y0 + r0 + i, x0 + 4 * sq, sc_live && sq < qpr && r0 + i < th);
+        for (int i = 0; i < PR; ++i) {
+            const int n = i * 32 + sch;
+            const int sh = (int)((n * inv) >> 16), rr = n - sh * w.th;
+            if (n < S * w.th) {
+                const int q = rr * w.qpr + sq;
 #pragma unroll
-                for (int i = 0; i < NB; ++i)
-                    if (sq < qpr && r0 + i < th) {
-                        float* o = xl + sch * a.QST + (r0 + i) * TC + 4 * sq;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = v[i][e];
-                    }
-            }
-            // the R columns on each side of the tile's 4 * qpr
-            constexpr int HL = 2 * R, RPI = 8 / HL;
-            for (int r = sq / HL; r < th + 2 * R; r += RPI) {
-                const int h = sq % HL;
-                const int y = y0 + r - R;
-                const int col = h < R ? h : 4 * qpr + h;    // column of the LDS row
-                const int x = x0 + col - R;
-                const bool in = sc_live && y >= 0 && y < H && x >= 0 && x < W;
-                const float v = Elem<T>::load(yc + (in ? (long)y * W + x : 0));
-                yl[sch * a.KST + r * RS + col] = in ? v : 0.0f;
-            }
-            const float* pc = pb + (b * a.heads + m) * S * HW;
-            const int np = S * th;
-            for (int i0 = 0; i0 < np; i0 += 32) {
-                const int i = i0 + sch;
-                const int s = i / th, r = i - s * th;
-                if (i < np && sq < qpr) {
-                    const float* g = pc + (long)s * HW + (long)(y0 + r) * W + x0 + 4 * sq;
-                    float v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = 4 * sq + e < tw ? g[e] : 0.0f;
-                    const int q = r * qpr + sq;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (s < SM) al[q * AQ + e * SM + s] = v[e];
-                        else ll[q * 4 + e] = v[e];
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    if (sh < SM) al[q * AQ + e * SM + sh] = pv[i][e];
+                    else ll[q * 4 + e] = pv[i][e];
                 }
             }
         }
+    };
+
+    const long t0 = a.tiles * chunk / a.chunks, t1 = a.tiles * (chunk + 1) / a.chunks;
+    Where at{}, next{};
+    if (t0 < t1) next = locate(t0);
+    if (AHEAD && t0 < t1) { fetch_y(next); fetch_x(next); }
+    for (long tile = t0; tile < t1; ++tile) {
+        at = next;
+        if (!AHEAD) fetch_y(at);
+        __syncthreads();                                    // the tile before is no longer read
+        put_y(at);
+        if (!AHEAD) {
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_x(at);
+        }
+        put_x(at);
+        if (tile + 1 < t1) {
+            next = locate(tile + 1);
+            if (AHEAD) { fetch_y(next); fetch_x(next); }
+        }
         __syncthreads();
+        const int tw = at.tw, qpr = at.qpr, nq = at.th * at.qpr;
 
         const uint32_t inv = (65536u + qpr - 1) / qpr;      // qi / qpr for qi < 256 (qpr <= 8)
         for (int q0 = 0; q0 < nq; q0 += WALK) {
@@ -448,64 +528,74 @@ dw32_kernel(const DwArgs a)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) ye[e] = yq[4 * RS + 4 + e];
             }
+            // (a vector instruction between two matrix instructions costs the issue of about one more, measured:
+            // a pixel's vector work comes first, then its matrix instructions back to back)
             unroll<4>([&](auto ec) {
                 constexpr int e = decltype(ec)::value;
+                float g[NTAP], ge = 0.0f;
+#pragma unroll
+                for (int i = 0; i < NTAP; ++i) {
+                    g[i] = x[e] * y[i][e];
+                    if (!VEC) g[i] = e < live ? g[i] : 0.0f;
+                    last[i] = fmaf(L[e], g[i], last[i]);
+                }
+                if (EXTRA) {
+                    ge = x[e] * ye[e];
+                    if (!VEC) ge = e < live ? ge : 0.0f;
+                    xlast = fmaf(L[e], ge, xlast);
+                }
+                __builtin_amdgcn_sched_barrier(0);
                 unroll<NTAP>([&](auto ic) {
                     constexpr int i = decltype(ic)::value;
-                    float g = x[e] * y[i][e];
-                    if (!VEC) g = e < live ? g : 0.0f;
                     unroll<SB>([&](auto sc) {
                         constexpr int blk = e * SB + decltype(sc)::value;
-                        acc[i][decltype(sc)::value] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[blk / 8], g, acc[i][decltype(sc)::value], 3, blk % 8, 0);
+                        acc[i][decltype(sc)::value] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[blk / 8], g[i], acc[i][decltype(sc)::value], 3, blk % 8, 0);
                     });
-                    last[i] = fmaf(L[e], g, last[i]);
                 });
                 if (EXTRA) {
-                    float g = x[e] * ye[e];
-                    if (!VEC) g = e < live ? g : 0.0f;
-                    xacc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, g, xacc[0], 3, e * 2, 0);
-                    xacc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, g, xacc[1], 3, e * 2 + 1, 0);
-                    xlast = fmaf(L[e], g, xlast);
+                    xacc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, ge, xacc[0], 3, e * 2, 0);
+                    xacc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, ge, xacc[1], 3, e * 2 + 1, 0);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             });
         }
     }
 
-    // the two walkers of a wave, then (3x3) the four waves in order, through LDS [channel][s][t]
-    float* red = smem;                                      // [32][S * S]
+    // the two walkers of a wave, then (3x3) the four waves in order, through LDS [wave][channel][s][t]
+    constexpr int NRED = KS == 3 ? 4 : 1;
+    float* red = smem + (KS == 3 ? wave : 0) * DW_CH * S * S;
     const float f = a.f[side];
-    auto fold = [&](float v) { return v + __shfl_xor(v, 32); };
     __syncthreads();
-#pragma unroll 1
-    for (int w = 0; w < (KS == 3 ? 4 : 1); ++w) {
-        if (KS == 5 || wave == w) {
-            auto put = [&](int s, int t, float v) {
-                v = fold(v);
-                if (half == 0) {
-                    float* o = red + ch * (S * S) + s * S + t;
-                    *o = (KS == 3 && w > 0) ? *o + v : v;
-                }
-            };
+    {
+        auto add = [&](int sh, int t, float v) {
+            const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+            v = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+            if (half == 0) red[ch * (S * S) + sh * S + t] = v;
+        };
 #pragma unroll
-            for (int i = 0; i < NTAP; ++i) {
+        for (int i = 0; i < NTAP; ++i) {
 #pragma unroll
-                for (int s = 0; s < SM; ++s) put(s, role * NTAP + i, acc[i][s / 4][s % 4]);
-                put(SM, role * NTAP + i, last[i]);
-            }
-            if (EXTRA) {
-                if (role < 3) {
+            for (int sh = 0; sh < SM; ++sh) add(sh, role * NTAP + i, acc[i][sh / 4][sh % 4]);
+            add(SM, role * NTAP + i, last[i]);
+        }
+        if (EXTRA) {
+            if (role < 3) {
 #pragma unroll
-                    for (int s = 0; s < 8; ++s) put(role * 8 + s, 24, xacc[s / 4][s % 4]);
-                } else {
-                    put(SM, 24, xlast);
-                }
+                for (int sh = 0; sh < 8; ++sh) add(role * 8 + sh, 24, xacc[sh / 4][sh % 4]);
+            } else {
+                add(SM, 24, xlast);
             }
         }
-        __syncthreads();
     }
+    __syncthreads();
     const int nch = min(DW_CH, d - cb * DW_CH);
     float* out = a.partial + (((long)chunk * 2 + side) * a.C + (long)m * d + cb * DW_CH) * S * S;
-    for (int i = tid; i < nch * S * S; i += 256) out[i] = f * red[i];
+    for (int i = tid; i < nch * S * S; i += 256) {
+        float sum = smem[i];
+#pragma unroll
+        for (int w = 1; w < NRED; ++w) sum += smem[w * DW_CH * S * S + i];
+        out[i] = f * sum;
+    }
 
     if (side == 0 && cb == 0 && a.bias_partial) {
         __syncthreads();
@@ -538,10 +628,10 @@ static DwPlan plan_dw(const Problem& p)
         t.KST = ((TR + 2 * R) * (t.TC + 2 * R)) | 1;        // odd: 32 channels, 32 banks
         t.QST = (TR * t.TC) | 1;
         const size_t tile = (size_t)DW_CH * (t.KST + t.QST) + (size_t)TR * t.TC + DW_ZEROS + (size_t)TR * (t.TC / 4) * (4 * (S - 1) + 1);
-        const size_t red = (size_t)DW_CH * S * S;
+        const size_t red = (size_t)DW_CH * S * S * (p.ksize == 3 ? 4 : 1);
         return (tile > red ? tile : red) * sizeof(float);
     };
-    int TR = 16;
+    int TR = dw_max_rows(p.ksize);
     while (TR > 1 && lds(TR) > 80 * 1024) --TR;             // two blocks per compute unit
     t.ntr = (p.H + TR - 1) / TR;
     t.TR = (p.H + t.ntr - 1) / t.ntr;
