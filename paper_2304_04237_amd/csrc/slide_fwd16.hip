@@ -284,8 +284,11 @@ __device__ __forceinline__ ShareGeom share_geom(const Tile& t)
     return s;
 }
 
+// RAGGED: rows start at any even address and W is no multiple of 8; `left` is the number of bytes from the
+// head's first element to the tensor's end (a chunk there is loaded element by element)
+template <bool RAGGED>
 __device__ __forceinline__ void share_load(const FwdArgs& a, const Tile& t, const ShareGeom& sg, int hb,
-                                           int lane, uint32_t hw2, uint4_t (&r)[4])
+                                           int lane, uint32_t hw2, uint4_t (&r)[4], uint32_t left = 0)
 {
     const int u = (hb >> 1) * 64 + lane;
     const int cq = u & 7, rest = u >> 3;
@@ -297,9 +300,36 @@ __device__ __forceinline__ void share_load(const FwdArgs& a, const Tile& t, cons
         return;
     }
     const char* base = (const char*)(((hb & 1) ? a.v : a.k) + t.head_base);   // wave-uniform
-    const uint32_t off = (uint32_t)(4 * cq) * hw2 + (uint32_t)(gi * a.g.W + t.gxa + 8 * x) * 2u;
+    const int gx = t.gxa + 8 * x;
+    const uint32_t off = (uint32_t)(4 * cq) * hw2 + (uint32_t)(gi * a.g.W + gx) * 2u;
+    if (!RAGGED) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = *(const uint4_t*)(base + (off + (uint32_t)e * hw2));
+        for (int e = 0; e < 4; ++e) r[e] = *(const uint4_t*)(base + (off + (uint32_t)e * hw2));
+        return;
+    }
+    const int n = a.g.W - gx;                           // columns of the map that the chunk holds
+    if (off + 3u * hw2 + 16u <= left) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = *(const uint4_any_t*)(base + (off + (uint32_t)e * hw2));
+        if (n < 8) {
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const uint32_t keep = 2 * y + 1 < n ? 0xffffffffu : (2 * y < n ? 0xffffu : 0u);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[e][y] &= keep;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bf16_bits* src = (const bf16_bits*)(base + (off + (uint32_t)e * hw2));
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const uint32_t lo = 2 * y < n ? src[2 * y] : 0, hi = 2 * y + 1 < n ? src[2 * y + 1] : 0;
+                r[e][y] = lo | (hi << 16);
+            }
+        }
+    }
 }
 
 template <bool EDGE_CHECK>
@@ -350,7 +380,7 @@ __device__ __forceinline__ void pipe_zero_pad(const TileGrid& a, const Tile& t, 
     }
 }
 
-template <int TW, bool LSE>
+template <int TW, bool LSE, bool RAGGED = false>
 __global__ void __launch_bounds__(PIPE_WAVES * 64, 2)
 fwd16_pipe_kernel(const FwdArgs a)
 {
@@ -360,7 +390,16 @@ fwd16_pipe_kernel(const FwdArgs a)
     const int lane = tid & 63, wave = tid >> 6;
     const int p = lane & 15, g = lane >> 4;
     const int HC = (TW ? TW : a.g.tw) + 2;
-    const bool single_col = a.g.n_tc == 1;              // then no staged column falls outside a tile
+    const bool single_col = a.g.n_tc == 1 && !RAGGED;   // then no staged column falls outside a tile
+    // bytes from a head's first element to the end of its tensor, as far as 32-bit offsets reach
+    auto bytes_left = [&](const Tile& t) -> uint32_t {
+        const long n = ((long)a.g.B * a.g.C * a.g.H * a.g.W - t.head_base) * 2;
+        return (uint32_t)(n < 0x7fffffffL ? n : 0x7fffffffL);
+    };
+    // columns that passes count a tile row as: eight pixels of a pass are one run of memory, so (RAGGED) the
+    // rows of a narrower tile than the map are rounded up to whole runs; a tile that is as
+    // wide as the map is one run from its first pixel to its last
+    auto pass_cols = [&](const Tile& t) { return RAGGED && a.g.n_tc > 1 ? (t.cols + 7) & ~7 : t.cols; };
     const uint32_t hw2 = (uint32_t)a.g.H * (uint32_t)a.g.W * 2u;
     const int n_tiles = a.g.TA + a.g.TB;
     unsigned char* wbuf = smem + a.a_base + wave * WAVE_SCRATCH;
@@ -375,10 +414,11 @@ fwd16_pipe_kernel(const FwdArgs a)
     // the first tile is staged without overlap, two shares per lane in flight
     {
         const ShareGeom sg = share_geom(tcur);
+        const uint32_t left = RAGGED ? bytes_left(tcur) : 0;
         for (int hb = wave; hb < sg.n_groups; hb += 2 * WAVES) {
             uint4_t r0[4], r1[4];
-            share_load(a, tcur, sg, hb, lane, hw2, r0);
-            if (hb + WAVES < sg.n_groups) share_load(a, tcur, sg, hb + WAVES, lane, hw2, r1);
+            share_load<RAGGED>(a, tcur, sg, hb, lane, hw2, r0, left);
+            if (hb + WAVES < sg.n_groups) share_load<RAGGED>(a, tcur, sg, hb + WAVES, lane, hw2, r1, left);
             share_store<true>(tcur, sg, hb, lane, HC, r0, smem);
             if (hb + WAVES < sg.n_groups) share_store<true>(tcur, sg, hb + WAVES, lane, HC, r1, smem);
         }
@@ -398,25 +438,39 @@ fwd16_pipe_kernel(const FwdArgs a)
         const Tile tnext = decode_tile(a.g, has_next ? nxt : cur);
         ShareGeom sg = share_geom(tnext);
         if (!has_next) sg.n_groups = 0;
-        const int npix = tcur.rows * tcur.cols;
+        const int pc = pass_cols(tcur);
+        const int npix = tcur.rows * pc;
         const int npass = (npix + 15) >> 4;
-        const float inv_tw = 1.0f / (float)tcur.cols;
+        const float inv_tw = 1.0f / (float)pc;
+        const uint32_t left = RAGGED ? bytes_left(tcur) : 0, left_next = RAGGED ? bytes_left(tnext) : 0;
         const char* qb = (const char*)(a.q + tcur.head_base);
         char* ob = (char*)(a.out + tcur.head_base);
-        auto seg_offset = [&](int pass, bool& ok) -> uint32_t {
+        // offset of the lane's eight pixels of a pass, and how many of them there are
+        auto seg_offset = [&](int pass, int& cnt) -> uint32_t {
             const int n0 = pass * 16 + 8 * seg_h;
-            ok = n0 < npix;
-            const int nn = ok ? n0 : 0;
+            const int nn = n0 < npix ? n0 : 0;
             const int sti = (int)(((float)nn + 0.5f) * inv_tw);
-            const int stj = nn - sti * tcur.cols;
+            const int stj = nn - sti * pc;
+            cnt = n0 < npix ? 8 : 0;
+            if (RAGGED && n0 < npix) cnt = min(8, a.g.n_tc > 1 ? tcur.cols - stj : npix - n0);
             return (uint32_t)seg_c * hw2 + ((uint32_t)(tcur.i0 + sti) * a.g.W + tcur.j0 + stj) * 2u;
         };
         // q segment of this wave's first pass
-        uint4_t qseg;
-        {
-            bool ok;
-            qseg = *(const uint4_t*)(qb + seg_offset(min(wave, npass - 1), ok));
-        }
+        auto load_q = [&](int pass) -> uint4_t {
+            int cnt;
+            const uint32_t off = seg_offset(pass, cnt);     // (valid even when the segment is not)
+            if (!RAGGED) return *(const uint4_t*)(qb + off);
+            if (off + 16u <= left) return *(const uint4_any_t*)(qb + off);
+            uint4_t v;
+            const bf16_bits* src = (const bf16_bits*)(qb + off);
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                const uint32_t lo = 2 * y < cnt ? src[2 * y] : 0, hi = 2 * y + 1 < cnt ? src[2 * y + 1] : 0;
+                v[y] = lo | (hi << 16);
+            }
+            return v;
+        };
+        uint4_t qseg = load_q(min(wave, npass - 1));
         __syncthreads();                                // buf is complete, buf_next is free
         if (tcur.m != m_loaded) {
             if (it > 0) {                               // the block moves on to another head
@@ -444,7 +498,7 @@ fwd16_pipe_kernel(const FwdArgs a)
             int n = pass * 16 + p;
             n = n < npix ? n : npix - 1;
             const int ti = (int)(((float)n + 0.5f) * inv_tw);
-            const int tj = n - ti * tcur.cols;
+            const int tj = n - ti * pc;
             // q segment -> per-lane channels through the wave's scratch
             uint32_t qraw[8];
             __builtin_amdgcn_wave_barrier();
@@ -454,19 +508,15 @@ fwd16_pipe_kernel(const FwdArgs a)
             for (int e = 0; e < 8; ++e) qraw[e] = *(const bf16_bits*)(wbuf + chan_row(8 * g + e) + p * 2);
             __builtin_amdgcn_wave_barrier();
             // q of the wave's next pass, then this pass's share of the next tile
-            {
-                bool ok;
-                const uint32_t off = seg_offset(min(pass + WAVES, npass - 1), ok);
-                qseg = *(const uint4_t*)(qb + off);     // (the offset is valid even when the segment is not)
-            }
+            qseg = load_q(min(pass + WAVES, npass - 1));
             uint4_t pre[4];
-            if (pass < sg.n_groups) share_load(a, tnext, sg, pass, lane, hw2, pre);
+            if (pass < sg.n_groups) share_load<RAGGED>(a, tnext, sg, pass, lane, hw2, pre, left_next);
 
             float o[8];
             half2_t qs[4];
             q_halves(qraw, qs);
             float* lse_dst = nullptr;
-            if (LSE && g == 0 && pass * 16 + p < npix)
+            if (LSE && g == 0 && pass * 16 + p < npix && (!RAGGED || tj < tcur.cols))
                 lse_dst = a.lse + tcur.head_base / D + (long)(tcur.i0 + ti) * a.g.W + tcur.j0 + tj;
             slide_pass<LSE>(buf, 2 * HC * 64, HC * 64, ti, tj, g, qs, A1, A2, bias2, a.scale_log2e, o, lse_dst);
 
@@ -482,15 +532,23 @@ fwd16_pipe_kernel(const FwdArgs a)
             // before the store, and nothing is left pending that a later wait would have to cover
             asm volatile("" :: "v"(qseg), "v"(pre[0]), "v"(pre[1]), "v"(pre[2]), "v"(pre[3]));
             {
-                bool ok;
-                const uint32_t off = seg_offset(pass, ok);
-                if (ok) *(uint4_t*)(ob + off) = ov;
+                int cnt;
+                const uint32_t off = seg_offset(pass, cnt);
+                if (!RAGGED) {
+                    if (cnt) *(uint4_t*)(ob + off) = ov;
+                } else if (cnt == 8) {
+                    *(uint4_any_t*)(ob + off) = ov;
+                } else {
+#pragma unroll
+                    for (int x = 0; x < 7; ++x)
+                        if (x < cnt) ((bf16_bits*)(ob + off))[x] = (bf16_bits)(ov[x >> 1] >> (16 * (x & 1)));
+                }
             }
         }
         // what the passes did not cover of the next tile (short tiles before tall ones)
         for (int hb = wave + ((npass - wave + WAVES - 1) / WAVES) * WAVES; hb < sg.n_groups; hb += WAVES) {
             uint4_t pre[4];
-            share_load(a, tnext, sg, hb, lane, hw2, pre);
+            share_load<RAGGED>(a, tnext, sg, hb, lane, hw2, pre, left_next);
             store_share(hb, pre);
             asm volatile("" :: "v"(pre[0]), "v"(pre[1]), "v"(pre[2]), "v"(pre[3]));
         }
@@ -528,7 +586,7 @@ size_t fwd_mfma_workspace_bytes(const Problem& p)
 }
 
 namespace f16path {
-// Which 3x3 kernel serves a problem.  The pipelined kernel needs 16-byte aligned rows and
+// Which 3x3 kernel serves a problem whose rows are 16-byte aligned.  The pipelined kernel needs 16-byte aligned rows and
 // pointers, at least two tiles per persistent block, and a tile buffer large enough to hold a
 // head's operand image plus the raw kernels it is gathered from (the block builds the image in
 // the tile buffer that is free at that moment).
@@ -540,6 +598,19 @@ static bool choose_pipelined(const Problem& p, bool aligned16, TilePlan& t)
                            t.buf_bytes >= IMG_RAW_AT + IMG_RAW_BYTES;
     if (!pipelined) t = plan_fwd(p, false);
     return pipelined;
+}
+
+// Rows that are no multiple of 8 pixels: the pipelined kernel's RAGGED form, whatever the number of tiles
+// (its blocks build the operand image themselves, so a small map is one launch instead of two).  One tile
+// per block against this, MI355X: 1 x 200x333, C=96, 3 heads 39 + 5 (image) -> 32 us; B=128, 28x28,
+// C=128, 4 heads 41 + 5 -> 42 us.
+// Without 16-byte aligned kernels, or on maps narrower than one 16-byte load: one tile per block.
+static bool choose_ragged(const Problem& p, const float* wk, const float* wv, TilePlan& t)
+{
+    if (p.W % 8 == 0 || p.W < 8 || ((uintptr_t)wk | (uintptr_t)wv) % 16 != 0) return false;
+    t = plan_fwd(p, true);
+    if (t.buf_bytes < IMG_RAW_AT + IMG_RAW_BYTES) t.buf_bytes = IMG_RAW_AT + IMG_RAW_BYTES;
+    return true;
 }
 
 }  // namespace f16path
@@ -577,7 +648,8 @@ hipError_t launch_fwd_mfma(const Problem& p, const void* q, const void* k, const
     if (fwd_ring_enabled() && fwd_ring_strip_supported(p, aligned))
         return launch_fwd_ring_strip(p, q, k, v, wk, wv, bias, out, lse, false, st);
     TilePlan t;
-    const bool pipelined = choose_pipelined(p, aligned, t);
+    const bool ragged = choose_ragged(p, wk, wv, t);
+    const bool pipelined = ragged || choose_pipelined(p, aligned, t);
     uint32_t* image = (uint32_t*)workspace;
     if (!pipelined)
         hipLaunchKernelGGL(prep_weights_kernel, dim3(S, (unsigned)p.heads), dim3(256), 0, st,
@@ -595,20 +667,23 @@ hipError_t launch_fwd_mfma(const Problem& p, const void* q, const void* k, const
     static LdsOptIn opt_in;
     hipError_t e = opt_in.ensure({(const void*)fwd16_kernel<FWD_WAVES>,
                                   (const void*)fwd16_pipe_kernel<0, false>, (const void*)fwd16_pipe_kernel<64, false>,
-                                  (const void*)fwd16_pipe_kernel<0, true>, (const void*)fwd16_pipe_kernel<64, true>},
+                                  (const void*)fwd16_pipe_kernel<0, true>, (const void*)fwd16_pipe_kernel<64, true>,
+                                  (const void*)fwd16_pipe_kernel<0, false, true>, (const void*)fwd16_pipe_kernel<0, true, true>},
                                  LDS_LIMIT);
     if (e != hipSuccess) return e;
     const long n_tiles = (long)t.TA + t.TB;
     if (pipelined) {
         const int lds_bytes = a.a_base + PIPE_WAVES * WAVE_SCRATCH;
-        const dim3 grid((unsigned)device_cu_count()), block(PIPE_WAVES * 64);
-#define SLIDE_PIPE(TWV)                                                                                      \
-        do {                                                                                                 \
-            if (lse) hipLaunchKernelGGL((fwd16_pipe_kernel<TWV, true>), grid, block, (size_t)lds_bytes, st, a);  \
-            else     hipLaunchKernelGGL((fwd16_pipe_kernel<TWV, false>), grid, block, (size_t)lds_bytes, st, a); \
+        const long n_cu = device_cu_count();
+        const dim3 grid((unsigned)(n_tiles < n_cu ? n_tiles : n_cu)), block(PIPE_WAVES * 64);
+#define SLIDE_PIPE(TWV, RAG)                                                                                      \
+        do {                                                                                                      \
+            if (lse) hipLaunchKernelGGL((fwd16_pipe_kernel<TWV, true, RAG>), grid, block, (size_t)lds_bytes, st, a);  \
+            else     hipLaunchKernelGGL((fwd16_pipe_kernel<TWV, false, RAG>), grid, block, (size_t)lds_bytes, st, a); \
         } while (0)
-        if (t.tw == 64) SLIDE_PIPE(64);
-        else            SLIDE_PIPE(0);
+        if (ragged)          SLIDE_PIPE(0, true);
+        else if (t.tw == 64) SLIDE_PIPE(64, false);
+        else                 SLIDE_PIPE(0, false);
 #undef SLIDE_PIPE
     } else {
         const int lds_bytes = a.a_base + FWD_WAVES * WAVE_SCRATCH;

@@ -269,6 +269,7 @@ inline TilePlan plan_tiles(const Problem& p, int lds_budget, int px_bytes_a, int
     TilePlan t;
     t.tw = p.W <= 64 ? p.W : 64;
     t.n_tc = (p.W + t.tw - 1) / t.tw;
+    if (t.n_tc > 1 && p.W % 8 != 0) t.tw = ((p.W + t.n_tc - 1) / t.n_tc + 7) & ~7;  // even shares, in whole staging chunks
     const int px_bytes = px_bytes_a + px_bytes_b + px_bytes_extra;
     int th_max = (lds_budget - 256) / (px_bytes * (t.tw + r2)) - r2;
     if (th_max < 1) th_max = 1;
@@ -279,7 +280,9 @@ inline TilePlan plan_tiles(const Problem& p, int lds_budget, int px_bytes_a, int
     // and the per-tile overhead)
     double best = 1e300;
     t.th = th_max; t.nA = p.H / th_max; t.nB = (p.H % th_max) ? 1 : 0; t.hb = p.H % th_max;
-    for (int th = th_max; th >= 1 && th >= th_max / 2; --th) {
+    // (tiles below half the tallest only where those would leave compute units without one)
+    const bool few = planes * ((p.H + th_max - 1) / th_max) < n_cu;
+    for (int th = th_max; th >= 1 && (few || th >= th_max / 2); --th) {
         for (int drop = 0; drop < 2; ++drop) {
             const int nA = p.H / th - drop;
             if (nA < 0) continue;
