@@ -45,6 +45,29 @@ __device__ __forceinline__ float lane_of(float x, int lane)
     return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), lane));
 }
 
+// four neighbouring elements at any element's address (the hardware takes unaligned vector loads and stores)
+template <typename T> struct Four;
+template <> struct Four<float> {
+    typedef f4 Any __attribute__((aligned(4)));
+    static __device__ __forceinline__ f4 load(const float* p) { return *(const Any*)p; }
+    static __device__ __forceinline__ void store(float* p, f4 v) { *(Any*)p = v; }
+};
+template <> struct Four<bf16_bits> {
+    typedef uint32_t Raw __attribute__((ext_vector_type(2)));
+    typedef Raw Any __attribute__((aligned(2)));
+    static __device__ __forceinline__ f4 load(const bf16_bits* p)
+    {
+        const Raw r = *(const Any*)p;
+        return f4{__uint_as_float(r[0] << 16), __uint_as_float(r[0] & 0xffff0000u),
+                  __uint_as_float(r[1] << 16), __uint_as_float(r[1] & 0xffff0000u)};
+    }
+    static __device__ __forceinline__ void store(bf16_bits* p, f4 v)
+    {
+        *(Any*)p = Raw{f32_to_bf16(v[0]) | (uint32_t)f32_to_bf16(v[1]) << 16,
+                       f32_to_bf16(v[2]) | (uint32_t)f32_to_bf16(v[3]) << 16};
+    }
+};
+
 // what is derived from x, y and v is formed after this point (keeps the compiler from reading every
 // tap and weight of a channel ahead of the first product)
 template <int N>

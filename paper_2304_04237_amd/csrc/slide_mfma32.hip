@@ -35,7 +35,9 @@ struct PixelArgs {
 // thread per pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: forward 335 -> 50
 // us, backward 503 -> 77 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 337 us; one
 // 14x14 map of 2 heads, forward: 18.9 -> 9.4 us.
-template <typename T, int KS, int PG, int CG, int CQ, bool BWD>
+// FOUR: a quad's channels are neighbours in memory (channels last, whole quads): one load, one store instead of
+// four (bf16, 3x3, B=64, 27x27, C=128, 4 heads: 84 -> 58 us per call; float32, B=32, 56x56, C=64: 123 -> 76).
+template <typename T, int KS, int PG, int CG, int CQ, bool BWD, bool FOUR>
 __global__ void __launch_bounds__(64 * PG * CG, CG > 1 ? 2 : (KS == 3 ? 4 : 2))
 pixel32_kernel(const PixelArgs a)
 {
@@ -98,6 +100,7 @@ pixel32_kernel(const PixelArgs a)
     // channels c..c+3 of the head (past d: the last one again, their weights are zeros)
     auto load4 = [&](const T* base, long o, int c) -> f4 {
         f4 r;
+        if (FOUR) return Four<T>::load(base + o + min(c, d - 4));
 #pragma unroll
         for (int u = 0; u < 4; ++u) r[u] = Elem<T>::load(base + o + (long)min(c + u, d - 1) * a.sc);
         return r;
@@ -266,12 +269,20 @@ pixel32_kernel(const PixelArgs a)
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
+            f4 ov;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 float o = p[SM] * last[e];
 #pragma unroll
                 for (int s = 0; s < SM; ++s) o = fmaf(p[s], acc[e][s / 4][s % 4], o);
-                if (live && c + e < d) Elem<T>::store(ob + (long)(c + e) * a.sc, f * o);
+                ov[e] = f * o;
+            }
+            if (FOUR) {
+                if (live) Four<T>::store(ob + c, ov);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (live && c + e < d) Elem<T>::store(ob + (long)(c + e) * a.sc, ov[e]);
             }
         });
     };
@@ -312,7 +323,7 @@ pixel32_kernel(const PixelArgs a)
     }
 }
 
-template <typename T, int KS, int PG, int CG, int CQ, bool BWD>
+template <typename T, int KS, int PG, int CG, int CQ, bool BWD, bool FOUR>
 static hipError_t launch_pixel(const Problem& p, PixelArgs& a, hipStream_t st)
 {
     using D = Dim<KS>;
@@ -322,21 +333,23 @@ static hipError_t launch_pixel(const Problem& p, PixelArgs& a, hipStream_t st)
     const size_t red = CG > 1 ? (size_t)CG * D::S * PX * sizeof(float) : 0;
     if (lds < red) lds = red;
     static LdsOptIn opt_in;
-    hipError_t e = opt_in.ensure({(const void*)pixel32_kernel<T, KS, PG, CG, CQ, BWD>}, 160 * 1024);
+    hipError_t e = opt_in.ensure({(const void*)pixel32_kernel<T, KS, PG, CG, CQ, BWD, FOUR>}, 160 * 1024);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(a.cut.ns * a.cut.runs), (unsigned)p.heads, (unsigned)p.B);
-    hipLaunchKernelGGL((pixel32_kernel<T, KS, PG, CG, CQ, BWD>), grid, dim3(64 * PG * CG), lds, st, a);
+    hipLaunchKernelGGL((pixel32_kernel<T, KS, PG, CG, CQ, BWD, FOUR>), grid, dim3(64 * PG * CG), lds, st, a);
     return hipGetLastError();
 }
 
-template <typename T, int KS, bool BWD>
+template <typename T, int KS, bool BWD, bool FOUR = false>
 static hipError_t launch_pixel_t(const Problem& p, PixelArgs& a, hipStream_t st)
 {
     // blocks of 256 pixels where those give every compute unit two; else 64 pixels whose channels
     // eight waves share
+    if constexpr (!BWD && !FOUR)
+        if (p.nhwc && p.d() % 4 == 0) return launch_pixel_t<T, KS, false, true>(p, a, st);
     const long blocks = (p.plane() + 255) / 256 * p.heads * p.B;
-    if (blocks >= 512) return launch_pixel<T, KS, 4, 1, KS == 3 ? 2 : 1, BWD>(p, a, st);
-    return launch_pixel<T, KS, 1, 8, 8, BWD>(p, a, st);
+    if (blocks >= 512) return launch_pixel<T, KS, 4, 1, KS == 3 ? 2 : 1, BWD, FOUR>(p, a, st);
+    return launch_pixel<T, KS, 1, 8, 8, BWD, FOUR>(p, a, st);
 }
 
 static PixelArgs pixel_args(const Problem& p, const void* q, const void* k, const void* v, const float* wk,
