@@ -7,6 +7,7 @@
 #include <initializer_list>
 #include <cmath>
 #include <mutex>
+#include "slide_plan.h"
 
 namespace slide {
 

@@ -78,25 +78,11 @@ __device__ __forceinline__ void pin(int& x, int& y, float (&v)[N])
     for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i]));
 }
 
-// How a plane is cut: column strips of TW (the last one narrower), each flattened row by row and
-// cut into runs of PX pixels, so that nearly every lane has a pixel whatever the map's width.  A run
-// touches NR - 2R rows; LDS holds those rows and the halo, RP = TW + 2R pixels each.
-struct Cut { int TW, ns, runs, NR, RP, npx; };
-
-inline Cut plan_cut(int H, int W, int PX, int R, int max_tw)
+// column strip of a plane: first column and width
+__device__ __forceinline__ void strip_of(const Cut& c, int strip, int& j0, int& tw)
 {
-    Cut c;
-    c.ns = (W + max_tw - 1) / max_tw;
-    c.TW = (W + c.ns - 1) / c.ns;
-    c.ns = (W + c.TW - 1) / c.TW;
-    c.runs = (int)(((long)H * c.TW + PX - 1) / PX);
-    const int narrow = W - (c.ns - 1) * c.TW;               // the last strip: its runs touch the most rows
-    int rows = (PX - 2) / narrow + 2;
-    if (rows > H) rows = H;
-    c.NR = rows + 2 * R;
-    c.RP = c.TW + 2 * R;
-    c.npx = c.NR * c.RP;
-    return c;
+    j0 = strip * c.TW + min(strip, c.wider);
+    tw = c.TW + (strip < c.wider);
 }
 
 }  // namespace m32

@@ -58,8 +58,8 @@ pixel32_kernel(const PixelArgs a)
     const int m = blockIdx.y, b = blockIdx.z;
     const long HW = (long)H * W;
     const int strip = blockIdx.x / a.cut.runs, run = blockIdx.x - strip * a.cut.runs;
-    const int j0 = strip * a.cut.TW;
-    const int tw = min(a.cut.TW, W - j0);
+    int j0, tw;
+    strip_of(a.cut, strip, j0, tw);
     const int n0 = run * PX;
     if (n0 >= H * tw) return;
     const int npx = a.cut.npx, RP = a.cut.RP;
@@ -338,33 +338,27 @@ pixel32_kernel(const PixelArgs a)
     }
 }
 
-template <typename T, int KS, int PG, int CG, int CQ, bool BWD, bool FOUR>
+template <typename T, int KS, bool FEW, bool BWD, bool FOUR>
 static hipError_t launch_pixel(const Problem& p, PixelArgs& a, hipStream_t st)
 {
-    using D = Dim<KS>;
-    constexpr int PX = 64 * PG;
-    a.cut = plan_cut(p.H, p.W, PX, D::R, 64 - 2 * D::R);
-    size_t lds = (size_t)CQ * (a.cut.npx * 4 + D::QUAD_W + PX * 4) * sizeof(float);
-    const size_t red = CG > 1 ? (size_t)CG * D::S * PX * sizeof(float) : 0;
-    if (lds < red) lds = red;
+    constexpr Block b = pixel_block(KS, FEW);
+    constexpr auto kernel = pixel32_kernel<T, KS, b.PG, b.CG, b.NQ, BWD, FOUR>;
+    a.cut = plan_cut(p.H, p.W, KS, b);
     static LdsOptIn opt_in;
-    hipError_t e = opt_in.ensure({(const void*)pixel32_kernel<T, KS, PG, CG, CQ, BWD, FOUR>}, 160 * 1024);
+    hipError_t e = opt_in.ensure({(const void*)kernel}, (int)CU_LDS_BYTES);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(a.cut.ns * a.cut.runs), (unsigned)p.heads, (unsigned)p.B);
-    hipLaunchKernelGGL((pixel32_kernel<T, KS, PG, CG, CQ, BWD, FOUR>), grid, dim3(64 * PG * CG), lds, st, a);
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * b.PG * b.CG), pixel_lds(a.cut, KS, b), st, a);
     return hipGetLastError();
 }
 
 template <typename T, int KS, bool BWD, bool FOUR = false>
 static hipError_t launch_pixel_t(const Problem& p, PixelArgs& a, hipStream_t st)
 {
-    // blocks of 256 pixels where those give every compute unit two; else 64 pixels whose channels
-    // eight waves share
     if constexpr (!BWD && !FOUR)
         if (p.nhwc && p.d() % 4 == 0) return launch_pixel_t<T, KS, false, true>(p, a, st);
-    const long blocks = (p.plane() + 255) / 256 * p.heads * p.B;
-    if (blocks >= 512) return launch_pixel<T, KS, 4, 1, KS == 3 ? 2 : 1, BWD, FOUR>(p, a, st);
-    return launch_pixel<T, KS, 1, 8, 8, BWD, FOUR>(p, a, st);
+    if (pixel_few(p.B, p.heads, p.H, p.W)) return launch_pixel<T, KS, true, BWD, FOUR>(p, a, st);
+    return launch_pixel<T, KS, false, BWD, FOUR>(p, a, st);
 }
 
 static PixelArgs pixel_args(const Problem& p, const void* q, const void* k, const void* v, const float* wk,

@@ -95,8 +95,8 @@ dkdv32_kernel(const DkdvArgs a)
     const int m = blockIdx.y, side = blockIdx.x & 1, b = blockIdx.z;
     const long HW = (long)H * W;
     const int strip = (blockIdx.x >> 1) / a.cut.runs, run = (blockIdx.x >> 1) - strip * a.cut.runs;
-    const int j0 = strip * a.cut.TW;
-    const int tw = min(a.cut.TW, W - j0);
+    int j0, tw;
+    strip_of(a.cut, strip, j0, tw);
     const int n0 = run * PX;
     if (n0 >= H * tw) return;
     const int npx = a.cut.npx, RP = a.cut.RP;
@@ -239,33 +239,24 @@ dkdv32_kernel(const DkdvArgs a)
     }
 }
 
-template <typename T, int KS, int PG, int CG, int NQ>
-static size_t dkdv_lds(const Cut& c)
-{
-    return (size_t)c.npx * (NQ * sizeof(typename Quad<T>::Raw) + Dim<KS>::S * sizeof(float)) + (size_t)NQ * Dim<KS>::QUAD_W * sizeof(float);
-}
-template <typename T, int KS, int PG, int CG, int NQ>
+template <typename T, int KS, bool FEW>
 static hipError_t launch_dkdv(const Problem& p, DkdvArgs& a, hipStream_t st)
 {
+    constexpr Block b = dkdv_block(KS, sizeof(T), FEW);
+    constexpr auto kernel = dkdv32_kernel<T, KS, b.PG, b.CG, b.NQ>;
+    a.cut = plan_cut(p.H, p.W, KS, b);
     static LdsOptIn opt_in;
-    hipError_t e = opt_in.ensure({(const void*)dkdv32_kernel<T, KS, PG, CG, NQ>}, 160 * 1024);
+    hipError_t e = opt_in.ensure({(const void*)kernel}, (int)CU_LDS_BYTES);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(2 * a.cut.ns * a.cut.runs), (unsigned)p.heads, (unsigned)p.B);
-    const size_t lds = dkdv_lds<T, KS, PG, CG, NQ>(a.cut);
-    hipLaunchKernelGGL((dkdv32_kernel<T, KS, PG, CG, NQ>), grid, dim3(64 * PG * CG), lds, st, a);
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * b.PG * b.CG), dkdv_lds(a.cut, KS, sizeof(T), b), st, a);
     return hipGetLastError();
 }
 template <typename T, int KS>
 static hipError_t launch_dkdv_t(const Problem& p, DkdvArgs& a, hipStream_t st)
 {
-    // blocks of 256 pixels where those give every compute unit two and two fit its LDS (maps of a
-    // few columns have tall runs with much halo); else 64 pixels whose channels four waves share
-    constexpr int NQ = KS == 3 ? (sizeof(T) == 2 ? 8 : 4) : (sizeof(T) == 2 ? 2 : 1);
-    const long blocks = (p.plane() + 255) / 256 * p.heads * 2 * p.B;
-    a.cut = plan_cut(p.H, p.W, 256, Dim<KS>::R, 64 - 2 * Dim<KS>::R);
-    if (blocks >= 512 && dkdv_lds<T, KS, 4, 1, NQ>(a.cut) <= 80 * 1024) return launch_dkdv<T, KS, 4, 1, NQ>(p, a, st);
-    a.cut = plan_cut(p.H, p.W, 64, Dim<KS>::R, 64 - 2 * Dim<KS>::R);
-    return launch_dkdv<T, KS, 1, 4, (KS == 3 ? 8 : 4)>(p, a, st);
+    if (dkdv_few(p.B, p.heads, p.H, p.W, KS, sizeof(T))) return launch_dkdv<T, KS, true>(p, a, st);
+    return launch_dkdv<T, KS, false>(p, a, st);
 }
 
 // ---- kernel and bias gradients

@@ -83,3 +83,9 @@ def test_against_oracle(shape, two_branch):
             _check(name, got, want, 1e-5, 0.0)
         else:
             _check(name, got, want, 2e-2, 1.0)
+
+
+@pytest.mark.parametrize("shape", [(1, 8, 2715, 4, 1, 5, "f32", False), (1, 32, 3600, 4, 1, 3, "f32", False), (1, 40, 3010, 8, 2, 5, "bf16", False)])
+def test_strips_of_wide_maps(shape):
+    """Widths whose strips of equal width would leave a last one of a few columns."""
+    test_against_oracle(shape, False)
