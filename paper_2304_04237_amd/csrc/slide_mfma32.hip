@@ -45,7 +45,7 @@ pixel32_kernel(const PixelArgs a)
     constexpr int S = D::S, SM = D::SM, SB = D::SB, R = D::R;
     constexpr int NT = 64 * PG * CG, PX = 64 * PG;
     constexpr int EW = 256, TG = NT / EW, QPT = CQ / TG;    // staging: EW pixels wide, TG quad groups, QPT quads per thread
-    constexpr int NI = 2;                                   // pixels per thread fetched ahead
+    constexpr int NI = KS == 5 && CG > 1 ? 1 : 2;           // pixels per thread fetched ahead (5x5, shared channels: two would spill registers)
     constexpr int NW = (CQ * 4 * S * S + NT - 1) / NT;      // weights per thread
     constexpr bool AHEAD_W = NW <= 24;
     static_assert(NT % EW == 0 && CQ % TG == 0 && CQ % CG == 0, "");
@@ -182,58 +182,76 @@ pixel32_kernel(const PixelArgs a)
         }
     };
 
-    // sums over shifts: acc[s] += sum over channels and taps of W[c,s,t] x[c] y[c,t]
-    auto contract = [&](const void* yp, const void* xp, const float* w, float (&sum)[S]) {
-        f4 acc[SB];
-        float last = 0.0f;
+    // win[e][s] = sum over taps of W[c+e,s,t] y[c+e,t] of a quad's four channels: the sums over shifts s < SM in
+    // acc[e], the last shift's in last[e]
+    auto window_sums = [&](int yo, int wo, f4 (&acc)[4][SB], float (&last)[4]) {
+        float wv[D::WV], wlast[D::LASTV];
 #pragma unroll
-        for (int i = 0; i < SB; ++i) acc[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-        phase(yp, xp, w, [&](int, int yo, int wo, const float* xq) {
-            const f4 x = *(const f4*)xq;
-            float wv[D::WV], wlast[D::LASTV];
-            // (a window row's sums start at zero and are added to the others' as a whole: one sum over all
-            // channels and taps would round more than the general kernels, which add a channel at a time; error of
-            // out against 64 bits, float32, 5x5, 28x28, 32 channels per head: 2.6e-7 as one sum, 2.0e-7 like this, 2.3e-7 there)
-            f4 part[SB];
-            float part_last;
+        for (int e = 0; e < 4; ++e) {
+            last[e] = 0.0f;
 #pragma unroll
-            for (int j = 0; j < D::LASTV; ++j) wlast[j] = smem[wo + loff[j]];
-            unroll<S>([&](auto tc) {
-                constexpr int t = decltype(tc)::value;
-                if (t % KS == 0) pin(yo, wo, wlast);        // (one window row in registers at a time)
-                if (t % D::UT == 0)
+            for (int i = 0; i < SB; ++i) acc[e][i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
 #pragma unroll
-                    for (int j = 0; j < D::WV; ++j) wv[j] = smem[wo + woff[j] + t];
-                const f4 yt = *(const f4*)(smem + yo + ((t / KS) * RP + t % KS) * 4);
-                if (t % KS == 0) {
-                    part_last = 0.0f;
+        for (int j = 0; j < D::LASTV; ++j) wlast[j] = smem[wo + loff[j]];
+        unroll<S>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            if (t % KS == 0) pin(yo, wo, wlast);            // (one window row in registers at a time)
+            if (t % D::UT == 0)
 #pragma unroll
-                    for (int i = 0; i < SB; ++i) part[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-                }
-                // (vector work first, then the matrix instructions back to back: between two of them a
-                // vector instruction costs the issue of about one more, measured)
-                const f4 g = x * yt;
-                unroll<4>([&](auto ec) {
-                    constexpr int e = decltype(ec)::value;
-                    part_last = fmaf(lane_of(wlast[(4 * t + e) / 64], (4 * t + e) % 64), g[e], part_last);
-                });
-                asm volatile("" : "+v"(part_last));
-                __builtin_amdgcn_sched_barrier(0);
-                unroll<4>([&](auto ec) {
-                    constexpr int e = decltype(ec)::value;
-                    outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, g[e], part);
-                });
-                __builtin_amdgcn_sched_barrier(0);
-                if (t % KS == KS - 1) {
-#pragma unroll
-                    for (int i = 0; i < SB; ++i) acc[i] += part[i];
-                    last += part_last;
-                }
+                for (int j = 0; j < D::WV; ++j) wv[j] = smem[wo + woff[j] + t];
+            const f4 yt = *(const f4*)(smem + yo + ((t / KS) * RP + t % KS) * 4);
+            // (vector work first, then the matrix instructions back to back: between two of them a
+            // vector instruction costs the issue of about one more, measured)
+            unroll<4>([&](auto ec) {
+                constexpr int e = decltype(ec)::value;
+                last[e] = fmaf(lane_of(wlast[(4 * t + e) / 64], (4 * t + e) % 64), yt[e], last[e]);
             });
+            asm volatile("" : "+v"(last[0]), "+v"(last[1]), "+v"(last[2]), "+v"(last[3]));
+            __builtin_amdgcn_sched_barrier(0);
+            unroll<4>([&](auto ec) {
+                constexpr int e = decltype(ec)::value;
+                outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, yt[e], acc[e]);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    // sums over shifts: sum[s] += sum over channels of x[c] * (sum over taps of W[c,s,t] y[c,t])
+    auto contract = [&](const void* yp, const void* xp, const float* w, float (&sum)[S]) {
+        // A channel's window is summed before x multiplies it, as in the general kernels, and the channels are added
+        // in fours, the fours in fours: their sum is what rounds most.  Error of out against 64 bits (2-norm), float32,
+        // merged kernels, 32 channels per head: 1.26e-7 (3x3, 56x56), 1.94e-7 (5x5, 28x28), the general kernels 1.26e-7 and
+        // 1.94e-7; with x multiplied in first and the rows of all quads added one by one 1.47e-7 and 2.36e-7, at the same time.
+        // (CG > 1: a wave has few quads, and the shares are added as a tree)
+        float part[S];
+        int left = 4;                                       // quads until part is added to the total, which lies in LDS
+        float* const total = xl + CQ * PX * 4 + pg * 64 + lane;     // [S][PX], CG == 1
+#pragma unroll
+        for (int s = 0; s < S; ++s) part[s] = 0.0f;
+        if (CG == 1)
+#pragma unroll
+            for (int s = 0; s < S; ++s) total[s * PX] = 0.0f;
+        phase(yp, xp, w, [&](int, int yo, int wo, const float* xq) {
+            f4 acc[4][SB];
+            float last[4];
+            window_sums(yo, wo, acc, last);
+            const f4 x = *(const f4*)xq;
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                float four = x[0] * (s < SM ? acc[0][s / 4 % SB][s % 4] : last[0]);
+#pragma unroll
+                for (int e = 1; e < 4; ++e) four = fmaf(x[e], s < SM ? acc[e][s / 4 % SB][s % 4] : last[e], four);
+                part[s] += four;
+            }
+            if (CG == 1 && --left == 0) {
+                left = 4;
+#pragma unroll
+                for (int s = 0; s < S; ++s) { total[s * PX] += part[s]; part[s] = 0.0f; }
+            }
         });
 #pragma unroll
-        for (int s = 0; s < SM; ++s) sum[s] = acc[s / 4][s % 4];
-        sum[SM] = last;
+        for (int s = 0; s < S; ++s) sum[s] = CG == 1 ? total[s * PX] + part[s] : part[s];
         if (CG > 1) {                                       // the channel groups' shares, added in a fixed order
             float* red = smem;                              // [CG][S][PX]
             __syncthreads();
@@ -242,9 +260,14 @@ pixel32_kernel(const PixelArgs a)
             __syncthreads();
 #pragma unroll
             for (int s = 0; s < S; ++s) {
-                sum[s] = 0.0f;
+                float r[CG];
 #pragma unroll
-                for (int c = 0; c < CG; ++c) sum[s] += red[(c * S + s) * PX + pg * 64 + lane];
+                for (int c = 0; c < CG; ++c) r[c] = red[(c * S + s) * PX + pg * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < CG; w *= 2)
+#pragma unroll
+                    for (int c = 0; c + w < CG; c += 2 * w) r[c] += r[c + w];
+                sum[s] = r[0];
                 asm volatile("" : "+v"(sum[s]) :: "memory");
             }
             // (the next phase starts with a barrier before it writes LDS)
@@ -256,34 +279,7 @@ pixel32_kernel(const PixelArgs a)
         phase(yp, nullptr, w, [&](int c, int yo, int wo, const float*) {
             f4 acc[4][SB];
             float last[4];
-            float wv[D::WV], wlast[D::LASTV];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                last[e] = 0.0f;
-#pragma unroll
-                for (int i = 0; i < SB; ++i) acc[e][i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            }
-#pragma unroll
-            for (int j = 0; j < D::LASTV; ++j) wlast[j] = smem[wo + loff[j]];
-            unroll<S>([&](auto tc) {
-                constexpr int t = decltype(tc)::value;
-                if (t % KS == 0) pin(yo, wo, wlast);        // (one window row in registers at a time)
-                if (t % D::UT == 0)
-#pragma unroll
-                    for (int j = 0; j < D::WV; ++j) wv[j] = smem[wo + woff[j] + t];
-                const f4 yt = *(const f4*)(smem + yo + ((t / KS) * RP + t % KS) * 4);
-                unroll<4>([&](auto ec) {
-                    constexpr int e = decltype(ec)::value;
-                    last[e] = fmaf(lane_of(wlast[(4 * t + e) / 64], (4 * t + e) % 64), yt[e], last[e]);
-                });
-                asm volatile("" : "+v"(last[0]), "+v"(last[1]), "+v"(last[2]), "+v"(last[3]));
-                __builtin_amdgcn_sched_barrier(0);
-                unroll<4>([&](auto ec) {
-                    constexpr int e = decltype(ec)::value;
-                    outer_blocks<((t % D::UT) * 4 + e) * SB>(wv, yt[e], acc[e]);
-                });
-                __builtin_amdgcn_sched_barrier(0);
-            });
+            window_sums(yo, wo, acc, last);
             f4 ov;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -315,24 +311,33 @@ pixel32_kernel(const PixelArgs a)
     for (int s = 0; s < S; ++s) { p[s] = expf(p[s] - mx); den += p[s]; }
     const float inv = 1.0f / den;
 #pragma unroll
-    for (int s = 0; s < S; ++s) p[s] *= inv;
+    for (int s = 0; s < S; ++s) {                           // p / den: the reciprocal's own rounding is taken out again
+        const float e = p[s];
+        p[s] = e * inv;
+        p[s] = fmaf(fmaf(-p[s], den, e), inv, p[s]);
+    }
     if (!BWD) {
         if (a.lse && live && cg == 0) a.lse[((long)b * (a.C / d) + m) * HW + pix] = mx + logf(den);
         expand(a.v, a.wv, p, 1.0f);
     } else {
+        // (p waits in a_ws while da is summed: the sums need the registers.  The barriers of `contract` order the
+        // stores before the other channel groups' loads)
+        float* const a_px = a.a_ws + ((long)b * (a.C / d) + m) * S * HW + pix;
+        float* const dl_px = a.dl_ws + ((long)b * (a.C / d) + m) * S * HW + pix;
+        if (live && cg == 0)
+#pragma unroll
+            for (int s = 0; s < S; ++s) a_px[(long)s * HW] = p[s];
         float da[S];
         contract(a.v, a.dout, a.wv, da);
+#pragma unroll
+        for (int s = 0; s < S; ++s) p[s] = a_px[(long)s * HW];
         float dsum = 0.0f;
 #pragma unroll
         for (int s = 0; s < S; ++s) dsum = fmaf(p[s], da[s], dsum);
-        const long ws = ((long)b * (a.C / d) + m) * S * HW + pix;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             da[s] = p[s] * (da[s] - dsum);
-            if (live && cg == 0) {
-                a.a_ws[ws + (long)s * HW] = p[s];
-                a.dl_ws[ws + (long)s * HW] = da[s];
-            }
+            if (live && cg == 0) dl_px[(long)s * HW] = da[s];
         }
         expand(a.k, a.wk, da, a.scale);
     }

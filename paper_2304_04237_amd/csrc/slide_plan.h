@@ -43,12 +43,13 @@ inline Cut plan_cut(int H, int W, int PX, int R, int max_tw)
 }
 inline Cut plan_cut(int H, int W, int ks, const Block& b) { return plan_cut(H, W, 64 * b.PG, ks / 2, 64 - 2 * (ks / 2)); }
 
-// LDS bytes of a block: tile, kernels and x of a step (or the channel groups' sums) ...
+// LDS bytes of a block: tile, kernels and x of a step, the pixels' sums over channels (where channel groups share a
+// pixel: those of every group, in the place of the step) ...
 inline size_t pixel_lds(const Cut& c, int ks, const Block& b)
 {
     const size_t S = (size_t)ks * ks, PX = 64 * (size_t)b.PG;
-    const size_t step = (size_t)b.NQ * ((size_t)c.npx * 4 + 4 * S * S + PX * 4), sums = b.CG > 1 ? (size_t)b.CG * S * PX : 0;
-    return (step > sums ? step : sums) * sizeof(float);
+    const size_t step = (size_t)b.NQ * ((size_t)c.npx * 4 + 4 * S * S + PX * 4), sums = (size_t)b.CG * S * PX;
+    return (b.CG == 1 ? step + sums : step > sums ? step : sums) * sizeof(float);
 }
 // ... tile and kernels of a step, a (or dl) of the tile
 inline size_t dkdv_lds(const Cut& c, int ks, int element_bytes, const Block& b)
