@@ -427,7 +427,7 @@ bwd_dw_partial_kernel(const T* __restrict__ dout, const T* __restrict__ q, const
 // Step 4: add the per-chunk partials.  A block handles 64 consecutive output entries (the
 // loads of a wave are 256 contiguous bytes); its 16 waves each add every 16th chunk in order,
 // with 8 loads in flight, and the 16 sums per entry are combined in a fixed order through
-// LDS, so the result does not depend on timing.  n = 2 * C*S*S entries.  Blocks past those
+// LDS, so the result does not depend on timing; both as trees, which round less than a running sum.  n = 2 * C*S*S entries.  Blocks past those
 // entries add the bias-gradient partials [n_chunks][nbias] the same way (nbias may be 0).
 constexpr int RED_GROUPS = 16;
 __global__ void __launch_bounds__(64 * RED_GROUPS)
@@ -452,17 +452,20 @@ bwd_dw_reduce_kernel(const float* __restrict__ partial, float* __restrict__ dwk,
             const int ch = base + u * RED_GROUPS;
             x[u] = (live && ch < n_chunks) ? src[(long)ch * n + e] : 0.0f;
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += x[u];
+        acc += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
     }
     part[grp][el] = acc;
     __syncthreads();
     if (grp == 0 && live) {
-        float sum = part[0][el];
+        float sum[RED_GROUPS];
 #pragma unroll
-        for (int g2 = 1; g2 < RED_GROUPS; ++g2) sum += part[g2][el];
+        for (int g2 = 0; g2 < RED_GROUPS; ++g2) sum[g2] = part[g2][el];
+#pragma unroll
+        for (int w = 1; w < RED_GROUPS; w *= 2)
+#pragma unroll
+            for (int g2 = 0; g2 < RED_GROUPS; g2 += 2 * w) sum[g2] += sum[g2 + w];
         float* dst = bias_job ? dbias + e : (e < side ? dwk + e : dwv + (e - side));
-        *dst = accumulate ? *dst + sum : sum;
+        *dst = accumulate ? *dst + sum[0] : sum[0];
     }
 }
 

@@ -32,7 +32,6 @@ struct Problem {
 // Compute units of the current device, read from the runtime once per device and process
 // (thread-safe).  MAX_CU_PLANNED when the query fails; never more than MAX_CU_PLANNED, which is
 // what the host-only workspace query sizes per-block partial results for.
-constexpr int MAX_CU_PLANNED = 256;
 int device_cu_count();
 
 // Opt-in of a set of kernels to `bytes` of dynamic LDS: the attribute belongs to the device that

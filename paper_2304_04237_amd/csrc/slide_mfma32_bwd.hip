@@ -275,12 +275,8 @@ struct DwArgs {
     long tiles;                             // all of them, over the batch
     int chunks;
     int KST, QST;                           // floats per channel of the y and x tiles in LDS
+    int group;                              // quads of a walker between two additions to its totals
 };
-
-constexpr int DW_CH = 32;                   // channels per block
-constexpr int DW_ZEROS = 160;               // as many as the taps of a quad span: 4 * 36 + 8
-
-constexpr int dw_max_rows(int ks) { return ks == 3 ? 8 : 6; }   // rows of a tile at most
 
 // pixels x..x+3 of row y, zeros outside the map and where !ok, by one load from wherever the row
 // starts (the hardware takes any element's address); VEC: W % 4 == 0, a quad is whole.  Otherwise the last
@@ -309,24 +305,32 @@ template <typename T, bool VEC> struct Row4 {
 // half of the wave one of two walkers over the tile's quads of four pixels; per pixel the products
 // x * y of the taps are formed once and the matrix cores multiply them with S - 1 shifts' dl (or a),
 // four rows at a time, broadcast inside a half (cbsz = 3); the last shift is a vector
-// multiply-add.  The S^2 sums of a channel stay in registers: all 81 of a 3x3 window in
-// each of the four waves, which share the pixels; with a 5x5 window a wave holds six taps and the
-// four waves see the same pixels (tap 24 is dealt out by blocks of shifts).  MI355X, against one block
-// per channel and shift (slide_generic.hip) and a launch of its own for dbias: float32, 3x3, B=32,
-// 56x56, C=64, 2 heads: 598 -> 59 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: 6875 -> 174 us; bf16, 3x3,
-// B=128, 28x28, C=128, 4 heads: 1854 -> 86 us (160 with each tile loaded when its turn comes and the waves'
-// sums added one wave after the other, 101 with vector and matrix instructions mixed).
+// multiply-add.  The S^2 sums of a channel stay in registers: all 81 of a 3x3 window in each of four waves,
+// which share the pixels; with a 5x5 window a wave holds three taps and eight waves see the same pixels (tap
+// 24 is dealt out by blocks of four shifts).
+// A running sum over a whole chunk would round with every pixel, so a walker's sums start at zero every few quads
+// (a.group; the first products need no accumulator, so that is free) and are added to totals, two values to a
+// register: the halves of the wave are summed on the way, the lower lanes keep one value, the upper ones the
+// next.  The totals take the registers that tiles of eight rows and, at 5x5, six taps per wave had.  A vector
+// instruction costs 5.6 cycles between the matrix instructions (by the counters), which is why the quad's
+// addresses are 24-bit arithmetic and only the waves that sum dbias do so.  MI355X, against one block per channel and shift
+// (slide_generic.hip) and a launch of its own for dbias: float32, 3x3, B=32, 56x56, C=64, 2 heads: 598 -> 61 us; bf16,
+// 5x5, B=64, 28x28, C=128, 4 heads: 6875 -> 223 us; bf16, 3x3, B=128, 28x28, C=128, 4 heads: 1854 -> 94 us.  With
+// running sums over the chunk they took 62, 195 and 88 us.  Error of dwv against 64 bits (2-norm, two-branch; those kernels,
+// the running sums, these): 3x3 float32 as above 1.91, 2.47, 1.61e-7; 5x5 as above in float32 2.56, 4.11, 2.26e-7.
 template <typename T, int KS, bool VEC>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(dw_threads(KS), 2)
 dw32_kernel(const DwArgs a)
 {
     using D = Dim<KS>;
     constexpr int S = D::S, SM = D::SM, SB = D::SB, R = D::R;
-    constexpr int ROLES = KS == 3 ? 1 : 4, NTAP = KS == 3 ? 9 : 6;
-    constexpr bool EXTRA = KS == 5;                         // tap 24: two blocks of shifts in each of waves 0..2
-    constexpr int WALK = 8 / ROLES;
+    constexpr int NT = dw_threads(KS), WAVES = NT / 64;
+    constexpr int ROLES = KS == 3 ? 1 : 8, NTAP = KS == 3 ? 9 : 3;
+    constexpr bool EXTRA = KS == 5;                         // tap 24: a block of shifts in each of waves 0..5, the last shift in wave 6
+    constexpr int WALK = 2 * WAVES / ROLES;
     constexpr int AR = 4 * SM / 32;                         // registers of the four pixels' shifts
     constexpr int AQ = 4 * SM + 1;                          // floats per quad in LDS (odd: the quads' writes spread over the banks)
+    constexpr int NV = NTAP * S + (EXTRA ? 5 : 0), NP = (NV + 1) / 2;   // a lane's sums, totals
 
     extern __shared__ __align__(16) float smem_raw[];
     float* const smem = smem_raw;
@@ -349,44 +353,61 @@ dw32_kernel(const DwArgs a)
     const T* xb = (const T*)a.x[side];
     const float* pb = a.p[side];
 
-    f4 acc[NTAP][SB];
-    float last[NTAP];
+    // sums of a group: value v < NTAP * S is shift v % S of tap v / S of this wave, the others are tap 24's
+    f4 acc[NTAP][SB], xacc;
+    float last[NTAP], xlast = 0.0f;
+    float bsum[AR] = {}, blast = 0.0f;
+    float total[NP], btotal[AR], bltotal = 0.0f;
 #pragma unroll
-    for (int i = 0; i < NTAP; ++i) {
-        last[i] = 0.0f;
+    for (int j = 0; j < NP; ++j) total[j] = 0.0f;
 #pragma unroll
-        for (int s = 0; s < SB; ++s) acc[i][s] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-    f4 xacc[2] = {f4{0.0f, 0.0f, 0.0f, 0.0f}, f4{0.0f, 0.0f, 0.0f, 0.0f}};
-    float xlast = 0.0f;
-    float bsum[AR], blast = 0.0f;
-#pragma unroll
-    for (int j = 0; j < AR; ++j) bsum[j] = 0.0f;
+    for (int j = 0; j < AR; ++j) btotal[j] = 0.0f;
+    const bool sums_bias = side == 0 && cb == 0 && role == 0 && a.bias_partial;
+    const int y_at = ch * a.KST, x_at = DW_CH * a.KST + ch * a.QST, l_at = (int)(ll - smem), zero_at = (int)(zl - smem), a_at = (int)(al - smem);
     int toff[NTAP];
 #pragma unroll
     for (int i = 0; i < NTAP; ++i) {
         const int t = role * NTAP + i;
         toff[i] = (t / KS) * RS + t % KS;
     }
+    auto add_group = [&]() {
+        unroll<NP>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            auto value = [&](auto vc) -> float {
+                constexpr int v = decltype(vc)::value;
+                if constexpr (v < NTAP * S) {
+                    if constexpr (v % S < SM) return acc[v / S][v % S / 4][v % S % 4];
+                    else return last[v / S];
+                } else if constexpr (v < NTAP * S + 4 && v < NV) return xacc[v - NTAP * S];
+                else if constexpr (v < NV) return xlast;
+                else return 0.0f;
+            };
+            const auto swapped = __builtin_amdgcn_permlane32_swap(__float_as_uint(value(std::integral_constant<int, 2 * j>{})),
+                                                                  __float_as_uint(value(std::integral_constant<int, 2 * j + 1>{})), false, false);
+            total[j] += __uint_as_float(swapped[0]) + __uint_as_float(swapped[1]);
+        });
+        if (sums_bias) {
+#pragma unroll
+            for (int j = 0; j < AR; ++j) btotal[j] += bsum[j];
+            bltotal += blast;
+        }
+    };
 
     if (tid < DW_ZEROS) zl[tid] = 0.0f;
-    // staging: eight lanes per channel, one column quad each
-    const int sch = tid >> 3, sq = tid & 7;
+    // staging: LN lanes per channel, of which 2^w.lg (>= the tile's quads per row) take a row
+    constexpr int LN = NT / DW_CH;
+    const int sch = tid / LN, sl = tid % LN;
     const bool sc_live = cb * DW_CH + sch < d;
     const long chan = (long)m * d + min(cb * DW_CH + sch, d - 1);
 
-    // a tile's elements on their way from memory to LDS.  With a 3x3 window there are registers left to
-    // fetch the next tile while this one is multiplied.
-    constexpr bool AHEAD = KS == 3;
-    constexpr int MAX_TR = dw_max_rows(KS);
-    constexpr int YR = MAX_TR + 2 * R, XR = MAX_TR;   // rows of y and x
-    constexpr int HL = 2 * R, RPI = 8 / HL, HR = (YR + RPI - 1) / RPI;      // halo columns; rows of them per step, steps
-    constexpr int PR = (S * MAX_TR + 31) / 32;           // rows of dl (or a): 32 at a time
+    // a tile's elements on their way from memory to LDS: fetched while the tile before is multiplied
+    constexpr DwLoads LOADS = dw_loads(KS, sizeof(T), VEC);
+    constexpr int HL = 2 * R, RPI = LN / HL, HR = (DW_MAX_ROWS + 2 * R + RPI - 1) / RPI;    // halo columns; rows of them per step, steps
     using Raw = typename Quad<T>::Raw;
-    Raw yv[YR], xv[XR];
+    Raw yv[LOADS.y], xv[LOADS.x];
     T hv[HR];
-    f4 pv[PR];
-    struct Where { long b; int y0, x0, th, tw, qpr; };
+    f4 pv[LOADS.p];
+    struct Where { long b; int y0, x0, th, tw, qpr, lg; };
     auto locate = [&](long tile) -> Where {
         Where w;
         w.b = tile / (a.ntr * a.ntc);
@@ -395,82 +416,81 @@ dw32_kernel(const DwArgs a)
         w.y0 = ty * TR; w.x0 = tx * TC;
         w.th = min(TR, H - w.y0); w.tw = min(TC, W - w.x0);
         w.qpr = (w.tw + 3) >> 2;
+        w.lg = dw_row_lanes_log2(w.qpr);
         return w;
     };
-    auto fetch_y = [&](const Where& w) {
+    // n / by for n < 1024, by <= 8 (24-bit multiplications: a vector instruction costs 5-6 cycles between the matrix
+    // instructions, a 32-bit product four times that)
+    auto inverse = [](int by) -> unsigned { return (65536u + by - 1) / by; };
+    auto divided = [](int n, unsigned inv) -> int { return (int)(__umul24((unsigned)n, inv) >> 16); };
+    auto fetch = [&](const Where& w) {
         const T* yc = yb + (w.b * a.C + chan) * HW;
+        const T* xc = xb + (w.b * a.C + chan) * HW;
         const long left = (a.items * a.C - (w.b * a.C + chan)) * HW;
-        const int x = w.x0 + 4 * sq;
-        const bool col = sc_live && sq < w.qpr;
+        const int r0 = sl >> w.lg, step = LN >> w.lg, q = sl & ((1 << w.lg) - 1), x = w.x0 + 4 * q;
+        const bool col = sc_live && q < w.qpr;
 #pragma unroll
-        for (int i = 0; i < YR; ++i) {
-            const int y = w.y0 + i - R;
-            yv[i] = Row4<T, VEC>::load(yc, y, x, W, col && i < w.th + 2 * R && y >= 0 && y < H, left);
+        for (int i = 0; i < LOADS.y; ++i) {
+            const int rr = r0 + i * step, y = w.y0 + rr - R;
+            yv[i] = Row4<T, VEC>::load(yc, y, x, W, col && rr < w.th + 2 * R && y >= 0 && y < H, left);
         }
         // the R columns on each side of the tile's 4 * qpr
 #pragma unroll
         for (int i = 0; i < HR; ++i) {
-            const int rr = sq / HL + i * RPI, h = sq % HL;
+            const int rr = sl / HL + i * RPI, h = sl % HL;
             const int y = w.y0 + rr - R, xx = w.x0 + (h < R ? h - R : 4 * w.qpr + h - R);
             const bool in = sc_live && rr < w.th + 2 * R && y >= 0 && y < H && xx >= 0 && xx < W;
             hv[i] = in ? yc[(long)y * W + xx] : T(0);
         }
-    };
-    auto fetch_x = [&](const Where& w) {
-        const T* xc = xb + (w.b * a.C + chan) * HW;
-        const long left = (a.items * a.C - (w.b * a.C + chan)) * HW;
-        const int x = w.x0 + 4 * sq;
-        const bool col = sc_live && sq < w.qpr;
 #pragma unroll
-        for (int i = 0; i < XR; ++i) xv[i] = Row4<T, VEC>::load(xc, w.y0 + i, x, W, col && i < w.th, left);
-        const uint32_t inv = (65536u + w.th - 1) / w.th;
+        for (int i = 0; i < LOADS.x; ++i) xv[i] = Row4<T, VEC>::load(xc, w.y0 + r0 + i * step, x, W, col && r0 + i * step < w.th, left);
+        const unsigned ir = inverse(w.th);
 #pragma unroll
-        for (int i = 0; i < PR; ++i) {
-            const int n = i * 32 + sch;
-            const int sh = (int)((n * inv) >> 16), rr = n - sh * w.th;
+        for (int i = 0; i < LOADS.p; ++i) {
+            const int r = (tid >> w.lg) + i * (NT >> w.lg), sh = divided(r, ir), rr = r - sh * w.th;
             const long plane = (w.b * a.heads + m) * S + min(sh, SM);
-            pv[i] = Row4<float, VEC>::load(pb + plane * HW, w.y0 + rr, x, W, n < S * w.th && sq < w.qpr, (a.items * a.heads * S - plane) * HW);
+            pv[i] = Row4<float, VEC>::load(pb + plane * HW, w.y0 + rr, x, W, sh < S && q < w.qpr, (a.items * a.heads * S - plane) * HW);
         }
     };
-    auto put_y = [&](const Where& w) {
-        if (sq < w.qpr) {
-#pragma unroll
-            for (int i = 0; i < YR; ++i)
-                if (i < w.th + 2 * R) {
-                    float* o = yl + sch * a.KST + i * RS + R + 4 * sq;
-                    const f4 v = Row4<T, VEC>::cut(yv[i], w.x0 + 4 * sq, W);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = v[e];
-                }
-        }
+    auto put = [&](const Where& w) {
+        const int r0 = sl >> w.lg, step = LN >> w.lg, q = sl & ((1 << w.lg) - 1), x = w.x0 + 4 * q;
 #pragma unroll
         for (int i = 0; i < HR; ++i) {
-            const int rr = sq / HL + i * RPI, h = sq % HL;
+            const int rr = sl / HL + i * RPI, h = sl % HL;
             if (rr < w.th + 2 * R) yl[sch * a.KST + rr * RS + (h < R ? h : 4 * w.qpr + h)] = Elem<T>::load(&hv[i]);
         }
-    };
-    auto put_x = [&](const Where& w) {
-        if (sq >= w.qpr) return;
+        if (q >= w.qpr) return;
 #pragma unroll
-        for (int i = 0; i < XR; ++i)
-            if (i < w.th) {
-                float* o = xl + sch * a.QST + i * TC + 4 * sq;
-                const f4 v = Row4<T, VEC>::cut(xv[i], w.x0 + 4 * sq, W);
+        for (int i = 0; i < LOADS.y; ++i) {
+            const int rr = r0 + i * step;
+            if (rr < w.th + 2 * R) {
+                float* o = yl + sch * a.KST + rr * RS + R + 4 * q;
+                const f4 v = Row4<T, VEC>::cut(yv[i], x, W);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) o[e] = v[e];
             }
-        const uint32_t inv = (65536u + w.th - 1) / w.th;
+        }
 #pragma unroll
-        for (int i = 0; i < PR; ++i) {
-            const int n = i * 32 + sch;
-            const int sh = (int)((n * inv) >> 16), rr = n - sh * w.th;
-            if (n < S * w.th) {
-                const int q = rr * w.qpr + sq;
-                const f4 v = Row4<float, VEC>::cut(pv[i], w.x0 + 4 * sq, W);
+        for (int i = 0; i < LOADS.x; ++i) {
+            const int rr = r0 + i * step;
+            if (rr < w.th) {
+                float* o = xl + sch * a.QST + rr * TC + 4 * q;
+                const f4 v = Row4<T, VEC>::cut(xv[i], x, W);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = v[e];
+            }
+        }
+        const unsigned ir = inverse(w.th);
+#pragma unroll
+        for (int i = 0; i < LOADS.p; ++i) {
+            const int r = (tid >> w.lg) + i * (NT >> w.lg), sh = divided(r, ir), rr = r - sh * w.th;
+            if (sh < S) {
+                const int qi = rr * w.qpr + q;
+                const f4 v = Row4<float, VEC>::cut(pv[i], x, W);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    if (sh < SM) al[q * AQ + e * SM + sh] = v[e];
-                    else ll[q * 4 + e] = v[e];
+                    if (sh < SM) al[qi * AQ + e * SM + sh] = v[e];
+                    else ll[qi * 4 + e] = v[e];
                 }
             }
         }
@@ -478,49 +498,39 @@ dw32_kernel(const DwArgs a)
 
     const long t0 = a.tiles * chunk / a.chunks, t1 = a.tiles * (chunk + 1) / a.chunks;
     Where at{}, next{};
-    if (t0 < t1) next = locate(t0);
-    if (AHEAD && t0 < t1) { fetch_y(next); fetch_x(next); }
+    if (t0 < t1) { next = locate(t0); fetch(next); }
     for (long tile = t0; tile < t1; ++tile) {
         at = next;
-        if (!AHEAD) fetch_y(at);
         __syncthreads();                                    // the tile before is no longer read
-        put_y(at);
-        if (!AHEAD) {
-            __builtin_amdgcn_sched_barrier(0);
-            fetch_x(at);
-        }
-        put_x(at);
-        if (tile + 1 < t1) {
-            next = locate(tile + 1);
-            if (AHEAD) { fetch_y(next); fetch_x(next); }
-        }
+        put(at);
+        if (tile + 1 < t1) { next = locate(tile + 1); fetch(next); }
         __syncthreads();
         const int tw = at.tw, qpr = at.qpr, nq = at.th * at.qpr;
 
-        const uint32_t inv = (65536u + qpr - 1) / qpr;      // qi / qpr for qi < 256 (qpr <= 8)
-        for (int q0 = 0; q0 < nq; q0 += WALK) {
+        const unsigned iq = inverse(qpr);
+        // one quad of each walker; FIRST of a group: the sums start with its products
+        auto round = [&](auto first, int q0) {
+            constexpr bool FIRST = decltype(first)::value;
             const int qi = min(q0 + walker, nq - 1);
             const bool mine = q0 + walker < nq;
-            const int row = (int)((qi * inv) >> 16), qx = qi - row * qpr;
-            const int live = mine ? min(4, tw - 4 * qx) : 0;    // pixels of the quad
+            const int row = divided(qi, iq);
+            const int live = VEC ? 4 : mine ? min(4, tw - 4 * (qi - __mul24(row, qpr))) : 0;   // pixels of the quad
             // (products of pixels that are none must be zeros also where a neighbour is infinite: rows that
-            // are no whole quads are masked, a walker past the last quad reads zeros)
-            const float* yq = VEC && !mine ? zl : yl + ch * a.KST + row * RS + 4 * qx;
-            const float* xq = VEC && !mine ? zl : xl + ch * a.QST + row * TC + 4 * qx;
+            // are no whole quads are masked, a walker past the last quad reads zeros, of dl and a too)
+            const float* yq = smem + (VEC && !mine ? zero_at : y_at + 4 * qi + __mul24(row, RS - 4 * qpr));
+            const float* xq = smem + (VEC && !mine ? zero_at : x_at + 4 * qi + __mul24(row, TC - 4 * qpr));
+            const float* aq = smem + (mine ? a_at + __mul24(qi, AQ) : zero_at);
             float A[AR];
 #pragma unroll
-            for (int j = 0; j < AR; ++j) {
-                const float v = al[qi * AQ + j * 32 + ch];
-                A[j] = mine ? v : 0.0f;
-                bsum[j] += A[j];
-            }
-            f4 L = *(const f4*)(ll + qi * 4);
-            if (!mine) L = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            blast += ch < 4 ? L[ch & 3] : 0.0f;
-            float A2 = 0.0f;
-            if (EXTRA) {
-                const float v = al[qi * AQ + (ch >> 3) * SM + min(role * 8, SM - 8) + (ch & 7)];
-                A2 = mine ? v : 0.0f;
+            for (int j = 0; j < AR; ++j) A[j] = aq[j * 32 + ch];
+            const f4 L = *(const f4*)(smem + (mine ? l_at + 4 * qi : zero_at));
+            float A2 = 0.0f;                                // lanes 4e..4e+3: pixel e, this wave's four shifts of tap 24
+            if (EXTRA) A2 = aq[((ch >> 2) & 3) * SM + min(role * 4, SM - 4) + (ch & 3)];
+            if (sums_bias) {
+#pragma unroll
+                for (int j = 0; j < AR; ++j) bsum[j] = FIRST ? A[j] : bsum[j] + A[j];
+                const float l = ch < 4 ? L[ch & 3] : 0.0f;
+                blast = FIRST ? l : blast + l;
             }
             float x[4], y[NTAP][4], ye[4];
 #pragma unroll
@@ -547,69 +557,68 @@ dw32_kernel(const DwArgs a)
             // a pixel's vector work comes first, then its matrix instructions back to back)
             unroll<4>([&](auto ec) {
                 constexpr int e = decltype(ec)::value;
+                constexpr bool NEW = FIRST && e == 0;
+                const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
                 float g[NTAP], ge = 0.0f;
 #pragma unroll
                 for (int i = 0; i < NTAP; ++i) {
                     g[i] = x[e] * y[i][e];
                     if (!VEC) g[i] = e < live ? g[i] : 0.0f;
-                    last[i] = fmaf(L[e], g[i], last[i]);
+                    last[i] = NEW ? L[e] * g[i] : fmaf(L[e], g[i], last[i]);
                 }
                 if (EXTRA) {
                     ge = x[e] * ye[e];
                     if (!VEC) ge = e < live ? ge : 0.0f;
-                    xlast = fmaf(L[e], ge, xlast);
+                    xlast = NEW ? L[e] * ge : fmaf(L[e], ge, xlast);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 unroll<NTAP>([&](auto ic) {
                     constexpr int i = decltype(ic)::value;
                     unroll<SB>([&](auto sc) {
-                        constexpr int blk = e * SB + decltype(sc)::value;
-                        acc[i][decltype(sc)::value] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[blk / 8], g[i], acc[i][decltype(sc)::value], 3, blk % 8, 0);
+                        constexpr int sb = decltype(sc)::value, blk = e * SB + sb;
+                        acc[i][sb] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[blk / 8], g[i], NEW ? zero : acc[i][sb], 3, blk % 8, 0);
                     });
                 });
-                if (EXTRA) {
-                    xacc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, ge, xacc[0], 3, e * 2, 0);
-                    xacc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, ge, xacc[1], 3, e * 2 + 1, 0);
-                }
+                if (EXTRA) xacc = __builtin_amdgcn_mfma_f32_4x4x1f32(A2, ge, NEW ? zero : xacc, 3, e, 0);
                 __builtin_amdgcn_sched_barrier(0);
             });
+        };
+        for (int q0 = 0; q0 < nq;) {
+            const int end = min(nq, q0 + a.group * WALK);
+            round(std::true_type{}, q0);
+            for (q0 += WALK; q0 < end; q0 += WALK) round(std::false_type{}, q0);
+            add_group();
         }
     }
 
-    // the two walkers of a wave, then (3x3) the four waves in order, through LDS [wave][channel][s][t]
-    constexpr int NRED = KS == 3 ? 4 : 1;
-    float* red = smem + (KS == 3 ? wave : 0) * DW_CH * S * S;
+    // the waves' totals through LDS [wave][channel][s][t] (5x5: one such array, a wave writes its taps)
+    constexpr int NRED = KS == 3 ? WAVES : 1;
+    float* red = smem + (KS == 3 ? wave : 0) * DW_CH * S * S + ch * (S * S);
     const float f = a.f[side];
     __syncthreads();
-    {
-        auto add = [&](int sh, int t, float v) {
-            const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-            v = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
-            if (half == 0) red[ch * (S * S) + sh * S + t] = v;
-        };
-#pragma unroll
-        for (int i = 0; i < NTAP; ++i) {
-#pragma unroll
-            for (int sh = 0; sh < SM; ++sh) add(sh, role * NTAP + i, acc[i][sh / 4][sh % 4]);
-            add(SM, role * NTAP + i, last[i]);
+    unroll<NP>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        int at_[2]; bool ok[2];
+        for (int h = 0; h < 2; ++h) {
+            const int v = 2 * j + h, x = v - NTAP * S;
+            if (x < 0) { at_[h] = (v % S) * S + role * NTAP + v / S; ok[h] = true; }
+            else if (x < 4) { at_[h] = (role * 4 + x) * S + 24; ok[h] = EXTRA && role < 6; }
+            else { at_[h] = SM * S + 24; ok[h] = EXTRA && x == 4 && role == 6; }
         }
-        if (EXTRA) {
-            if (role < 3) {
-#pragma unroll
-                for (int sh = 0; sh < 8; ++sh) add(role * 8 + sh, 24, xacc[sh / 4][sh % 4]);
-            } else {
-                add(SM, 24, xlast);
-            }
-        }
-    }
+        if (half ? ok[1] : ok[0]) red[half ? at_[1] : at_[0]] = total[j];
+    });
     __syncthreads();
     const int nch = min(DW_CH, d - cb * DW_CH);
     float* out = a.partial + (((long)chunk * 2 + side) * a.C + (long)m * d + cb * DW_CH) * S * S;
-    for (int i = tid; i < nch * S * S; i += 256) {
-        float sum = smem[i];
+    for (int i = tid; i < nch * S * S; i += NT) {
+        float sum[NRED];
 #pragma unroll
-        for (int w = 1; w < NRED; ++w) sum += smem[w * DW_CH * S * S + i];
-        out[i] = f * sum;
+        for (int w = 0; w < NRED; ++w) sum[w] = smem[w * DW_CH * S * S + i];
+#pragma unroll
+        for (int w = 1; w < NRED; w *= 2)
+#pragma unroll
+            for (int c = 0; c + w < NRED; c += 2 * w) sum[c] += sum[c + w];
+        out[i] = f * sum[0];
     }
 
     if (side == 0 && cb == 0 && a.bias_partial) {
@@ -617,57 +626,32 @@ dw32_kernel(const DwArgs a)
         // [wave][half][pixel x shift], then the last shift's four pixels
         constexpr int BW = 4 * SM + 4;
         float* bl = smem + (wave * 2 + half) * BW;
+        if (role == 0) {
 #pragma unroll
-        for (int j = 0; j < AR; ++j) bl[j * 32 + ch] = bsum[j];
-        if (ch < 4) bl[4 * SM + ch] = blast;
+            for (int j = 0; j < AR; ++j) bl[j * 32 + ch] = btotal[j];
+            if (ch < 4) bl[4 * SM + ch] = bltotal;
+        }
         __syncthreads();
         if (tid < S) {
             float sum = 0.0f;
-            for (int w = 0; w < (KS == 3 ? 8 : 2); ++w)     // (5x5: the waves saw the same pixels)
-                for (int e = 0; e < 4; ++e) sum += smem[w * BW + (tid < SM ? e * SM + tid : 4 * SM + e)];
+            for (int w = 0; w < WALK; ++w) {                // (5x5: the waves saw the same pixels)
+                float four = 0.0f;
+                for (int e = 0; e < 4; ++e) four += smem[w * BW + (tid < SM ? e * SM + tid : 4 * SM + e)];
+                sum += four;
+            }
             a.bias_partial[((long)chunk * a.heads + m) * S + tid] = sum;
         }
     }
-}
-
-struct DwPlan { int TR, TC, ntr, ntc, KST, QST, chunks; long tiles; size_t lds; };
-
-static DwPlan plan_dw(const Problem& p)
-{
-    const int S = p.S(), R = p.ksize / 2;
-    DwPlan t;
-    t.ntc = (p.W + 31) / 32;
-    t.TC = ((p.W + t.ntc - 1) / t.ntc + 3) & ~3;            // <= 32: eight staging lanes, one quad each
-    t.ntc = (p.W + t.TC - 1) / t.TC;
-    auto lds = [&](int TR) {
-        t.KST = ((TR + 2 * R) * (t.TC + 2 * R)) | 1;        // odd: 32 channels, 32 banks
-        t.QST = (TR * t.TC) | 1;
-        const size_t tile = (size_t)DW_CH * (t.KST + t.QST) + (size_t)TR * t.TC + DW_ZEROS + (size_t)TR * (t.TC / 4) * (4 * (S - 1) + 1);
-        const size_t red = (size_t)DW_CH * S * S * (p.ksize == 3 ? 4 : 1);
-        return (tile > red ? tile : red) * sizeof(float);
-    };
-    int TR = dw_max_rows(p.ksize);
-    while (TR > 1 && lds(TR) > 80 * 1024) --TR;             // two blocks per compute unit
-    t.ntr = (p.H + TR - 1) / TR;
-    t.TR = (p.H + t.ntr - 1) / t.ntr;
-    t.ntr = (p.H + t.TR - 1) / t.TR;
-    t.lds = lds(t.TR);
-    t.tiles = (long)p.B * t.ntr * t.ntc;
-    const long jobs = 2L * p.heads * ((p.d() + DW_CH - 1) / DW_CH);
-    long n = (2 * MAX_CU_PLANNED + jobs - 1) / jobs;
-    if (n > t.tiles) n = t.tiles;
-    t.chunks = (int)n;
-    return t;
 }
 
 template <typename T, int KS, bool VEC>
 static hipError_t launch_dw(const Problem& p, const DwArgs& a, const DwPlan& t, hipStream_t st)
 {
     static LdsOptIn opt_in;
-    hipError_t e = opt_in.ensure({(const void*)dw32_kernel<T, KS, VEC>}, 160 * 1024);
+    hipError_t e = opt_in.ensure({(const void*)dw32_kernel<T, KS, VEC>}, (int)CU_LDS_BYTES);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(2 * t.chunks * ((p.d() + DW_CH - 1) / DW_CH)), (unsigned)p.heads);
-    hipLaunchKernelGGL((dw32_kernel<T, KS, VEC>), grid, dim3(256), t.lds, st, a);
+    hipLaunchKernelGGL((dw32_kernel<T, KS, VEC>), grid, dim3(dw_threads(KS)), t.lds, st, a);
     return hipGetLastError();
 }
 
@@ -676,7 +660,7 @@ static hipError_t launch_dw(const Problem& p, const DwArgs& a, const DwPlan& t, 
 size_t bwd_dw_m32_partial_floats(const Problem& p)
 {
     if (!m32_supported(p)) return 0;
-    const m32::DwPlan t = m32::plan_dw(p);
+    const m32::DwPlan t = m32::plan_dw(p.B, p.H, p.W, p.C, p.heads, p.ksize, p.dtype == 0 ? 4 : 2);
     return (size_t)t.chunks * (2 * (size_t)p.C * p.S() * p.S() + (size_t)p.heads * p.S());
 }
 
@@ -697,7 +681,7 @@ hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, 
                              const float* attn_ws, const float* dl_ws, float* partial, float* dwk, float* dwv,
                              float* dbias, hipStream_t st)
 {
-    const m32::DwPlan t = m32::plan_dw(p);
+    const m32::DwPlan t = m32::plan_dw(p.B, p.H, p.W, p.C, p.heads, p.ksize, p.dtype == 0 ? 4 : 2);
     const long side = (long)p.C * p.S() * p.S();
     m32::DwArgs a{};
     a.y[0] = k; a.y[1] = v; a.x[0] = q; a.x[1] = dout; a.p[0] = dl_ws; a.p[1] = attn_ws;
@@ -706,7 +690,7 @@ hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, 
     a.f[0] = p.logit_scale(); a.f[1] = 1.0f;
     a.H = p.H; a.W = p.W; a.C = p.C; a.d = p.d(); a.heads = p.heads;
     a.TR = t.TR; a.TC = t.TC; a.ntr = t.ntr; a.ntc = t.ntc; a.items = p.B; a.tiles = t.tiles; a.chunks = t.chunks;
-    a.KST = t.KST; a.QST = t.QST;
+    a.KST = t.KST; a.QST = t.QST; a.group = t.group;
     const bool vec = p.W % 4 == 0;
     hipError_t e;
 #define SLIDE_DW(T, KS) (vec ? m32::launch_dw<T, KS, true>(p, a, t, st) : m32::launch_dw<T, KS, false>(p, a, t, st))

@@ -2,9 +2,12 @@
 // every size on a machine without a GPU.
 #pragma once
 #include <stddef.h>
+#include <initializer_list>
 
 namespace slide {
 
+// the most compute units that anything is planned for
+constexpr int MAX_CU_PLANNED = 256;
 constexpr size_t CU_LDS_BYTES = 160 * 1024;                    // of a compute unit
 
 namespace m32 {
@@ -66,6 +69,70 @@ inline bool dkdv_few(int B, int heads, int H, int W, int ks, int element_bytes)
     if (((long)H * W + 255) / 256 * heads * 2 * B < 512) return true;
     const Block b = dkdv_block(ks, element_bytes, false);
     return dkdv_lds(plan_cut(H, W, ks, b), ks, element_bytes, b) > CU_LDS_BYTES / 2;
+}
+
+// ---- kernel and bias gradients: chunks of tiles of TR rows and TC columns
+constexpr int DW_CH = 32;                                   // channels per block
+constexpr int DW_ZEROS = 160;                               // as many as the taps of a quad span: 4 * 36 + 8
+constexpr int dw_threads(int ks) { return ks == 3 ? 256 : 512; }
+// quads of four pixels that a thread fetches of y, x and a (or dl) for one tile: what the registers beside the sums
+// hold.  whole: W % 4 == 0, rows are whole quads (else a quad costs some registers for its bounds)
+struct DwLoads { int y, x, p; };
+constexpr DwLoads dw_loads(int ks, int element_bytes, bool whole)
+{
+    return ks == 5 ? DwLoads{6, 4, 3} : element_bytes == 4 ? DwLoads{6, 4, 2} : whole ? DwLoads{10, 8, 3} : DwLoads{8, 6, 2};
+}
+// lanes that stage a row of so many quads
+constexpr int dw_row_lanes_log2(int quads) { return quads > 4 ? 3 : quads > 2 ? 2 : quads > 1 ? 1 : 0; }
+constexpr int DW_MAX_ROWS = 8;                              // rows of a tile
+struct DwPlan { int TR, TC, ntr, ntc, KST, QST, chunks, group; long tiles; size_t lds; };
+
+inline DwPlan plan_dw(int B, int H, int W, int C, int heads, int ks, int element_bytes)
+{
+    const int S = ks * ks, R = ks / 2, d = C / heads;
+    DwPlan t;
+    auto lds = [&](int TR, int TC) {
+        t.KST = ((TR + 2 * R) * (TC + 2 * R)) | 1;          // odd: 32 channels, 32 banks
+        t.QST = (TR * TC) | 1;
+        const size_t tile = (size_t)DW_CH * (t.KST + t.QST) + (size_t)TR * TC + DW_ZEROS + (size_t)TR * (TC / 4) * (4 * (S - 1) + 1);
+        const size_t red = (size_t)DW_CH * S * S * (ks == 3 ? dw_threads(ks) / 64 : 1);
+        return (tile > red ? tile : red) * sizeof(float);
+    };
+    // blocks: eight waves on every compute unit.  Tiles: those that cost the fewest rounds of one quad per walker,
+    // halo and barriers counted as part of a round; Where that
+    // gives far fewer tiles than chunks wanted, lower ones, down to 8 pixels of each walker: more blocks, and
+    // their sums are as short as those of the general kernel's threads
+    const int per_cu = 512 / dw_threads(ks), walkers = ks == 3 ? 8 : 2;
+    const long jobs = 2L * heads * ((d + DW_CH - 1) / DW_CH);
+    long n = (per_cu * MAX_CU_PLANNED + jobs - 1) / jobs;
+    auto rounds = [&](int th, int tw) { return (th * ((tw + 3) / 4) + walkers - 1) / walkers; };
+    const int strips = (W + 31) / 32, even = ((W + strips - 1) / strips + 3) & ~3;
+    double best = 0;
+    const DwLoads most = dw_loads(ks, element_bytes, W % 4 == 0);
+    const int lanes = dw_threads(ks) / DW_CH;               // that stage a channel
+    for (int TR = DW_MAX_ROWS < H ? DW_MAX_ROWS : H; TR >= 1; --TR)
+        for (int TC : {even, 32}) {
+            const int quads = 1 << dw_row_lanes_log2(TC / 4);
+            if (lds(TR, TC) > CU_LDS_BYTES / per_cu || (TR + 2 * R) * quads > lanes * most.y || TR * quads > lanes * most.x ||
+                S * TR * quads > dw_threads(ks) * most.p) continue;
+            const int ntr = (H + TR - 1) / TR, ntc = (W + TC - 1) / TC, lr = H - (ntr - 1) * TR, lc = W - (ntc - 1) * TC;
+            const double tiles = (double)ntr * ntc, halo = (double)(H + 2 * R * ntr) * ntc;
+            const double cost = (ntr - 1.0) * ((ntc - 1.0) * rounds(TR, TC) + rounds(TR, lc)) + (ntc - 1.0) * rounds(lr, TC) + rounds(lr, lc) +
+                                0.5 * tiles + 0.1 * halo;
+            if (best == 0 || cost < best) { best = cost; t.TR = TR; t.TC = TC; }
+        }
+    t.ntc = (W + t.TC - 1) / t.TC;
+    while (t.TR > 1 && 4L * B * ((H + t.TR - 1) / t.TR) * t.ntc < 3 * n && t.TR * t.TC > 8 * walkers) --t.TR;
+    t.ntr = (H + t.TR - 1) / t.TR;
+    t.lds = lds(t.TR, t.TC);
+    t.tiles = (long)B * t.ntr * t.ntc;
+    if (n > t.tiles) n = t.tiles;
+    t.chunks = (int)n;
+    // quads of a walker between two additions to its totals: 32 pixels, fewer where its whole share is not much
+    // more (the additions cost nothing there), 64 of long shares of the 5x5 window, where 32 cost 6 % more time
+    const long share = t.tiles / n * rounds(t.TR, t.TC);
+    t.group = share <= (ks == 3 ? 16 : 32) ? 3 : ks == 3 || share <= 128 ? 8 : 16;
+    return t;
 }
 
 }  // namespace m32

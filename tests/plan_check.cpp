@@ -33,6 +33,29 @@ static void cuts(int H, int W, bool brute)
             }
 }
 
+// tiles cover the map, what is staged of one fits the threads' loads and the LDS, chunks are not empty
+static void gradients(int B, int H, int W, int C, int heads)
+{
+    for (int ks : {3, 5})
+        for (int esz : {2, 4}) {
+            const m32::DwPlan t = m32::plan_dw(B, H, W, C, heads, ks, esz);
+            const m32::DwLoads most = m32::dw_loads(ks, esz, W % 4 == 0);
+            const int R = ks / 2, S = ks * ks, NT = m32::dw_threads(ks), lanes = NT / m32::DW_CH;
+            CHECK(t.TR >= 1 && t.TR <= m32::DW_MAX_ROWS && t.TC >= 4 && t.TC <= 32 && t.TC % 4 == 0 && (long)t.ntr * t.TR >= H && (t.ntr - 1) * t.TR < H &&
+                  (long)t.ntc * t.TC >= W && (t.ntc - 1) * t.TC < W, "tiles of %dx%d, window %d", H, W, ks);
+            CHECK(t.tiles == (long)B * t.ntr * t.ntc && t.chunks >= 1 && t.chunks <= t.tiles && t.group >= 1, "chunks of %dx%dx%d", B, H, W);
+            for (int cols : {t.TC, W - (t.ntc - 1) * t.TC}) {
+                const int row = 1 << m32::dw_row_lanes_log2((cols + 3) / 4);
+                CHECK((cols + 3) / 4 <= row && row <= lanes, "quads of %dx%d", H, W);
+                CHECK(t.TR + 2 * R <= lanes / row * most.y && t.TR <= lanes / row * most.x && S * t.TR <= NT / row * most.p, "loads of %dx%d, window %d, %d-byte elements", H, W, ks, esz);
+            }
+            CHECK(t.KST % 2 && t.QST % 2 && t.KST >= (t.TR + 2 * R) * (t.TC + 2 * R) && t.QST >= t.TR * t.TC, "rows of %dx%d", H, W);
+            const size_t floats = (size_t)m32::DW_CH * (t.KST + t.QST) + t.TR * t.TC + m32::DW_ZEROS + (size_t)t.TR * (t.TC / 4) * (4 * (S - 1) + 1);
+            CHECK(t.lds >= floats * 4 && t.lds >= (size_t)m32::DW_CH * S * S * (ks == 3 ? 4 : 1) * 4 && t.lds <= CU_LDS_BYTES / (512 / NT), "LDS of %dx%d, window %d: %zu", H, W, ks, t.lds);
+            CHECK((ks - 1) * (t.TC + 2 * R) + ks + 3 <= m32::DW_ZEROS, "zeros of %dx%d", H, W);
+        }
+}
+
 int main()
 {
     const long plane = 0x7fffffffL / 64;                    // the largest map the library accepts
@@ -41,6 +64,10 @@ int main()
         for (int W = 1; W <= 12000 && (long)H * W <= plane; ++W) cuts(H, W, H <= 300 && W <= 200);
     for (int H = 1; H <= 300; ++H) cuts(H, (int)(plane / H), false);
     for (int W = 1; W <= 300; ++W) cuts((int)(plane / W), W, false);
+    for (int H : {1, 2, 3, 5, 7, 8, 13, 14, 16, 28, 31, 41, 56, 64, 200, 224, 1000})
+        for (int W = 1; W <= 700; ++W)
+            for (int B : {1, 3, 64, 1000})
+                for (int heads : {1, 4, 33}) gradients(B, H, W, heads * (W % 3 == 0 ? 8 : W % 3 == 1 ? 32 : 65), heads);
     printf("%d wrong\n", wrong);
     return wrong != 0;
 }

@@ -9,6 +9,7 @@ import torch
 
 import paper_2304_04237_amd as sa
 from paper_2304_04237_amd import synth
+from oracle import slide_oracle as oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +94,24 @@ def test_forward_rounds_no_more_than_the_plain_order(shape):
     error = [np.linalg.norm(x - exact) / np.linalg.norm(exact) for x in (out[b, :, i, j], plain)]
     assert error[0] <= 1.04 * error[1], "%.3e, plain order %.3e" % tuple(error)
     print("%.3e, plain order %.3e" % tuple(error))
+
+
+@pytest.mark.parametrize("shape", [(32, 28, 28, 128, 32, 3), (16, 28, 28, 64, 16, 5), (1, 31, 30, 8, 2, 5)])
+def test_kernel_gradients_are_no_long_running_sums(shape):
+    """Many heads, so that few blocks share a head's pixels and each sums thousands of them.  A running sum of n terms of
+    either sign rounds like n / 2 roundings of its result, each 0.41 * 2^-24 of it (root mean square).  Groups of at
+    most 64 pixels, their totals, the walkers and the chunks come to no more than 60 such roundings; the terms bring the
+    error of a and dl with them, which dv and dk show.  One running sum per walker: 196 roundings here."""
+    B, H, W, C, heads, ks = shape
+    print("float32 kernel gradients", shape, flush=True)
+    dd = synth.make_inputs(B, H, W, C, heads, ks, "f32", seed=21, with_dout=True)
+    wk, wv = (sa.slide_reparam(dd[n].cuda()) for n in ("wk_learned", "wv_learned"))
+    acts = [dd[n].cuda() for n in ("dout", "q", "k", "v")]
+    bias = dd["bias"].cuda()
+    grads = sa.slide_attn_bwd(*acts, wk, wv, bias, heads, ks)
+    ref = oracle.bwd(*(x.double().cpu().numpy() for x in (*acts, wk, wv, bias)), heads, ks)
+    dq, dk, dv, dwk, dwv, dbias = (float(np.linalg.norm(g.double().cpu().numpy() - r) / np.linalg.norm(r)) for g, r in zip(grads, ref))
+    print("dk %.2e dv %.2e dwk %.2e dwv %.2e dbias %.2e" % (dk, dv, dwk, dwv, dbias))
+    chain = 60 ** 0.5 * 0.41 * 2.0 ** -24
+    assert dwk <= np.hypot(dk, chain)
+    assert dwv <= np.hypot(dv, chain)
