@@ -10,6 +10,99 @@ namespace slide {
 constexpr int MAX_CU_PLANNED = 256;
 constexpr size_t CU_LDS_BYTES = 160 * 1024;                    // of a compute unit
 
+// ---- half-precision tile kernels: a (batch, head) plane is cut into tiles of th x tw pixels
+namespace t16 {
+
+struct TilePlan {
+    int th, tw, n_tc, nA, nB, hb, TA, TB;
+    int v_off, buf_bytes;    // the two halo tensors of a tile occupy buf_bytes of LDS
+    int halo_px;             // halo pixels of a full tile: (th + 2r) * (tw + 2r)
+};
+
+// makespan of dealing big-first: TA tiles of cost cA first, then TB tiles of cost cB, G blocks
+inline double queue_makespan(long TA, double cA, long TB, double cB, int G)
+{
+    const long qa = TA / G, ra = TA % G;
+    const double lo = qa * cA, hi = (ra ? qa + 1 : qa) * cA;
+    if (TB == 0) return hi;
+    // smallest M with sum_b floor((M - L_b) / cB) >= TB, tried on the grid lo + j*cB, hi + j*cB
+    double best = 1e300;
+    for (long j = 0; j <= TB / G + 2; ++j) {
+        for (int w = 0; w < 2; ++w) {
+            const double M = (w ? hi : lo) + j * cB;
+            if (M < hi) continue;
+            const long cap = (G - ra) * (long)((M - lo) / cB + 1e-9) + ra * (long)((M - hi) / cB + 1e-9);
+            if (cap >= TB && M < best) best = M;
+        }
+    }
+    return best;
+}
+
+// Tile heights for a kernel that may spend lds_budget bytes on one tile buffer holding two
+// halo tensors of px_bytes per halo pixel each (64 for a staged activation tensor).
+// px_bytes_extra: further LDS bytes per halo pixel that the kernel places after the buffer.
+// pass_waves > 0: the kernel deals the 16-pixel passes of a tile to that many waves and does
+// not overlap the staging of a tile with its passes; a tile then costs the rounds of passes
+// its busiest wave runs plus a staging share, instead of its rows.
+inline TilePlan plan_tiles(int B, int H, int W, int heads, int ksize, int n_cu, int lds_budget, int px_bytes_a, int px_bytes_b,
+                           int px_bytes_extra, int pass_waves)
+{
+    const int r2 = 2 * (ksize / 2);
+    TilePlan t;
+    t.tw = W <= 64 ? W : 64;
+    t.n_tc = (W + t.tw - 1) / t.tw;
+    if (t.n_tc > 1 && W % 8 != 0) t.tw = ((W + t.n_tc - 1) / t.n_tc + 7) & ~7;  // even shares, in whole staging chunks
+    const int px_bytes = px_bytes_a + px_bytes_b + px_bytes_extra;
+    int th_max = (lds_budget - 256) / (px_bytes * (t.tw + r2)) - r2;
+    if (th_max < 1) th_max = 1;
+    if (th_max > H) th_max = H;
+    const long planes = (long)B * heads * t.n_tc;
+    // choose the tile heights that minimise the makespan of dealing the tiles to one block
+    // per compute unit slot (cost of a tile: its rows plus a fixed share for the halo rows
+    // and the per-tile overhead)
+    double best = 1e300;
+    t.th = th_max; t.nA = H / th_max; t.nB = (H % th_max) ? 1 : 0; t.hb = H % th_max;
+    int tallest = th_max, lowest = th_max / 2 < 1 ? 1 : th_max / 2;
+    if (planes * ((H + th_max - 1) / th_max) < n_cu) {
+        // such tiles leave compute units without one, so lower ones are tried too, from the height on at which
+        // every tile has a unit of its own (a taller one takes longer and leaves more units idle)
+        // (bf16, 3x3, 2 heads, 24x24: forward 10.9 -> 8.6 us; trying every height took 5 us of host time there, 17 at 64x9)
+        const int per_plane = (int)(n_cu / planes);
+        tallest = (H + per_plane - 1) / per_plane;
+        lowest = 1;
+        if (tallest > th_max) tallest = th_max;
+    }
+    for (int th = tallest; th >= lowest; --th) {
+        for (int drop = 0; drop < 2; ++drop) {
+            const int nA = H / th - drop;
+            if (nA < 0) continue;
+            const int rem = H - nA * th;
+            for (int nB = (rem + th - 1) / th; nB <= (rem + th - 1) / th + 2; ++nB) {
+                if ((rem == 0) != (nB == 0)) continue;
+                const int hb = nB ? (rem + nB - 1) / nB : 0;
+                if (nB && (hb < 1 || (long)hb * (nB - 1) >= rem)) continue;
+                auto cost = [&](int rows) {
+                    if (pass_waves <= 0) return rows + 1.5;
+                    const int passes = (rows * t.tw + 15) / 16;
+                    return (double)((passes + pass_waves - 1) / pass_waves) + 0.35 + 0.035 * (rows + r2);
+                };
+                const double ms = queue_makespan(planes * nA, cost(th), planes * nB, cost(hb), n_cu);
+                if (ms < best - 1e-9) { best = ms; t.th = th; t.nA = nA; t.nB = nB; t.hb = hb; }
+            }
+        }
+    }
+    t.TA = (int)(planes * t.nA);
+    t.TB = (int)(planes * t.nB);
+    const int halo_px = (t.th + r2) * (t.tw + r2);
+    t.halo_px = halo_px;
+    t.v_off = halo_px * px_bytes_a;
+    if ((t.v_off & 127) == 0) t.v_off += 64;             // the two tensors start 64 B apart mod 128
+    t.buf_bytes = (t.v_off + halo_px * px_bytes_b + 127) & ~127;
+    return t;
+}
+
+}  // namespace t16
+
 namespace m32 {
 
 // ---- float32 matrix-core kernels (slide_mfma32.hip, slide_mfma32_bwd.hip)

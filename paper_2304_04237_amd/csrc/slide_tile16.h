@@ -228,87 +228,11 @@ __device__ __forceinline__ void zero_pad_columns(const TileGrid& a, const Tile& 
 }
 
 // ------------------------------------------------------------------ host side
-constexpr int LDS_LIMIT = 160 * 1024;
+constexpr int LDS_LIMIT = (int)CU_LDS_BYTES;
 
-struct TilePlan {
-    int th, tw, n_tc, nA, nB, hb, TA, TB;
-    int v_off, buf_bytes;    // the two halo tensors of a tile occupy buf_bytes of LDS
-    int halo_px;             // halo pixels of a full tile: (th + 2r) * (tw + 2r)
-};
-
-// makespan of dealing big-first: TA tiles of cost cA first, then TB tiles of cost cB, G blocks
-inline double queue_makespan(long TA, double cA, long TB, double cB, int G)
+inline TilePlan plan_tiles(const Problem& p, int lds_budget, int px_bytes_a, int px_bytes_b, int px_bytes_extra = 0, int pass_waves = 0)
 {
-    const long qa = TA / G, ra = TA % G;
-    const double lo = qa * cA, hi = (ra ? qa + 1 : qa) * cA;
-    if (TB == 0) return hi;
-    // smallest M with sum_b floor((M - L_b) / cB) >= TB, tried on the grid lo + j*cB, hi + j*cB
-    double best = 1e300;
-    for (long j = 0; j <= TB / G + 2; ++j) {
-        for (int w = 0; w < 2; ++w) {
-            const double M = (w ? hi : lo) + j * cB;
-            if (M < hi) continue;
-            const long cap = (G - ra) * (long)((M - lo) / cB + 1e-9) + ra * (long)((M - hi) / cB + 1e-9);
-            if (cap >= TB && M < best) best = M;
-        }
-    }
-    return best;
-}
-
-// Tile heights for a kernel that may spend lds_budget bytes on one tile buffer holding two
-// halo tensors of px_bytes per halo pixel each (64 for a staged activation tensor).
-// px_bytes_extra: further LDS bytes per halo pixel that the kernel places after the buffer.
-// pass_waves > 0: the kernel deals the 16-pixel passes of a tile to that many waves and does
-// not overlap the staging of a tile with its passes; a tile then costs the rounds of passes
-// its busiest wave runs plus a staging share, instead of its rows.
-inline TilePlan plan_tiles(const Problem& p, int lds_budget, int px_bytes_a, int px_bytes_b,
-                           int px_bytes_extra = 0, int pass_waves = 0)
-{
-    const int r2 = 2 * (p.ksize / 2);
-    const int n_cu = device_cu_count();
-    TilePlan t;
-    t.tw = p.W <= 64 ? p.W : 64;
-    t.n_tc = (p.W + t.tw - 1) / t.tw;
-    if (t.n_tc > 1 && p.W % 8 != 0) t.tw = ((p.W + t.n_tc - 1) / t.n_tc + 7) & ~7;  // even shares, in whole staging chunks
-    const int px_bytes = px_bytes_a + px_bytes_b + px_bytes_extra;
-    int th_max = (lds_budget - 256) / (px_bytes * (t.tw + r2)) - r2;
-    if (th_max < 1) th_max = 1;
-    if (th_max > p.H) th_max = p.H;
-    const long planes = (long)p.B * p.heads * t.n_tc;
-    // choose the tile heights that minimise the makespan of dealing the tiles to one block
-    // per compute unit slot (cost of a tile: its rows plus a fixed share for the halo rows
-    // and the per-tile overhead)
-    double best = 1e300;
-    t.th = th_max; t.nA = p.H / th_max; t.nB = (p.H % th_max) ? 1 : 0; t.hb = p.H % th_max;
-    // (tiles below half the tallest only where those would leave compute units without one)
-    const bool few = planes * ((p.H + th_max - 1) / th_max) < n_cu;
-    for (int th = th_max; th >= 1 && (few || th >= th_max / 2); --th) {
-        for (int drop = 0; drop < 2; ++drop) {
-            const int nA = p.H / th - drop;
-            if (nA < 0) continue;
-            const int rem = p.H - nA * th;
-            for (int nB = (rem + th - 1) / th; nB <= (rem + th - 1) / th + 2; ++nB) {
-                if ((rem == 0) != (nB == 0)) continue;
-                const int hb = nB ? (rem + nB - 1) / nB : 0;
-                if (nB && (hb < 1 || (long)hb * (nB - 1) >= rem)) continue;
-                auto cost = [&](int rows) {
-                    if (pass_waves <= 0) return rows + 1.5;
-                    const int passes = (rows * t.tw + 15) / 16;
-                    return (double)((passes + pass_waves - 1) / pass_waves) + 0.35 + 0.035 * (rows + r2);
-                };
-                const double ms = queue_makespan(planes * nA, cost(th), planes * nB, cost(hb), n_cu);
-                if (ms < best - 1e-9) { best = ms; t.th = th; t.nA = nA; t.nB = nB; t.hb = hb; }
-            }
-        }
-    }
-    t.TA = (int)(planes * t.nA);
-    t.TB = (int)(planes * t.nB);
-    const int halo_px = (t.th + r2) * (t.tw + r2);
-    t.halo_px = halo_px;
-    t.v_off = halo_px * px_bytes_a;
-    if ((t.v_off & 127) == 0) t.v_off += 64;             // the two tensors start 64 B apart mod 128
-    t.buf_bytes = (t.v_off + halo_px * px_bytes_b + 127) & ~127;
-    return t;
+    return plan_tiles(p.B, p.H, p.W, p.heads, p.ksize, device_cu_count(), lds_budget, px_bytes_a, px_bytes_b, px_bytes_extra, pass_waves);
 }
 
 inline void fill_grid(TileGrid& g, const Problem& p, const TilePlan& t, const void* src_a, const void* src_b)

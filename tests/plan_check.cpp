@@ -1,6 +1,7 @@
 // Checks of the host-side plans (slide_plan.h) over all sizes; prints what is wrong and returns 1.
 #include "slide_plan.h"
 #include <algorithm>
+#include <chrono>
 #include <cstdio>
 #include <vector>
 
@@ -56,6 +57,41 @@ static void gradients(int B, int H, int W, int C, int heads)
         }
 }
 
+// the half-precision tile kernels' heights: as good as those found by trying every height down to one row where the tallest
+// tiles leave compute units without one, down to half the tallest elsewhere
+static double tile_makespan(int H, long planes, int th, int nA, int nB, int hb, int tw, int r2, int waves)
+{
+    auto cost = [&](int rows) {
+        if (waves <= 0) return rows + 1.5;
+        const int passes = (rows * tw + 15) / 16;
+        return (double)((passes + waves - 1) / waves) + 0.35 + 0.035 * (rows + r2);
+    };
+    return t16::queue_makespan(planes * nA, cost(th), planes * nB, cost(hb), MAX_CU_PLANNED);
+}
+static void tiles(int B, int H, int W, int heads, int ks, int budget, int waves)
+{
+    const t16::TilePlan t = t16::plan_tiles(B, H, W, heads, ks, MAX_CU_PLANNED, budget, 64, 64, 0, waves);
+    const int r2 = 2 * (ks / 2);
+    const long planes = (long)B * heads * t.n_tc;
+    CHECK((long)t.n_tc * t.tw >= W && (t.n_tc - 1) * t.tw < W && t.nA * t.th + t.nB * t.hb >= H && (t.nB ? t.nA * t.th + (t.nB - 1) * t.hb < H : t.nA * t.th == H) &&
+          t.TA == planes * t.nA && t.TB == planes * t.nB && t.hb <= t.th && (t.th == 1 || t.buf_bytes <= budget), "tiles of %dx%dx%d", B, H, W);
+    int th_max = std::min(H, std::max(1, (budget - 256) / (128 * (t.tw + r2)) - r2));
+    const bool few = planes * ((H + th_max - 1) / th_max) < MAX_CU_PLANNED;
+    double best = 1e300;
+    for (int th = th_max; th >= (few ? 1 : std::max(1, th_max / 2)); --th)
+        for (int nA = H / th; nA >= 0 && nA >= H / th - 1; --nA) {
+            const int rem = H - nA * th;
+            for (int nB = (rem + th - 1) / th; nB <= (rem + th - 1) / th + 2; ++nB) {
+                if ((rem == 0) != (nB == 0)) continue;
+                const int hb = nB ? (rem + nB - 1) / nB : 0;
+                if (nB && (hb < 1 || hb * (nB - 1) >= rem)) continue;
+                best = std::min(best, tile_makespan(H, planes, th, nA, nB, hb, t.tw, r2, waves));
+            }
+        }
+    const double now = tile_makespan(H, planes, t.th, t.nA, t.nB, t.hb, t.tw, r2, waves);
+    CHECK(now <= best + 1e-6, "tiles of %dx%dx%d, %d heads: %g, there are some of %g", B, H, W, heads, now, best);
+}
+
 int main()
 {
     const long plane = 0x7fffffffL / 64;                    // the largest map the library accepts
@@ -68,6 +104,20 @@ int main()
         for (int W = 1; W <= 700; ++W)
             for (int B : {1, 3, 64, 1000})
                 for (int heads : {1, 4, 33}) gradients(B, H, W, heads * (W % 3 == 0 ? 8 : W % 3 == 1 ? 32 : 65), heads);
+    for (int H : {1, 2, 3, 5, 9, 14, 16, 28, 41, 56, 64, 150, 200, 300, 1000})
+        for (int W = 1; W <= 350; W += W < 70 ? 1 : 7)
+            for (int B : {1, 2, 8, 64})
+                for (int heads : {1, 2, 8}) {
+                    tiles(B, H, W, heads, 3, 77000, 0);
+                    tiles(B, H, W, heads, 3, 81920, 0);
+                    tiles(B, H, W, heads, 5, 60000, 8);
+                }
+    // planning is part of every call: it must stay a fraction of a microsecond
+    const auto t0 = std::chrono::steady_clock::now();
+    long sum = 0;
+    for (int i = 0; i < 100000; ++i) sum += t16::plan_tiles(1, 64, 9 + (i & 1), 2, 3, MAX_CU_PLANNED, 77000, 64, 64, 0, 0).th;
+    const double us = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() * 10;
+    CHECK(us < 4, "planning 64x9 takes %.2f us (%ld)", us, sum);
     printf("%d wrong\n", wrong);
     return wrong != 0;
 }
