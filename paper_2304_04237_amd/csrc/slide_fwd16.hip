@@ -285,7 +285,7 @@ __device__ __forceinline__ ShareGeom share_geom(const Tile& t)
 }
 
 // RAGGED: rows start at any even address and W is no multiple of 8; `left` is the number of bytes from the
-// head's first element to the tensor's end (a chunk there is loaded element by element)
+// head's first element to the tensor's end
 template <bool RAGGED>
 __device__ __forceinline__ void share_load(const FwdArgs& a, const Tile& t, const ShareGeom& sg, int hb,
                                            int lane, uint32_t hw2, uint4_t (&r)[4], uint32_t left = 0)
@@ -307,27 +307,16 @@ __device__ __forceinline__ void share_load(const FwdArgs& a, const Tile& t, cons
         for (int e = 0; e < 4; ++e) r[e] = *(const uint4_t*)(base + (off + (uint32_t)e * hw2));
         return;
     }
+    // (the chunk that runs past the tensor's end is loaded from its last 16 bytes and moved into place)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = *(const uint4_any_t*)(base + min(off + (uint32_t)e * hw2, left - 16u));
     const int n = a.g.W - gx;                           // columns of the map that the chunk holds
-    if (off + 3u * hw2 + 16u <= left) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = *(const uint4_any_t*)(base + (off + (uint32_t)e * hw2));
-        if (n < 8) {
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const uint32_t keep = 2 * y + 1 < n ? 0xffffffffu : (2 * y < n ? 0xffffu : 0u);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) r[e][y] &= keep;
-            }
-        }
-    } else {
+    if (n < 8) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const bf16_bits* src = (const bf16_bits*)(base + (off + (uint32_t)e * hw2));
+            r[e] = from8_before(r[e], (const bf16_bits*)(base + (off + (uint32_t)e * hw2)), (const bf16_bits*)(base + left));
 #pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const uint32_t lo = 2 * y < n ? src[2 * y] : 0, hi = 2 * y + 1 < n ? src[2 * y + 1] : 0;
-                r[e][y] = lo | (hi << 16);
-            }
+            for (int y = 0; y < 4; ++y) r[e][y] &= 2 * y + 1 < n ? 0xffffffffu : (2 * y < n ? 0xffffu : 0u);
         }
     }
 }
@@ -391,10 +380,10 @@ fwd16_pipe_kernel(const FwdArgs a)
     const int p = lane & 15, g = lane >> 4;
     const int HC = (TW ? TW : a.g.tw) + 2;
     const bool single_col = a.g.n_tc == 1 && !RAGGED;   // then no staged column falls outside a tile
-    // bytes from a head's first element to the end of its tensor, as far as 32-bit offsets reach
+    // bytes from a head's first element to the end of its tensor (or more than an offset inside a head, < 2^31, reaches)
     auto bytes_left = [&](const Tile& t) -> uint32_t {
         const long n = ((long)a.g.B * a.g.C * a.g.H * a.g.W - t.head_base) * 2;
-        return (uint32_t)(n < 0x7fffffffL ? n : 0x7fffffffL);
+        return (uint32_t)(n < 0xfffffff0L ? n : 0xfffffff0L);
     };
     // columns that passes count a tile row as: eight pixels of a pass are one run of memory, so (RAGGED) the
     // rows of a narrower tile than the map are rounded up to whole runs; a tile that is as
@@ -460,15 +449,8 @@ fwd16_pipe_kernel(const FwdArgs a)
             int cnt;
             const uint32_t off = seg_offset(pass, cnt);     // (valid even when the segment is not)
             if (!RAGGED) return *(const uint4_t*)(qb + off);
-            if (off + 16u <= left) return *(const uint4_any_t*)(qb + off);
-            uint4_t v;
-            const bf16_bits* src = (const bf16_bits*)(qb + off);
-#pragma unroll
-            for (int y = 0; y < 4; ++y) {
-                const uint32_t lo = 2 * y < cnt ? src[2 * y] : 0, hi = 2 * y + 1 < cnt ? src[2 * y + 1] : 0;
-                v[y] = lo | (hi << 16);
-            }
-            return v;
+            const uint4_t v = *(const uint4_any_t*)(qb + min(off, left - 16u));
+            return from8_before(v, (const bf16_bits*)(qb + off), (const bf16_bits*)(qb + left));
         };
         uint4_t qseg = load_q(min(wave, npass - 1));
         __syncthreads();                                // buf is complete, buf_next is free

@@ -71,3 +71,10 @@ def test_against_oracle(shape, shift, two_branch):
     _check("lse", lse, ref_lse)
     for name, got, want in zip("dq dk dv dwk dwv dbias".split(), grads, oracle.bwd(*n, heads, 3)):
         _check(name, got, want)
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 32, 1), (1, 2, 2, 32, 1), (3, 4, 4, 64, 2), (1, 1, 15, 32, 1), (1, 1, 17, 64, 2)])
+def test_last_pieces_of_tiny_tensors(shape, shift):
+    """Most 16-byte pieces of these run past the tensor's end, by up to seven elements."""
+    test_against_oracle(shape, shift, False)
