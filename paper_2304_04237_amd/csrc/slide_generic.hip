@@ -174,6 +174,15 @@ fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __
     }
 }
 
+// 3x3 forwards of narrow heads on few pixels: eight lanes per pixel and head take them in one pass over a channel or
+// less, in the launch's own time; the float32 matrix-core kernels fetch tiles and kernels first.  In a graph, MI355X,
+// float32, 15x15: one head of 6 channels 7.5 us here, 8.7 there, 8 heads of 8 channels 8.1 and 8.6; 45x45, 8 heads
+// (16200 pixels and heads) of 8 channels 10.5 and 9.0, of 16 channels at 15x15 11.7 and 9.3.
+bool fwd_few_products(const Problem& p)
+{
+    return p.ksize == 3 && p.d() <= 8 && (long)p.B * p.heads * p.plane() <= 8192;
+}
+
 // small problems: 8 lanes per pixel and head
 static bool few_pixels(const Problem& p) { return (long)p.B * p.heads * p.plane() < 262144; }
 
@@ -220,7 +229,7 @@ hipError_t launch_fwd_generic(const Problem& p, const void* q, const void* k, co
                               const float* wk, const float* wv, const float* bias, void* out,
                               float* lse, hipStream_t st)
 {
-    if (wk && m32_supported(p)) return launch_fwd_m32(p, q, k, v, wk, wv, bias, out, lse, st);
+    if (wk && m32_supported(p) && !fwd_few_products(p)) return launch_fwd_m32(p, q, k, v, wk, wv, bias, out, lse, st);
     SLIDE_DISPATCH(launch_fwd_t, p, q, k, v, wk, wv, bias, out, lse, st);
 }
 

@@ -64,6 +64,7 @@ hipError_t launch_reparam(const float* w_learned, float* w_merged, int C, int ks
 hipError_t launch_fwd_generic(const Problem& p, const void* q, const void* k, const void* v,
                               const float* wk, const float* wv, const float* bias, void* out,
                               float* lse, hipStream_t st);
+bool fwd_few_products(const Problem& p);               // ... which launch_fwd_generic does not hand to launch_fwd_m32
 size_t bwd_generic_workspace_bytes(const Problem& p);
 hipError_t launch_bwd_generic(const Problem& p, const void* dout, const void* q, const void* k,
                               const void* v, const float* wk, const float* wv, const float* bias,

@@ -126,14 +126,23 @@ pixel32_kernel(const PixelArgs a)
         const float* wb = w + (long)m * d * S * S;
         f4 yr[NI][QPT], xr[CQ / CG];
         float wr[AHEAD_W ? NW : 1];
-        auto fetch = [&](int c0) {
+        // (a step stages the quads that the head still has: the eight of the shared form are 32 channels.  The forward's large
+        // blocks stage two quads whatever the head: leaving one out cost them registers, 54 -> 56 us at stage 1)
+        auto fetch_quads = [&](int c0, auto all) {
+            constexpr bool ALL = decltype(all)::value;
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int u = 0; u < QPT; ++u) yr[i][u] = load4(yb, off[i], c0 + 4 * (tg + u * TG));
+                for (int u = 0; u < QPT; ++u)
+                    if (ALL || c0 + 4 * (tg + u * TG) < d) yr[i][u] = load4(yb, off[i], c0 + 4 * (tg + u * TG));
             if (xb)
 #pragma unroll
-                for (int u = 0; u < CQ / CG; ++u) xr[u] = load4(xb, xoff, c0 + 4 * (peg + u * CG));
+                for (int u = 0; u < CQ / CG; ++u)
+                    if (ALL || c0 + 4 * (peg + u * CG) < d) xr[u] = load4(xb, xoff, c0 + 4 * (peg + u * CG));
+        };
+        auto fetch = [&](int c0) {
+            if ((CG == 1 && !BWD) || c0 + 4 * CQ <= d) fetch_quads(c0, std::true_type{});
+            else fetch_quads(c0, std::false_type{});
             if (AHEAD_W)
 #pragma unroll
                 for (int u = 0; u < NW; ++u) {
@@ -362,7 +371,7 @@ static hipError_t launch_pixel_t(const Problem& p, PixelArgs& a, hipStream_t st)
 {
     if constexpr (!BWD && !FOUR)
         if (p.nhwc && p.d() % 4 == 0) return launch_pixel_t<T, KS, false, true>(p, a, st);
-    if (pixel_few(p.B, p.heads, p.H, p.W)) return launch_pixel<T, KS, true, BWD, FOUR>(p, a, st);
+    if (pixel_few(p.B, p.heads, p.H, p.W, p.d(), KS)) return launch_pixel<T, KS, true, BWD, FOUR>(p, a, st);
     return launch_pixel<T, KS, false, BWD, FOUR>(p, a, st);
 }
 

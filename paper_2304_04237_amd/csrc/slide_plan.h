@@ -154,9 +154,22 @@ inline size_t dkdv_lds(const Cut& c, int ks, int element_bytes, const Block& b)
     return (size_t)c.npx * ((size_t)b.NQ * 4 * element_bytes + S * sizeof(float)) + (size_t)b.NQ * 4 * S * S * sizeof(float);
 }
 
-// blocks of 256 pixels where those give every compute unit two; the dk/dv kernel: and two fit its LDS (maps of a
-// few columns have tall runs with much halo).  Else 64 pixels whose channels eight (dk/dv: four) waves share
-inline bool pixel_few(int B, int heads, int H, int W) { return ((long)H * W + 255) / 256 * heads * B < 512; }
+// Blocks of 256 pixels, or of 64 whose channels eight waves share.  The large ones take 2.5 (3x3) or 8.7 us (5x5) per
+// quad of channels up to two to a compute unit; of the small ones a unit holds one, and each set of 256 of them
+// takes 7.6 us, or 16 and 2.2 for every quad, per eight quads (MI355X, float32 forward, 1..24 channels per head, maps of
+// 15x15 to 93x93 with 8 heads; three compute units' worth of 5x5 blocks slow each other down by 1.6).  Choosing by
+// the number of blocks alone (small ones below 512 large) took 38 us instead of 9 for 93x93 and heads of 4 channels.
+inline bool pixel_few(int B, int heads, int H, int W, int d, int ks)
+{
+    const long large = ((long)H * W + 255) / 256 * heads * B;
+    if (large >= 512) return false;
+    const long sets = (((long)H * W + 63) / 64 * heads * B + MAX_CU_PLANNED - 1) / MAX_CU_PLANNED;
+    const int quads = (d + 3) / 4, eights = (quads + 7) / 8;
+    if (ks == 3) return sets * (5.3 + 2.3 * eights) < 3.5 + 2.5 * quads;
+    return sets * eights * (16 + 2.2 * (quads < 8 ? quads : 8)) < (3.5 + 8.7 * quads) * (large > MAX_CU_PLANNED ? 1.6 : 1.0);
+}
+// dk/dv kernel: blocks of 256 pixels where those give every compute unit two and two fit its LDS (maps of a few columns
+// have tall runs with much halo), else 64 pixels whose channels four waves share
 inline bool dkdv_few(int B, int heads, int H, int W, int ks, int element_bytes)
 {
     if (((long)H * W + 255) / 256 * heads * 2 * B < 512) return true;

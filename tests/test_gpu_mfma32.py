@@ -89,3 +89,14 @@ def test_against_oracle(shape, two_branch):
 def test_strips_of_wide_maps(shape):
     """Widths whose strips of equal width would leave a last one of a few columns."""
     test_against_oracle(shape, False)
+
+
+@pytest.mark.parametrize("shape", [
+    # narrow maps with heads beyond those that the general forward serves; both block forms at the same number of pixels
+    (1, 5, 1, 9, 1, 3, "f32", False), (2, 150, 2, 27, 3, 3, "f32", False), (1, 1, 1, 10, 1, 3, "f32", True),
+    (1, 63, 63, 32, 8, 3, "f32", False), (1, 61, 63, 80, 8, 3, "f32", True), (1, 31, 33, 80, 8, 3, "bf16", True), (1, 62, 61, 24, 8, 5, "f32", False),
+    # the general forward: up to eight channels per head on few pixels
+    (1, 31, 33, 64, 8, 3, "f32", True), (2, 15, 13, 12, 4, 3, "bf16", False),
+])
+def test_narrow_heads_and_maps(shape):
+    test_against_oracle(shape, True)
