@@ -74,7 +74,7 @@ int slide_reparam(const float* w_learned, float* w_merged, int C, int ksize, voi
  * includes what the matrix-core kernels need to serve that head size (partial sums exchanged
  * between half heads; copies padded to 32 channels per head: several times the size of an
  * activation tensor).  slide_attn_bwd requires it; a forward call that brings less scratch than
- * this (but enough for the general path: none) is served by the general kernel instead.
+ * this (but enough for the float32 kernels: none) is served by those instead.
  */
 size_t slide_attn_workspace_bytes(int B, int H, int W, int C, int heads, int ksize,
                                   int dtype, int backward);
@@ -199,8 +199,8 @@ const char* slide_status_string(int status);
 
 /*
  * Which forward implementation slide_attn_fwd would run for this problem:
- * 0 = invalid arguments, 1 = general kernel (any supported ksize / head size /
- * dtype, float32 vector arithmetic), 2 = matrix-core kernel (bf16, ksize 3, d = 32, or
+ * 0 = invalid arguments, 1 = float32 kernels (any supported ksize / head size /
+ * dtype; windows of 3 and 5 on float32 matrix instructions), 2 = matrix-core kernel (bf16, ksize 3, d = 32, or
  * d = 64 on maps the streaming kernel takes), 3 = matrix-core kernel for ksize 5 (bf16,
  * d = 32).  For tests and benchmarks.
  */
@@ -208,19 +208,21 @@ int slide_attn_fwd_path(int B, int H, int W, int C, int heads, int ksize, int dt
 
 /*
  * The kernel inside that implementation, for tests that must know which code ran:
- * 0 = invalid arguments, 10 = general kernel, 20 = ksize-3 matrix-core kernel with one tile
+ * 0 = invalid arguments, 10 = general kernel (float32 vector arithmetic), 11 = float32 matrix-core kernel
+ * (ksize 3 and 5, except ksize-3 heads of up to 8 channels on up to 8192 pixels and heads), 20 = ksize-3 matrix-core kernel with one tile
  * per block, 21 / 23 = pipelined ksize-3 tile kernel (persistent blocks, next tile staged
  * during the passes of the current one) with the tile width taken from its arguments / fixed
- * at 64, 24 = streaming ksize-3 kernel (a block walks down a band of rows, K/V rows in an LDS
+ * at 64, 22 = its form for rows that are no multiple of 8 pixels (W >= 8), 24 = streaming ksize-3 kernel (a block walks down a band of rows, K/V rows in an LDS
  * ring; maps 32..64 columns wide; head size 32, or 24 with the fourth channel octet of every
  * head left empty), 26 = the streaming kernel on column strips of 48, 40 or 32 (maps wider than 64
  * columns, W % 8 == 0, strips covering at most 1.25 W), 25 = two launches of the streaming kernel for heads of 64 channels (each
  * head as two halves of 32 whose shares of the logits cross the workspace; a call that brings
- * less workspace than slide_attn_workspace_bytes says runs on the general kernel), 30 = ksize-5
+ * less workspace than slide_attn_workspace_bytes says runs on the float32 matrix-core kernel), 30 = ksize-5
  * matrix-core kernel, 100 + v = heads narrower than 32 channels (bf16, ksize 3, H * W % 8 == 0)
  * through kernel v on copies of q, k, v and the kernels padded to 32 channels per head in the
- * workspace (again the general kernel for a call with less workspace).  aligned16: whether
- * q, k, v, out, wk, wv are all 16-byte aligned (kernels 21, 23, 24 need that).  Launches
+ * workspace (again a float32 kernel for a call with less workspace).  aligned16: whether
+ * q, k, v, out, wk, wv are all 16-byte aligned (kernels 21 and 23 to 26 need that; 0 stands for unaligned activations,
+ * while 22 needs aligned wk and wv, else 20 runs).  Launches
  * nothing; reads the compute-unit count of the current device (256 if there is none).
  */
 int slide_attn_fwd_variant(int B, int H, int W, int C, int heads, int ksize, int dtype,
@@ -228,9 +230,9 @@ int slide_attn_fwd_variant(int B, int H, int W, int C, int heads, int ksize, int
 
 /*
  * The kernels slide_attn_bwd would run, for tests that must know which code ran: 0 = invalid
- * arguments, 10 = general kernels (float32 vector arithmetic), 20 = tiled matrix-core kernels
- * (bf16, d = 32, ksize 3; the kernel-gradient kernel also needs W % 8 == 0, else the general
- * one takes that part); 1 is added where the key and value gradients run in the streaming
+ * arguments, 10 = general kernels (float32 vector arithmetic; ksize 1 and 7), 11 = float32 matrix-core kernels
+ * (ksize 3 and 5), 20 = tiled matrix-core kernels (bf16, d = 32, ksize 3; the kernel-gradient kernel also needs
+ * W % 8 == 0, else the float32 matrix-core one takes that part); 1 is added where the key and value gradients run in the streaming
  * kernel (maps 32..56 columns wide, W % 8 == 0, bands and rings that fit the LDS), 2 where the
  * per-pixel part (attention recompute, logit and query gradients) does (maps 32..64 columns
  * wide), 4 where the kernel and bias gradients do (maps 32..56 columns wide): 21 .. 27.
@@ -258,7 +260,7 @@ int slide_attn_bwd_variant(int B, int H, int W, int C, int heads, int ksize, int
  * and with k*k instead of k^4 multiply-adds per pixel and channel.
  * q, k, v, bias, out, lse, the shape arguments, dtype, the number-format contract and the
  * error codes are those of slide_attn_fwd; there is no workspace.  Where
- * slide_attn_fwd_variant(...) says 24 the streaming matrix-core kernel runs in its plain
+ * slide_attn_fwd_variant(...) says 24 or 26 the streaming matrix-core kernel runs in its plain
  * form; every other problem runs on the general kernel.
  */
 int slide_attn_fwd_shift(const void* q, const void* k, const void* v, const float* bias,
@@ -274,7 +276,7 @@ int slide_attn_fwd_shift(const void* q, const void* k, const void* v, const floa
  * codes -- is as for slide_attn_fwd; there is no workspace.  SLIDE_BF16 problems with head size
  * 32, ksize 3, 32 <= W <= 64, W % 8 == 0 and 16-byte aligned pointers run on the streaming
  * matrix-core kernel (the 8 channels a lane works on are 16 contiguous bytes in this layout:
- * nothing is transposed); every other problem runs on the general kernel.
+ * nothing is transposed); every other problem runs on the float32 kernels (10 and 11 of slide_attn_fwd_variant).
  */
 int slide_attn_fwd_nhwc(const void* q, const void* k, const void* v,
                         const float* wk, const float* wv, const float* bias,

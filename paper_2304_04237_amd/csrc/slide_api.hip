@@ -101,7 +101,7 @@ extern "C" int slide_attn_fwd_variant(int B, int H, int W, int C, int heads, int
     if (slide::fwd_ring_enabled() && slide::fwd_ring_wide_supported(p, aligned16 != 0)) return 25;
     Problem p32;
     if (aligned16 && slide::fwd_padded_problem(p, p32)) return 100 + slide::fwd_mfma_variant(p32, true);
-    return slide::fwd_mfma5_supported(p) ? 30 : 10;
+    return slide::fwd_mfma5_supported(p) ? 30 : slide::fwd_uses_m32(p) ? 11 : 10;
 }
 
 extern "C" int slide_attn_bwd_variant(int B, int H, int W, int C, int heads, int ksize, int dtype,

@@ -568,31 +568,28 @@ size_t fwd_mfma_workspace_bytes(const Problem& p)
 }
 
 namespace f16path {
-// Which 3x3 kernel serves a problem whose rows are 16-byte aligned.  The pipelined kernel needs 16-byte aligned rows and
-// pointers, at least two tiles per persistent block, and a tile buffer large enough to hold a
-// head's operand image plus the raw kernels it is gathered from (the block builds the image in
-// the tile buffer that is free at that moment).
-static bool choose_pipelined(const Problem& p, bool aligned16, TilePlan& t)
+// Which 3x3 tile kernel serves a problem, by its number in slide_attn_fwd_variant, and its tiles.
+//  21, 23  the pipelined kernel: needs 16-byte aligned rows and pointers, at least two tiles per persistent block,
+//          and a tile buffer large enough to hold a head's operand image plus the raw kernels it is gathered
+//          from (the block builds the image in the tile buffer that is free at that moment);
+//  22      its RAGGED form: rows that are no multiple of 8 pixels, whatever the number of tiles (its blocks build the
+//          operand image themselves, so a small map is one launch instead of two).  One tile per block against
+//          this, MI355X: 1 x 200x333, C=96, 3 heads 39 + 5 (image) -> 30 us; B=128, 28x28, C=128, 4 heads
+//          41 + 5 -> 43 us;
+//  20      one tile per block: everything else, maps narrower than one 16-byte load and kernels that are not 16-byte
+//          aligned among it.
+static int choose_tiles(const Problem& p, bool aligned16, bool kernels16, TilePlan& t)
 {
-    t = plan_fwd(p, true);
-    const bool pipelined = aligned16 && (p.W % 8 == 0) &&
-                           ((long)t.TA + t.TB >= 2L * device_cu_count()) &&
-                           t.buf_bytes >= IMG_RAW_AT + IMG_RAW_BYTES;
-    if (!pipelined) t = plan_fwd(p, false);
-    return pipelined;
-}
-
-// Rows that are no multiple of 8 pixels: the pipelined kernel's RAGGED form, whatever the number of tiles
-// (its blocks build the operand image themselves, so a small map is one launch instead of two).  One tile
-// per block against this, MI355X: 1 x 200x333, C=96, 3 heads 39 + 5 (image) -> 32 us; B=128, 28x28,
-// C=128, 4 heads 41 + 5 -> 42 us.
-// Without 16-byte aligned kernels, or on maps narrower than one 16-byte load: one tile per block.
-static bool choose_ragged(const Problem& p, const float* wk, const float* wv, TilePlan& t)
-{
-    if (p.W % 8 == 0 || p.W < 8 || ((uintptr_t)wk | (uintptr_t)wv) % 16 != 0) return false;
-    t = plan_fwd(p, true);
-    if (t.buf_bytes < IMG_RAW_AT + IMG_RAW_BYTES) t.buf_bytes = IMG_RAW_AT + IMG_RAW_BYTES;
-    return true;
+    if (p.W % 8 != 0 ? p.W >= 8 && kernels16 : aligned16) {
+        t = plan_fwd(p, true);
+        if (p.W % 8 != 0) {
+            if (t.buf_bytes < IMG_RAW_AT + IMG_RAW_BYTES) t.buf_bytes = IMG_RAW_AT + IMG_RAW_BYTES;
+            return 22;
+        }
+        if ((long)t.TA + t.TB >= 2L * device_cu_count() && t.buf_bytes >= IMG_RAW_AT + IMG_RAW_BYTES) return t.tw == 64 ? 23 : 21;
+    }
+    t = plan_fwd(p, false);
+    return 20;
 }
 
 }  // namespace f16path
@@ -614,8 +611,7 @@ int fwd_mfma_variant(const Problem& p, bool aligned16)
     if (fwd_ring_enabled() && fwd_ring_supported(p, aligned16)) return 24;
     if (fwd_ring_enabled() && fwd_ring_strip_supported(p, aligned16)) return 26;
     TilePlan t;
-    if (!choose_pipelined(p, aligned16, t)) return 20;
-    return t.tw == 64 ? 23 : 21;
+    return choose_tiles(p, aligned16, true, t);
 }
 
 hipError_t launch_fwd_mfma(const Problem& p, const void* q, const void* k, const void* v,
@@ -630,8 +626,8 @@ hipError_t launch_fwd_mfma(const Problem& p, const void* q, const void* k, const
     if (fwd_ring_enabled() && fwd_ring_strip_supported(p, aligned))
         return launch_fwd_ring_strip(p, q, k, v, wk, wv, bias, out, lse, false, st);
     TilePlan t;
-    const bool ragged = choose_ragged(p, wk, wv, t);
-    const bool pipelined = ragged || choose_pipelined(p, aligned, t);
+    const int kernel = choose_tiles(p, aligned, ((uintptr_t)wk | (uintptr_t)wv) % 16 == 0, t);
+    const bool pipelined = kernel != 20;
     uint32_t* image = (uint32_t*)workspace;
     if (!pipelined)
         hipLaunchKernelGGL(prep_weights_kernel, dim3(S, (unsigned)p.heads), dim3(256), 0, st,
@@ -663,9 +659,9 @@ hipError_t launch_fwd_mfma(const Problem& p, const void* q, const void* k, const
             if (lse) hipLaunchKernelGGL((fwd16_pipe_kernel<TWV, true, RAG>), grid, block, (size_t)lds_bytes, st, a);  \
             else     hipLaunchKernelGGL((fwd16_pipe_kernel<TWV, false, RAG>), grid, block, (size_t)lds_bytes, st, a); \
         } while (0)
-        if (ragged)          SLIDE_PIPE(0, true);
-        else if (t.tw == 64) SLIDE_PIPE(64, false);
-        else                 SLIDE_PIPE(0, false);
+        if (kernel == 22)      SLIDE_PIPE(0, true);
+        else if (kernel == 23) SLIDE_PIPE(64, false);
+        else                   SLIDE_PIPE(0, false);
 #undef SLIDE_PIPE
     } else {
         const int lds_bytes = a.a_base + FWD_WAVES * WAVE_SCRATCH;

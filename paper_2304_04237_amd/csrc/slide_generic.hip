@@ -178,10 +178,12 @@ fwd_generic_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __
 // less, in the launch's own time; the float32 matrix-core kernels fetch tiles and kernels first.  In a graph, MI355X,
 // float32, 15x15: one head of 6 channels 7.5 us here, 8.7 there, 8 heads of 8 channels 8.1 and 8.6; 45x45, 8 heads
 // (16200 pixels and heads) of 8 channels 10.5 and 9.0, of 16 channels at 15x15 11.7 and 9.3.
-bool fwd_few_products(const Problem& p)
+static bool fwd_few_products(const Problem& p)
 {
     return p.ksize == 3 && p.d() <= 8 && (long)p.B * p.heads * p.plane() <= 8192;
 }
+
+bool fwd_uses_m32(const Problem& p) { return m32_supported(p) && !fwd_few_products(p); }
 
 // small problems: 8 lanes per pixel and head
 static bool few_pixels(const Problem& p) { return (long)p.B * p.heads * p.plane() < 262144; }
@@ -229,7 +231,7 @@ hipError_t launch_fwd_generic(const Problem& p, const void* q, const void* k, co
                               const float* wk, const float* wv, const float* bias, void* out,
                               float* lse, hipStream_t st)
 {
-    if (wk && m32_supported(p) && !fwd_few_products(p)) return launch_fwd_m32(p, q, k, v, wk, wv, bias, out, lse, st);
+    if (wk && fwd_uses_m32(p)) return launch_fwd_m32(p, q, k, v, wk, wv, bias, out, lse, st);
     SLIDE_DISPATCH(launch_fwd_t, p, q, k, v, wk, wv, bias, out, lse, st);
 }
 
@@ -731,7 +733,7 @@ int bwd_variant(const Problem& p, bool all_aligned16)
     if (all_aligned16 && bwd_padded_problem(p, p32)) return 100 + bwd_variant(p32, true);
     if (all_aligned16 && bwd_wide_problem(p, p32)) return 200 + bwd_variant(p32, true);
     const bool fast = bwd_dkdv_mfma_supported(p) && all_aligned16;
-    if (!fast) return 10;
+    if (!fast) return m32_supported(p) ? 11 : 10;
     const bool half_ws = bwd_dw_mfma_supported(p);
     if (!half_ws || !fwd_ring_enabled()) return 20;
     return 20 + (bwd_dkdv_ring_supported(p, all_aligned16) ? 1 : 0) + (bwd_pixel_ring_supported(p, all_aligned16) ? 2 : 0) +

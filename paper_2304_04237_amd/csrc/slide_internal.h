@@ -64,7 +64,7 @@ hipError_t launch_reparam(const float* w_learned, float* w_merged, int C, int ks
 hipError_t launch_fwd_generic(const Problem& p, const void* q, const void* k, const void* v,
                               const float* wk, const float* wv, const float* bias, void* out,
                               float* lse, hipStream_t st);
-bool fwd_few_products(const Problem& p);               // ... which launch_fwd_generic does not hand to launch_fwd_m32
+bool fwd_uses_m32(const Problem& p);                   // launch_fwd_generic hands the problem to launch_fwd_m32
 size_t bwd_generic_workspace_bytes(const Problem& p);
 hipError_t launch_bwd_generic(const Problem& p, const void* dout, const void* q, const void* k,
                               const void* v, const float* wk, const float* wv, const float* bias,
@@ -102,7 +102,7 @@ hipError_t launch_bwd_nhwc(const Problem& p, const void* dout, const void* q, co
                            void* dq, void* dk, void* dv, float* dwk, float* dwv, float* dbias,
                            void* workspace, hipStream_t st);
 
-// which kernels launch_bwd_generic runs: 10 general, 20 tiled matrix-core kernels, + 1 with the
+// which kernels launch_bwd_generic runs: 10 general, 11 float32 matrix-core kernels, 20 tiled matrix-core kernels, + 1 with the
 // streaming dk/dv kernel, + 2 with the streaming per-pixel kernel, + 4 with the streaming form
 // of the kernel-gradient kernel; aligned16: every pointer is 16-byte aligned
 int bwd_variant(const Problem& p, bool aligned16);
@@ -165,7 +165,8 @@ hipError_t launch_bwd_dkdv_ring(const Problem& p, const void* dout, const void* 
 bool fwd_mfma_supported(const Problem& p);
 size_t fwd_mfma_workspace_bytes(const Problem& p);     // prepared weight operands, per head
 // 20: one tile per block; 21, 23: pipelined tile kernel with the tile width read from its
-// arguments / fixed at 64; 24: streaming kernel.  aligned16: every pointer is 16-byte aligned.
+// arguments / fixed at 64; 22: its form for rows that are no multiple of 8 pixels; 24: streaming kernel, 26 on column
+// strips.  aligned16: every pointer is 16-byte aligned (0: the kernels still are).
 int fwd_mfma_variant(const Problem& p, bool aligned16);
 hipError_t launch_fwd_mfma(const Problem& p, const void* q, const void* k, const void* v,
                            const float* wk, const float* wv, const float* bias, void* out,

@@ -74,13 +74,13 @@ def test_forward_rejects_bad_arguments_on_the_host(lib):
 
 def test_variant_query_knows_head_size_24():
     # head size 24 runs on the streaming kernel where the map fits it, else on padded copies
-    # through the other matrix-core kernels, else on the general kernel
+    # through the other matrix-core kernels, else on the float32 ones
     assert sa.slide_attn_fwd_variant(2, 56, 56, 48, 2, 3, 1, True) == 24
-    assert sa.slide_attn_fwd_variant(2, 56, 56, 48, 2, 3, 1, False) == 10
+    assert sa.slide_attn_fwd_variant(2, 56, 56, 48, 2, 3, 1, False) == 11
     assert sa.slide_attn_fwd_variant(2, 56, 72, 48, 2, 3, 1, True) == 126     # wider than the ring takes: padded to 32 channels per head, streaming kernel on column strips
-    assert sa.slide_attn_fwd_variant(2, 9, 21, 48, 2, 3, 1, True) == 10       # H * W % 8 != 0: general kernel
-    assert sa.slide_attn_fwd_variant(2, 56, 56, 48, 2, 5, 1, True) == 10      # 5x5 window
-    assert sa.slide_attn_fwd_variant(2, 56, 56, 48, 2, 3, 0, True) == 10      # float32
+    assert sa.slide_attn_fwd_variant(2, 9, 21, 48, 2, 3, 1, True) == 11       # H * W % 8 != 0: float32 matrix-core kernel
+    assert sa.slide_attn_fwd_variant(2, 56, 56, 48, 2, 5, 1, True) == 11      # 5x5 window
+    assert sa.slide_attn_fwd_variant(2, 56, 56, 48, 2, 3, 0, True) == 11      # float32
 
 
 def test_shift_forward_rejects_bad_arguments_on_the_host(lib):
@@ -158,7 +158,7 @@ def test_reparam_rejects_bad_arguments(lib):
 
 
 def test_forward_path_selection(lib):
-    assert lib.slide_attn_fwd_path(1, 14, 14, 64, 2, 3, 0) == 1     # float32 -> general kernel
+    assert lib.slide_attn_fwd_path(1, 14, 14, 64, 2, 3, 0) == 1     # float32 kernels
     assert lib.slide_attn_fwd_path(1, 14, 14, 64, 3, 3, 0) == 0
     assert lib.slide_attn_fwd_path(64, 56, 56, 64, 2, 3, 1) == 2    # bf16, head size 32, 3x3 -> matrix cores
     assert lib.slide_attn_fwd_path(64, 28, 28, 128, 4, 5, 1) == 3   # 5x5 -> matrix cores, 5x5 kernel
@@ -173,7 +173,11 @@ def test_forward_variant_selection(lib):
     assumed when there is no device)."""
     v = lib.slide_attn_fwd_variant
     assert v(1, 14, 14, 64, 3, 3, 0, 1) == 0                       # invalid
-    assert v(1, 14, 14, 64, 2, 3, 0, 1) == 10                      # float32: general kernel
+    assert v(1, 14, 14, 64, 2, 3, 0, 1) == 11                      # float32: matrix-core kernel
+    assert v(1, 14, 14, 16, 2, 3, 0, 1) == 10                      # ... heads of up to 8 channels on few pixels: general kernel
+    assert v(1, 93, 93, 16, 2, 3, 0, 1) == 11
+    assert v(1, 14, 14, 16, 2, 5, 0, 1) == 11
+    assert v(1, 14, 14, 64, 2, 7, 0, 1) == 10 == v(1, 14, 14, 64, 2, 1, 1, 1)   # windows of 7 and 1
     assert v(64, 28, 28, 128, 4, 5, 1, 1) == 30                    # 5x5
     assert v(64, 56, 56, 64, 2, 3, 1, 1) == 24                     # stage 1: streaming kernel
     assert v(64, 56, 56, 64, 2, 3, 1, 0) == 20                     # unaligned pointers: one tile per block
@@ -183,15 +187,16 @@ def test_forward_variant_selection(lib):
     assert v(96, 48, 48, 64, 2, 3, 1, 1) == 24                     # streaming kernel, 48 columns
     assert v(96, 40, 40, 64, 2, 3, 1, 1) == 21                     # 40 columns need too much LDS there: pipelined tiles
     assert v(300, 24, 24, 64, 2, 3, 1, 1) == 21                    # narrower than 32: pipelined tiles, width from the arguments
-    assert v(2, 9, 21, 64, 2, 3, 1, 1) == 20                       # W % 8 != 0
+    assert v(2, 9, 21, 64, 2, 3, 1, 1) == 22 == v(2, 9, 21, 64, 2, 3, 1, 0)     # W % 8 != 0: pipelined tiles, unaligned rows
+    assert v(2, 9, 7, 64, 2, 3, 1, 1) == 20                        # ... narrower than one 16-byte piece
     assert v(8, 100, 128, 32, 1, 3, 1, 1) == 26                    # 128 columns: three strips
     assert v(8, 100, 128, 32, 1, 3, 1, 0) == 20                    # ... not from unaligned pointers: one tile per block
     # many small planes: enough tiles, but a tile buffer too small to build the operand image in
     assert v(128, 8, 8, 128, 4, 3, 1, 1) == 20
     assert v(256, 2, 64, 64, 2, 3, 1, 1) == 24                     # two-row planes: streaming kernel
     assert v(64, 56, 56, 64, 1, 3, 1, 1) == 25                     # one head of 64 channels: two launches over half heads
-    assert v(64, 56, 56, 64, 1, 3, 1, 0) == 10                     # ... not from unaligned pointers
-    assert v(8, 100, 128, 64, 1, 3, 1, 1) == 10                    # ... nor on a map the streaming kernel does not take
+    assert v(64, 56, 56, 64, 1, 3, 1, 0) == 11                     # ... not from unaligned pointers
+    assert v(8, 100, 128, 64, 1, 3, 1, 1) == 11                    # ... nor on a map the streaming kernel does not take
     assert lib.slide_attn_workspace_bytes(64, 56, 56, 64, 1, 3, 1, 0) == 64 * 2 * 9 * 56 * 56 * 4   # the halves' partial logits
     assert lib.slide_attn_fwd_path(64, 56, 56, 64, 1, 3, 1) == 2
 
@@ -201,21 +206,22 @@ def test_backward_variant_selection(lib):
     no device)."""
     v = lib.slide_attn_bwd_variant
     assert v(1, 14, 14, 64, 3, 3, 0, 1) == 0                       # invalid
-    assert v(1, 14, 14, 64, 2, 3, 0, 1) == 10                      # float32: general kernels
-    assert v(64, 28, 28, 128, 4, 5, 1, 1) == 10                    # 5x5
+    assert v(1, 14, 14, 64, 2, 3, 0, 1) == 11                      # float32: matrix-core kernels
+    assert v(64, 28, 28, 128, 4, 5, 1, 1) == 11                    # 5x5
+    assert v(1, 14, 14, 64, 2, 7, 0, 1) == 10                      # 7x7: general kernels
     assert v(128, 56, 56, 64, 2, 3, 1, 1) == 27                    # stage-1 training: all three streaming kernels
-    assert v(128, 56, 56, 64, 2, 3, 1, 0) == 10                    # unaligned pointers: general kernels
+    assert v(128, 56, 56, 64, 2, 3, 1, 0) == 11                    # unaligned pointers: float32 kernels
     assert v(2, 33, 32, 64, 2, 3, 1, 1) == 26                      # too narrow for the dk/dv kernel's record rings
     assert v(3, 40, 64, 32, 1, 3, 1, 1) == 22                      # 64 columns: a dl / a row is more than one load
     assert v(2, 13, 72, 32, 1, 3, 1, 1) == 20                      # wider than 64: tiled kernels
     assert v(50, 20, 40, 96, 3, 3, 1, 1) == 24                     # bands of 20 rows of 40 columns need too deep a ring: only the kernel gradients stream
-    assert v(2, 9, 21, 64, 2, 3, 1, 1) == 20                       # W % 8 != 0: tiled kernels, general kernel-gradient part
+    assert v(2, 9, 21, 64, 2, 3, 1, 1) == 20                       # W % 8 != 0: tiled kernels, float32 kernel-gradient part
     assert v(128, 56, 56, 48, 2, 3, 1, 1) == 127                   # 24 channels per head: the streaming kernels on padded copies
-    assert v(128, 56, 56, 48, 2, 3, 1, 0) == 10                    # ... not from unaligned pointers
+    assert v(128, 56, 56, 48, 2, 3, 1, 0) == 11                    # ... not from unaligned pointers
     assert v(4, 13, 72, 16, 2, 3, 1, 1) == 120                     # 8 channels per head, wide map: the tiled kernels on padded copies
-    assert v(4, 13, 72, 128, 2, 3, 1, 1) == 10                     # 64 channels per head on a wide map: general kernels
+    assert v(4, 13, 72, 128, 2, 3, 1, 1) == 11                     # 64 channels per head on a wide map: float32 kernels
     assert v(128, 56, 56, 64, 1, 3, 1, 1) == 227                   # 64 channels per head: half heads through the streaming kernels
-    assert v(128, 56, 56, 64, 1, 3, 1, 0) == 10
+    assert v(128, 56, 56, 64, 1, 3, 1, 0) == 11
 
 
 def test_binding_rejects_mismatched_parameter_shapes(lib):

@@ -44,6 +44,11 @@ def _check(name, got, want, tol, floor):
 def test_against_oracle(shape, two_branch):
     B, H, W, C, heads, ks, dtype, last = shape
     print("float32 matrix-core case", shape, two_branch, flush=True)
+    if dtype == "f32" or last:      # (the channels-last forward of these shapes follows the rule of float32)
+        narrow = ks == 3 and C // heads <= 8 and B * heads * H * W <= 8192
+        assert sa.slide_attn_fwd_variant(B, H, W, C, heads, ks, 0) == (10 if narrow else 11)
+    if dtype == "f32" or ks == 5:
+        assert sa.slide_attn_bwd_variant(B, H, W, C, heads, ks, 0 if dtype == "f32" else 1) == 11
     dev = torch.device("cuda:0")
     dd = synth.make_inputs(B, H, W, C, heads, ks, dtype, seed=300 + H + W + C, with_dout=True)
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16

@@ -65,6 +65,8 @@ def _oracle(acts, wk, wv, bias, heads, ks):
 def test_against_oracle(shape, shift):
     heads, ks, dtype = shape[4:]
     print("float32 matrix-core gradients", shape, shift, flush=True)
+    code = 0 if dtype == "f32" else 1
+    assert sa.slide_attn_bwd_variant(*shape[:5], ks, code, shift == 0) == (20 if dtype == "bf16" and ks == 3 and shape[3] // heads == 32 and not shift else 11)
     acts, wk, wv, bias = _inputs(shape, 500 + sum(shape[1:4]))
     grads = sa.slide_attn_bwd(*(_shifted(a, shift) for a in acts), wk, wv, bias, heads, ks)
     # the same again, added to what is there

@@ -44,6 +44,8 @@ def _check(name, got, want):
 def test_against_oracle(shape, shift, two_branch):
     B, H, W, C, heads = shape
     print("ragged rows", shape, shift, two_branch, flush=True)
+    assert sa.slide_attn_fwd_variant(B, H, W, C, heads, 3, 1) == (22 if W >= 8 else 20)
+    assert sa.slide_attn_bwd_variant(B, H, W, C, heads, 3, 1, shift == 0) == (11 if shift else 20)
     dev = torch.device("cuda:0")
     dd = synth.make_inputs(B, H, W, C, heads, 3, "bf16", seed=900 + H + W, with_dout=True)
     do, q, k, v = (_placed(dd[n].to(dev).to(torch.bfloat16), shift) for n in ("dout", "q", "k", "v"))
