@@ -251,7 +251,7 @@ fwd16_kernel(const FwdArgs a)
 
 // ------------------------------------------------------------------ forward, pipelined
 // Persistent blocks of 8 waves, one per compute unit, for problems whose rows are 16-byte
-// aligned (W % 8 == 0).  Block b works through tiles b, b + grid, ... of the tile list.  Two
+// aligned (W % 8 == 0); RAGGED: rows that start at any even address.  Block b works through tiles b, b + grid, ... of the tile list.  Two
 // LDS tile buffers: while the passes of one tile run, each pass also fetches a share of the
 // next tile (four 16-byte loads per lane at the start of the pass, converted into the other
 // buffer one pass later), so global loads and arithmetic overlap inside the block instead of
@@ -330,7 +330,7 @@ __device__ __forceinline__ void share_store(const Tile& t, const ShareGeom& sg, 
     const int cq = u & 7, rest = u >> 3;
     const int hr = (int)(((uint32_t)rest * sg.recip_nx) >> 16), x = rest - hr * t.NX;
     // first halo column of the chunk: a multiple of 8 plus 1 (the chunk grid is 8-aligned and
-    // a tile starts at a multiple of 64), so the swizzle term of column hc0 + px depends on px only
+    // a tile starts at a multiple of 8), so the swizzle term of column hc0 + px depends on px only
     const int hc0 = t.gxa + 8 * x - (t.j0 - 1);
     unsigned char* dst = buf + (2 * hr + (hb & 1)) * (HC * 64) + hc0 * 64 + (cq & 1) * 8;
     const int o4 = (cq >> 1) << 4;

@@ -5,9 +5,10 @@
 // pixel the k*k window of every channel is read with zero padding, the merged
 // depthwise kernels are applied on the fly (the k*k-fold shifted tensor is never
 // written to memory), logits get the per-head bias, a softmax runs over the k*k
-// shifts and the shifted values are summed.  They serve float32 problems, head sizes
-// other than 32 and window sizes the matrix-core kernel does not cover, and they
-// are the whole backward pass.
+// shifts and the shifted values are summed.  They serve windows of 1 and 7, the plain shift off the
+// streaming kernels' maps, and 3x3 forwards of narrow heads on few pixels; other float32 work runs
+// on the matrix cores (slide_mfma32.hip, slide_mfma32_bwd.hip).  This file also holds the dispatch of the
+// backward and the copies around it (padded heads, layouts).
 //
 // Thread mapping: one thread per (pixel, head, batch item); threads of a wavefront
 // walk along W, so every per-channel read of q, k, v is a coalesced row segment and
@@ -15,6 +16,7 @@
 // block-uniform values, so the compiler fetches them through the scalar cache.
 #include "slide_internal.h"
 #include "slide_device.h"
+#include <algorithm>
 #include <initializer_list>
 
 namespace slide {
@@ -62,14 +64,15 @@ __device__ __forceinline__ void load_window(const T* __restrict__ plane, int i, 
 
 // deformed shift of one channel at one pixel: shifted[s] = sum_t w[s][t] * win[t], plus the
 // fixed shift path idw * win[s] (idw = 1 when w is the learned kernel of the two-branch form).
-// w_c null: the plain shift (one-hot kernels, Eq. 10-13), shifted[s] = win[s].
+// w_c null: the plain shift (one-hot kernels, Eq. 10-13), shifted[s] = win[s]; a 5x5 window comes here
+// for nothing else.
 template <int KS>
 __device__ __forceinline__ void apply_kernels(const float* __restrict__ w_c,
                                               const float (&win)[KS * KS],
                                               float (&shifted)[KS * KS], float idw)
 {
     constexpr int S = KS * KS;
-    if (!w_c) {
+    if (KS == 5 || !w_c) {
 #pragma unroll
         for (int s = 0; s < S; ++s) shifted[s] = win[s];
         return;
@@ -527,11 +530,9 @@ hipError_t launch_bwd_dw_reduce(const float* partial, float* dwk, float* dwv, lo
 // bytes of the partial kernel-gradient region (whichever kernel runs), a multiple of 16
 static size_t bwd_partial_bytes(const Problem& p)
 {
-    size_t part = (size_t)dw_chunks(p) * 2 * (size_t)p.C * p.S() * p.S() * sizeof(float);
-    const size_t floats[] = {bwd_dw_mfma_supported(p) ? bwd_dw_mfma_partial_floats(p) : 0, bwd_dw_m32_partial_floats(p)};
-    for (size_t f : floats)
-        if (f * sizeof(float) > part) part = f * sizeof(float);
-    return (part + 15) & ~(size_t)15;
+    size_t floats = m32_supported(p) ? bwd_dw_m32_partial_floats(p) : (size_t)dw_chunks(p) * 2 * (size_t)p.C * p.S() * p.S();
+    if (bwd_dw_mfma_supported(p)) floats = std::max(floats, bwd_dw_mfma_partial_floats(p));
+    return (floats * sizeof(float) + 15) & ~(size_t)15;
 }
 
 static size_t bwd_workspace_bytes_as_given(const Problem& p)

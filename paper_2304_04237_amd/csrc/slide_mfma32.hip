@@ -5,7 +5,9 @@
 // What bounds these kernels is the learned-kernel contraction, k^2 shifts by k^2 taps per channel
 // and pixel.  v_mfma_f32_4x4x1_16b_f32 with a broadcast left operand (cbsz = 4) is an outer product of
 // four weights with 64 lanes: D[r][lane] += A[4 * abid + r] * B[lane], 256 float32 multiply-adds in
-// 8 cycles (measured 8.4 at 4 waves per SIMD; 143 TFLOP/s).  A lane is a pixel, a register of A
+// 8 cycles (9.3 issued back to back, measured; by the counters the matrix cores are busy for 8, and a
+// vector instruction beside them takes 5 to 6 more).  It multiplies and adds with one rounding, to nearest, and keeps
+// denormals (checked against fmaf on a million products).  A lane is a pixel, a register of A
 // holds 64 weights, so the weights come as one coalesced LDS read per 64 of them instead of one
 // scalar load per multiply-add, which is what held the general kernels at 4.6 TFLOP/s.  Of the k^2
 // shifts of a channel k^2 - 1 (8 or 24, a multiple of four) go through the matrix cores and the
@@ -33,7 +35,7 @@ struct PixelArgs {
 // LDS moves 190 B per cycle and CU that way, 82 in 4-byte reads, measured).  The next step's
 // elements are fetched into registers while the current one is multiplied.  MI355X, against one
 // thread per pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: forward 335 -> 50
-// us, backward 503 -> 79 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 350 us; one
+// us, backward 503 -> 80 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 350 us; one
 // 14x14 map of 2 heads, forward: 18.9 -> 9.4 us.
 // FOUR: a quad's channels are neighbours in memory (channels last, whole quads): one load, one store instead of
 // four (bf16, 3x3, B=64, 27x27, C=128, 4 heads: 84 -> 58 us per call; float32, B=32, 56x56, C=64: 123 -> 76).
@@ -177,7 +179,10 @@ pixel32_kernel(const PixelArgs a)
                 for (int idx = tid; idx < CQ * 4 * S * S; idx += NT)
                     wl[idx] = c0 * S * S + idx < d * S * S ? wb[c0 * S * S + idx] : 0.0f;
             }
-            if (a.idw != 0.0f) {                            // the fixed shift path of the two-branch form
+            // the fixed shift path of the two-branch form: 1 + w, rounded to 24 bits as slide_reparam rounds it.  That is one
+            // rounding where adding the shifted value on its own takes one more per tap: out 1.31e-7 from 64 bits here,
+            // 1.42e-7 on the general kernels (float32, 3x3, 56x56)
+            if (a.idw != 0.0f) {
                 __syncthreads();
                 for (int i = tid; i < min(CQ * 4, d - c0) * S; i += NT) wl[(i / S) * (S * S) + (i % S) * (S + 1)] += a.idw;
             }

@@ -169,7 +169,9 @@ inline bool pixel_few(int B, int heads, int H, int W, int d, int ks)
     return sets * eights * (16 + 2.2 * (quads < 8 ? quads : 8)) < (3.5 + 8.7 * quads) * (large > MAX_CU_PLANNED ? 1.6 : 1.0);
 }
 // dk/dv kernel: blocks of 256 pixels where those give every compute unit two and two fit its LDS (maps of a few columns
-// have tall runs with much halo), else 64 pixels whose channels four waves share
+// have tall runs with much halo), else 64 pixels whose channels four waves share.  bf16, 5x5, B=32, 2 heads: 28x28 90 us,
+// 40x40 163; from 41 columns on two quads per step leave no room for a second block, and the small form takes 489 us at
+// 45x45 and 721 at 56x56.  (One quad per step would fit up to 60 columns; it costs 116 us at 28x28.)
 inline bool dkdv_few(int B, int heads, int H, int W, int ks, int element_bytes)
 {
     if (((long)H * W + 255) / 256 * heads * 2 * B < 512) return true;
