@@ -105,3 +105,60 @@ def test_strips_of_wide_maps(shape):
 ])
 def test_narrow_heads_and_maps(shape):
     test_against_oracle(shape, True)
+
+
+@pytest.mark.parametrize("shape", [(2, 13, 27, 64, 2, 3, "bf16"), (1, 9, 21, 24, 2, 5, "f32"), (40, 33, 29, 16, 1, 3, "f32"), (4, 30, 63, 128, 2, 5, "bf16")])
+def test_channels_last_at_any_element(shape):
+    """Four channels are loaded and stored at once, at any element's address: tensors one element past an aligned one, NaN
+    around the inputs, a pattern around the output that stays."""
+    B, H, W, C, heads, ks, dtype = shape
+    print("channels last, unaligned", shape, flush=True)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dd = synth.make_inputs(B, H, W, C, heads, ks, dtype, seed=31)
+
+    def placed(t, fill):
+        buf = torch.full((t.numel() + 9,), fill, dtype=tdt, device="cuda")
+        view = buf[1:1 + t.numel()].view(t.shape)
+        view.copy_(t)
+        return buf, view
+    q, k, v = (placed(dd[n].permute(0, 2, 3, 1).to(tdt), float("nan"))[1] for n in ("q", "k", "v"))
+    buf, out = placed(torch.zeros(B, H, W, C), 7.0)
+    wk, wv = (sa.slide_reparam(dd[n].cuda()) for n in ("wk_learned", "wv_learned"))
+    bias = dd["bias"].cuda()
+    sa.slide_attn_fwd_nhwc(q, k, v, wk, wv, bias, heads, ks, out=out)
+    aligned = sa.slide_attn_fwd_nhwc(*(x.clone() for x in (q, k, v)), wk, wv, bias, heads, ks)
+    torch.cuda.synchronize()
+    assert (buf[:1] == 7.0).all() and (buf[1 + out.numel():] == 7.0).all()
+    n = {x: dd[x].double().numpy() for x in ("q", "k", "v", "bias")}
+    ref = oracle.fwd(n["q"], n["k"], n["v"], wk.double().cpu().numpy(), wv.double().cpu().numpy(), n["bias"], heads, ks)
+    _check("out", out.permute(0, 3, 1, 2), ref, 1e-5 if dtype == "f32" else 2e-2, 0.0 if dtype == "f32" else 1.0)
+    if W not in range(32, 65, 8):        # (the streaming kernel takes aligned tensors of those widths)
+        assert torch.equal(out, aligned)
+
+
+@pytest.mark.parametrize("ks", [3, 5])
+@pytest.mark.parametrize("shape", [(2, 21, 23, 12, 2), (34, 40, 33, 12, 2)])     # both block forms
+def test_infinite_values_stay_in_reach(shape, ks):
+    """One infinite element of k, v or dO: results of other batch items, of other heads and of pixels that do not see it are
+    those without it, bit by bit; kernel gradients of the other head too."""
+    B, H, W, C, heads = shape
+    print("infinite values", shape, ks, flush=True)
+    dd = synth.make_inputs(B, H, W, C, heads, ks, "f32", seed=41, with_dout=True)
+    base = {n: dd[n].cuda() for n in ("dout", "q", "k", "v")}
+    wk, wv = (sa.slide_reparam(dd[n].cuda()) for n in ("wk_learned", "wv_learned"))
+    bias = dd["bias"].cuda()
+
+    def results(a):
+        return (sa.slide_attn_fwd(a["q"], a["k"], a["v"], wk, wv, bias, heads, ks),
+                *sa.slide_attn_bwd(a["dout"], a["q"], a["k"], a["v"], wk, wv, bias, heads, ks))
+    want = results(base)
+    i, j, c, reach = 10, 11, 2, 2 * (ks // 2)
+    for name in ("k", "v", "dout"):
+        acts = {n: t.clone() for n, t in base.items()}
+        acts[name][1, c, i, j] = float("inf")
+        for what, got, clean in list(zip("out dq dk dv".split(), results(acts), want)):
+            touched = torch.zeros_like(got, dtype=torch.bool)
+            touched[1, :C // heads, max(0, i - reach):i + reach + 1, max(0, j - reach):j + reach + 1] = True
+            assert torch.equal(got[~touched], clean[~touched]), (name, what)
+        for what, got, clean in list(zip("dwk dwv".split(), results(acts)[4:6], want[4:6])):
+            assert torch.equal(got[C // heads:], clean[C // heads:]), (name, what)

@@ -80,3 +80,25 @@ def test_against_oracle(shape, shift, two_branch):
 def test_last_pieces_of_tiny_tensors(shape, shift):
     """Most 16-byte pieces of these run past the tensor's end, by up to seven elements."""
     test_against_oracle(shape, shift, False)
+
+
+@pytest.mark.parametrize("two_branch", [False, True])
+@pytest.mark.parametrize("shape", [(2, 15, 14, 64, 2), (3, 9, 65, 64, 2), (1, 21, 131, 96, 3)])
+def test_kernels_that_are_not_16_byte_aligned(shape, two_branch):
+    """The pipelined kernel loads the kernels 16 bytes at a time; others take one tile per block, here in column tiles of
+    even shares."""
+    B, H, W, C, heads = shape
+    print("ragged rows, unaligned kernels", shape, two_branch, flush=True)
+    dd = synth.make_inputs(B, H, W, C, heads, 3, "bf16", seed=950 + W)
+    q, k, v = (dd[n].cuda().to(torch.bfloat16) for n in ("q", "k", "v"))
+    bias = dd["bias"].cuda()
+    merged = [sa.slide_reparam(dd[n].cuda()) for n in ("wk_learned", "wv_learned")]
+    given = [dd[n].cuda() for n in ("wk_learned", "wv_learned")] if two_branch else merged
+    wk, wv = (_placed(w, 1) for w in given)
+    lse = torch.full((B, heads, H, W), float("nan"), dtype=torch.float32, device="cuda")
+    fwd = sa.slide_attn_fwd_two_branch if two_branch else sa.slide_attn_fwd
+    out = fwd(q, k, v, wk, wv, bias, heads, 3, lse=lse)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle.fwd(*(x.double().cpu().numpy() for x in (q, k, v, *merged, bias)), heads, 3, return_lse=True)
+    _check("out", out, ref)
+    _check("lse", lse, ref_lse)
