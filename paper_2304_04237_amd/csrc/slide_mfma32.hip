@@ -143,7 +143,7 @@ pixel32_kernel(const PixelArgs a)
                     if (ALL || c0 + 4 * (peg + u * CG) < d) xr[u] = load4(xb, xoff, c0 + 4 * (peg + u * CG));
         };
         auto fetch = [&](int c0) {
-            if ((CG == 1 && !BWD) || c0 + 4 * CQ <= d) fetch_quads(c0, std::true_type{});
+            if (CQ == 1 || (CG == 1 && !BWD) || c0 + 4 * CQ <= d) fetch_quads(c0, std::true_type{});
             else fetch_quads(c0, std::false_type{});
             if (AHEAD_W)
 #pragma unroll
