@@ -206,13 +206,13 @@ inline DwPlan plan_dw(int B, int H, int W, int C, int heads, int ks, int element
         const size_t red = (size_t)DW_CH * S * S * (ks == 3 ? dw_threads(ks) / 64 : 1);
         return (tile > red ? tile : red) * sizeof(float);
     };
-    // blocks: eight waves on every compute unit.  Tiles: those that cost the fewest rounds of one quad per walker,
-    // halo and barriers counted as part of a round; Where that
+    // blocks: eight waves on every compute unit.  Tiles: those that cost the fewest rounds of one quad per walker.  Where that
     // gives far fewer tiles than chunks wanted, lower ones, down to 8 pixels of each walker: more blocks, and
     // their sums are as short as those of the general kernel's threads
     const int per_cu = 512 / dw_threads(ks), walkers = ks == 3 ? 8 : 2;
     const long jobs = 2L * heads * ((d + DW_CH - 1) / DW_CH);
-    long n = (per_cu * MAX_CU_PLANNED + jobs - 1) / jobs;
+    long n = per_cu * MAX_CU_PLANNED / jobs;                // (a few blocks more would run after all others)
+    if (n < 1) n = 1;
     auto rounds = [&](int th, int tw) { return (th * ((tw + 3) / 4) + walkers - 1) / walkers; };
     const int strips = (W + 31) / 32, even = ((W + strips - 1) / strips + 3) & ~3;
     double best = 0;
@@ -224,9 +224,13 @@ inline DwPlan plan_dw(int B, int H, int W, int C, int heads, int ks, int element
             if (lds(TR, TC) > CU_LDS_BYTES / per_cu || (TR + 2 * R) * quads > lanes * most.y || TR * quads > lanes * most.x ||
                 S * TR * quads > dw_threads(ks) * most.p) continue;
             const int ntr = (H + TR - 1) / TR, ntc = (W + TC - 1) / TC, lr = H - (ntr - 1) * TR, lc = W - (ntc - 1) * TC;
-            const double tiles = (double)ntr * ntc, halo = (double)(H + 2 * R * ntr) * ntc;
-            const double cost = (ntr - 1.0) * ((ntc - 1.0) * rounds(TR, TC) + rounds(TR, lc)) + (ntc - 1.0) * rounds(lr, TC) + rounds(lr, lc) +
-                                0.5 * tiles + 0.1 * halo;
+            // a tile costs its rounds, the rows it stages and its barriers; a chunk has whole tiles, so the block with the most of
+            // them has up to one more than the average (bf16, 5x5, 30 x 54x40, 3 heads: 395 us with tiles of the fewest rounds and two
+            // blocks more than there is room for, 223 like this; 3x3, 1 x 200x333, 3 heads 73 and 66)
+            auto tile = [&](int th, int tw) { return rounds(th, tw) + 1.5 + 0.1 * (th + 2 * R); };
+            const double plane = (ntr - 1.0) * ((ntc - 1.0) * tile(TR, TC) + tile(TR, lc)) + (ntc - 1.0) * tile(lr, TC) + tile(lr, lc);
+            const long tiles = (long)B * ntr * ntc, chunks = n < tiles ? n : tiles;
+            const double cost = B * plane / chunks + tile(TR, TC) * ((tiles + chunks - 1) / chunks - (double)tiles / chunks) + 0.02 * chunks;
             if (best == 0 || cost < best) { best = cost; t.TR = TR; t.TC = TC; }
         }
     t.ntc = (W + t.TC - 1) / t.TC;
