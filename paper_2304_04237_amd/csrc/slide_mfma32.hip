@@ -34,9 +34,9 @@ struct PixelArgs {
 // lies in LDS as [quad][pixel][4 channels], so a tap is one 16-byte read for four channels (the
 // LDS moves 190 B per cycle and CU that way, 82 in 4-byte reads, measured).  The next step's
 // elements are fetched into registers while the current one is multiplied.  MI355X, against one
-// thread per pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: forward 335 -> 50
-// us, backward 503 -> 80 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 350 us; one
-// 14x14 map of 2 heads, forward: 18.9 -> 9.4 us.
+// thread per pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: forward 335 -> 56
+// us, backward 503 -> 89 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 384 us; one
+// 14x14 map of 2 heads, forward: 18.9 -> 10 us.
 // FOUR: a quad's channels are neighbours in memory (channels last, whole quads): one load, one store instead of
 // four (bf16, 3x3, B=64, 27x27, C=128, 4 heads: 84 -> 58 us per call; float32, B=32, 56x56, C=64: 123 -> 76).
 template <typename T, int KS, int PG, int CG, int CQ, bool BWD, bool FOUR>
