@@ -240,10 +240,14 @@ inline DwPlan plan_dw(int B, int H, int W, int C, int heads, int ks, int element
     t.tiles = (long)B * t.ntr * t.ntc;
     if (n > t.tiles) n = t.tiles;
     t.chunks = (int)n;
-    // quads of a walker between two additions to its totals: 32 pixels, fewer where its whole share is not much
-    // more (the additions cost nothing there), 64 of long shares of the 5x5 window, where 32 cost 6 % more time
+    // quads of a walker between two additions to its totals: 3x3 32 pixels, 12 where its whole share is not much more (the
+    // additions cost nothing there).  5x5: a share of n quads in groups of g rounds like 2 g + n / 2 g roundings, least at
+    // g = sqrt(n) / 2, which is what is taken up to 64 quads; beyond, longer groups for time (32 pixels cost 6 % more than 64).
+    // Merged kernels, float32, C=64, 2 heads, dwv against 64 bits (mean of 10 inputs), dw kernel, MI355X: 4 x 28x28 (7 quads)
+    // groups of 3 1.791e-7, 19.6 us, of 2 1.771e-7, 20.2 us (general kernels 1.762e-7); 4 x 56x56 (28) of 3 1.869e-7, 46.7 us,
+    // of 2 1.868e-7, 49.6 us; 32 x 28x28 (50) of 8 2.024e-7, 66.6 us, of 4 1.955e-7, 71.1 us (general kernels 1.996e-7)
     const long share = t.tiles / n * rounds(t.TR, t.TC);
-    t.group = share <= (ks == 3 ? 16 : 32) ? 3 : ks == 3 || share <= 128 ? 8 : 16;
+    t.group = ks == 3 ? (share <= 16 ? 3 : 8) : share <= 16 ? 2 : share <= 32 ? 3 : share <= 64 ? 4 : share <= 128 ? 8 : 16;
     return t;
 }
 

@@ -1,5 +1,6 @@
 // Checks of the host-side plans (slide_plan.h) over all sizes; prints what is wrong and returns 1.
 #include "slide_plan.h"
+#include <cmath>
 #include <algorithm>
 #include <chrono>
 #include <cstdio>
@@ -45,6 +46,13 @@ static void gradients(int B, int H, int W, int C, int heads)
             CHECK(t.TR >= 1 && t.TR <= m32::DW_MAX_ROWS && t.TC >= 4 && t.TC <= 32 && t.TC % 4 == 0 && (long)t.ntr * t.TR >= H && (t.ntr - 1) * t.TR < H &&
                   (long)t.ntc * t.TC >= W && (t.ntc - 1) * t.TC < W, "tiles of %dx%d, window %d", H, W, ks);
             CHECK(t.tiles == (long)B * t.ntr * t.ntc && t.chunks >= 1 && t.chunks <= t.tiles && t.group >= 1, "chunks of %dx%dx%d", B, H, W);
+            // a walker's share of n quads in groups of g: a group is a sum of 4 g terms, the totals one of n / g, and a running sum of
+            // m terms rounds like m / 2 roundings of its result: 2 g + n / 2 g, 2 sqrt(n) at best; short shares of
+            // the 5x5 window stay within what whole groups allow
+            if (const double n = (double)(t.tiles / t.chunks * ((t.TR * (t.TC / 4) + 1) / 2)); ks == 5 && n <= 64) {
+                const double group = t.group < n ? t.group : n;
+                CHECK(2 * group + n / (2 * group) <= 2 * std::sqrt(n) + 1.7, "sums of %dx%dx%d, %d channels, %d heads: %g quads in groups of %d", B, H, W, C, heads, n, t.group);
+            }
             for (int cols : {t.TC, W - (t.ntc - 1) * t.TC}) {
                 const int row = 1 << m32::dw_row_lanes_log2((cols + 3) / 4);
                 CHECK((cols + 3) / 4 <= row && row <= lanes, "quads of %dx%d", H, W);
