@@ -535,9 +535,16 @@ static size_t bwd_partial_bytes(const Problem& p)
     return (floats * sizeof(float) + 15) & ~(size_t)15;
 }
 
+// where what the split kernels keep lies, behind a, dl and the partial sums
+static size_t bwd_split_offset(const Problem& p)
+{
+    return (2 * (size_t)p.B * p.heads * p.S() * (size_t)p.plane() * sizeof(float) + bwd_partial_bytes(p) + 15) & ~(size_t)15;
+}
+
 static size_t bwd_workspace_bytes_as_given(const Problem& p)
 {
     size_t per = (size_t)p.B * p.heads * p.S() * (size_t)p.plane() * sizeof(float);
+    if (split_supported(p)) return bwd_split_offset(p) + split_workspace_bytes(p);
     return 2 * per + bwd_partial_bytes(p) + (bwd_dkdv_mfma_supported(p) ? bwd_dkdv_mfma_image_bytes(p) + bwd_pixel_mfma_image_bytes(p) : 0);
 }
 
@@ -647,6 +654,8 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
                                void* workspace, hipStream_t st)
 {
     constexpr bool M32 = KS == 3 || KS == 5;    // the general kernels serve the other windows
+    constexpr bool SPLIT = KS == 5 && sizeof(T) == 2;
+    [[maybe_unused]] void* split_ws = (char*)workspace + bwd_split_offset(p);
     const int S = p.S();
     const size_t per = (size_t)p.B * p.heads * S * (size_t)p.plane();
     float* attn_ws = (float*)workspace;
@@ -665,6 +674,10 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
         const bool streaming = half_ws && fwd_ring_enabled() && bwd_pixel_ring_supported(p, aligned16({dq}));
         e = launch_bwd_pixel_mfma(p, dout, q, k, v, wk, wv, bias, dq, attn_ws, dl_ws, half_ws, image_ws,
                                   dkdv_image_ws, streaming, st);
+    } else if constexpr (SPLIT) {
+        e = launch_split_prep(p, wk, wv, split_ws, st);
+        if (e != hipSuccess) return e;
+        e = launch_bwd_pixel_split(p, dout, q, k, v, bias, dq, attn_ws, dl_ws, split_ws, st);
     } else if constexpr (M32) {
         e = launch_bwd_pixel_m32(p, dout, q, k, v, wk, wv, bias, dq, attn_ws, dl_ws, st);
     } else {
@@ -687,6 +700,8 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
             e = launch_bwd_dkdv_ring(p, dout, q, attn_ws, dl_ws, dk, dv, image_ws, st);
         else
             e = launch_bwd_dkdv_mfma(p, dout, q, wk, wv, attn_ws, dl_ws, half_ws, dk, dv, image_ws, st);
+    } else if constexpr (SPLIT) {
+        e = launch_bwd_dkdv_split(p, split_ws, dk, dv, st);
     } else if constexpr (M32) {
         e = launch_bwd_dkdv_m32(p, dout, q, wk, wv, attn_ws, dl_ws, dk, dv, st);
     } else {

@@ -86,6 +86,15 @@ hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, 
                              const float* attn_ws, const float* dl_ws, float* partial, float* dwk, float* dwv,
                              float* dbias, hipStream_t st);
 
+// ---- float32 work on the 16-bit matrix cores by splitting (slide_split.hip): bf16, ksize 5, any head size and map.  ws: what the
+// kernels keep between them, split_workspace_bytes, 16-byte aligned; launch_split_prep comes first
+bool split_supported(const Problem& p);
+size_t split_workspace_bytes(const Problem& p);
+hipError_t launch_split_prep(const Problem& p, const float* wk, const float* wv, void* ws, hipStream_t st);
+hipError_t launch_bwd_pixel_split(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
+                                  const float* bias, void* dq, float* a_ws, float* dl_ws, void* ws, hipStream_t st);
+hipError_t launch_bwd_dkdv_split(const Problem& p, const void* ws, void* dk, void* dv, hipStream_t st);
+
 // forward of heads narrower than 32 channels (bf16, ksize 3, H * W % 8 == 0) through the
 // matrix-core kernels on copies padded to 32 channels per head (p32: the padded problem)
 bool fwd_padded_problem(const Problem& p, Problem& p32);

@@ -35,7 +35,7 @@ struct PixelArgs {
 // LDS moves 190 B per cycle and CU that way, 82 in 4-byte reads, measured).  The next step's
 // elements are fetched into registers while the current one is multiplied.  MI355X, against one
 // thread per pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: forward 335 -> 56
-// us, backward 503 -> 89 us; bf16, 5x5, B=64, 28x28, C=128, 4 heads: backward 4387 -> 384 us; one
+// us, backward 503 -> 89 us; one
 // 14x14 map of 2 heads, forward: 18.9 -> 10 us.
 // FOUR: a quad's channels are neighbours in memory (channels last, whole quads): one load, one store instead of
 // four (bf16, 3x3, B=64, 27x27, C=128, 4 heads: 84 -> 58 us per call; float32, B=32, 56x56, C=64: 123 -> 76).
@@ -414,7 +414,7 @@ hipError_t launch_bwd_pixel_m32(const Problem& p, const void* dout, const void* 
     a.dout = dout; a.a_ws = a_ws; a.dl_ws = dl_ws;
     if (p.dtype == 0)
         return p.ksize == 3 ? m32::launch_pixel_t<float, 3, true>(p, a, st) : m32::launch_pixel_t<float, 5, true>(p, a, st);
-    return p.ksize == 3 ? m32::launch_pixel_t<bf16_bits, 3, true>(p, a, st) : m32::launch_pixel_t<bf16_bits, 5, true>(p, a, st);
+    return m32::launch_pixel_t<bf16_bits, 3, true>(p, a, st);           // (5x5: slide_split.hip)
 }
 
 }  // namespace slide

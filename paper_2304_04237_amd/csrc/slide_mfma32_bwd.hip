@@ -28,9 +28,7 @@ struct DkdvArgs {
 // LDS holds a (or dl) of the run's rows and halo as [pixel][s], NQ quads of channels of dO (or q) as
 // [quad][pixel][4] and their kernels.  A tap costs S 4-byte LDS reads per lane whatever the number of
 // quads, so NQ is as large as two blocks per compute unit allow.  MI355X, against one thread per
-// pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: 846 -> 53 us; bf16, 5x5, B=64,
-// 28x28, C=128, 4 heads: 4855 -> 327 us (with a (or dl) as planes, a step's elements loaded when it begins and
-// idle waves computing, 368 in a run in which this form took 289).
+// pixel (slide_generic.hip): float32, 3x3, B=32, 56x56, C=64, 2 heads: 846 -> 53 us.
 template <typename T> struct Quad;
 template <> struct Quad<float> {
     typedef f4 Raw;
@@ -674,7 +672,7 @@ hipError_t launch_bwd_dkdv_m32(const Problem& p, const void* dout, const void* q
     a.idw = p.two_branch ? 1.0f : 0.0f;
     if (p.dtype == 0)
         return p.ksize == 3 ? m32::launch_dkdv_t<float, 3>(p, a, st) : m32::launch_dkdv_t<float, 5>(p, a, st);
-    return p.ksize == 3 ? m32::launch_dkdv_t<bf16_bits, 3>(p, a, st) : m32::launch_dkdv_t<bf16_bits, 5>(p, a, st);
+    return m32::launch_dkdv_t<bf16_bits, 3>(p, a, st);                  // (5x5: slide_split.hip)
 }
 
 hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, const void* k, const void* v,

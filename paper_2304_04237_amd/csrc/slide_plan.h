@@ -252,4 +252,64 @@ inline DwPlan plan_dw(int B, int H, int W, int C, int heads, int ks, int element
 }
 
 }  // namespace m32
+namespace split {
+
+// ---- 5x5 window, float32 work on the bf16 matrix cores (slide_split.hip)
+constexpr int SPLIT_PX = 256;                               // pixels of a block
+constexpr int SPLIT_TILE = 768;                             // places of its halo tile, three per thread
+
+// The planes of several items as one tall map: R empty rows between two of them are the lower halo of one and the upper halo
+// of the next.  It is cut into even column strips (Cut says why), a strip flattened row by row (without the empty rows) and cut
+// into runs of px pixels, of which only the last is not full.  A run's halo tile is NR rows of RP pixels.
+struct Stack { int planes, TW, wider, ns, px, runs, NR, RP, npx; };
+
+inline Stack plan_stack(int planes, int H, int W)
+{
+    constexpr int R = 2, MAX_TW = 64 - 2 * R;
+    Stack c;
+    c.planes = planes;
+    c.ns = (W + MAX_TW - 1) / MAX_TW;
+    c.TW = W / c.ns;
+    c.wider = W - c.ns * c.TW;
+    const int widest = c.TW + (c.wider > 0);
+    c.RP = widest + 2 * R;
+    for (c.px = SPLIT_PX;; c.px -= 32) {                    // (less than 256 on maps of a few columns or rows)
+        long rows = (c.px - 2) / c.TW + 2, gaps;            // that a run touches, and the empty ones between them
+        if (rows > (long)planes * H) rows = (long)planes * H;
+        gaps = (rows - 1 + H - 1) / H;
+        if (gaps > planes - 1) gaps = planes - 1;
+        c.NR = (int)(rows + R * gaps) + 2 * R;
+        c.npx = c.NR * c.RP;
+        if (c.npx <= SPLIT_TILE || c.px <= 32) break;
+    }
+    c.runs = (int)(((long)planes * H * widest + c.px - 1) / c.px);
+    return c;
+}
+// how many planes are stacked: all, unless a run's tile may reach further from its first plane than 32-bit offsets do
+inline int stack_planes(int B, int H, int W, int C)
+{
+    const long reach = plan_stack(B, H, W).NR / (H + 2) + 2;
+    return 2L * C * H * W * reach < (1L << 32) ? B : 1;
+}
+
+// key and value gradients: jobs of 32 columns (of all items) by a band of rows, dealt to the waves of at most one block per
+// compute unit for `sets` sets of operands.  A row of a band costs 25 chains, a band about as much as two rows besides.
+struct Bands { int rows, blocks; long groups, jobs; };
+inline Bands plan_bands(int B, int H, int W, int sets)
+{
+    Bands t;
+    t.groups = ((long)B * W + 31) / 32;
+    const long most = MAX_CU_PLANNED / sets > 1 ? MAX_CU_PLANNED / sets : 1;
+    double best = 0;
+    for (int rows = 1; rows <= H && rows <= 512; ++rows) {
+        const int bands = (H + rows - 1) / rows;
+        if (rows > 1 && (H + rows - 2) / (rows - 1) == bands) continue;     // (as many bands as with fewer rows)
+        const long jobs = t.groups * bands, blocks = (jobs + 7) / 8 < most ? (jobs + 7) / 8 : most;
+        const double cost = ((jobs + 8 * blocks - 1) / (8 * blocks)) * (rows + 1.5) * (blocks * sets > MAX_CU_PLANNED ? (double)(blocks * sets) / MAX_CU_PLANNED : 1.0);
+        if (best == 0 || cost < best) { best = cost; t.rows = rows; t.blocks = (int)blocks; t.jobs = jobs; }
+    }
+    return t;
+}
+
+}  // namespace split
 }  // namespace slide

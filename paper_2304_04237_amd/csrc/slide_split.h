@@ -1,0 +1,91 @@
+// Shared by the kernels that do float32 work on the 16-bit matrix cores by splitting (slide_split.hip, slide_split_bwd.hip):
+// bf16 activations, 5x5 window.
+//
+// A float32 weight is the sum of three bf16 values (8 significant bits each) exactly; a bf16 activation is one.  Their
+// products are exact in float32, and a matrix instruction adds sixteen of them and its accumulator with little more than one
+// rounding (measured, products of bf16 numbers, 16 terms and an accumulator of their size: 3.2e-8 from 64 bits, a chain of
+// float32 fused multiply-adds 3.8e-8; unbiased).  So a float32 contraction over K taps is a bf16 one over 3 K slots, at sixteen
+// times the float32 matrix rate per slot.
+#pragma once
+#include "slide_internal.h"
+#include "slide_device.h"
+
+namespace slide {
+namespace split {
+
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32_any __attribute__((aligned(2)));
+
+constexpr int KS = 5, S = 25, R = 2;
+
+// ---- operand image of the per-pixel kernels: per channel five left operands of 32 shifts (rows 25..31 zeros) by 16 slots,
+// 16 bytes per lane: lane = shift + 32 * half of the slots.  The slots of one lane are four dwords of two taps each:
+//   half h: d0 = row 2h, columns 0 1; d1 = row 2h, columns 2 3; d2, d3 = the same of row 2h + 1; d4 = row 4, columns 2h, 2h + 1;
+//   d5 = column 4 of rows 2h and 2h + 1; x = row 4, column 4 and nothing.
+// Instruction 0: d0..d3 with the third term of the weights, 1: with the second, 2: d4 d5 third, d4 d5 second, 3: d0..d3 first,
+// 4: d4 d5 first, x x with the first and second terms (half 0), the third and nothing (half 1): small products first.
+constexpr int PX_MM = 5;                                    // matrix instructions per channel
+constexpr int PX_CH = PX_MM * 64;                           // 16-byte pieces per channel
+// tap of dword d (0..6: d0..d5, x) element e of half h, -1: none
+__host__ __device__ constexpr int px_tap(int h, int d, int e)
+{
+    return d < 4 ? (2 * h + d / 2) * KS + 2 * (d % 2) + e : d == 4 ? 4 * KS + 2 * h + e : d == 5 ? (2 * h + e) * KS + 4 : e == 0 ? S - 1 : -1;
+}
+// term (0..2) and dword of instruction j, dword position w, half h; term -1: nothing
+__host__ __device__ constexpr int px_term(int j, int w, int h)
+{
+    return j == 0 ? 2 : j == 1 ? 1 : j == 2 ? (w < 2 ? 2 : 1) : j == 3 ? 0 : w < 2 ? 0 : h == 0 ? w - 2 : w == 2 ? 2 : -1;
+}
+__host__ __device__ constexpr int px_dword(int j, int w) { return j == 2 ? 4 + w % 2 : j == 4 ? (w < 2 ? 4 + w : 6) : w; }
+
+// ---- key and value gradients: a (or dl) times the kernels, both as two halves of 11 bits (22 bits with the second one's sign
+// 23).  So that halves hold any value, a pixel's are scaled by a power of two that brings the largest into [2^14, 2^15), and
+// a channel's weights likewise.
+// Record of a pixel, seven 16-byte pieces: A(h) first halves of shifts 4h..4h+3 and 8+4h..8+4h+3; B(h) first halves, then second
+// ones of shifts 16+4h..16+4h+3; C(h) second halves of A's; last: first, second, first half of shift 24, nothing, then the
+// inverse of the scale as a float.
+constexpr int REC_BYTES = 112, REC_A = 0, REC_B = 32, REC_C = 64, REC_LAST = 96;
+// Left operands: [column of the tap][row of the tap] of five instructions; lane = channel of 32 + 32 * half of the slots.
+// 0: second halves of the weights for A; 1: first for C; 2: second for B's first four, then last piece (half 0: first, first,
+// second); 3: first, first for B; 4: first for A.
+constexpr int KV_MM = 5, KV_TAP = KV_MM * 64, KV_IMG = S * KV_TAP;     // 16-byte pieces
+__host__ __device__ constexpr int kv_shift(int j, int h, int x)         // shift of slot x
+{
+    return j == 2 ? (x < 4 ? 16 + 4 * h + x : h == 0 && x < 7 ? S - 1 : -1) : j == 3 ? 16 + 4 * h + x % 4 : 8 * (x / 4) + 4 * h + x % 4;
+}
+__host__ __device__ constexpr bool kv_second(int j, int x) { return j == 0 || (j == 2 && (x < 4 || x == 6)); }
+// channel of row r = 16 h + i of 32 as the matrix results have it: where a pixel's q (or dO) stands for it
+__host__ __device__ constexpr int kv_place(int c) { return ((c >> 2) & 1) * 16 + (c >> 3) * 4 + (c & 3); }
+
+// the power of two that brings x into [2^14, 2^15), and its inverse (1 for zero, infinities and NaN)
+__device__ __forceinline__ void scale_for(float x, float& up, float& down)
+{
+    const uint32_t e = (__float_as_uint(x) >> 23) & 0xffu, ex = max(e, 20u);
+    const bool plain = e == 0xffu || x == 0.0f;
+    up = plain ? 1.0f : __uint_as_float((268u - ex) << 23);
+    down = plain ? 1.0f : __uint_as_float((ex - 14u) << 23);
+}
+__device__ __forceinline__ uint32_t half_bits(_Float16 x) { return __builtin_bit_cast(uint16_t, x); }
+__device__ __forceinline__ void split2(float v, uint32_t& hi, uint32_t& lo)
+{
+    const _Float16 a = (_Float16)v;
+    hi = half_bits(a);
+    lo = half_bits((_Float16)(v - (float)a));
+}
+
+// 16 bytes per lane from base + voff to LDS at lds_base + 16 * lane, without registers in flight; the wave waits for it by vmcnt
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %2\n\t"
+                 "s_nop 0\n\t"
+                 "global_load_lds_dwordx4 %1, %0"
+                 :: "s"(base), "v"(voff), "s"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_offset(const void* p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p; }
+
+}  // namespace split
+}  // namespace slide

@@ -65,6 +65,30 @@ static void gradients(int B, int H, int W, int C, int heads)
         }
 }
 
+// the split kernels: strips cover the map, a run's rows and the empty ones between planes fit the tile, offsets fit 32 bits; bands
+static void stacks(int B, int H, int W, int C)
+{
+    const int planes = split::stack_planes(B, H, W, C), R = 2;
+    CHECK(planes == B || planes == 1, "planes of %dx%dx%d", B, H, W);
+    const split::Stack c = split::plan_stack(planes, H, W);
+    const int widest = c.TW + (c.wider > 0);
+    CHECK(c.TW >= 1 && c.wider >= 0 && c.wider < c.ns && (long)c.ns * c.TW + c.wider == W && c.RP == widest + 2 * R, "strips of %dx%d", H, W);
+    CHECK(c.px >= 32 && c.px % 32 == 0 && c.px <= split::SPLIT_PX && c.npx == c.NR * c.RP && c.npx <= split::SPLIT_TILE, "tile of %dx%dx%d: %d", B, H, W, c.npx);
+    CHECK((long)c.runs * c.px >= (long)planes * H * widest, "runs of %dx%dx%d", B, H, W);
+    for (int tw = c.TW; tw <= widest; ++tw)
+        for (long n0 = 0; n0 < (long)planes * H * tw && n0 < 40L * c.px; n0 += c.px) {
+            const long l0 = n0 / tw, l1 = (std::min((long)planes * H * tw, n0 + c.px) - 1) / tw;
+            CHECK(l1 - l0 + R * (l1 / H - l0 / H) + 1 + 2 * R <= c.NR, "a run of %dx%dx%d touches more rows than are staged", B, H, W);
+        }
+    // (a tile starts at most R rows above its first pixel's plane row and is NR rows tall)
+    CHECK(planes == 1 || 2L * C * H * W * (c.NR / (H + R) + 2) < (1L << 32), "reach of %dx%dx%d, %d channels", B, H, W, C);
+    for (int sets : {2, 8, 66, 600}) {
+        const split::Bands t = split::plan_bands(B, H, W, sets);
+        const long bands = (H + t.rows - 1) / t.rows;
+        CHECK(t.rows >= 1 && t.blocks >= 1 && t.groups * 32 >= (long)B * W && (t.groups - 1) * 32 < (long)B * W && t.jobs == t.groups * bands, "bands of %dx%dx%d", B, H, W);
+    }
+}
+
 // the half-precision tile kernels' heights: as good as those found by trying every height down to one row where the tallest
 // tiles leave compute units without one, down to half the tallest elsewhere
 static double tile_makespan(int H, long planes, int th, int nA, int nB, int hb, int tw, int r2, int waves)
@@ -120,6 +144,11 @@ int main()
                     tiles(B, H, W, heads, 3, 81920, 0);
                     tiles(B, H, W, heads, 5, 60000, 8);
                 }
+    for (int H : {1, 2, 3, 5, 7, 14, 28, 41, 57, 200, 1000})
+        for (int W = 1; W <= 700; W += W < 140 ? 1 : 9)
+            for (int B : {1, 2, 3, 64, 1000})
+                for (int C : {1, 96, 4096}) stacks(B, H, W, C);
+    stacks(1, 1, (int)plane, 1); stacks(2, (int)plane, 1, 64); stacks(2, 5000, 6000, 512);
     // planning is part of every call: it must stay a fraction of a microsecond
     const auto t0 = std::chrono::steady_clock::now();
     long sum = 0;

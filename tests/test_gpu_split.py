@@ -1,0 +1,83 @@
+"""Backward of bf16 activations with a 5x5 window on the kernels that split float32 operands in 16-bit terms, against the CPU
+oracle where their tiling can go wrong: one pixel, one column, one row, planes that share a run of 256 pixels, several
+column strips, rows of odd length, heads that are no whole quad or block of 32 channels, more than one block of them, more
+column groups than waves, activations at odd addresses, activations far from one.
+
+Tolerances: the rounded gradients 2e-2 of max(1, largest entry) as everywhere; kernel and bias gradients 1e-5 of the
+largest entry, what float32 arithmetic gives (the split terms hold 23 or 24 bits)."""
+import pytest
+import torch
+
+import numpy as np
+import paper_2304_04237_amd as sa
+from paper_2304_04237_amd import synth
+from oracle import slide_oracle as oracle
+
+pytestmark = pytest.mark.gpu
+
+NAMES = "dq dk dv dwk dwv dbias".split()
+SHAPES = [
+    # B, H, W, C, heads
+    (1, 1, 1, 3, 1), (2, 1, 1, 4, 1), (3, 1, 9, 10, 2), (5, 9, 1, 6, 1), (2, 2, 3, 5, 1), (7, 5, 4, 8, 2), (3, 14, 14, 64, 2),
+    (2, 28, 28, 32, 1), (1, 19, 61, 33, 1), (1, 7, 130, 40, 1), (2, 31, 45, 64, 1), (1, 13, 60, 24, 1), (40, 6, 11, 8, 1),
+]
+
+
+def _inputs(shape, seed):
+    B, H, W, C, heads = shape
+    dev = torch.device("cuda:0")
+    dd = synth.make_inputs(B, H, W, C, heads, 5, "bf16", seed=seed, with_dout=True)
+    acts = [dd[n].to(dev).bfloat16() for n in ("dout", "q", "k", "v")]
+    wk, wv = (sa.slide_reparam(dd[n].to(dev)) for n in ("wk_learned", "wv_learned"))
+    return acts, wk, wv, dd["bias"].to(dev), [dd[n].to(dev) for n in ("wk_learned", "wv_learned")]
+
+
+def _odd(t):
+    buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+    out = buf[1:].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+def _compare(grads, acts, wk, wv, bias, heads, floor=1.0):
+    want = oracle.bwd(*[x.double().cpu().numpy() for x in (*acts, wk, wv, bias)], heads, 5)
+    for name, got, w in zip(NAMES, grads, want):
+        got = got.double().cpu().numpy()
+        assert got.shape == w.shape, name
+        err, top = float(np.abs(got - w).max()), float(np.abs(w).max())
+        bound = 1e-5 * top if name in ("dwk", "dwv", "dbias") else 2e-2 * max(floor, top)
+        assert err <= bound, "%s: max abs err %.3e > %.3e" % (name, err, bound)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_against_oracle(shape):
+    heads = shape[4]
+    print("split kernels", shape, flush=True)
+    acts, wk, wv, bias, learned = _inputs(shape, 300 + sum(shape))
+    _compare(sa.slide_attn_bwd(*[_odd(a) for a in acts], wk, wv, bias, heads, 5), acts, wk, wv, bias, heads)
+    _compare(sa.slide_attn_bwd_two_branch(*acts, *learned, bias, heads, 5), acts, wk, wv, bias, heads)
+
+
+@pytest.mark.parametrize("size", [1e-12, 1e10])
+def test_gradients_of_any_size(size):
+    """dO a power of two away from one: every gradient but da's softmax is linear in it, so the results are the same numbers."""
+    shape = (2, 9, 13, 32, 1)
+    acts, wk, wv, bias, _ = _inputs(shape, 41)
+    factor = 2.0 ** round(np.log2(size))
+    plain = sa.slide_attn_bwd(*acts, wk, wv, bias, 1, 5)
+    scaled = sa.slide_attn_bwd(acts[0] * factor, *acts[1:], wk, wv, bias, 1, 5)
+    for name, a, b in zip(NAMES, plain, scaled):
+        assert torch.equal(a.float() * factor, b.float()), name
+
+
+def test_infinite_key_reaches_its_window_only():
+    shape = (1, 11, 17, 8, 1)
+    acts, wk, wv, bias, _ = _inputs(shape, 42)
+    acts[2][0, 3, 5, 8] = float("inf")
+    dq, dk, dv = sa.slide_attn_bwd(*acts, wk, wv, bias, 1, 5)[:3]
+    for t, reach in ((dq, 2), (dk, 4), (dv, 4)):            # (dk and dv of a pixel see the pixels whose windows it is in)
+        bad = ~torch.isfinite(t[0]).all(0).cpu()
+        ii, jj = torch.meshgrid(torch.arange(11), torch.arange(17), indexing="ij")
+        near = torch.maximum((ii - 5).abs(), (jj - 8).abs()) <= reach
+        assert not (bad & ~near).any()
+        assert bad[5, 8]
