@@ -530,7 +530,7 @@ hipError_t launch_bwd_dw_reduce(const float* partial, float* dwk, float* dwv, lo
 // bytes of the partial kernel-gradient region (whichever kernel runs), a multiple of 16
 static size_t bwd_partial_bytes(const Problem& p)
 {
-    size_t floats = m32_supported(p) ? bwd_dw_m32_partial_floats(p) : (size_t)dw_chunks(p) * 2 * (size_t)p.C * p.S() * p.S();
+    size_t floats = split_supported(p) ? split_dw_partial_floats(p) : m32_supported(p) ? bwd_dw_m32_partial_floats(p) : (size_t)dw_chunks(p) * 2 * (size_t)p.C * p.S() * p.S();
     if (bwd_dw_mfma_supported(p)) floats = std::max(floats, bwd_dw_mfma_partial_floats(p));
     return (floats * sizeof(float) + 15) & ~(size_t)15;
 }
@@ -721,7 +721,9 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
         // kernel and bias gradients on the matrix cores
         return launch_bwd_dw_mfma(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
     }
-    if constexpr (M32) {
+    if constexpr (SPLIT) {
+        return launch_bwd_dw_split(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
+    } else if constexpr (M32) {
         return launch_bwd_dw_m32(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
     } else {
         const int n_chunks = dw_chunks(p);

@@ -93,6 +93,10 @@ size_t split_workspace_bytes(const Problem& p);
 hipError_t launch_split_prep(const Problem& p, const float* wk, const float* wv, void* ws, hipStream_t st);
 hipError_t launch_bwd_pixel_split(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
                                   const float* bias, void* dq, float* a_ws, float* dl_ws, void* ws, hipStream_t st);
+size_t split_dw_partial_floats(const Problem& p);
+hipError_t launch_bwd_dw_split(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
+                               const float* attn_ws, const float* dl_ws, float* partial, float* dwk, float* dwv,
+                               float* dbias, hipStream_t st);         // (slide_split_dw.hip) with the reduction
 hipError_t launch_bwd_dkdv_split(const Problem& p, const void* ws, void* dk, void* dv, hipStream_t st);
 
 // forward of heads narrower than 32 channels (bf16, ksize 3, H * W % 8 == 0) through the

@@ -311,5 +311,19 @@ inline Bands plan_bands(int B, int H, int W, int sets)
     return t;
 }
 
+// kernel gradients: tiles of 4 rows and 32 columns, dealt in chunks to one block per compute unit for `sets` sets of 32 channels
+constexpr int DW_ROWS = 4, DW_COLS = 32;
+struct DwSplitPlan { int ntr, ntc, chunks; long tiles; };
+inline DwSplitPlan plan_dw_split(int B, int H, int W, int sets)
+{
+    DwSplitPlan t;
+    t.ntr = (H + DW_ROWS - 1) / DW_ROWS;
+    t.ntc = (W + DW_COLS - 1) / DW_COLS;
+    t.tiles = (long)B * t.ntr * t.ntc;
+    const long n = MAX_CU_PLANNED / sets > 1 ? MAX_CU_PLANNED / sets : 1;
+    t.chunks = (int)(n < t.tiles ? n : t.tiles);
+    return t;
+}
+
 }  // namespace split
 }  // namespace slide

@@ -85,6 +85,9 @@ static void stacks(int B, int H, int W, int C)
     for (int sets : {2, 8, 66, 600}) {
         const split::Bands t = split::plan_bands(B, H, W, sets);
         const long bands = (H + t.rows - 1) / t.rows;
+        const split::DwSplitPlan w = split::plan_dw_split(B, H, W, sets);
+        CHECK(w.ntr * 4L >= H && (w.ntr - 1) * 4L < H && w.ntc * 32L >= W && (w.ntc - 1) * 32L < W && w.tiles == (long)B * w.ntr * w.ntc &&
+              w.chunks >= 1 && w.chunks <= w.tiles, "kernel gradients of %dx%dx%d", B, H, W);
         CHECK(t.rows >= 1 && t.blocks >= 1 && t.groups * 32 >= (long)B * W && (t.groups - 1) * 32 < (long)B * W && t.jobs == t.groups * bands, "bands of %dx%dx%d", B, H, W);
     }
 }

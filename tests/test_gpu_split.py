@@ -19,7 +19,7 @@ NAMES = "dq dk dv dwk dwv dbias".split()
 SHAPES = [
     # B, H, W, C, heads
     (1, 1, 1, 3, 1), (2, 1, 1, 4, 1), (3, 1, 9, 10, 2), (5, 9, 1, 6, 1), (2, 2, 3, 5, 1), (7, 5, 4, 8, 2), (3, 14, 14, 64, 2),
-    (2, 28, 28, 32, 1), (1, 19, 61, 33, 1), (1, 7, 130, 40, 1), (2, 31, 45, 64, 1), (1, 13, 60, 24, 1), (40, 6, 11, 8, 1),
+    (2, 28, 28, 32, 1), (9, 30, 37, 32, 1), (1, 19, 61, 33, 1), (1, 7, 130, 40, 1), (2, 31, 45, 64, 1), (1, 13, 60, 24, 1), (40, 6, 11, 8, 1),
 ]
 
 
@@ -81,3 +81,22 @@ def test_infinite_key_reaches_its_window_only():
         near = torch.maximum((ii - 5).abs(), (jj - 8).abs()) <= reach
         assert not (bad & ~near).any()
         assert bad[5, 8]
+
+
+@pytest.mark.parametrize("W", [3, 20, 21, 33])
+def test_infinite_value_reaches_no_other_tap(W):
+    """An infinite v in the last column: the kernel gradient of a tap that never reads that column stays finite."""
+    acts, wk, wv, bias, _ = _inputs((1, 6, W, 8, 1), 43)
+    acts[3][:, :, :, -1] = float("inf")
+    dwv = sa.slide_attn_bwd(*acts, wk, wv, bias, 1, 5)[4].view(8, 25, 5, 5)
+    assert torch.isfinite(dwv[:, :, :, :2]).all()
+    assert not torch.isfinite(dwv[:, :, :, 2]).any()
+
+
+def test_gradients_are_added():
+    acts, wk, wv, bias, learned = _inputs((3, 11, 18, 40, 2), 44)
+    once = sa.slide_attn_bwd_two_branch(*acts, *learned, bias, 2, 5)
+    twice = [torch.full_like(g, 3.0) for g in once]
+    sa.slide_attn_bwd_two_branch(*acts, *learned, bias, 2, 5, outputs=twice, accumulate=True)
+    for name, a, b in list(zip(NAMES, twice, once))[3:]:
+        assert torch.equal(a, b + 3.0), name
