@@ -52,7 +52,8 @@ struct Args {
 };
 
 // RPG: most rows a group of new rows can have (rows that one epoch is the first to read).
-template <int RPG>
+// TOKENS: dk and dv are [B, H, W, C]: a lane's eight channels of its pixel are sixteen bytes there and go out as they are
+template <int RPG, bool TOKENS>
 __global__ void __launch_bounds__(THREADS)
 bwd16_ring_dkdv_kernel(const Args a)
 {
@@ -423,6 +424,23 @@ bwd16_ring_dkdv_kernel(const Args a)
                 ovk[y] = __builtin_bit_cast(uint32_t, __builtin_convertvector(fk, bf16x2_t));
                 ovv[y] = __builtin_bit_cast(uint32_t, __builtin_convertvector(fv, bf16x2_t));
             }
+            if (TOKENS) {
+                // (through the wave's slot all the same: stored as they are the compiler spills 278 registers)
+                const long o = (((long)b * H + y0) * W + nb) * a.C + m * D;
+                const int op = lane >> 2, og = lane & 3, rd = (og * 16 + op) * 16;      // (four lanes per pixel: 64 contiguous bytes)
+                const uint32_t lane_o = (uint32_t)(op * a.C + 8 * og) * 2u;
+                *(uint4_t*)(o_slot + lane * 16) = ovk;
+                asm volatile("" ::: "memory");
+                const uint4_t tk = *(const uint4_t*)(o_slot + rd);
+                asm volatile("" ::: "memory");
+                *(uint4_t*)(o_slot + lane * 16) = ovv;
+                asm volatile("" ::: "memory");
+                const uint4_t tv = *(const uint4_t*)(o_slot + rd);
+                if (nb + op < npix) {
+                    *(uint4_t*)((char*)(a.dk + o) + lane_o) = tk;
+                    *(uint4_t*)((char*)(a.dv + o) + lane_o) = tv;
+                }
+            } else {
             // pixel-major -> 8 pixels of one channel per lane, through the wave's own slot: dk, then
             // dv (the LDS unit serves a wave's accesses in the order of their issue)
             const int wr = p * 64 + ((g ^ ((p >> 2) & 3)) << 4);
@@ -443,6 +461,7 @@ bwd16_ring_dkdv_kernel(const Args a)
             if (n0 < npix) {
                 *(uint4_t*)(dk_base + (uint32_t)n0 * 2u) = uint4_t{ka[0], ka[1], kb[0], kb[1]};
                 *(uint4_t*)(dv_base + (uint32_t)n0 * 2u) = uint4_t{va[0], va[1], vb[0], vb[1]};
+            }
             }
         }
         nb += PX_EPOCH;
@@ -511,7 +530,8 @@ struct PixelArgs {
 // halves arrive at the same a and dl (each writes its copy, which the other two backward kernels
 // read per half head), and each forms dq of its own 32 channels from its key rows.  MODE 0:
 // heads of 32 channels, one launch.
-template <int RPG, int MODE = 0>
+// TOKENS: dq is [B, H, W, C] (MODE 0).
+template <int RPG, int MODE = 0, bool TOKENS = false>
 __global__ void __launch_bounds__(THREADS)
 bwd16_ring_pixel_kernel(const PixelArgs a)
 {
@@ -887,6 +907,14 @@ bwd16_ring_pixel_kernel(const PixelArgs a)
                 const float2_t f2 = {o[2 * y] * a.scale, o[2 * y + 1] * a.scale};
                 ov[y] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2, bf16x2_t));
             }
+            if (TOKENS) {
+                const int op = lane >> 2, og = lane & 3;    // (four lanes per pixel: 64 contiguous bytes)
+                const uint32_t lane_o = (uint32_t)(op * a.C + 8 * og) * 2u;
+                *(uint4_t*)(o_slot + lane * 16) = ov;
+                asm volatile("" ::: "memory");
+                const uint4_t t = *(const uint4_t*)(o_slot + (og * 16 + op) * 16);
+                if (nb + op < npix) *(uint4_t*)((char*)(a.dq + (((long)b * H + y0) * W + nb) * a.C + m * D) + lane_o) = t;
+            } else {
             *(uint4_t*)(o_slot + p * 64 + ((g ^ ((p >> 2) & 3)) << 4)) = ov;
             const int grp = lane >> 4, nn = lane & 15;
             const int sa = nn & 3, sj = nn >> 2;
@@ -896,6 +924,7 @@ bwd16_ring_pixel_kernel(const PixelArgs a)
             const uint2_t rb2 = lds_read_tr(o_slot + P1 * 64 + ((oct_s ^ ((P1 >> 2) & 3)) << 4) + (sa & 1) * 8);
             const int n0 = nb + 8 * st_hh;
             if (n0 < npix) *(uint4_t*)(dq_base + (uint32_t)n0 * 2u) = uint4_t{ra2[0], ra2[1], rb2[0], rb2[1]};
+            }
             }
         }
         nb += PX_EPOCH;
@@ -960,13 +989,15 @@ hipError_t launch_bwd_dkdv_ring(const Problem& p, const void* dout, const void* 
     a.magic_r = (uint32_t)(((1ULL << 32) + r.rr.R - 1) / r.rr.R);
     a.scale = p.logit_scale();
     static LdsOptIn opt_in;
-    hipError_t e = opt_in.ensure({(const void*)bwd16_ring_dkdv_kernel<2>, (const void*)bwd16_ring_dkdv_kernel<3>,
-                                  (const void*)bwd16_ring_dkdv_kernel<4>}, t16::LDS_LIMIT);
+    hipError_t e = opt_in.ensure({(const void*)bwd16_ring_dkdv_kernel<2, false>, (const void*)bwd16_ring_dkdv_kernel<3, false>,
+                                  (const void*)bwd16_ring_dkdv_kernel<4, false>, (const void*)bwd16_ring_dkdv_kernel<2, true>,
+                                  (const void*)bwd16_ring_dkdv_kernel<3, true>, (const void*)bwd16_ring_dkdv_kernel<4, true>}, t16::LDS_LIMIT);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)r.rr.n_blocks), block(THREADS);
-    if (r.rr.rpg == 2) hipLaunchKernelGGL(bwd16_ring_dkdv_kernel<2>, grid, block, (size_t)r.lds_bytes, st, a);
-    else if (r.rr.rpg == 3) hipLaunchKernelGGL(bwd16_ring_dkdv_kernel<3>, grid, block, (size_t)r.lds_bytes, st, a);
-    else hipLaunchKernelGGL(bwd16_ring_dkdv_kernel<4>, grid, block, (size_t)r.lds_bytes, st, a);
+    const auto kernel = r.rr.rpg == 2 ? (p.out_nhwc ? bwd16_ring_dkdv_kernel<2, true> : bwd16_ring_dkdv_kernel<2, false>)
+                      : r.rr.rpg == 3 ? (p.out_nhwc ? bwd16_ring_dkdv_kernel<3, true> : bwd16_ring_dkdv_kernel<3, false>)
+                                      : (p.out_nhwc ? bwd16_ring_dkdv_kernel<4, true> : bwd16_ring_dkdv_kernel<4, false>);
+    hipLaunchKernelGGL(kernel, grid, block, (size_t)r.lds_bytes, st, a);
     return hipGetLastError();
 }
 
@@ -1002,14 +1033,15 @@ hipError_t launch_bwd_pixel_ring(const Problem& p, const void* dout, const void*
     if (mode < 0 || mode > 2 || (mode != 0 && !part)) return hipErrorInvalidValue;
     static LdsOptIn opt_in;
 #define SLIDE_PX_KERNELS(RPGV) (const void*)bwd16_ring_pixel_kernel<RPGV, 0>, (const void*)bwd16_ring_pixel_kernel<RPGV, 1>, \
-                               (const void*)bwd16_ring_pixel_kernel<RPGV, 2>
+                               (const void*)bwd16_ring_pixel_kernel<RPGV, 2>, (const void*)bwd16_ring_pixel_kernel<RPGV, 0, true>
     hipError_t e = opt_in.ensure({SLIDE_PX_KERNELS(2), SLIDE_PX_KERNELS(3), SLIDE_PX_KERNELS(4)}, t16::LDS_LIMIT);
 #undef SLIDE_PX_KERNELS
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)r.rr.n_blocks), block(THREADS);
 #define SLIDE_PX_LAUNCH(RPGV)                                                                                      \
     do {                                                                                                           \
-        if (mode == 0)      hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 0>), grid, block, (size_t)r.lds_bytes, st, a); \
+        if (mode == 0 && p.out_nhwc) hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 0, true>), grid, block, (size_t)r.lds_bytes, st, a); \
+        else if (mode == 0) hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 0>), grid, block, (size_t)r.lds_bytes, st, a); \
         else if (mode == 1) hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 1>), grid, block, (size_t)r.lds_bytes, st, a); \
         else                hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 2>), grid, block, (size_t)r.lds_bytes, st, a); \
     } while (0)
