@@ -52,7 +52,9 @@ struct Args {
 };
 
 // RPG: most rows a group of new rows can have (rows that one epoch is the first to read).
-// TOKENS: dk and dv are [B, H, W, C]: a lane's eight channels of its pixel are sixteen bytes there and go out as they are
+// TOKENS: activations and their gradients are [B, H, W, C].  The eight channels of a pixel that a lane works on are sixteen
+// contiguous bytes there, so nothing is transposed: a unit of staging work is 16 pixels of all four octets instead of an octet of all
+// pixels, lane = pixel x octet, and results go out as they are.
 template <int RPG, bool TOKENS>
 __global__ void __launch_bounds__(THREADS)
 bwd16_ring_dkdv_kernel(const Args a)
@@ -109,7 +111,14 @@ bwd16_ring_dkdv_kernel(const Args a)
         const int raw = a.off_raw + unit_id(u) * (2 * RPG * SLOT);
         return s < 2 * RPG ? raw + s * SLOT : a.off_rec + (2 * unit_id(u) + (s - 2 * RPG)) * SLOT;
     };
+    const bf16_bits* tok_base = (mj ? a.dout : a.q) + (long)b * a.C * HW + m * D;
+    const int tok_px = lane >> 2, tok_oct = lane & 3;
     auto load_row = [&](int u, uint32_t row_off, int off) {
+        if (TOKENS) {                                                  // (every lane: pixels past the row load its last one)
+            const int px = min(16 * (unit_id(u) & 3) + tok_px, W - 1);
+            load_to_lds(tok_base, row_off * (uint32_t)a.C + (uint32_t)(px * a.C + 8 * tok_oct) * 2u, lds0 + off);
+            return;
+        }
         const bf16_bits* src = kv_base + (long)(8 * (unit_id(u) & 3)) * HW;
         if (lane < W) load_to_lds(src, kv_lane_off + row_off, lds0 + off);
     };
@@ -124,6 +133,11 @@ bwd16_ring_dkdv_kernel(const Args a)
     struct RawRow { uint2_t lo, hi; };
     auto read_row = [&](int off) {
         RawRow r;
+        if (TOKENS) {
+            const uint4_t v = *(const uint4_t*)(smem + off + lane * 16);
+            r.lo = uint2_t{v[0], v[1]}; r.hi = uint2_t{v[2], v[3]};
+            return r;
+        }
         const unsigned char* src = smem + off + cv_src_off;
         r.lo = lds_read_tr(src);
         r.hi = lds_read_tr(src + 4 * (W * 2));
@@ -135,7 +149,10 @@ bwd16_ring_dkdv_kernel(const Args a)
             h4[0] = bf16x2_to_half2(r.lo[0]); h4[1] = bf16x2_to_half2(r.lo[1]);
             h4[2] = bf16x2_to_half2(r.hi[0]); h4[3] = bf16x2_to_half2(r.hi[1]);
         }
-        if (lane < W) *(uint4_t*)(smem + unit_id(u) * PS + (lane + 1) * 16 + ring_off) = h4;
+        if (TOKENS) {
+            const int px = 16 * (unit_id(u) & 3) + tok_px;
+            if (px < W) *(uint4_t*)(smem + (4 * mj + tok_oct) * PS + (px + 1) * 16 + ring_off) = h4;
+        } else if (lane < W) *(uint4_t*)(smem + unit_id(u) * PS + (lane + 1) * 16 + ring_off) = h4;
     };
     // A landed dl / a row -> records.  In the 16-lane group g, lane n of piece q16 gets the
     // shifts g, 4 + g, 8 + g, 12 + g of pixel 16 q16 + n (slots 4g .. 4g + 3): lane s of the group
@@ -530,7 +547,7 @@ struct PixelArgs {
 // halves arrive at the same a and dl (each writes its copy, which the other two backward kernels
 // read per half head), and each forms dq of its own 32 channels from its key rows.  MODE 0:
 // heads of 32 channels, one launch.
-// TOKENS: dq is [B, H, W, C] (MODE 0).
+// TOKENS: as above (MODE 0).
 template <int RPG, int MODE = 0, bool TOKENS = false>
 __global__ void __launch_bounds__(THREADS)
 bwd16_ring_pixel_kernel(const PixelArgs a)
@@ -581,13 +598,25 @@ bwd16_ring_pixel_kernel(const PixelArgs a)
         const int pw = 2 * oct + j;
         return s < 2 * RPG ? raw + s * SLOT : (s == 2 * RPG ? a.off_q : a.off_do) + pw * (2 * SLOT) + SLOT;
     };
+    const bf16_bits* tok_src[2] = {a.k + (long)b * a.C * HW + m * D, a.v + (long)b * a.C * HW + m * D};
+    const int tok_px = lane >> 2, tok_oct = lane & 3;
     auto load_row = [&](int j, uint32_t row_off, int off) {
+        if (TOKENS) {                                                  // (every lane: pixels past the row load its last one)
+            const int px = min(16 * oct + tok_px, W - 1);
+            load_to_lds(tok_src[j], row_off * (uint32_t)a.C + (uint32_t)(px * a.C + 8 * tok_oct) * 2u, lds0 + off);
+            return;
+        }
         if (lane < W) load_to_lds(kv_src[j], kv_lane_off + row_off, lds0 + off);
     };
     const int cv_src_off = ((lane & 15) >> 2) * (W * 2) + (16 * (lane >> 4) + 4 * (lane & 3)) * 2;
     struct RawRow { uint2_t lo, hi; };
     auto read_row = [&](int off) {
         RawRow r;
+        if (TOKENS) {
+            const uint4_t v = *(const uint4_t*)(smem + off + lane * 16);
+            r.lo = uint2_t{v[0], v[1]}; r.hi = uint2_t{v[2], v[3]};
+            return r;
+        }
         const unsigned char* src = smem + off + cv_src_off;
         r.lo = lds_read_tr(src);
         r.hi = lds_read_tr(src + 4 * (W * 2));
@@ -599,7 +628,10 @@ bwd16_ring_pixel_kernel(const PixelArgs a)
             h4[0] = bf16x2_to_half2(r.lo[0]); h4[1] = bf16x2_to_half2(r.lo[1]);
             h4[2] = bf16x2_to_half2(r.hi[0]); h4[3] = bf16x2_to_half2(r.hi[1]);
         }
-        if (lane < W) *(uint4_t*)(smem + (4 * j + oct) * PS + (lane + 1) * 16 + ring_off) = h4;
+        if (TOKENS) {
+            const int px = 16 * oct + tok_px;
+            if (px < W) *(uint4_t*)(smem + (4 * j + tok_oct) * PS + (px + 1) * 16 + ring_off) = h4;
+        } else if (lane < W) *(uint4_t*)(smem + (4 * j + oct) * PS + (lane + 1) * 16 + ring_off) = h4;
     };
     // q (x = 0) or dO (x = 1) of pass wave pw, pass starting at band pixel n_first, into slot sl of that wave
     const bf16_bits* qd_src[2] = {a.q + head_base + (long)y0 * W, a.dout + head_base + (long)y0 * W};
@@ -608,7 +640,10 @@ bwd16_ring_pixel_kernel(const PixelArgs a)
         const bool real = n_first < npix;
         const int nf = real ? n_first : 0;
         const int off = real ? (x ? a.off_do : a.off_q) + pw * (2 * SLOT) + sl * SLOT : a.off_dummy;
-        if (nf + 8 * (lane & 1) < npix) load_to_lds(qd_src[x], q_lane_off + (uint32_t)nf * 2u, lds0 + off);
+        if (TOKENS) {                                                  // [pixel][octet]
+            const int n = min(nf + tok_px, npix - 1);
+            load_to_lds((x ? a.dout : a.q) + ((long)b * H + y0) * W * a.C + m * D, (uint32_t)(n * a.C + 8 * tok_oct) * 2u, lds0 + off);
+        } else if (nf + 8 * (lane & 1) < npix) load_to_lds(qd_src[x], q_lane_off + (uint32_t)nf * 2u, lds0 + off);
     };
 
     // ---- start-up
@@ -758,7 +793,7 @@ bwd16_ring_pixel_kernel(const PixelArgs a)
     char* dq_base = (char*)(a.dq + head_base + (long)y0 * W) + (uint32_t)st_c * hw2;
     _Float16* a_base = a.attn + (long)plane * S * HW + (long)y0 * W;
     _Float16* dl_base = a.dl + (long)plane * S * HW + (long)y0 * W;
-    const int q_rd = (8 * g + (p >> 2)) * 32 + (p & 3) * 8;            // the lane's piece of a [32 channels][16 pixels] slot
+    const int q_rd = TOKENS ? (4 * p + g) * 16 : (8 * g + (p >> 2)) * 32 + (p & 3) * 8;     // the lane's piece of a [32 channels][16 pixels] slot
     const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     // lane (p, g) holds the shifts g, 4 + g, 8 + g of pixel p
     float* part_out = MODE == 1 ? a.part + (long)plane * 2 * S * HW + (long)y0 * W : nullptr;
@@ -793,8 +828,14 @@ bwd16_ring_pixel_kernel(const PixelArgs a)
             half2_t xs[4];
             float4_t acc = zero4, accb = zero4;
             if (MODE != 2) {
+            if (TOKENS) {
+                const uint4_t qr = *(const uint4_t*)(smem + a.off_q + slot), dr = *(const uint4_t*)(smem + a.off_do + slot);
+                q0 = uint2_t{qr[0], qr[1]}; q1 = uint2_t{qr[2], qr[3]};
+                d0 = uint2_t{dr[0], dr[1]}; d1 = uint2_t{dr[2], dr[3]};
+            } else {
             q0 = lds_read_tr(smem + a.off_q + slot); q1 = lds_read_tr(smem + a.off_q + slot + 4 * 32);
             d0 = lds_read_tr(smem + a.off_do + slot); d1 = lds_read_tr(smem + a.off_do + slot + 4 * 32);
+            }
 #pragma unroll
             for (int t = 0; t < S; ++t) xd[t] = *(const uint4_t*)(kb[t / KS] + (t % KS) * 16);
             xs[0] = as_half2(bf16x2_to_half2(q0[0])) * sc; xs[1] = as_half2(bf16x2_to_half2(q0[1])) * sc;
@@ -994,9 +1035,9 @@ hipError_t launch_bwd_dkdv_ring(const Problem& p, const void* dout, const void* 
                                   (const void*)bwd16_ring_dkdv_kernel<3, true>, (const void*)bwd16_ring_dkdv_kernel<4, true>}, t16::LDS_LIMIT);
     if (e != hipSuccess) return e;
     const dim3 grid((unsigned)r.rr.n_blocks), block(THREADS);
-    const auto kernel = r.rr.rpg == 2 ? (p.out_nhwc ? bwd16_ring_dkdv_kernel<2, true> : bwd16_ring_dkdv_kernel<2, false>)
-                      : r.rr.rpg == 3 ? (p.out_nhwc ? bwd16_ring_dkdv_kernel<3, true> : bwd16_ring_dkdv_kernel<3, false>)
-                                      : (p.out_nhwc ? bwd16_ring_dkdv_kernel<4, true> : bwd16_ring_dkdv_kernel<4, false>);
+    const auto kernel = r.rr.rpg == 2 ? (p.nhwc ? bwd16_ring_dkdv_kernel<2, true> : bwd16_ring_dkdv_kernel<2, false>)
+                      : r.rr.rpg == 3 ? (p.nhwc ? bwd16_ring_dkdv_kernel<3, true> : bwd16_ring_dkdv_kernel<3, false>)
+                                      : (p.nhwc ? bwd16_ring_dkdv_kernel<4, true> : bwd16_ring_dkdv_kernel<4, false>);
     hipLaunchKernelGGL(kernel, grid, block, (size_t)r.lds_bytes, st, a);
     return hipGetLastError();
 }
@@ -1040,7 +1081,7 @@ hipError_t launch_bwd_pixel_ring(const Problem& p, const void* dout, const void*
     const dim3 grid((unsigned)r.rr.n_blocks), block(THREADS);
 #define SLIDE_PX_LAUNCH(RPGV)                                                                                      \
     do {                                                                                                           \
-        if (mode == 0 && p.out_nhwc) hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 0, true>), grid, block, (size_t)r.lds_bytes, st, a); \
+        if (mode == 0 && p.nhwc) hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 0, true>), grid, block, (size_t)r.lds_bytes, st, a); \
         else if (mode == 0) hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 0>), grid, block, (size_t)r.lds_bytes, st, a); \
         else if (mode == 1) hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 1>), grid, block, (size_t)r.lds_bytes, st, a); \
         else                hipLaunchKernelGGL((bwd16_ring_pixel_kernel<RPGV, 2>), grid, block, (size_t)r.lds_bytes, st, a); \

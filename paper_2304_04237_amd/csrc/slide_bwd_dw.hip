@@ -31,6 +31,7 @@
 // write partial sums that a second kernel adds in a fixed order (reproducible results).
 #include "slide_internal.h"
 #include "slide_device.h"
+#include "slide_fwd16_ops.h"
 
 namespace slide {
 namespace dwpath {
@@ -413,7 +414,8 @@ constexpr int OFF_K = 0, OFF_V = OFF_K + K_BYTES, OFF_K1 = OFF_V + K_BYTES + 32,
               OFF_Q = OFF_V1 + K_BYTES + 32, OFF_DO = OFF_Q + Q_BYTES, OFF_ZERO = OFF_DO + Q_BYTES,
               LDS_BYTES = OFF_ZERO + 256;
 static_assert(K_BYTES % 256 == 0 && OFF_K % 256 == 0 && OFF_K1 % 256 == 32 && OFF_V1 % 256 == 32 && OFF_Q % 16 == 0, "bank phase of the copies");
-static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+constexpr int OFF_TURN = LDS_BYTES, LDS_BYTES_TOKENS = OFF_TURN + MOVERS * 4 * 1024;     // per mover 1 KB per tensor
+static_assert(LDS_BYTES_TOKENS <= 160 * 1024 && OFF_TURN % 16 == 0, "LDS");
 
 // the tap windows of the three window rows of a step: four consecutive dwords from each of
 // three dword-aligned LDS addresses per tensor, as 8-byte two-dword reads (see lds_read_windows)
@@ -478,6 +480,9 @@ __device__ __forceinline__ void lds_read_row_windows(uint32_t ak, uint32_t av, R
     w.v[1][0] = v1a[0]; w.v[1][1] = v1a[1]; w.v[1][2] = v1b[0]; w.v[1][3] = v1b[1];
 }
 
+// TOKENS: k, v, q, dO are [B, H, W, C].  Mover j loads pixels 16j..16j+15 of all channels (lane = pixel x octet, sixteen bytes),
+// turns them through a piece of LDS of its own into eight pixels of a channel per lane, and goes on as above.
+template <bool TOKENS>
 __global__ void __launch_bounds__(THREADS_R)
 bwd_dw_ring_kernel(const Args a)
 {
@@ -503,7 +508,8 @@ bwd_dw_ring_kernel(const Args a)
     if (mover) {
         // ---- movers: lane = (channel mv * 8 + lane / 8, piece lane % 8) of a row of k, v, q, dO
         const int mv = wave - WAVES;
-        const int ch = mv * 8 + (lane >> 3), x = lane & 7;
+        // (TOKENS: channel 8 (lane / 16) + lane % 8, piece 2 mv + lane / 8 % 2: what the transposing reads give a lane)
+        const int ch = TOKENS ? 8 * g + (i & 7) : mv * 8 + (lane >> 3), x = TOKENS ? 2 * mv + (i >> 3) : lane & 7;
         const bool has = x < NXC;
         const int xs = has ? x : 0;                                // (idle lanes load piece 0 and store nothing)
         struct Stage { uint4_t k, v, q, d; uint32_t kl, vl; };
@@ -518,6 +524,16 @@ bwd_dw_ring_kernel(const Args a)
             // the loads in flight.
             auto load_stage = [&](int s, Stage& r) {
                 const int ykv = min(max(y0 + s + 2, 0), H - 1), yq = min(max(y0 + s + 1, 0), H - 1);
+                if (TOKENS) {
+                    const long row = ((long)b * H + ykv) * W, rowq = ((long)b * H + yq) * W;
+                    const int px = min(16 * mv + (lane >> 2), W - 1), left = max(8 * xs - 1, 0);
+                    const long at = (row + px) * a.C + m * D + 8 * (lane & 3), atq = (rowq + px) * a.C + m * D + 8 * (lane & 3);
+                    const long lat = (row + left) * a.C + m * D + ch;
+                    r.k = *(const uint4_t*)(a.k + at); r.v = *(const uint4_t*)(a.v + at);
+                    r.kl = a.k[lat]; r.vl = a.v[lat];
+                    r.q = *(const uint4_t*)(a.q + atq); r.d = *(const uint4_t*)(a.dout + atq);
+                    return;
+                }
                 const bf16_bits* pk = a.k + ch_base + (long)ykv * W;
                 const bf16_bits* pv = a.v + ch_base + (long)ykv * W;
                 r.k = *(const uint4_t*)pk; r.v = *(const uint4_t*)pv;
@@ -541,7 +557,22 @@ bwd_dw_ring_kernel(const Args a)
                 *(uint2_t*)(smem + off_moved + at + 8) = uint2_t{mvd[2], mvd[3]};
                 if (x == NXC - 1) *(uint16_t*)(smem + off_moved + at + 16) = (uint16_t)(val[3] >> 16);
             };
-            auto write_stage = [&](int s, const Stage& r) {
+            auto write_stage = [&](int s, const Stage& raw) {
+                Stage r = raw;
+                if (TOKENS) {
+                    // [pixel][32 channels] -> eight pixels of a channel per lane (a wave's LDS accesses are served in order)
+                    unsigned char* turn = smem + OFF_TURN + mv * 4096;
+                    *(uint4_t*)(turn + lane * 16) = raw.k; *(uint4_t*)(turn + 1024 + lane * 16) = raw.v;
+                    *(uint4_t*)(turn + 2048 + lane * 16) = raw.q; *(uint4_t*)(turn + 3072 + lane * 16) = raw.d;
+                    asm volatile("" ::: "memory");
+                    const unsigned char* src = turn + (8 * ((i >> 1) & 1) + (i >> 2)) * 64 + (8 * g + 4 * (i & 1)) * 2;
+                    auto turned = [&](int o) {
+                        const uint2_t lo = f16ops::lds_read_tr(src + o), hi = f16ops::lds_read_tr(src + o + 4 * 64);
+                        return uint4_t{lo[0], lo[1], hi[0], hi[1]};
+                    };
+                    r.k = turned(0); r.v = turned(1024); r.q = turned(2048); r.d = turned(3072);
+                    asm volatile("" ::: "memory");
+                }
                 if (!has) return;
                 const int ykv = y0 + s + 2, yq = y0 + s + 1;
                 const bool kv_in = ykv >= 0 && ykv < H;
@@ -774,10 +805,11 @@ hipError_t launch_bwd_dw_mfma(const Problem& p, const void* dout, const void* q,
         a.NB = (int)nb;
         a.dbias_partial = partial + (size_t)a.NB * 2 * p.C * 81;
         static LdsOptIn opt_in_ring;
-        hipError_t er = opt_in_ring.ensure({(const void*)ring::bwd_dw_ring_kernel}, ring::LDS_BYTES);
+        hipError_t er = opt_in_ring.ensure({(const void*)ring::bwd_dw_ring_kernel<false>, (const void*)ring::bwd_dw_ring_kernel<true>}, ring::LDS_BYTES_TOKENS);
         if (er != hipSuccess) return er;
-        hipLaunchKernelGGL(ring::bwd_dw_ring_kernel, dim3((unsigned)(a.NB * p.heads)), dim3(ring::THREADS_R),
-                           (size_t)ring::LDS_BYTES, st, a);
+        const auto kernel = p.nhwc ? ring::bwd_dw_ring_kernel<true> : ring::bwd_dw_ring_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(a.NB * p.heads)), dim3(ring::THREADS_R),
+                           (size_t)(p.nhwc ? ring::LDS_BYTES_TOKENS : ring::LDS_BYTES), st, a);
     } else {
         static LdsOptIn opt_in;
         hipError_t e = opt_in.ensure({(const void*)bwd_dw_kernel}, LDS_BYTES);

@@ -1048,14 +1048,20 @@ size_t bwd_nhwc_workspace_bytes(const Problem& p)
     return ((bwd_generic_workspace_bytes(p) + 255) & ~(size_t)255) + 7 * nhwc_act_bytes(p);
 }
 
-// both kernels that write dq, dk and dv are the streaming ones, on the heads as they are
-static bool bwd_stores_nhwc(const Problem& p) { return bwd_variant(p, true) == 23 || bwd_variant(p, true) == 27; }
+// All three backward kernels are the streaming ones, on the heads as they are: they read and write channels-last tensors
+// (MI355X, B=64, 56x56, C=64: the layout changes took 61 us of the 155 of the call).  A row's offset inside an item has 32 bits.
+static bool bwd_streams_nhwc(const Problem& p) { return bwd_variant(p, true) == 27 && p.plane() * p.C * 2 < (1L << 31); }
 
 hipError_t launch_bwd_nhwc(const Problem& p, const void* dout, const void* q, const void* k,
                            const void* v, const float* wk, const float* wv, const float* bias,
                            void* dq, void* dk, void* dv, float* dwk, float* dwv, float* dbias,
                            void* workspace, hipStream_t st)
 {
+    if (bwd_streams_nhwc(p) && aligned16({dout, q, k, v, dq, dk, dv, workspace})) {
+        Problem tokens = p;
+        tokens.nhwc = 1;
+        return launch_bwd_generic(tokens, dout, q, k, v, wk, wv, bias, dq, dk, dv, dwk, dwv, dbias, workspace, st);
+    }
     const size_t inner = (bwd_generic_workspace_bytes(p) + 255) & ~(size_t)255;
     const size_t act = nhwc_act_bytes(p);
     char* base = (char*)workspace + inner;
@@ -1064,12 +1070,6 @@ hipError_t launch_bwd_nhwc(const Problem& p, const void* dout, const void* q, co
     const void* src[4] = {dout, q, k, v};
     hipError_t e = launch_relayout(p, src, planar, 4, true, st);
     if (e != hipSuccess) return e;
-    // the streaming per-pixel and dk/dv kernels store channels-last gradients themselves (MI355X, B=64, 56x56, C=64: the layout
-    // change back took 27 us of the 155 of the call)
-    Problem direct = p;
-    direct.out_nhwc = bwd_stores_nhwc(p) && aligned16({dq, dk, dv, planar[0]});
-    if (direct.out_nhwc)
-        return launch_bwd_generic(direct, planar[0], planar[1], planar[2], planar[3], wk, wv, bias, dq, dk, dv, dwk, dwv, dbias, workspace, st);
     e = launch_bwd_generic(p, planar[0], planar[1], planar[2], planar[3], wk, wv, bias, planar[4], planar[5],
                            planar[6], dwk, dwv, dbias, workspace, st);
     if (e != hipSuccess) return e;

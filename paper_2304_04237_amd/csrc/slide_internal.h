@@ -18,13 +18,11 @@ struct Problem {
     int two_branch = 0;
     // backward: add the kernel and bias gradients to what dwk, dwv, dbias hold (micro-batches)
     int accumulate = 0;
-    // activations are stored [B, H, W, C] (channels last) instead of [B, C, H, W]; forward only
+    // activations are stored [B, H, W, C] (channels last) instead of [B, C, H, W]; backward: the streaming kernels only
     int nhwc = 0;
     // channels per head that the logit scale 1/sqrt(d) is taken from when the tensors handed to
     // the kernels carry heads padded to more channels (backward of heads narrower than 32); 0: d()
     int scale_dim = 0;
-    // backward: dq, dk and dv are [B, H, W, C] while the inputs are planar (the streaming kernels can store them so)
-    int out_nhwc = 0;
     int d() const { return C / heads; }
     float logit_scale() const { return 1.0f / sqrtf((float)(scale_dim ? scale_dim : d())); }
     int S() const { return ksize * ksize; }
