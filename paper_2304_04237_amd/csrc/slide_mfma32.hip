@@ -121,13 +121,16 @@ pixel32_kernel(const PixelArgs a)
         loff[j] = (f & 3) * (S * S) + SM * S + (f >> 2);
     }
 
-    // runs `body(quad, offset of the quad's tile, of its weights, x of this lane)` over this wave's quads
-    auto phase = [&](const void* yp, const void* xp, const float* w, auto&& body) {
-        const T* yb = (const T*)yp + item;
-        const T* xb = xp ? (const T*)xp + item : nullptr;
-        const float* wb = w + (long)m * d * S * S;
-        f4 yr[NI][QPT], xr[CQ / CG];
-        float wr[AHEAD_W ? NW : 1];
+    // what a step stages, on its way from memory: of a tensor y, of x (q or dO; null: none) and of the kernels w
+    f4 yr[NI][QPT], xr[CQ / CG];
+    float wr[AHEAD_W ? NW : 1];
+    struct Source { const T* y; const T* x; const float* w; };
+    auto source = [&](const void* yp, const void* xp, const float* w) {
+        return Source{(const T*)yp + item, xp ? (const T*)xp + item : nullptr, w + (long)m * d * S * S};
+    };
+    auto fetch = [&](const Source& src, int c0) {
+        const T *yb = src.y, *xb = src.x;
+        const float* wb = src.w;
         // (a step stages the quads that the head still has: the eight of the shared form are 32 channels.  The forward's large
         // blocks stage two quads whatever the head: leaving one out cost them registers, 54 -> 56 us at stage 1)
         auto fetch_quads = [&](int c0, auto all) {
@@ -142,17 +145,20 @@ pixel32_kernel(const PixelArgs a)
                 for (int u = 0; u < CQ / CG; ++u)
                     if (ALL || c0 + 4 * (peg + u * CG) < d) xr[u] = load4(xb, xoff, c0 + 4 * (peg + u * CG));
         };
-        auto fetch = [&](int c0) {
-            if (CQ == 1 || (CG == 1 && !BWD) || c0 + 4 * CQ <= d) fetch_quads(c0, std::true_type{});
-            else fetch_quads(c0, std::false_type{});
-            if (AHEAD_W)
+        if (CQ == 1 || (CG == 1 && !BWD) || c0 + 4 * CQ <= d) fetch_quads(c0, std::true_type{});
+        else fetch_quads(c0, std::false_type{});
+        if (AHEAD_W)
 #pragma unroll
-                for (int u = 0; u < NW; ++u) {
-                    const int idx = tid + u * NT;
-                    wr[u] = (idx < CQ * 4 * S * S && c0 * S * S + idx < d * S * S) ? wb[c0 * S * S + idx] : 0.0f;
-                }
-        };
-        fetch(0);
+            for (int u = 0; u < NW; ++u) {
+                const int idx = tid + u * NT;
+                wr[u] = (idx < CQ * 4 * S * S && c0 * S * S + idx < d * S * S) ? wb[c0 * S * S + idx] : 0.0f;
+            }
+    };
+    // runs `body(quad, offset of the quad's tile, of its weights, x of this lane)` over this wave's quads
+    auto phase = [&](const Source& src, auto&& body) {
+        const T *yb = src.y, *xb = src.x;
+        const float* wb = src.w;
+        fetch(src, 0);
         for (int c0 = 0; c0 < d; c0 += 4 * CQ) {
             __syncthreads();                                // the step before is no longer read
 #pragma unroll
@@ -187,7 +193,7 @@ pixel32_kernel(const PixelArgs a)
                 for (int i = tid; i < min(CQ * 4, d - c0) * S; i += NT) wl[(i / S) * (S * S) + (i % S) * (S + 1)] += a.idw;
             }
             __syncthreads();
-            if (c0 + 4 * CQ < d) fetch(c0 + 4 * CQ);
+            if (c0 + 4 * CQ < d) fetch(src, c0 + 4 * CQ);
 #pragma unroll 1
             for (int u = cg; u < CQ && wave_live; u += CG) {
                 if (c0 + 4 * u >= d) break;
@@ -232,7 +238,7 @@ pixel32_kernel(const PixelArgs a)
     };
 
     // sums over shifts: sum[s] += sum over channels of x[c] * (sum over taps of W[c,s,t] y[c,t])
-    auto contract = [&](const void* yp, const void* xp, const float* w, float (&sum)[S]) {
+    auto contract = [&](const Source& src, float (&sum)[S]) {
         // A channel's window is summed before x multiplies it, as in the general kernels, and the channels are added
         // in fours, the fours in fours: their sum is what rounds most.  Error of out against 64 bits (2-norm), float32,
         // merged kernels, 32 channels per head: 1.26e-7 (3x3, 56x56), 1.94e-7 (5x5, 28x28), the general kernels 1.26e-7 and
@@ -246,7 +252,7 @@ pixel32_kernel(const PixelArgs a)
         if (CG == 1)
 #pragma unroll
             for (int s = 0; s < S; ++s) total[s * PX] = 0.0f;
-        phase(yp, xp, w, [&](int, int yo, int wo, const float* xq) {
+        phase(src, [&](int, int yo, int wo, const float* xq) {
             f4 acc[4][SB];
             float last[4];
             window_sums(yo, wo, acc, last);
@@ -288,9 +294,9 @@ pixel32_kernel(const PixelArgs a)
         }
     };
     // out[c] = f * sum over shifts of p[s] * (sum over taps of W[c,s,t] y[c,t])
-    auto expand = [&](const void* yp, const float* w, const float (&p)[S], float f) {
+    auto expand = [&](const Source& src, const float (&p)[S], float f) {
         T* ob = (T*)a.out + item + pix * a.sp;
-        phase(yp, nullptr, w, [&](int c, int yo, int wo, const float*) {
+        phase(src, [&](int c, int yo, int wo, const float*) {
             f4 acc[4][SB];
             float last[4];
             window_sums(yo, wo, acc, last);
@@ -313,7 +319,7 @@ pixel32_kernel(const PixelArgs a)
     };
 
     float p[S];
-    contract(a.k, a.q, a.wk, p);
+    contract(source(a.k, a.q, a.wk), p);
     float mx = -INFINITY;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -332,7 +338,7 @@ pixel32_kernel(const PixelArgs a)
     }
     if (!BWD) {
         if (a.lse && live && cg == 0) a.lse[((long)b * (a.C / d) + m) * HW + pix] = mx + logf(den);
-        expand(a.v, a.wv, p, 1.0f);
+        expand(source(a.v, nullptr, a.wv), p, 1.0f);
     } else {
         // (p waits in a_ws while da is summed: the sums need the registers.  The barriers of `contract` order the
         // stores before the other channel groups' loads)
@@ -342,7 +348,7 @@ pixel32_kernel(const PixelArgs a)
 #pragma unroll
             for (int s = 0; s < S; ++s) a_px[(long)s * HW] = p[s];
         float da[S];
-        contract(a.v, a.dout, a.wv, da);
+        contract(source(a.v, a.dout, a.wv), da);
 #pragma unroll
         for (int s = 0; s < S; ++s) p[s] = a_px[(long)s * HW];
         float dsum = 0.0f;
@@ -353,7 +359,7 @@ pixel32_kernel(const PixelArgs a)
             da[s] = p[s] * (da[s] - dsum);
             if (live && cg == 0) dl_px[(long)s * HW] = da[s];
         }
-        expand(a.k, a.wk, da, a.scale);
+        expand(source(a.k, nullptr, a.wk), da, a.scale);
     }
 }
 
