@@ -71,8 +71,8 @@ int slide_reparam(const float* w_learned, float* w_merged, int C, int ksize, voi
  * invalid or no scratch is needed.  Launches nothing; reads the compute-unit count of the
  * current device (256 if there is none).
  * For bf16 problems with ksize 3 whose heads have 64 channels or fewer than 32 the figure
- * includes what the matrix-core kernels need to serve that head size (partial sums exchanged
- * between half heads; copies padded to 32 channels per head: several times the size of an
+ * includes what the matrix-core kernels need to serve that head size (attention weights or partial
+ * sums that one launch leaves for the next; copies padded to 32 channels per head: several times the size of an
  * activation tensor).  slide_attn_bwd requires it; a forward call that brings less scratch than
  * this (but enough for the float32 kernels: none) is served by those instead.
  */
@@ -215,8 +215,8 @@ int slide_attn_fwd_path(int B, int H, int W, int C, int heads, int ksize, int dt
  * at 64, 22 = its form for rows that are no multiple of 8 pixels (W >= 8), 24 = streaming ksize-3 kernel (a block walks down a band of rows, K/V rows in an LDS
  * ring; maps 32..64 columns wide; head size 32, or 24 with the fourth channel octet of every
  * head left empty), 26 = the streaming kernel on column strips of 48, 40 or 32 (maps wider than 64
- * columns, W % 8 == 0, strips covering at most 1.25 W), 25 = two launches of the streaming kernel for heads of 64 channels (each
- * head as two halves of 32 whose shares of the logits cross the workspace; a call that brings
+ * columns, W % 8 == 0, strips covering at most 1.25 W), 25 = two launches of the streaming kernel for heads of 64 channels (the
+ * attention weights of whole heads, which cross the workspace, then the value side of half heads; a call that brings
  * less workspace than slide_attn_workspace_bytes says runs on the float32 matrix-core kernel), 30 = ksize-5
  * matrix-core kernel, 100 + v = heads narrower than 32 channels (bf16, ksize 3, H * W % 8 == 0)
  * through kernel v on copies of q, k, v and the kernels padded to 32 channels per head in the

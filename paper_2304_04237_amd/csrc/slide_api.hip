@@ -71,7 +71,7 @@ extern "C" size_t slide_attn_workspace_bytes(int B, int H, int W, int C, int hea
     if (check_problem(B, H, W, C, heads, ksize, dtype) != SLIDE_OK) return 0;
     Problem p{B, H, W, C, heads, ksize, dtype};
     if (backward) return slide::bwd_generic_workspace_bytes(p);
-    // heads of 64 channels: what the two-launch streaming forward exchanges (a caller that brings
+    // heads of 64 channels: the weights between the two launches of the streaming forward (a caller that brings
     // less gets the general kernel, which needs none)
     if (slide::fwd_ring_enabled() && slide::fwd_ring_wide_supported(p, true)) return slide::fwd_ring_wide_workspace_bytes(p);
     // heads narrower than 32 channels: the padded copies (head size 24 on the streaming kernel's maps needs none)
@@ -209,7 +209,7 @@ extern "C" int slide_attn_fwd_noalloc(const void* q, const void* k, const void* 
     if (st != SLIDE_OK) return st;
     if (!q || !k || !v || !wk || !wv || !out) return SLIDE_ERR_NULL;
     size_t need = slide_attn_workspace_bytes(B, H, W, C, heads, ksize, dtype, 0);
-    {   // (heads of 64 channels whose partial logits do not fit the scratch run on the general kernel, which needs none)
+    {   // (heads of 64 channels whose attention weights do not fit the scratch run on the general kernel, which needs none)
         Problem pw{B, H, W, C, heads, ksize, dtype};
         Problem p32;
         if (need > NOALLOC_SCRATCH_BYTES && (slide::fwd_ring_wide_supported(pw, true) || slide::fwd_padded_problem(pw, p32))) need = 0;

@@ -111,27 +111,31 @@ constexpr int IMG_RAW_BYTES = 2 * HEAD_W * 4;             // 20736
 // part of the index arithmetic taken out of its loop: thread (lane, y, th) writes dwords y of
 // that lane for every second tap (A1 part) and for every fourth product (A2 part).
 template <int THREADS>
-__device__ __forceinline__ void image_from_raw(const float* raw, const float* __restrict__ bias, int m, float idw,
-                                               uint32_t* dst, int tid)
+__device__ __forceinline__ void key_image_from_raw(const float* raw, float idw, uint32_t* dst, int tid)
 {
     static_assert(THREADS == 512, "thread-to-dword mapping below");
     const int lane = tid & 63, i = lane & 15, g = lane >> 4;
-    {
-        // A1: dword (t * 64 + lane) * 4 + y = K weights of channels 8g + 2y, 8g + 2y + 1 for the shift of logit row i at tap t
-        const int y = (tid >> 6) & 3, th = tid >> 8;
-        const int s = shift_of_row(i);
-        const bool ok = s >= 0;
-        const float* w = raw + ((8 * g + 2 * y) * S + max(s, 0)) * S;
+    // A1: dword (t * 64 + lane) * 4 + y = K weights of channels 8g + 2y, 8g + 2y + 1 for the shift of logit row i at tap t
+    const int y = (tid >> 6) & 3, th = tid >> 8;
+    const int s = shift_of_row(i);
+    const bool ok = s >= 0;
+    const float* w = raw + ((8 * g + 2 * y) * S + max(s, 0)) * S;
 #pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            const int t = th + 2 * k;
-            if (t < S) {
-                const float sub = (s == t) ? -idw : 0.0f;
-                const float w0 = w[t], w1 = w[t + S * S];
-                dst[IMG_A1 + (t * 64 + lane) * 4 + y] = ok ? pack_half((w0 - sub) * WK_SCALE, (w1 - sub) * WK_SCALE) : 0u;
-            }
+    for (int k = 0; k < 5; ++k) {
+        const int t = th + 2 * k;
+        if (t < S) {
+            const float sub = (s == t) ? -idw : 0.0f;
+            const float w0 = w[t], w1 = w[t + S * S];
+            dst[(t * 64 + lane) * 4 + y] = ok ? pack_half((w0 - sub) * WK_SCALE, (w1 - sub) * WK_SCALE) : 0u;
         }
     }
+}
+template <int THREADS>
+__device__ __forceinline__ void image_from_raw(const float* raw, const float* __restrict__ bias, int m, float idw,
+                                               uint32_t* dst, int tid)
+{
+    const int lane = tid & 63, i = lane & 15, g = lane >> 4;
+    key_image_from_raw<THREADS>(raw, idw, dst + IMG_A1, tid);
     {
         // A2: dword (u * 64 + lane) * 2 + y = V weights of the product's row i (a channel and a tap) for the shifts of logit rows 4g + 2y, 4g + 2y + 1
         const int y = (tid >> 6) & 1, uh = tid >> 7;

@@ -1,7 +1,7 @@
 // Streaming matrix-core forward of Slide Attention for gfx950: bf16 activations, head size
 // 32, 3x3 window, maps of 32..64 columns (a multiple of 8) whose rows and pointers are
 // 16-byte aligned; wider maps as column strips of up to 48 (template argument STRIP), heads of 24
-// channels with an empty fourth octet (DH), heads of 64 as two half heads (MODE).  Same arithmetic as the tiled kernels (operator of Sec. 4.1-4.3 with the
+// channels with an empty fourth octet (DH), heads of 64 in two launches (MODE).  Same arithmetic as the tiled kernels (operator of Sec. 4.1-4.3 with the
 // merged kernel W~ of Sec. 4.3 / Fig. 4 as matrix-core operands, see slide_fwd16_ops.h); what
 // differs is how data moves:
 //
@@ -57,7 +57,8 @@ struct RingArgs {
     int off_raw, off_dummy, off_q, off_out, off_out2;   // LDS byte offsets: K/V landing slots, dump slot, q slots, per-wave result slots, the block's two result buffers
     uint32_t magic_w, magic_r;                 // ceil(2^32 / W), ceil(2^32 / R): x / W == umulhi(x, magic_w) for x < 2^26
     float scale_log2e, idw;
-    float* part;                               // heads of 64 channels (MODE 1, 2): partial logits of every half head, [B, 2 heads, 9, H, W], times scale_log2e
+    uint2_t* weights;                          // heads of 64 channels (MODE 1, 2): [B, heads, H, W, 4], lane group g's three attention weights of a pixel as halves
+    int off_q2;                                // MODE 1: q slots of the upper 32 channels
     int Wf, n_strips;                          // STRIP: columns of the whole map (W is the strip's width), strips per plane
 };
 
@@ -79,13 +80,14 @@ struct RingArgs {
 // read and no operand image is built; the matrix core only adds the 32 channel products of a
 // tap, and every lane holds all nine logits of its pixel.
 //
-// MODE: heads of 64 channels run as two half heads of 32 (the arguments then describe twice as
-// many heads; bias and lse are indexed by the pair) in two launches.  The logit of Eq. 2 is a
-// sum over the channels of the head, so MODE 1 only forms each half head's share of the nine
-// logits (key side; nothing else is computed or stored, no value rows are staged) and writes it
-// to `part`; MODE 2 is the rest of the kernel (no q, no key rows, no key-side products): a pass
-// adds the two halves' shares, so both halves get the same attention weights, and applies them
-// to its own 32 value channels.  MODE 0: heads of DH channels, one launch.
+// MODE: heads of 64 channels run in two launches that exchange the attention weights.  MODE 1 works on whole heads (arguments
+// and blocks are those of the heads): the two units of a mover are the lower and the upper 32 channels of the key rows, a pass
+// adds both halves' products to the same logits, and what goes out is a pixel's nine weights as the halves that the value side
+// takes (in registers, where no launch lies between), 32 bytes to `weights`.  MODE 2 works on half heads (arguments describe twice as many heads): the value side alone, with a
+// half's 32 channels.  MODE 0: heads of DH channels, one launch.
+// MI355X, B=64, 56x56, C=64, one head: 44.0 us with a half's share of the logits as float32 from one launch to the
+// other, which wrote and read 72 and 144 bytes per pixel where this writes 32 and reads 64, and formed the softmax of a pixel twice;
+// 36.5 us like this (18 + 18).
 constexpr int MOVERS = 4, WAVES12 = WAVES + MOVERS, THREADS12 = WAVES12 * 64;
 
 template <int RPG, bool LSE, bool PLAIN, int DH, int MODE = 0, bool STRIP = false>
@@ -124,7 +126,8 @@ fwd16_ring_kernel(const RingArgs a)
     const int y0 = part * a.rows_pb;
     const int nr = min(a.rows_pb, H - y0);
     const long HW = (long)H * Wf;
-    const long head_base = ((long)b * a.C + (long)m * DH) * HW;   // element offset of channel 0 of the head
+    constexpr int HD = MODE == 1 ? 2 * DH : DH;
+    const long head_base = ((long)b * a.C + (long)m * HD) * HW;   // element offset of channel 0 of the head
     const bool oct_empty = DH < D && mover && 8 * mv >= DH;         // this mover's octet does not exist
     const int npix = nr * W, npass = (npix + 15) >> 4, E = (npass + WAVES - 1) / WAVES;
 
@@ -138,7 +141,8 @@ fwd16_ring_kernel(const RingArgs a)
     // ---- mover: K/V staging of units j = 0 (K), 1 (V), octet mv
     const int oct = mover ? mv : 0;
     const int src_oct = oct_empty ? 0 : oct;
-    const bf16_bits* kv_src[2] = {a.k + head_base + (long)(8 * src_oct) * HW, a.v + head_base + (long)(8 * src_oct) * HW};
+    const bf16_bits* kv_src[2] = {a.k + head_base + (long)(8 * src_oct) * HW,
+                                  (MODE == 1 ? a.k + (long)DH * HW : a.v) + head_base + (long)(8 * src_oct) * HW};
     // a row of a unit lands as [8 channels][WL pixels]; STRIP: the strip and the 8 pixels either
     // side of it (WL = W + 16 <= 64), of which the ring takes one column left and right
     const int WL = STRIP ? W + 16 : W;
@@ -156,7 +160,7 @@ fwd16_ring_kernel(const RingArgs a)
     auto slot_off = [&](int j, int s) {
         const int raw = a.off_raw + (4 * j + oct) * (2 * RPG * SLOT);
         const int pw = 2 * oct + j;
-        return s < 2 * RPG ? raw + s * SLOT : (s == 2 * RPG ? a.off_q + pw * (3 * SLOT) + 2 * SLOT : a.off_out + pw * SLOT);
+        return s < 2 * RPG ? raw + s * SLOT : (s == 2 * RPG ? a.off_q + pw * (3 * SLOT) + 2 * SLOT : MODE == 1 ? a.off_q2 + pw * (3 * SLOT) + 2 * SLOT : a.off_out + pw * SLOT);
     };
     // (an empty octet reads channel 0 of the head's first octet into the dump slot)
     auto load_row = [&](int j, uint32_t row_off, int off) {
@@ -198,24 +202,25 @@ fwd16_ring_kernel(const RingArgs a)
     };
     const bf16_bits* q_src = a.q + head_base + (long)y0 * Wf;
     const uint32_t q_lane_off = (uint32_t)(lane >> 1) * hw2 + (STRIP ? 0u : (uint32_t)(lane & 1) * 16u);
-    auto load_q = [&](int pw, int n_first, int qo) {
+    // (x: MODE 1, the lower or the upper 32 channels)
+    auto load_q = [&](int pw, int n_first, int qo, int x = 0) {
         const bool real = n_first < npix;
         const int nf = real ? n_first : 0;
-        const int off = real ? a.off_q + pw * (3 * SLOT) + qo : a.off_dummy;
+        const int off = real ? (x ? a.off_q2 : a.off_q) + pw * (3 * SLOT) + qo : a.off_dummy;
         if (nf + 8 * (lane & 1) < npix && (lane >> 1) < DH)
-            load_to_lds(q_src, q_lane_off + (STRIP ? px_off(nf + 8 * (lane & 1)) : (uint32_t)nf * 2u), lds0 + off);
+            load_to_lds(q_src + (x ? (long)DH * HW : 0L), q_lane_off + (STRIP ? px_off(nf + 8 * (lane & 1)) : (uint32_t)nf * 2u), lds0 + off);
     };
 
     // ---- start-up.  The first access to a tensor takes microseconds (cold translation): the
     // bias is fetched first thing, next to the kernels, not where it is used.
     float bias_early = 0.0f;                                           // PLAIN: bias of shift `lane`; else the image's bias word of logit row `tid`
-    const int mb = MODE ? m >> 1 : m;                                  // head that the bias and lse belong to
-    if (a.bias && !mover && MODE != 1) {
+    const int mb = m;                                                  // (MODE 2 needs no bias)
+    if (a.bias && !mover && MODE != 2) {
         if (PLAIN) { if (lane < S) bias_early = a.bias[mb * S + lane]; }
         else if (tid < IMG_DWORDS - IMG_BIAS && shift_of_row(tid) >= 0) bias_early = a.bias[mb * S + shift_of_row(tid)];
     }
-    // tensors a mover stages: K (j = 0) unless the logits come in whole, V (j = 1) unless only logits are formed
-    constexpr int J0 = MODE == 2 ? 1 : 0, J1 = MODE == 1 ? 1 : 2, NJ = J1 - J0;
+    // tensors a mover stages: K (j = 0) and V (j = 1), both halves of K, or V alone
+    constexpr int J0 = MODE == 2 ? 1 : 0, J1 = 2, NJ = J1 - J0, NX = MODE == 1 ? 2 : 1;
     constexpr bool HAS_Q = MODE != 2;                                  // q is loaded (the key side is computed)
     const int v0 = srn(0), v1 = srn(1), v2 = srn(2);
     int n_after_g0 = 0;                                                // mover: loads issued after group 0
@@ -227,8 +232,9 @@ fwd16_ring_kernel(const RingArgs a)
         for (int L = wave; L * 64 < 2 * CHUNKS; L += WAVES) {
             const int c = L * 64 + lane;
             const int cc = c >= CHUNKS ? c - CHUNKS : c;
-            const float* src = (c >= CHUNKS ? a.wv : a.wk) + (long)m * head_w + 4 * cc;
-            if (c < 2 * CHUNKS) {
+            // (MODE 1: the K kernels of the head's two halves; MODE 2: V kernels alone)
+            const float* src = MODE == 1 ? a.wk + (long)m * (2 * head_w) + 4 * c : (c >= CHUNKS ? a.wv : a.wk) + (long)m * head_w + 4 * cc;
+            if (c < 2 * CHUNKS && (MODE != 2 || c >= CHUNKS)) {
                 if (DH == D || cc < chunks_d) load_to_lds_addr(src, lds0 + IMG_RAW_AT + L * 1024);
                 else *(uint4_t*)(smem + IMG_RAW_AT + c * 16) = uint4_t{0u, 0u, 0u, 0u};
             }
@@ -242,10 +248,12 @@ fwd16_ring_kernel(const RingArgs a)
         }
         if (HAS_Q) {
             for (int i = 0; i < 2; ++i) {
-                load_q(2 * mv + i, 16 * (2 * mv + i), 0);
-                load_q(2 * mv + i, 16 * (2 * mv + i) + PX_EPOCH, SLOT);
+                for (int x = 0; x < NX; ++x) {
+                    load_q(2 * mv + i, 16 * (2 * mv + i), 0, x);
+                    load_q(2 * mv + i, 16 * (2 * mv + i) + PX_EPOCH, SLOT, x);
+                }
             }
-            n_after_g0 = 4;
+            n_after_g0 = 4 * NX;
         }
         for (int k = 0; k < v1 - v0; ++k) {                            // group 1 into set 1
             const int gy = y0 + v0 + k;
@@ -257,18 +265,28 @@ fwd16_ring_kernel(const RingArgs a)
     }
     half8_t A1[S];
     half4_t A2[2 * S];
+    half8_t A1b[S];                                                    // MODE 1: the upper half's
     float bias2[3];
     float bias9[S];
     if (!PLAIN) {
         if (!mover) wait_vmem(0);                                      // the kernels have landed
         block_barrier();
         if (tid < THREADS) {
-            image_from_raw<THREADS>((const float*)(smem + IMG_RAW_AT), nullptr, m, a.idw, (uint32_t*)smem, tid);
+            if (MODE == 1) {                                           // (the second key image in the place of the value image)
+                key_image_from_raw<THREADS>((const float*)(smem + IMG_RAW_AT), a.idw, (uint32_t*)smem + IMG_A1, tid);
+                key_image_from_raw<THREADS>((const float*)(smem + IMG_RAW_AT) + HEAD_W, a.idw, (uint32_t*)smem + IMG_A2, tid);
+            } else
+                image_from_raw<THREADS>((const float*)(smem + IMG_RAW_AT), nullptr, m, a.idw, (uint32_t*)smem, tid);
             if (tid < IMG_DWORDS - IMG_BIAS)                           // (overwrites the zero-bias words that image_from_raw wrote)
                 ((uint32_t*)smem)[IMG_BIAS + tid] = __float_as_uint(shift_of_row(tid) >= 0 ? bias_early * 1.44269504088896341f : -INFINITY);
         }
         block_barrier();
-        if (!mover) load_operands((const uint32_t*)smem, lane, g, A1, A2, bias2);
+        if (!mover) {
+            load_operands((const uint32_t*)smem, lane, g, A1, A2, bias2);
+            if (MODE == 1)
+#pragma unroll
+                for (int t = 0; t < S; ++t) A1b[t] = __builtin_bit_cast(half8_t, *(const uint4_t*)((const uint32_t*)smem + IMG_A2 + (t * 64 + lane) * 4));
+        }
         block_barrier();
     } else if (!mover) {
 #pragma unroll
@@ -289,7 +307,7 @@ fwd16_ring_kernel(const RingArgs a)
         }
     };
     if (DH < D) zero_q_rows(tid, 2 * WAVES, THREADS12, 0, 2);
-    constexpr int NL = NJ * RPG + (HAS_Q ? 2 : 0);                     // loads of a mover per epoch
+    constexpr int NL = NJ * RPG + (HAS_Q ? 2 * NX : 0);                     // loads of a mover per epoch
     if (mover) {
         wait_vmem(n_after_g0);                                         // group 0 has landed
         for (int k = 0; k <= v0; ++k) {                                // group 0 -> ring rows 0 .. v0
@@ -314,8 +332,7 @@ fwd16_ring_kernel(const RingArgs a)
                 load_row(j, (uint32_t)min(max(gy, 0), H - 1) * w2, real ? slot_off(j, k) : a.off_dummy);
         }
         if (HAS_Q) {
-            load_q(0, npix, 0);
-            load_q(0, npix, 0);                                        // (two dump loads complete the round)
+            for (int x = 0; x < 2 * NX; ++x) load_q(0, npix, 0);       // (dump loads complete the round)
         }
         wait_vmem(NL);                                                 // everything but that round: group 1, q of epochs 0 and 1
     }
@@ -400,7 +417,9 @@ fwd16_ring_kernel(const RingArgs a)
             }
             if (HAS_Q) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i) load_q(2 * mv + i, PX_EPOCH * (e + 2) + 16 * (2 * mv + i), qo_2);
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int x = 0; x < NX; ++x) load_q(2 * mv + i, PX_EPOCH * (e + 2) + 16 * (2 * mv + i), qo_2, x);
             }
             // conversion of group e + 1 into the ring
             const int cnt = (cvB >> 10) & 7;
@@ -432,7 +451,9 @@ fwd16_ring_kernel(const RingArgs a)
             else if (NL == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
             else if (NL == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
             else if (NL == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
+            else if (NL == 10) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+            static_assert(NL == 2 || NL == 3 || NL == 4 || NL == 5 || NL == 6 || NL == 8 || NL == 10 || NL == 12, "");
             block_barrier();
         }
         if (MODE != 1) store_results(PX_EPOCH * (E - 1), out2_rd);
@@ -447,27 +468,18 @@ fwd16_ring_kernel(const RingArgs a)
     const unsigned char* tap_base = smem + g * PS;
     const int st_c = 16 * ((lane >> 4) & 1) + (lane & 15), st_hh = lane >> 5;
     int nb = 16 * wave;
-    float* lse_ptr = LSE ? a.lse + ((long)(MODE ? plane >> 1 : plane) * H + y0) * Wf : nullptr;
+    float* lse_ptr = LSE ? a.lse + ((long)plane * H + y0) * Wf : nullptr;
     auto lse_at = [&](int n) {                                         // band pixel -> index from the band's first row
         if (!STRIP) return n;
         const int r = div_w(n);
         return r * Wf + x0 + (n - r * W);
     };
-    // MODE 1: this half head's share of the logits goes out; MODE 2: the other half's comes in,
-    // fetched one epoch ahead (lane (p, g) holds the shifts g, 4 + g, 8 + g of pixel p)
-    float* part_out = MODE == 1 ? a.part + (long)plane * S * HW + (long)y0 * W : nullptr;
-    const float* part_own = MODE == 2 ? a.part + (long)plane * S * HW + (long)y0 * W : nullptr;
-    const float* part_in = MODE == 2 ? a.part + (long)(plane ^ 1) * S * HW + (long)y0 * W : nullptr;
-    float oth[3] = {0.0f, 0.0f, 0.0f};                                 // the two halves' shares, added
-    auto fetch_shares = [&](int n_first) {
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            const bool has = n_first + p < npix && (r < 2 || g == 0);
-            const long at = (long)(4 * r + g) * HW + n_first + p;
-            oth[r] = has ? part_own[at] + part_in[at] : 0.0f;
-        }
-    };
-    if (MODE == 2) fetch_shares(nb);
+    // MODE 1: the attention weights go out; MODE 2: they come in, fetched one epoch ahead (lane (p, g) holds the shifts g, 4 + g,
+    // 8 + g of pixel p)
+    uint2_t* const weights = MODE ? a.weights + ((long)(MODE == 2 ? plane >> 1 : plane) * HW + (long)y0 * W) * 4 + g : nullptr;
+    uint2_t given = {0u, 0u};
+    auto fetch_weights = [&](int n_first) { given = weights[(long)min(n_first + p, npix - 1) * 4]; };
+    if (MODE == 2) fetch_weights(nb);
     for (int e = 0; e < E; ++e) {
         const uint32_t p2 = __builtin_amdgcn_readlane(t_p2, e);
         if (p2 & 256u) {
@@ -538,32 +550,47 @@ fwd16_ring_kernel(const RingArgs a)
                     if (t & 1) acc1b = __builtin_amdgcn_mfma_f32_16x16x32_f16(A1[t], __builtin_bit_cast(half8_t, bb), acc1b, 0, 0, 0);
                     else       acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(A1[t], __builtin_bit_cast(half8_t, bb), acc1, 0, 0, 0);
                 }
+                if (MODE == 1) {                                       // the upper 32 channels, to the same sums
+                    const uint2_t u0 = lds_read_tr(qsrc + (a.off_q2 - a.off_q)), u1 = lds_read_tr(qsrc + (a.off_q2 - a.off_q) + 4 * 32);
+                    const half2_t sc = {(_Float16)G_SCALE, (_Float16)G_SCALE};
+                    qs[0] = as_half2(bf16x2_to_half2(u0[0])) * sc; qs[1] = as_half2(bf16x2_to_half2(u0[1])) * sc;
+                    qs[2] = as_half2(bf16x2_to_half2(u1[0])) * sc; qs[3] = as_half2(bf16x2_to_half2(u1[1])) * sc;
+#pragma unroll
+                    for (int t = 0; t < S; ++t) kd[t] = *(const uint4_t*)(kb[t / KS] + VD + (t % KS) * 16);
+#pragma unroll
+                    for (int t = 0; t < S; ++t) {
+                        uint4_t bb;
+#pragma unroll
+                        for (int y = 0; y < 4; ++y) bb[y] = as_dword(qs[y] * as_half2(kd[t][y]));
+                        if (t & 1) acc1b = __builtin_amdgcn_mfma_f32_16x16x32_f16(A1b[t], __builtin_bit_cast(half8_t, bb), acc1b, 0, 0, 0);
+                        else       acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(A1b[t], __builtin_bit_cast(half8_t, bb), acc1, 0, 0, 0);
+                    }
+                }
                 acc1 += acc1b;
                 }
-                if (MODE == 1) {
-                    if (nb + p < npix) {
-#pragma unroll
-                        for (int r = 0; r < 3; ++r)
-                            if (r < 2 || g == 0) part_out[(long)(4 * r + g) * HW + nb + p] = acc1[r] * a.scale_log2e;
-                    }
-                } else {
                 uint4_t vd[S];
+                if (MODE != 1)
 #pragma unroll
                 for (int t = 0; t < S; ++t) vd[t] = *(const uint4_t*)(kb[t / KS] + VD + (t % KS) * 16);
+                uint2_t b2 = given;
+                if (MODE == 2) fetch_weights(nb + PX_EPOCH);
+                else {
                 float l[3];
 #pragma unroll
-                for (int r = 0; r < 3; ++r) l[r] = MODE == 2 ? oth[r] + bias2[r] : fmaf(acc1[r], a.scale_log2e, bias2[r]);
-                if (MODE == 2) fetch_shares(nb + PX_EPOCH);
+                for (int r = 0; r < 3; ++r) l[r] = fmaf(acc1[r], a.scale_log2e, bias2[r]);
                 const float mx = allmax_groups(fmaxf(fmaxf(l[0], l[1]), l[2]));
                 float pr[3];
 #pragma unroll
                 for (int r = 0; r < 3; ++r) pr[r] = __builtin_amdgcn_exp2f(l[r] - mx);
                 const float den = allsum_groups(pr[0] + pr[1] + pr[2]);
                 const float inv = __builtin_amdgcn_rcpf(den);
-                if (LSE) { if (g == 0 && nb + p < npix && (MODE != 2 || (m & 1) == 0)) lse_ptr[lse_at(nb + p)] = LN2 * (mx + __builtin_amdgcn_logf(den)); }
-                uint2_t b2;
+                if (LSE) { if (g == 0 && nb + p < npix) lse_ptr[lse_at(nb + p)] = LN2 * (mx + __builtin_amdgcn_logf(den)); }
                 b2[0] = pack_half(pr[0] * inv, pr[1] * inv);
                 b2[1] = pack_half(pr[2] * inv, 0.0f);
+                }
+                if (MODE == 1) {
+                    if (nb + p < npix) weights[(long)(nb + p) * 4] = b2;
+                } else {
                 const half4_t B2 = __builtin_bit_cast(half4_t, b2);
                 const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
                 float4_t w[2 * S];
@@ -1123,7 +1150,7 @@ hipError_t launch_fwd_ring(const Problem& p, const void* q, const void* k, const
     a.magic_r = (uint32_t)(((1ULL << 32) + r.R - 1) / r.R);
     a.scale_log2e = 1.44269504088896341f * p.logit_scale();
     a.idw = p.two_branch ? 1.0f : 0.0f;
-    a.part = nullptr; a.Wf = p.W; a.n_strips = 1;
+    a.weights = nullptr; a.Wf = p.W; a.n_strips = 1;
     static LdsOptIn opt_in;
 #define SLIDE_RING_KERNELS2(RPGV, DHV)                                                                              \
     (const void*)fwd16_ring_kernel<RPGV, false, false, DHV>, (const void*)fwd16_ring_kernel<RPGV, true, false, DHV>, \
@@ -1220,7 +1247,7 @@ hipError_t launch_fwd_ring_strip(const Problem& p, const void* q, const void* k,
     a.magic_r = (uint32_t)(((1ULL << 32) + r.R - 1) / r.R);
     a.scale_log2e = 1.44269504088896341f * p.logit_scale();
     a.idw = p.two_branch ? 1.0f : 0.0f;
-    a.part = nullptr;
+    a.weights = nullptr;
     static LdsOptIn opt_in;
 #define SLIDE_STRIP_KERNELS(RPGV) (const void*)fwd16_ring_kernel<RPGV, false, false, 32, 0, true>, (const void*)fwd16_ring_kernel<RPGV, true, false, 32, 0, true>, \
                                   (const void*)fwd16_ring_kernel<RPGV, false, true, 32, 0, true>, (const void*)fwd16_ring_kernel<RPGV, true, true, 32, 0, true>
@@ -1255,10 +1282,11 @@ bool fwd_ring_wide_supported(const Problem& p, bool aligned16)
 {
     if (!aligned16 || p.dtype != 1 || p.ksize != 3 || p.C != p.heads * 64) return false;
     if ((long)p.H * p.W * 2 * f16ring::D >= (1L << 31)) return false;
-    if ((long)p.B * p.heads * 2 * 9 * p.H * p.W >= (1L << 31)) return false;   // index arithmetic of the partial logits
+    if ((long)p.B * p.heads * 2 * 9 * p.H * p.W >= (1L << 31)) return false;   // index arithmetic of what is exchanged
     return f16ring::plan_ring(half_head_problem(p)).ok;
 }
 
+// (more than the 32 bytes per pixel and head that are exchanged: callers sized their workspaces for float32 logits)
 size_t fwd_ring_wide_workspace_bytes(const Problem& p)
 {
     return (size_t)p.B * p.heads * 2 * 9 * (size_t)p.plane() * sizeof(float);
@@ -1270,38 +1298,43 @@ hipError_t launch_fwd_ring_wide(const Problem& p, const void* q, const void* k, 
 {
     using namespace f16ring;
     const Problem h = half_head_problem(p);
-    const RingPlan r = plan_ring(h);
-    if (!r.ok) return hipErrorInvalidValue;
-    RingArgs a;
-    a.q = (const bf16_bits*)q; a.k = (const bf16_bits*)k; a.v = (const bf16_bits*)v;
-    a.out = (bf16_bits*)out; a.lse = lse;
-    a.wk = wk; a.wv = wv; a.bias = bias;
-    a.B = h.B; a.H = h.H; a.W = h.W; a.C = h.C; a.heads = h.heads; a.d = D;
-    a.nbp = r.nbp; a.rows_pb = r.rows_pb; a.n_blocks = r.n_blocks;
-    a.R = r.R; a.RS = r.RS; a.PS = r.PS; a.off_raw = r.off_raw; a.off_dummy = r.off_dummy; a.off_q = r.off_q; a.off_out = r.off_out; a.off_out2 = r.off_out2;
-    a.magic_w = (uint32_t)(((1ULL << 32) + h.W - 1) / h.W);
-    a.magic_r = (uint32_t)(((1ULL << 32) + r.R - 1) / r.R);
-    a.scale_log2e = 1.44269504088896341f / sqrtf(64.0f);               // (the head has 64 channels)
-    a.idw = p.two_branch ? 1.0f : 0.0f;
-    a.part = (float*)workspace; a.Wf = h.W; a.n_strips = 1;
+    const RingPlan half = plan_ring(h);
+    if (!half.ok) return hipErrorInvalidValue;
+    RingPlan whole = plan_ring(p);
+    if (!whole.ok) { whole = half; whole.n_blocks = p.B * p.heads * half.nbp; }     // (its bands need a ring that does not fit: the halves' bands)
+    auto arguments = [&](const Problem& of, const RingPlan& r) {
+        RingArgs a{};
+        a.q = (const bf16_bits*)q; a.k = (const bf16_bits*)k; a.v = (const bf16_bits*)v;
+        a.out = (bf16_bits*)out; a.lse = lse;
+        a.wk = wk; a.wv = wv; a.bias = bias;
+        a.B = of.B; a.H = of.H; a.W = of.W; a.C = of.C; a.heads = of.heads; a.d = D;
+        a.nbp = r.nbp; a.rows_pb = r.rows_pb; a.n_blocks = r.n_blocks;
+        a.R = r.R; a.RS = r.RS; a.PS = r.PS; a.off_raw = r.off_raw; a.off_dummy = r.off_dummy; a.off_q = r.off_q; a.off_out = r.off_out; a.off_out2 = r.off_out2;
+        a.off_q2 = r.off_out;                                          // (MODE 1 stores no results)
+        a.magic_w = (uint32_t)(((1ULL << 32) + of.W - 1) / of.W);
+        a.magic_r = (uint32_t)(((1ULL << 32) + r.R - 1) / r.R);
+        a.scale_log2e = 1.44269504088896341f / sqrtf(64.0f);           // (the head has 64 channels)
+        a.idw = p.two_branch ? 1.0f : 0.0f;
+        a.weights = (uint2_t*)workspace; a.Wf = of.W; a.n_strips = 1;
+        return a;
+    };
+    const RingArgs a1 = arguments(p, whole), a2 = arguments(h, half);
+    static_assert(2 * WAVES * SLOT <= 2 * 32 * (2 * PX_EPOCH + 16), "the upper channels' q slots lie where the results would");
     static LdsOptIn opt_in;
 #define SLIDE_WIDE_KERNELS(RPGV)                                                                                    \
-    (const void*)fwd16_ring_kernel<RPGV, false, false, 32, 1>, (const void*)fwd16_ring_kernel<RPGV, false, false, 32, 2>, \
-    (const void*)fwd16_ring_kernel<RPGV, true, false, 32, 2>
+    (const void*)fwd16_ring_kernel<RPGV, false, false, 32, 1>, (const void*)fwd16_ring_kernel<RPGV, true, false, 32, 1>, \
+    (const void*)fwd16_ring_kernel<RPGV, false, false, 32, 2>
     hipError_t e = opt_in.ensure({SLIDE_WIDE_KERNELS(2), SLIDE_WIDE_KERNELS(3), SLIDE_WIDE_KERNELS(4)}, LDS_LIMIT);
 #undef SLIDE_WIDE_KERNELS
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)r.n_blocks), block12(THREADS12);
-#define SLIDE_WIDE_LAUNCH(RPGV)                                                                                     \
-    do {                                                                                                            \
-        hipLaunchKernelGGL((fwd16_ring_kernel<RPGV, false, false, 32, 1>), grid, block12, (size_t)r.lds_bytes, st, a); \
-        if (lse) hipLaunchKernelGGL((fwd16_ring_kernel<RPGV, true, false, 32, 2>), grid, block12, (size_t)r.lds_bytes, st, a);  \
-        else     hipLaunchKernelGGL((fwd16_ring_kernel<RPGV, false, false, 32, 2>), grid, block12, (size_t)r.lds_bytes, st, a); \
-    } while (0)
-    if (r.rpg == 2) SLIDE_WIDE_LAUNCH(2);
-    else if (r.rpg == 3) SLIDE_WIDE_LAUNCH(3);
-    else SLIDE_WIDE_LAUNCH(4);
-#undef SLIDE_WIDE_LAUNCH
+#define SLIDE_WIDE(RPG, LSE, MODE) fwd16_ring_kernel<RPG, LSE, false, 32, MODE>
+    const auto first = whole.rpg == 2 ? (lse ? SLIDE_WIDE(2, true, 1) : SLIDE_WIDE(2, false, 1))
+                     : whole.rpg == 3 ? (lse ? SLIDE_WIDE(3, true, 1) : SLIDE_WIDE(3, false, 1))
+                                      : (lse ? SLIDE_WIDE(4, true, 1) : SLIDE_WIDE(4, false, 1));
+    const auto second = half.rpg == 2 ? SLIDE_WIDE(2, false, 2) : half.rpg == 3 ? SLIDE_WIDE(3, false, 2) : SLIDE_WIDE(4, false, 2);
+#undef SLIDE_WIDE
+    hipLaunchKernelGGL(first, dim3((unsigned)whole.n_blocks), dim3(THREADS12), (size_t)whole.lds_bytes, st, a1);
+    hipLaunchKernelGGL(second, dim3((unsigned)half.n_blocks), dim3(THREADS12), (size_t)half.lds_bytes, st, a2);
     return hipGetLastError();
 }
 

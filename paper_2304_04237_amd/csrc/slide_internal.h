@@ -208,8 +208,8 @@ hipError_t launch_fwd_ring_strip(const Problem& p, const void* q, const void* k,
                                  float* lse, bool plain, hipStream_t st);
 
 // heads of 64 channels on the streaming forward (bf16, ksize 3, maps the streaming kernel
-// takes): two launches over half heads, the halves' shares of the logits exchanged through the
-// workspace (fwd_ring_wide_workspace_bytes, 16-byte aligned)
+// takes): the attention weights of whole heads, then the value side of half heads; the weights
+// go through the workspace (fwd_ring_wide_workspace_bytes, 16-byte aligned)
 bool fwd_ring_wide_supported(const Problem& p, bool aligned16);
 size_t fwd_ring_wide_workspace_bytes(const Problem& p);
 hipError_t launch_fwd_ring_wide(const Problem& p, const void* q, const void* k, const void* v,
