@@ -248,3 +248,21 @@ def test_binding_rejects_mismatched_parameter_shapes(lib):
         sa.slide_attn_bwd(q, q, q, q, w3, w3, bias, 2, 3, outputs=(q, q, q, w3, w3, None))
     with pytest.raises(sa.SlideAttnError, match="w_merged"):
         sa.slide_reparam(w3, w5)
+
+
+@pytest.mark.parametrize("name, change, message", [
+    ("q", lambda t: t[0], "activations must be"), ("q", lambda t: t.half(), "float32 or bfloat16"),
+    ("k", lambda t: t.bfloat16(), "k must match"), ("v", lambda t: t[..., :5], "v must match"),
+    ("wk", lambda t: t[:32], "wk must be"), ("wv", lambda t: t[..., :2], "wv must be"), ("bias", lambda t: t[:1], "bias must be"),
+    ("out", lambda t: t.bfloat16(), "out must match"), ("lse", lambda t: t[:, :1], "lse must be"),
+    ("workspace", lambda t: t, "workspace must live on the GPU"), ("q", lambda t: t, "q must live on the GPU")])
+def test_binding_names_the_first_wrong_argument(lib, name, change, message):
+    import torch
+    x = torch.zeros(1, 64, 6, 6)
+    arguments = dict(q=x, k=x, v=x, wk=torch.zeros(64, 9, 3, 3), wv=torch.zeros(64, 9, 3, 3), bias=torch.zeros(2, 9))
+    spare = dict(out=x, lse=torch.zeros(1, 2, 6, 6), workspace=torch.zeros(64))
+    arguments[name] = change(arguments[name] if name in arguments else spare[name])
+    if message == "float32 or bfloat16":
+        arguments.update(k=arguments["q"], v=arguments["q"])
+    with pytest.raises(sa.SlideAttnError, match=message):
+        sa.slide_attn_fwd(**arguments, heads=2, ksize=3)
