@@ -11,6 +11,14 @@
 // to the K/V halo tile and reads them as it goes; blocks are persistent and walk the tile
 // list, reloading the operands only when the head changes.  The 25 logits of a pixel live
 // in two 16-row MFMA tiles; lane group g owns rows 4g..4g+3 of both, i.e. 7 logits.
+//
+// Two waves per SIMD (the LDS is full with one block) do not hide a pass's chain of read, product and use by
+// themselves: the waves waited in 57 % of their cycles with the matrix cores busy in 19 and the LDS in 35.  So the chain is
+// taken apart by hand: operands are read two taps or three products ahead, and the multiplications with a product's
+// result stand behind the next product (barriers for the scheduler keep them there; it otherwise puts read, product and use
+// next to each other).  MI355X, B=64, 28x28, C=128, four heads: 49.9 us per call without, 44 (one card) to 46 with
+// it.  Two passes of a wave that share the reads of the operands, a third less of them: 52 to 63 us (the registers of
+// two passes do not fit).
 #include "slide_tile16.h"
 
 namespace slide {
@@ -19,6 +27,8 @@ using namespace t16;
 
 constexpr int K5 = 5, S5 = 25;
 constexpr int WAVES = 8, THREADS = WAVES * 64;
+// taps (K side) and products (V side) from the read of an operand to its use
+constexpr int AHEAD_K = 2, AHEAD_V = 3;
 constexpr float G_SCALE = 0.0625f, WK_SCALE = 16.0f;
 
 // Per-head operand image (dwords): A1: (tap t (25) x tile (2)) x lane (64) x 4; A2: product u
@@ -199,19 +209,39 @@ fwd16_k5_kernel(const Fwd5Args a)
 
             // ---- K side: 25 logits in two MFMA tiles
             float4_t accA = {0.0f, 0.0f, 0.0f, 0.0f}, accB = {0.0f, 0.0f, 0.0f, 0.0f};
+            uint4_t kd[AHEAD_K + 1], wa[AHEAD_K + 1], wb[AHEAD_K + 1];
+            auto read_k = [&](int t) {
+                const int x = t % (AHEAD_K + 1);
+                kd[x] = *(const uint4_t*)(kl + row0 + (t / K5) * HC * 64 + coff[t % K5]);
+                wa[x] = *(const uint4_t*)(wl + ((IMG_A1 + (t * 2) * 256) + lane * 4) * 4);
+                wb[x] = *(const uint4_t*)(wl + ((IMG_A1 + (t * 2 + 1) * 256) + lane * 4) * 4);
+            };
+#pragma unroll
+            for (int t = 0; t < AHEAD_K; ++t) read_k(t);
 #pragma unroll
             for (int t = 0; t < S5; ++t) {
-                const uint4_t kd = *(const uint4_t*)(kl + row0 + (t / K5) * HC * 64 + coff[t % K5]);
-                const half8_t A1a = __builtin_bit_cast(half8_t, *(const uint4_t*)(wl + ((IMG_A1 + (t * 2) * 256) + lane * 4) * 4));
-                const half8_t A1b = __builtin_bit_cast(half8_t, *(const uint4_t*)(wl + ((IMG_A1 + (t * 2 + 1) * 256) + lane * 4) * 4));
+                const int x = t % (AHEAD_K + 1);
+                if (t + AHEAD_K < S5) read_k(t + AHEAD_K);
                 uint4_t bb;
 #pragma unroll
-                for (int y = 0; y < 4; ++y) bb[y] = as_dword(qs[y] * as_half2(kd[y]));
+                for (int y = 0; y < 4; ++y) bb[y] = as_dword(qs[y] * as_half2(kd[x][y]));
                 const half8_t G = __builtin_bit_cast(half8_t, bb);
-                accA = __builtin_amdgcn_mfma_f32_16x16x32_f16(A1a, G, accA, 0, 0, 0);
-                accB = __builtin_amdgcn_mfma_f32_16x16x32_f16(A1b, G, accB, 0, 0, 0);
-                if (t % K5 == K5 - 1) __builtin_amdgcn_sched_barrier(0);     // one window row at a time
+                accA = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, wa[x]), G, accA, 0, 0, 0);
+                accB = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, wb[x]), G, accB, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            // what the first products of the V side read is under way during the softmax
+            uint4_t vd[2][4], wv[AHEAD_V + 1];
+            auto read_v = [&](int tq, int r) {
+                const int t = 4 * tq + r;
+                vd[tq & 1][r] = *(const uint4_t*)(vl + row0 + (t / K5) * HC * 64 + coff[t % K5]);
+            };
+            auto read_w = [&](int u) { wv[u % (AHEAD_V + 1)] = *(const uint4_t*)(wl + ((IMG_A2 + u * 256) + lane * 4) * 4); };
+#pragma unroll
+            for (int r = 0; r < 4; ++r) read_v(0, r);
+#pragma unroll
+            for (int u = 0; u < AHEAD_V; ++u) read_w(u);
+            __builtin_amdgcn_sched_barrier(0);
             // ---- softmax over the 25 shifts (7 per lane, 4 lane groups)
             float l[7], pr[7];
 #pragma unroll
@@ -237,45 +267,36 @@ fwd16_k5_kernel(const Fwd5Args a)
             b2[2] = pack_half(pr[4], pr[5]); b2[3] = pack_half(pr[6], 0.0f);
             const half8_t B2 = __builtin_bit_cast(half8_t, b2);
 
-            // ---- V side: product (e, tq) gives the weights g[c,t] of channel e for taps 4tq..4tq+3
+            // ---- V side: product u = 8 tq + e gives the weights g[c,t] of channel e for taps 4tq..4tq+3, products 48 and 49 those
+            // of tap 24 for channels 0..3 and 4..7
+            const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
             float o[8];
+            float4_t w[2];
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = 0.0f;
-#pragma unroll
-            for (int tq = 0; tq < 6; ++tq) {
-                const float4_t c4 = {0.0f, 0.0f, 0.0f, 0.0f};
-                uint4_t vd[4];
+            auto apply = [&](int u) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int t = 4 * tq + r;
-                    vd[r] = *(const uint4_t*)(vl + row0 + (t / K5) * HC * 64 + coff[t % K5]);
+                    const int e = u < 48 ? u & 7 : 4 * (u - 48) + r;
+                    const uint4_t x = vd[(u >> 3) & 1][u < 48 ? r : 0];
+                    o[e] = fmaf(w[u & 1][r], (float)as_half2(x[e >> 1])[e & 1], o[e]);
                 }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const half8_t A2 = __builtin_bit_cast(half8_t, *(const uint4_t*)(wl + ((IMG_A2 + (tq * 8 + e) * 256) + lane * 4) * 4));
-                    const float4_t w = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, B2, c4, 0, 0, 0);
+                for (int e = 0; e < 8; ++e)
+                    if (u < 48 ? e == (u & 7) : (e >> 2) == u - 48) asm volatile("" : "+v"(o[e]));   // (here, not all at the end)
+            };
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        o[e] = fmaf(w[r], (float)as_half2(vd[r][e >> 1])[e & 1], o[e]);
-                }
-#pragma unroll
-                for (int e = 0; e < 8; e += 2) asm volatile("" : "+v"(o[e]), "+v"(o[e + 1]));
+            for (int u = 0; u < 50; ++u) {
+                if (u + AHEAD_V < 50) read_w(u + AHEAD_V);
+                // the next quad of taps takes the place of the one before last, whose last use was in step 8 tq
+                if (u < 48 && (u & 7) >= 2 && (u & 7) < 6 && (u < 40 || (u & 7) == 2)) read_v((u >> 3) + 1, (u & 7) - 2);
+                w[u & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, wv[u % (AHEAD_V + 1)]), B2, zero4, 0, 0, 0);
+                asm volatile("" : "+v"(w[u & 1]));
+                __builtin_amdgcn_sched_barrier(0);
+                if (u > 0) apply(u - 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            {
-                const float4_t c24 = {0.0f, 0.0f, 0.0f, 0.0f};
-                const uint4_t vd24 = *(const uint4_t*)(vl + row0 + 4 * HC * 64 + coff[4]);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const half8_t A2 = __builtin_bit_cast(half8_t, *(const uint4_t*)(wl + ((IMG_A2 + (48 + j) * 256) + lane * 4) * 4));
-                    const float4_t w = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, B2, c24, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int e = 4 * j + r;
-                        o[e] = fmaf(w[r], (float)as_half2(vd24[e >> 1])[e & 1], o[e]);
-                    }
-                }
-            }
+            apply(49);
             if (valid) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
