@@ -122,13 +122,14 @@ pixel32_kernel(const PixelArgs a)
     }
 
     // what a step stages, on its way from memory: of a tensor y, of x (q or dO; null: none) and of the kernels w
-    f4 yr[NI][QPT], xr[CQ / CG];
-    float wr[AHEAD_W ? NW : 1];
+    struct Fetched { f4 y[NI][QPT], x[CQ / CG]; float w[AHEAD_W ? NW : 1]; };
+    Fetched shared_set;
     struct Source { const T* y; const T* x; const float* w; };
     auto source = [&](const void* yp, const void* xp, const float* w) {
         return Source{(const T*)yp + item, xp ? (const T*)xp + item : nullptr, w + (long)m * d * S * S};
     };
-    auto fetch = [&](const Source& src, int c0) {
+    auto fetch = [&](const Source& src, int c0, Fetched& to) {
+        auto &yr = to.y; auto &xr = to.x; auto &wr = to.w;
         const T *yb = src.y, *xb = src.x;
         const float* wb = src.w;
         // (a step stages the quads that the head still has: the eight of the shared form are 32 channels.  The forward's large
@@ -158,7 +159,12 @@ pixel32_kernel(const PixelArgs a)
     auto phase = [&](const Source& src, auto&& body) {
         const T *yb = src.y, *xb = src.x;
         const float* wb = src.w;
-        fetch(src, 0);
+        // The 3x3 backward spills seven registers with a set per phase, two with one set for all (float32, B=32, 56x56, C=64: 91 -> 86
+        // us); the 5x5 kernels spill none and take 1 to 2 % longer with one set (45x45, 13 planes: 111.7 -> 113.6 us).
+        Fetched own_set;
+        Fetched& to = KS == 5 ? own_set : shared_set;
+        auto &yr = to.y; auto &xr = to.x; auto &wr = to.w;
+        fetch(src, 0, to);
         for (int c0 = 0; c0 < d; c0 += 4 * CQ) {
             __syncthreads();                                // the step before is no longer read
 #pragma unroll
@@ -193,7 +199,7 @@ pixel32_kernel(const PixelArgs a)
                 for (int i = tid; i < min(CQ * 4, d - c0) * S; i += NT) wl[(i / S) * (S * S) + (i % S) * (S + 1)] += a.idw;
             }
             __syncthreads();
-            if (c0 + 4 * CQ < d) fetch(src, c0 + 4 * CQ);
+            if (c0 + 4 * CQ < d) fetch(src, c0 + 4 * CQ, to);
 #pragma unroll 1
             for (int u = cg; u < CQ && wave_live; u += CG) {
                 if (c0 + 4 * u >= d) break;
