@@ -312,8 +312,8 @@ template <typename T, bool VEC> struct Row4 {
 // next.  The totals take the registers that tiles of eight rows and, at 5x5, six taps per wave had.  A vector
 // instruction costs 5.6 cycles between the matrix instructions (by the counters), which is why the quad's
 // addresses are 24-bit arithmetic and only the waves that sum dbias do so.  MI355X, against one block per channel and shift
-// (slide_generic.hip) and a launch of its own for dbias: float32, 3x3, B=32, 56x56, C=64, 2 heads: 598 -> 61 us; bf16, 3x3, B=128, 28x28, C=128, 4 heads: 1854 -> 94 us.  With
-// running sums over the chunk they took 62 and 88 us.  Error of dwv against 64 bits (2-norm, two-branch; those kernels,
+// (slide_generic.hip) and a launch of its own for dbias: float32, 3x3, B=32, 56x56, C=64, 2 heads: 598 -> 61 us; bf16, 3x3,
+// B=128, 28x28, C=128, 4 heads: 1854 -> 94 us.  With running sums over the chunk they took 62 and 88 us.  Error of dwv against 64 bits (2-norm, two-branch; those kernels,
 // the running sums, these): 3x3 float32 as above 1.91, 2.47, 1.61e-7; 5x5 as above in float32 2.56, 4.11, 2.26e-7.
 template <typename T, int KS, bool VEC>
 __global__ void __launch_bounds__(dw_threads(KS), 2)

@@ -1,4 +1,4 @@
-// Shared by the kernels that do float32 work on the 16-bit matrix cores by splitting (slide_split.hip, slide_split_bwd.hip):
+// Shared by the kernels that do float32 work on the 16-bit matrix cores by splitting (slide_split.hip, slide_split_dw.hip):
 // bf16 activations, 5x5 window.
 //
 // A float32 weight is the sum of three bf16 values (8 significant bits each) exactly; a bf16 activation is one.  Their
