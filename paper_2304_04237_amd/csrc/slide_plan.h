@@ -170,8 +170,9 @@ inline bool pixel_few(int B, int heads, int H, int W, int d, int ks)
 }
 // dk/dv kernel: blocks of 256 pixels where those give every compute unit two and two fit its LDS (maps of a few columns
 // have tall runs with much halo), else 64 pixels whose channels four waves share.  5x5, B=32, 2 heads (measured with bf16
-// activations, which are on slide_split.hip now; the arithmetic is that of float32): 28x28 90 us, 40x40 163; from 41 columns on two quads per step leave no room for a second block, and the small form takes 489 us at
-// 45x45 and 721 at 56x56.  (One quad per step would fit up to 60 columns; it costs 116 us at 28x28.)
+// activations, which are on slide_split.hip now; the arithmetic is that of float32): 28x28 90 us, 40x40 163; from 41 columns
+// on two quads per step leave no room for a second block, and the small form takes 489 us at 45x45 and 721 at 56x56.  (One
+// quad per step would fit up to 60 columns; it costs 116 us at 28x28.)
 inline bool dkdv_few(int B, int heads, int H, int W, int ks, int element_bytes)
 {
     if (((long)H * W + 255) / 256 * heads * 2 * B < 512) return true;
