@@ -325,6 +325,11 @@ inline DwSplitPlan plan_dw_split(int B, int H, int W, int sets)
     t.chunks = (int)(n < t.tiles ? n : t.tiles);
     return t;
 }
+// where the vector of n elements that belongs at element e of a row of W (at least n) is read: inside the row, whatever e is
+constexpr int row_at(int e, int n, int W) { return e < 0 ? 0 : e < W - n ? e : W - n; }
+// the four vectors that hold elements x-2..x+9 of a row of whole fours: first element and length of vector i
+constexpr int fours_from(int i, int x) { return i == 0 ? x - 2 : x + 4 * (i - 1); }
+constexpr int fours_length(int i) { return i == 0 || i == 3 ? 2 : 4; }
 
 }  // namespace split
 }  // namespace slide

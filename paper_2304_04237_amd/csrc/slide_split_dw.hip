@@ -37,7 +37,7 @@ static_assert(Y_ROW % 16 == 9 && Y_COL == 5 && DW_LDS <= (int)CU_LDS_BYTES && DW
 template <bool NARROW>
 __device__ __forceinline__ u2 row4_load(const bf16_bits* row, int e0, int W)
 {
-    if (!NARROW) return *(const u2_any*)(row + min(max(e0, 0), W - 4));
+    if (!NARROW) return *(const u2_any*)(row + row_at(e0, 4, W));
     uint32_t e[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) e[i] = e0 + i >= 0 && e0 + i < W ? row[e0 + i] : 0u;
@@ -48,7 +48,7 @@ __device__ __forceinline__ u2 row4_cut(u2 raw, int e0, int W, bool row)
 {
     uint64_t v = (uint64_t)raw[1] << 32 | raw[0];
     if (!NARROW) {
-        const int past = e0 - min(max(e0, 0), W - 4);       // elements between where they belong and where they were loaded
+        const int past = e0 - row_at(e0, 4, W);       // elements between where they belong and where they were loaded
         v = past >= 0 ? v >> (16 * min(past, 3)) : v << (16 * min(-past, 3));
         row = row && past < 4 && past > -4;
     }
@@ -57,7 +57,7 @@ __device__ __forceinline__ u2 row4_cut(u2 raw, int e0, int W, bool row)
 template <bool NARROW>
 __device__ __forceinline__ f4 row4_load(const float* row, int e0, int W)
 {
-    if (!NARROW) return *(const f4_any*)(row + min(e0, W - 4));
+    if (!NARROW) return *(const f4_any*)(row + row_at(e0, 4, W));
     f4 v;
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] = e0 + i < W ? row[e0 + i] : 0.0f;
@@ -102,8 +102,9 @@ template <> struct Row12<4> {
     u2 v[2];
     __device__ __forceinline__ void load(const bf16_bits* row, int x, int W)
     {
-        a = *(const u1_any*)(row + max(x - 2, 0)); z = *(const u1_any*)(row + min(x + 8, W - 2));
-        v[0] = *(const u2_any*)(row + min(x, W - 4)); v[1] = *(const u2_any*)(row + min(x + 4, W - 4));
+        auto at = [&](int i) { return row + row_at(fours_from(i, x), fours_length(i), W); };
+        a = *(const u1_any*)at(0); z = *(const u1_any*)at(3);
+        v[0] = *(const u2_any*)at(1); v[1] = *(const u2_any*)at(2);
     }
     __device__ __forceinline__ void get(uint32_t (&d)[6], int x, int W, bool row) const
     {

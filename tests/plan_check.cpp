@@ -92,6 +92,27 @@ static void stacks(int B, int H, int W, int C)
     }
 }
 
+// the split kernel gradients' loads of a row lie inside it, for every column tile and every thread's piece of it, and hold
+// every element of the row that the piece wants
+static void rows(int W)
+{
+    for (int x0 = 0; x0 < W; x0 += split::DW_COLS)
+        for (int x = x0; x < x0 + split::DW_COLS; x += 8) {
+            if (W % 4 == 0)
+                for (int i = 0; i < 4; ++i) {
+                    const int e = split::fours_from(i, x), n = split::fours_length(i), at = split::row_at(e, n, W);
+                    CHECK(at >= 0 && at + n <= W, "vector %d of piece %d reads elements %d..%d of %d", i, x, at, at + n - 1, W);
+                    CHECK(at == e || e < 0 || e >= W, "vector %d of piece %d of %d is moved inside the row", i, x, W);
+                    CHECK(e == (i == 0 ? x - 2 : split::fours_from(i - 1, x) + split::fours_length(i - 1)), "vectors of piece %d", x);
+                }
+            if (W >= 4)
+                for (int e = x - 2; e < x + 10; e += 4) {
+                    const int at = split::row_at(e, 4, W);
+                    CHECK(at >= 0 && at + 4 <= W && (at == e || e < 0 || e > W - 4), "four elements at %d of %d read at %d", e, W, at);
+                }
+        }
+}
+
 // the half-precision tile kernels' heights: as good as those found by trying every height down to one row where the tallest
 // tiles leave compute units without one, down to half the tallest elsewhere
 static double tile_makespan(int H, long planes, int th, int nA, int nB, int hb, int tw, int r2, int waves)
@@ -152,6 +173,7 @@ int main()
             for (int B : {1, 2, 3, 64, 1000})
                 for (int C : {1, 96, 4096}) stacks(B, H, W, C);
     stacks(1, 1, (int)plane, 1); stacks(2, (int)plane, 1, 64); stacks(2, 5000, 6000, 512);
+    for (int W = 1; W <= 4096; ++W) rows(W);
     // planning is part of every call: it must stay a fraction of a microsecond
     const auto t0 = std::chrono::steady_clock::now();
     long sum = 0;
