@@ -22,6 +22,16 @@ typedef uint32_t u32_any __attribute__((aligned(2)));
 
 constexpr int KS = 5, S = 25, R = 2;
 
+// the three terms of w, largest first; an infinite or NaN w is its own first term
+__device__ __forceinline__ void split3(float w, float (&t)[3])
+{
+    t[0] = bf16_to_f32(f32_to_bf16(w));
+    const bool fin = __builtin_fabsf(t[0]) < INFINITY;
+    const float r1 = w - t[0];
+    t[1] = fin ? bf16_to_f32(f32_to_bf16(r1)) : 0.0f;
+    t[2] = fin ? r1 - t[1] : 0.0f;
+}
+
 // ---- operand image of the per-pixel kernels: per channel five left operands of 32 shifts (rows 25..31 zeros) by 16 slots,
 // 16 bytes per lane: lane = shift + 32 * half of the slots.  The slots of one lane are four dwords of two taps each:
 //   half h: d0 = row 2h, columns 0 1; d1 = row 2h, columns 2 3; d2, d3 = the same of row 2h + 1; d4 = row 4, columns 2h, 2h + 1;

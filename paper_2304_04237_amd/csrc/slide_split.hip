@@ -5,15 +5,6 @@
 namespace slide {
 namespace split {
 
-__device__ __forceinline__ void split3(float w, float (&t)[3])
-{
-    t[0] = bf16_to_f32(f32_to_bf16(w));
-    const bool fin = __builtin_fabsf(t[0]) < INFINITY;
-    const float r1 = w - t[0];
-    t[1] = fin ? bf16_to_f32(f32_to_bf16(r1)) : 0.0f;
-    t[2] = fin ? r1 - t[1] : 0.0f;
-}
-
 // Operand images of both kernels.  grid = (heads * channels in 32s, 2 tensors), block = 320; zeros past the head's channels.
 // d4: channels in fours.
 __global__ void __launch_bounds__(PX_CH)

@@ -8,7 +8,6 @@
 namespace slide {
 namespace split {
 
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef u2 u2_any __attribute__((aligned(2)));
 typedef f4 f4_any __attribute__((aligned(4)));
@@ -25,13 +24,16 @@ struct DwArgs {
 };
 
 constexpr int DW_NT = 512, DW_PXS = DW_ROWS * DW_COLS;      // threads, pixels of a tile
-// LDS in 16-byte pieces.  y: [channel][row][column of the tap][8 pixels], five of the four pieces of a row, so that the 25 taps of
-// a read lie in different banks (a row of the taps 25 pieces on, a column five).  x: [channel][8 pixels].  p: first and second
-// halves, [shift][8 pixels] and one more.
-constexpr int Y_COL = DW_COLS / 8 + 1, Y_ROW = KS * Y_COL, Y_CH = (DW_ROWS + 2 * R) * Y_ROW;
-constexpr int X_AT = 32 * Y_CH, X_CH = DW_PXS / 8, P_AT = X_AT + 32 * X_CH, P_S = DW_PXS / 8 + 1, F_AT = P_AT + 2 * S * P_S;
-constexpr int DW_LDS = (F_AT + 32 / 4 + 32 / 4) * 16;       // then the inverse scales of the shifts and of the channels
-static_assert(Y_ROW % 16 == 9 && Y_COL == 5 && DW_LDS <= (int)CU_LDS_BYTES && DW_ROWS == 4 && DW_COLS == 32, "");
+// LDS in 16-byte pieces.  y: [channel][row][column of the tap][8 pixels], five of the four pieces of a row, so that neighbouring taps'
+// reads lie in different banks (a column five pieces on, a row 25, a channel 205: 5, 25 and 125 modulo 16).  x: [channel][even
+// pixels, odd pixels] as floats.  p: first, second and third terms, [shift][8 pixels] and one more.
+constexpr int Y_COL = DW_COLS / 8 + 1, Y_ROW = KS * Y_COL, Y_CH = (DW_ROWS + 2 * R) * Y_ROW + 5;
+constexpr int X_AT = 32 * Y_CH, X_CH = 2 * DW_PXS / 8 + 4, P_AT = X_AT + 32 * X_CH, P_S = DW_PXS / 8 + 1;
+constexpr int DW_LDS = (P_AT + 3 * S * P_S) * 16;
+static_assert(Y_ROW % 16 == 9 && Y_COL == 5 && Y_CH % 16 == S * Y_COL % 16 && DW_LDS <= (int)CU_LDS_BYTES && DW_ROWS == 4 && DW_COLS == 32, "");
+// 25 taps of 32 channels are 25 tiles of 32 columns: three for each wave, one for all, which a wave has for one step of a pixel tile
+constexpr int DW_TILES = S, DW_OWN = DW_TILES / (DW_NT / 64);
+static_assert(DW_TILES == DW_OWN * (DW_NT / 64) + 1 && DW_PXS / 16 == DW_NT / 64, "");
 
 // elements e0..e0+3 of a row of W, zeros outside; NARROW: rows of less than four elements.  The load and, later, the rest.
 template <bool NARROW>
@@ -75,8 +77,8 @@ __device__ __forceinline__ f4 row4_cut(f4 v, int e0, int W, bool row)
     return row ? v : f4{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
-// (the dword by value: a bit cast of a vector's element takes the first one whatever the index)
-__device__ __forceinline__ h2 as_h2(uint32_t x) { return __builtin_bit_cast(h2, x); }
+// the upper halves of two floats: bf16 elements x, y, cut off
+__device__ __forceinline__ uint32_t upper_halves(float x, float y) { return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u); }
 
 // elements x-2..x+9 of a row as six dwords, zeros outside.  Rows of whole fours (4): every piece is all inside or all
 // outside, and x is a multiple of eight.
@@ -116,52 +118,30 @@ template <> struct Row12<4> {
     }
 };
 
-// largest of 16 neighbouring lanes, in all of them
-template <typename F>
-__device__ __forceinline__ uint32_t row_reduce(uint32_t x, F&& f)
+// sum of 16 neighbouring lanes, in all of them
+__device__ __forceinline__ float row_sum(float x)
 {
-    x = f(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false));     // row_ror:8, 4, 2, 1
-    x = f(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false));
-    x = f(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false));
-    return f(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false));
-}
-typedef int16_t s2 __attribute__((ext_vector_type(2)));
-// running maximum of the finite magnitudes in two bf16 elements, plus 0x80 (infinities and NaN become negative)
-__device__ __forceinline__ uint32_t max_finite(uint32_t m, uint32_t two)
-{
-    const s2 t = __builtin_bit_cast(s2, two & 0x7fff7fffu) + s2{0x80, 0x80};
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s2, m), t));
-}
-// the power of two that brings the largest of them into [2^6, 2^7), and its inverse
-__device__ __forceinline__ void scale_of_max(uint32_t m, float& up, float& down)
-{
-    m = row_reduce(m, [](uint32_t a, uint32_t b) {
-        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s2, a), __builtin_bit_cast(s2, b)));
-    });
-    const int top = max((int)(int16_t)m, (int)m >> 16) - 0x80, e = max(top >> 7, 12);       // (exponents below 12 are nothing)
-    up = __uint_as_float((uint32_t)min(254 + 6 - e, 254) << 23);
-    down = __uint_as_float((uint32_t)max(e - 6, 1) << 23);
-}
-// two scaled bf16 elements as halves
-__device__ __forceinline__ uint32_t to_halves(uint32_t two, float up)
-{
-    const h2 v = {(_Float16)(up * __uint_as_float(two << 16)), (_Float16)(up * __uint_as_float(two & 0xffff0000u))};
-    return __builtin_bit_cast(uint32_t, v);
+    auto turned = [&](auto by) { return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), decltype(by)::value, 0xf, 0xf, false)); };
+    x += turned(std::integral_constant<int, 0x128>{});      // row_ror:8, 4, 2, 1
+    x += turned(std::integral_constant<int, 0x124>{});
+    x += turned(std::integral_constant<int, 0x122>{});
+    return x + turned(std::integral_constant<int, 0x121>{});
 }
 
-// One block sums 32 channels of a head and side over its chunk of tiles of 4 rows and 32 columns.  A channel's products
-// q[p] k[p + off(t)] of 16 pixels are the right operand of a matrix instruction (25 of 32 columns are its taps), dl[s,p] the
-// left one (25 of 32 rows).  A product of two bf16 numbers is exactly the sum of two halves (one multiplication and one fused
-// multiply-add on pairs), dl is the sum of two halves to 23 bits, and three instructions take all but the product of the
-// two second terms (2^-24).  So that halves hold any value, a tile's channels and shifts are scaled by powers of two when they
-// go to LDS, and the tile's sums are added to float32 totals with their inverses: short sums, which is what float32 sums
-// over 10^5 pixels need anyway.  A wave has four channels, whose sums stay in its registers for the whole chunk.
+// One block sums 32 channels of a head and side over its chunk of tiles of 4 rows and 32 columns.  The products
+// q[p] k[p + off(t)] of 16 pixels, of 32 (channel, tap) pairs, are the right operand of a matrix instruction, dl[s,p] the left one
+// (25 of 32 rows).  A product of two bf16 numbers is exactly the sum of two bf16 numbers, dl of three, and five instructions take
+// all but the product of the last terms (2^-25 at most).  bf16 has the range of float32, so no number is too large or too
+// small beside others.  A tile's sums are added to float32 totals: short sums, which is what float32 sums over 10^5 pixels
+// need anyway.
 // k (or v) lies in LDS once for every column of the taps, moved by it, so that eight pixels of a tap are one aligned read;
 // a place whose pixel the map does not have holds zero, also where the neighbour that the tap reads is infinite.
-// Bound by the vector unit (half of the time: a tile's conversions, copies and scales are as much as its products) and the
-// matrix cores (a third), which take turns between a tile's two barriers.  MI355X, B=64, 28x28, C=128, 4 heads: 225 us with 4x4x1 float32
-// matrix instructions, 135 like this; 127 with the second terms' products in the same sums, but then dwv is 2.09e-7 from
-// 64 bits instead of 1.67e-7 (8 x 28x28; float32 instructions 1.87e-7).
+// Bound by the vector unit (ten instructions for the terms of two products) and the matrix cores, which overlap badly with two
+// waves per SIMD.  MI355X, B=64, 28x28, C=128, 4 heads: 225 us with 4x4x1 float32 matrix instructions, 135 like this; 130 with
+// halves scaled by the largest of a tile, which lose small numbers beside large ones.  Tried: what the first terms leave by
+// v_dot2_f32_bf16, two instructions less (151 us: it waits for the matrix cores); a channel's 25 taps to a matrix instruction
+// instead of 32 pairs (174 with the same); reads one step earlier (139: spills).
+// dwv is 1.43e-7 from 64 bits (8 x 28x28, 64 channels; float32 instructions 1.76e-7).
 // ROWS: 0 less than four columns, 1 any number, 4 whole fours
 template <int ROWS>
 __global__ void __launch_bounds__(DW_NT, 2)
@@ -170,7 +150,6 @@ dw_split_kernel(const DwArgs a)
     constexpr bool NARROW = ROWS == 0;
     extern __shared__ __align__(16) unsigned char smem[];
     u4* const lds = (u4*)smem;
-    float* const fs = (float*)(lds + F_AT);                 // inverse scales: shifts, channels
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, h = lane >> 5;
     const int H = a.H, W = a.W;
@@ -216,24 +195,14 @@ dw_split_kernel(const DwArgs a)
         uint32_t has[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) has[i] = x + 2 * i + 1 < W ? 0xffffffffu : x + 2 * i < W ? 0xffffu : 0u;
-        uint32_t yd[2][6], top = 0u;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int y = w.y0 + sr + 4 * i - R;
-            yv[i].get(yd[i], x, W, ch_live && y >= 0 && y < H);
-#pragma unroll
-            for (int j = 0; j < 6; ++j) top = max_finite(top, yd[i][j]);
-        }
-        float up, down, xup, xdown;
-        scale_of_max(top, up, down);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            u4* o = lds + grp * Y_CH + (sr + 4 * i) * Y_ROW + sb;
             uint32_t v[6], odd[5];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) v[j] = to_halves(yd[i][j], up);
+            yv[i].get(v, x, W, ch_live && y >= 0 && y < H);
 #pragma unroll
             for (int j = 0; j < 5; ++j) odd[j] = __builtin_amdgcn_alignbit(v[j + 1], v[j], 16);
+            u4* o = lds + grp * Y_CH + (sr + 4 * i) * Y_ROW + sb;
 #pragma unroll
             for (int c = 0; c < KS; ++c) {
                 u4 t;
@@ -244,59 +213,51 @@ dw_split_kernel(const DwArgs a)
         }
         const bool row = w.y0 + sr < H;
         u2 xd[2];
-        top = 0u;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            if (ROWS == 4) xd[j] = ch_live && row && x + 4 * j < W ? xv[j] : u2{0u, 0u};
-            else xd[j] = row4_cut<NARROW>(xv[j], x + 4 * j, W, ch_live && row);
-            top = max_finite(max_finite(top, xd[j][0]), xd[j][1]);
-        }
-        scale_of_max(top, xup, xdown);
-        lds[X_AT + grp * X_CH + (tid & 15)] = u4{to_halves(xd[0][0], xup), to_halves(xd[0][1], xup), to_halves(xd[1][0], xup), to_halves(xd[1][1], xup)};
-        if ((tid & 15) == 0) fs[32 + grp] = down * xdown;
-        // dl (or a)
         f4 pd[2];
-        float big = 0.0f, sum = 0.0f;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            if (ROWS == 4) pd[j] = s_live && row && x + 4 * j < W ? pv[j] : f4{0.0f, 0.0f, 0.0f, 0.0f};
-            else pd[j] = row4_cut<NARROW>(pv[j], x + 4 * j, W, s_live && row);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float mag = __builtin_fabsf(pd[j][e]);
-                big = fmaxf(big, mag < INFINITY ? mag : 0.0f);
-                sum += pd[j][e];
+            if (ROWS == 4) {
+                xd[j] = ch_live && row && x + 4 * j < W ? xv[j] : u2{0u, 0u};
+                pd[j] = s_live && row && x + 4 * j < W ? pv[j] : f4{0.0f, 0.0f, 0.0f, 0.0f};
+            } else {
+                xd[j] = row4_cut<NARROW>(xv[j], x + 4 * j, W, ch_live && row);
+                pd[j] = row4_cut<NARROW>(pv[j], x + 4 * j, W, s_live && row);
             }
         }
-        bsum += sum;
-        big = __uint_as_float(row_reduce(__float_as_uint(big), [](uint32_t p, uint32_t q) { return max(p, q); }));
-        scale_for(big, up, down);
-        u4 hi, lo;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint32_t h0, h1, l0, l1;
-            split2(pd[i / 2][2 * (i % 2)] * up, h0, l0);
-            split2(pd[i / 2][2 * (i % 2) + 1] * up, h1, l1);
-            hi[i] = h0 | h1 << 16; lo[i] = l0 | l1 << 16;
-        }
+        const u4 xs = {xd[0][0], xd[0][1], xd[1][0], xd[1][1]};
+        u4* const xo = lds + X_AT + grp * X_CH + (tid & 15);
+        xo[0] = xs << 16;
+        xo[DW_PXS / 8] = xs & 0xffff0000u;
         if (s_live) {
-            lds[P_AT + grp * P_S + (tid & 15)] = hi;
-            lds[P_AT + (S + grp) * P_S + (tid & 15)] = lo;
-            if ((tid & 15) == 0) fs[grp] = down;
+            u4 t[3];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float e0[3], e1[3];
+                split3(pd[i / 2][2 * (i % 2)], e0);
+                split3(pd[i / 2][2 * (i % 2) + 1], e1);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) t[j][i] = upper_halves(e0[j], e1[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j) lds[P_AT + (j * S + grp) * P_S + (tid & 15)] = t[j];
+        }
+        if (sums_bias) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) bsum += (pd[j][0] + pd[j][1]) + (pd[j][2] + pd[j][3]);
         }
     };
 
-    float total[4][13];
+    float total[DW_OWN + 1][13];
+    int y_at[DW_OWN + 1], x_at[DW_OWN + 1];                 // bytes
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int j = 0; j <= DW_OWN; ++j) {
 #pragma unroll
-        for (int i = 0; i < 13; ++i) total[e][i] = 0.0f;
-    const int t = min(col, S - 1), tr = t / KS, tc = t - tr * KS;
-    const u4* const yp = lds + wave * 4 * Y_CH + tr * Y_ROW + tc * Y_COL + h;
-    const u4* const xp = lds + X_AT + wave * 4 * X_CH + h;
-    const u4* const pp = lds + P_AT + t * P_S + h;
-    if (tid < 7) fs[S + tid] = 0.0f;
-
+        for (int i = 0; i < 13; ++i) total[j][i] = 0.0f;
+        const int n = 32 * (j < DW_OWN ? wave * DW_OWN + j : DW_TILES - 1) + col, c = n / S, t = n - c * S;
+        y_at[j] = (c * Y_CH + t / KS * Y_ROW + t % KS * Y_COL + h) * 16;
+        x_at[j] = (X_AT + c * X_CH + h) * 16;
+    }
+    const int p_at = (P_AT + min(col, S - 1) * P_S + h) * 16;
     const long t0 = a.tiles * chunk / a.chunks, t1 = a.tiles * (chunk + 1) / a.chunks;
     Where at{}, next{};
     if (t0 < t1) { next = locate(t0); fetch(next); }
@@ -306,62 +267,135 @@ dw_split_kernel(const DwArgs a)
         put(at);
         if (tile + 1 < t1) { next = locate(tile + 1); fetch(next); }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // (not for the loads in flight)
-        const int th = min(DW_ROWS, H - at.y0), nks = W - at.x0 > 16 ? 2 : 1;
-        // two channels at a time; the products with a second term have sums of their own, so that the others round once per 16
-        // pixels (added to them as they come: three times)
+        const int th = min(DW_ROWS, H - at.y0);
+        // A step is 16 pixels of a row.  While the matrix cores multiply the products of one column tile, the vector unit forms the
+        // next one's (fences for the scheduler deal them out: left alone, read, products and matrix instructions follow one
+        // another).  The products with a second term have sums of their own, so that the others
+        // round once per 16 pixels.
+        struct Raw { u4 y, even, odd; };
+        auto piece = [&](int at) { return *(const u4*)(smem + at); };
+        auto read = [&](int j, int r, int ks) -> Raw {
+            const int x = x_at[j] + (4 * r + 2 * ks) * 16;
+            return Raw{piece(y_at[j] + (r * Y_ROW + 2 * ks) * 16), piece(x), piece(x + DW_PXS * 2)};
+        };
+        auto read_p = [&](int j, int r, int ks) -> bf8 { return __builtin_bit_cast(bf8, piece(p_at + (j * S * P_S + 4 * r + 2 * ks) * 16)); };
+        // products of one dword's two pixels: first terms; what is left of them (`rest` holds it for the next call)
+        float rest[2];
+        auto form = [&](const Raw& raw, int i, u4& first, u4& second) {
+            if (i == 4) { second[3] = upper_halves(rest[0], rest[1]); return; }
+            const float g0 = __uint_as_float(raw.y[i] << 16) * __uint_as_float(raw.even[i]);
+            const float g1 = __uint_as_float(raw.y[i] & 0xffff0000u) * __uint_as_float(raw.odd[i]);
+            first[i] = upper_halves(g0, g1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i > 0) second[i - 1] = upper_halves(rest[0], rest[1]);
+            rest[0] = g0 - __uint_as_float(__float_as_uint(g0) & 0xffff0000u); rest[1] = g1 - __uint_as_float(__float_as_uint(g1) & 0xffff0000u);
+        };
+        auto mul = [&](const bf8& p, const u4& g, f16v& sum) { sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p, __builtin_bit_cast(bf8, g), sum, 0, 0, 0); };
+        auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+        auto add = [&](int j, const f16v& sum) {
 #pragma unroll
-        for (int e0 = 0; e0 < 4; e0 += 2) {
-            f16v acc[2] = {}, small[2] = {};
-#pragma unroll 1
-            for (int r = 0; r < th; ++r)
-#pragma unroll 1
-                for (int ks = 0; ks < nks; ++ks) {
-                    const u4 ph = pp[r * 4 + 2 * ks], pl = pp[S * P_S + r * 4 + 2 * ks];
-                    const h8 Ph = __builtin_bit_cast(h8, ph), Pl = __builtin_bit_cast(h8, pl);
+            for (int i = 0; i < 13; ++i) total[j][i] += sum[i];
+        };
+        auto rows = [&](auto nks) {
+            constexpr int NKS = decltype(nks)::value, NB = NKS == 2 ? 2 : 3;     // (a row's products come round to the buffer they began with)
+            bf8 P[3];
+            u4 G[NB], L[NB];
+            f16v acc[DW_OWN], small[DW_OWN];
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const u4 yd = yp[(e0 + e) * Y_CH + r * Y_ROW + 2 * ks], xd = xp[(e0 + e) * X_CH + r * 4 + 2 * ks];
-                        u4 g, gl;
+            for (int j = 0; j < 3; ++j) P[j] = read_p(j, 0, 0);
+            {
+                const Raw raw = read(0, 0, 0);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const h2 y2 = as_h2(yd[i]), x2 = as_h2(xd[i]);
-                            const h2 hi = y2 * x2;
-                            g[i] = __builtin_bit_cast(uint32_t, hi);
-                            gl[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(y2, x2, -hi));
-                        }
-                        const h8 G = __builtin_bit_cast(h8, g), L = __builtin_bit_cast(h8, gl);
-                        small[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ph, L, small[e], 0, 0, 0);
-                        small[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Pl, G, small[e], 0, 0, 0);
-                        acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ph, G, acc[e], 0, 0, 0);
-                    }
-                }
-            const float fc0 = fs[32 + wave * 4 + e0], fc1 = fs[33 + wave * 4 + e0];
-            asm volatile("" ::: "memory");                  // (the shifts' scales are read now and not kept over the loop)
-#pragma unroll
-            for (int i = 0; i < 13; ++i) {
-                const float fr = fs[8 * (i / 4) + 4 * h + i % 4];
-                total[e0][i] = fmaf(acc[0][i] + small[0][i], fr * fc0, total[e0][i]);
-                total[e0 + 1][i] = fmaf(acc[1][i] + small[1][i], fr * fc1, total[e0 + 1][i]);
+                for (int i = 0; i < 5; ++i) form(raw, i, G[0], L[0]);
             }
+            auto row = [&](auto at_row) {
+                constexpr int r = decltype(at_row)::value;
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+                    for (int j = 0; j < DW_OWN; ++j) {
+                        const bool first = r == 0 && ks == 0, last = j + 1 == DW_OWN;
+                        const int nr = ks + 1 < NKS ? r : r + 1, nk = ks + 1 < NKS ? ks + 1 : 0;       // the next step
+                        const bool more = !last || nr < DW_ROWS;
+                        const int now = (ks * DW_OWN + j) % NB, then = (now + 1) % NB;
+                        Raw raw;
+                        if (more) raw = last ? read(0, nr, nk) : read(j + 1, r, ks);
+                        auto next = [&](int i) { if (more) form(raw, i, G[then], L[then]); };
+                        auto next_p = [&](int i) { if (last && more) P[i] = read_p(i, nr, nk); };
+                        fence();
+                        if (first) small[j] = f16v{};
+                        mul(P[2], G[now], small[j]);
+                        next_p(2);
+                        mul(P[1], L[now], small[j]);
+                        fence();
+                        next(0);
+                        mul(P[1], G[now], small[j]);
+                        next_p(1);
+                        fence();
+                        next(1);
+                        mul(P[0], L[now], small[j]);
+                        fence();
+                        next(2);
+                        if (first) acc[j] = f16v{};
+                        mul(P[0], G[now], acc[j]);
+                        next_p(0);
+                        fence();
+                        next(3);
+                        next(4);
+                    }
+            };
+            row(std::integral_constant<int, 0>{});
+            if (th > 1) row(std::integral_constant<int, 1>{});
+            if (th > 2) row(std::integral_constant<int, 2>{});
+            if (th > 3) row(std::integral_constant<int, 3>{});
+#pragma unroll
+            for (int j = 0; j < DW_OWN; ++j) add(j, acc[j] + small[j]);
+        };
+        const bool two = W - at.x0 > 16;
+        if (two) rows(std::integral_constant<int, 2>{});
+        else rows(std::integral_constant<int, 1>{});
+        // the last column tile: each wave one step
+        const int r = two ? wave >> 1 : wave, ks = two ? wave & 1 : 0;
+        if (r < th) {
+            const Raw raw = read(DW_OWN, r, ks);
+            bf8 P[3];
+            u4 G, L;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) P[j] = read_p(j, r, ks);
+#pragma unroll
+            for (int i = 0; i < 5; ++i) form(raw, i, G, L);
+            f16v acc = {};
+            mul(P[2], G, acc);
+            mul(P[1], L, acc);
+            mul(P[1], G, acc);
+            mul(P[0], L, acc);
+            mul(P[0], G, acc);
+            add(DW_OWN, acc);
         }
     }
 
+    // the waves' sums of the last column tile: added in their order by the waves, a part of the rows each
+    __syncthreads();
+    float* const shared = (float*)smem;
+#pragma unroll
+    for (int i = 0; i < 13; ++i) shared[(wave * 13 + i) * 64 + lane] = total[DW_OWN][i];
+    __syncthreads();
     const float f = a.f[side];
-    if (col < S)
+    auto store = [&](int tile, int i, float v) {
+        const int n = 32 * tile + col, c = cb * 32 + n / S, t = n % S, s = 8 * (i / 4) + 4 * h + i % 4;
+        if (c < a.d && s < S) a.partial[((((long)chunk * 2 + side) * a.C + (long)m * a.d + c) * S + s) * S + t] = f * v;
+    };
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int c = cb * 32 + wave * 4 + e;
-            if (c >= a.d) continue;
-            float* out = a.partial + (((long)chunk * 2 + side) * a.C + (long)m * a.d + c) * S * S + t;
+    for (int j = 0; j < DW_OWN; ++j)
 #pragma unroll
-            for (int i = 0; i < 13; ++i) {
-                const int s = 8 * (i / 4) + 4 * h + i % 4;
-                if (s < S) out[s * S] = f * total[e][i];
-            }
-        }
+        for (int i = 0; i < 13; ++i) store(wave * DW_OWN + j, i, total[j][i]);
+    for (int i = wave; i < 13; i += DW_NT / 64) {
+        float v = 0.0f;
+        for (int w = 0; w < DW_NT / 64; ++w) v += shared[(w * 13 + i) * 64 + lane];
+        store(DW_TILES - 1, i, v);
+    }
     if (sums_bias) {
-        auto add = [](uint32_t p, uint32_t q) { return __float_as_uint(__uint_as_float(p) + __uint_as_float(q)); };
-        const float b = __uint_as_float(row_reduce(__float_as_uint(bsum), add));
+        const float b = row_sum(bsum);
         if (s_live && (tid & 15) == 0) a.bias_partial[((long)chunk * a.heads + m) * S + grp] = b;
     }
 }

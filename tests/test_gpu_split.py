@@ -70,6 +70,58 @@ def test_gradients_of_any_size(size):
         assert torch.equal(a.float() * factor, b.float()), name
 
 
+# An outlier of q and dO whose window of v is zero (no gradient of its logits), one of k and v that only pixels without dO
+# see, in one tile: every term with an outlier is zero, and what is left are sums of ordinary numbers.
+@pytest.mark.parametrize("power", [10, 14, 18, 24])
+def test_ordinary_terms_beside_outliers(power):
+    """Kernel gradients, entry by entry: a float32 sum rounds each of its steps by 2^-24 of what it has so far, at most the sum
+    of the magnitudes; an entry's value passes at most 25 taps, 32 channels, 25 shifts, 48 pixel steps."""
+    H, W, C, r = 4, 28, 32, 2
+    acts, wk, wv, bias, _ = _inputs((1, H, W, C, 1), 45)
+    dout, q, k, v = acts
+    big = 2.0 ** power
+    for t, j in ((q, 3), (dout, 3), (k, 20), (v, 20)):
+        t[0, :, 1, j] *= big
+    v[0, :, :, 1:6] = 0.0
+    dout[0, :, :, 18:23] = 0.0
+    grads = sa.slide_attn_bwd(*acts, wk, wv, bias, 1, 5)
+    d64, q64, k64, v64, wk64, wv64, b64 = (x.double().cpu() for x in (*acts, wk, wv, bias))
+
+    def windows(x):                                                 # [C, S, H * W]
+        return torch.nn.functional.unfold(x, 5, padding=r).view(C, 25, H * W)
+
+    kw, vw, qf, df = windows(k64), windows(v64), q64.view(C, -1), d64.view(C, -1)
+    flat = lambda w: w.view(C, 25, 25)
+    scale = C ** -0.5
+    a = torch.softmax(scale * torch.einsum("cp,cst,ctp->sp", qf, flat(wk64), kw) + b64.view(25, 1), 0)
+    da = torch.einsum("cp,cst,ctp->sp", df, flat(wv64), vw)
+    dl = a * (da - (a * da).sum(0))
+    size = a * (da.abs() + (a * da.abs()).sum(0))                   # what dl's own rounding is measured by
+    for name, got, p, mag, x, y, f in (("dwk", grads[3], dl, size, qf, kw, scale), ("dwv", grads[4], a, a, df, vw, 1.0)):
+        want = f * torch.einsum("sp,cp,ctp->cst", p, x, y)
+        bound = f * torch.einsum("sp,cp,ctp->cst", mag, x.abs(), y.abs()) * (25 + 32 + 25 + 48) * 2.0 ** -24
+        err = (got.double().cpu().view(C, 25, 25) - want).abs()
+        worst = float((err / bound.clamp_min(1e-300)).max())
+        print("2^%d %s: worst error / bound %.3g" % (power, name, worst), flush=True)
+        assert worst <= 1.0, "%s: %.3g times the bound" % (name, worst)
+
+
+@pytest.mark.parametrize("shape", [(4, 27, 27, 96, 3), (8, 28, 28, 64, 2), (2, 45, 45, 64, 1)])
+def test_kernel_gradients_round_no_more_than_float32_kernels(shape):
+    """The same numbers as float32 activations run on the float32 matrix instructions: the split kernels' results may be no further
+    from 64 bits than theirs."""
+    heads = shape[4]
+    acts, wk, wv, bias, _ = _inputs(shape, 47)
+    want = oracle.bwd(*[x.double().cpu().numpy() for x in (*acts, wk, wv, bias)], heads, 5)
+    error = []
+    for x in (acts, [t.float() for t in acts]):
+        grads = sa.slide_attn_bwd(*x, wk, wv, bias, heads, 5)
+        error.append([float(np.linalg.norm(g.double().cpu().numpy() - w) / np.linalg.norm(w)) for g, w in zip(grads[3:], want[3:])])
+    print(shape, "split", ["%.2e" % e for e in error[0]], "float32", ["%.2e" % e for e in error[1]], flush=True)
+    for name, split, plain in zip(NAMES[3:], *error):
+        assert split <= plain, name
+
+
 def test_infinite_key_reaches_its_window_only():
     shape = (1, 11, 17, 8, 1)
     acts, wk, wv, bias, _ = _inputs(shape, 42)
