@@ -701,7 +701,7 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
         else
             e = launch_bwd_dkdv_mfma(p, dout, q, wk, wv, attn_ws, dl_ws, half_ws, dk, dv, image_ws, st);
     } else if constexpr (SPLIT) {
-        e = launch_bwd_dkdv_split(p, split_ws, dk, dv, st);
+        e = launch_bwd_dkdv_split(p, attn_ws, dl_ws, split_ws, dk, dv, st);
     } else if constexpr (M32) {
         e = launch_bwd_dkdv_m32(p, dout, q, wk, wv, attn_ws, dl_ws, dk, dv, st);
     } else {

@@ -97,7 +97,8 @@ size_t split_dw_partial_floats(const Problem& p);
 hipError_t launch_bwd_dw_split(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
                                const float* attn_ws, const float* dl_ws, float* partial, float* dwk, float* dwv,
                                float* dbias, hipStream_t st);         // (slide_split_dw.hip) with the reduction
-hipError_t launch_bwd_dkdv_split(const Problem& p, const void* ws, void* dk, void* dv, hipStream_t st);
+hipError_t launch_bwd_dkdv_split(const Problem& p, const float* a_ws, const float* dl_ws, const void* ws, void* dk, void* dv,
+                                 hipStream_t st);
 
 // forward of heads narrower than 32 channels (bf16, ksize 3, H * W % 8 == 0) through the
 // matrix-core kernels on copies padded to 32 channels per head (p32: the padded problem)

@@ -5,7 +5,8 @@
 // products are exact in float32, and a matrix instruction adds sixteen of them and its accumulator with little more than one
 // rounding (measured, products of bf16 numbers, 16 terms and an accumulator of their size: 3.2e-8 from 64 bits, a chain of
 // float32 fused multiply-adds 3.8e-8; unbiased).  So a float32 contraction over K taps is a bf16 one over 3 K slots, at sixteen
-// times the float32 matrix rate per slot.
+// times the float32 matrix rate per slot.  bf16 has the range of float32; numbers below 2^-110 keep fewer bits, their last terms
+// being too small for it.
 #pragma once
 #include "slide_internal.h"
 #include "slide_device.h"
@@ -14,7 +15,6 @@ namespace slide {
 namespace split {
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
@@ -52,39 +52,34 @@ __host__ __device__ constexpr int px_term(int j, int w, int h)
 }
 __host__ __device__ constexpr int px_dword(int j, int w) { return j == 2 ? 4 + w % 2 : j == 4 ? (w < 2 ? 4 + w : 6) : w; }
 
-// ---- key and value gradients: a (or dl) times the kernels, both as two halves of 11 bits (22 bits with the second one's sign
-// 23).  So that halves hold any value, a pixel's are scaled by a power of two that brings the largest into [2^14, 2^15), and
-// a channel's weights likewise.
-// Record of a pixel, seven 16-byte pieces: A(h) first halves of shifts 4h..4h+3 and 8+4h..8+4h+3; B(h) first halves, then second
-// ones of shifts 16+4h..16+4h+3; C(h) second halves of A's; last: first, second, first half of shift 24, nothing, then the
-// inverse of the scale as a float.
-constexpr int REC_BYTES = 112, REC_A = 0, REC_B = 32, REC_C = 64, REC_LAST = 96;
-// Left operands: [column of the tap][row of the tap] of five instructions; lane = channel of 32 + 32 * half of the slots.
-// 0: second halves of the weights for A; 1: first for C; 2: second for B's first four, then last piece (half 0: first, first,
-// second); 3: first, first for B; 4: first for A.
+// ---- key and value gradients: a (or dl) times the kernels, both as three bf16 terms.  Of their nine products the six of first with
+// any, second with first and second, third with first terms are taken; the others are below 2^-26 of the whole.
+// A lane of half h holds a pixel's shifts 4h..4h+3, 8+4h..8+4h+3 (A), 16+4h..16+4h+3 (B), and 24.  Left operands: [column of the tap]
+// [row of the tap] of five pieces; lane = channel of 32 + 32 * half of the slots.  0, 1, 2: first, second and third terms for
+// A; 3: first and second for B; 4: third for B, then of shift 24 first, first, first, second (half 0), second, third (half 1),
+// for which the right operand has first, second, third, first and second, first terms.
 constexpr int KV_MM = 5, KV_TAP = KV_MM * 64, KV_IMG = S * KV_TAP;     // 16-byte pieces
-__host__ __device__ constexpr int kv_shift(int j, int h, int x)         // shift of slot x
+__host__ __device__ constexpr int kv_shift(int j, int h, int x)         // shift of slot x, -1: nothing
 {
-    return j == 2 ? (x < 4 ? 16 + 4 * h + x : h == 0 && x < 7 ? S - 1 : -1) : j == 3 ? 16 + 4 * h + x % 4 : 8 * (x / 4) + 4 * h + x % 4;
+    return j < 3 ? 8 * (x / 4) + 4 * h + x % 4 : j == 3 || x < 4 ? 16 + 4 * h + x % 4 : h == 0 || x < 6 ? S - 1 : -1;
 }
-__host__ __device__ constexpr bool kv_second(int j, int x) { return j == 0 || (j == 2 && (x < 4 || x == 6)); }
+__host__ __device__ constexpr int kv_term(int j, int h, int x)
+{
+    return j < 3 ? j : j == 3 ? x / 4 : x < 4 ? 2 : h == 0 ? (x == 7 ? 1 : 0) : x == 4 ? 1 : 2;
+}
 // channel of row r = 16 h + i of 32 as the matrix results have it: where a pixel's q (or dO) stands for it
 __host__ __device__ constexpr int kv_place(int c) { return ((c >> 2) & 1) * 16 + (c >> 3) * 4 + (c & 3); }
 
-// the power of two that brings x into [2^14, 2^15), and its inverse (1 for zero, infinities and NaN)
-__device__ __forceinline__ void scale_for(float x, float& up, float& down)
+// the three terms of two numbers, term by term (an infinite one gives NaN)
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split3_pair(float x, float y, uint32_t (&t)[3])
 {
-    const uint32_t e = (__float_as_uint(x) >> 23) & 0xffu, ex = max(e, 20u);
-    const bool plain = e == 0xffu || x == 0.0f;
-    up = plain ? 1.0f : __uint_as_float((268u - ex) << 23);
-    down = plain ? 1.0f : __uint_as_float((ex - 14u) << 23);
-}
-__device__ __forceinline__ uint32_t half_bits(_Float16 x) { return __builtin_bit_cast(uint16_t, x); }
-__device__ __forceinline__ void split2(float v, uint32_t& hi, uint32_t& lo)
-{
-    const _Float16 a = (_Float16)v;
-    hi = half_bits(a);
-    lo = half_bits((_Float16)(v - (float)a));
+    t[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x, y}, bf2));
+    const float x1 = x - __uint_as_float(t[0] << 16), y1 = y - __uint_as_float(t[0] & 0xffff0000u);
+    t[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{x1, y1}, bf2));
+    const float x2 = x1 - __uint_as_float(t[1] << 16), y2 = y1 - __uint_as_float(t[1] & 0xffff0000u);
+    t[2] = __builtin_amdgcn_perm(__float_as_uint(y2), __float_as_uint(x2), 0x07060302u);
 }
 
 // 16 bytes per lane from base + voff to LDS at lds_base + 16 * lane, without registers in flight; the wave waits for it by vmcnt

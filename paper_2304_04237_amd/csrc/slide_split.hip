@@ -5,30 +5,21 @@
 namespace slide {
 namespace split {
 
+constexpr int N = 13;                                       // shifts of a lane of half h: 4 h + 0..3 (+ 8, + 16), 24 (half 0)
+
 // Operand images of both kernels.  grid = (heads * channels in 32s, 2 tensors), block = 320; zeros past the head's channels.
 // d4: channels in fours.
 __global__ void __launch_bounds__(PX_CH)
 prep_split_kernel(const float* __restrict__ wk, const float* __restrict__ wv, u4* __restrict__ px_image, u4* __restrict__ kv_image,
-                  float* __restrict__ kv_factor, int d, int ncb, float idw)
+                  int d, int ncb, float idw)
 {
-    __shared__ float w[S * S], largest[PX_CH / 64];
+    __shared__ float w[S * S];
     const int m = blockIdx.x / (32 * ncb), c = blockIdx.x - m * (32 * ncb), heads = gridDim.x / (32 * ncb), tid = threadIdx.x;
     const int side = blockIdx.y, d4 = (d + 3) & ~3;
     const bool is = c < d;
     const float* src = (side ? wv : wk) + ((long)m * d + min(c, d - 1)) * S * S;
-    float mx = 0.0f;
-    for (int i = tid; i < S * S; i += PX_CH) {
-        const float x = is ? src[i] + (i % (S + 1) == 0 ? idw : 0.0f) : 0.0f;       // shift s reads tap s
-        w[i] = x;
-        mx = fmaxf(mx, __builtin_fabsf(x));
-    }
-    for (int i = 1; i < 64; i *= 2) mx = fmaxf(mx, __shfl_xor(mx, i));
-    if ((tid & 63) == 0) largest[tid >> 6] = mx;
+    for (int i = tid; i < S * S; i += PX_CH) w[i] = is ? src[i] + (i % (S + 1) == 0 ? idw : 0.0f) : 0.0f;       // shift s reads tap s
     __syncthreads();
-    for (int i = 0; i < PX_CH / 64; ++i) mx = fmaxf(mx, largest[i]);
-    float up, down;
-    scale_for(mx, up, down);
-    if (tid == 0) kv_factor[(side * heads + m) * 32 * ncb + c] = down;
     const int j = tid >> 6, lane = tid & 63, s = lane & 31, h = lane >> 5;
     if (c < d4) {
         u4 o = {0u, 0u, 0u, 0u};
@@ -44,36 +35,20 @@ prep_split_kernel(const float* __restrict__ wk, const float* __restrict__ wv, u4
         px_image[((long)(side * heads + m) * d4 + c) * PX_CH + tid] = o;
     }
     u4* kv = kv_image + ((long)(side * heads + m) * ncb + c / 32) * KV_IMG + c % 32;
-    for (int i = tid; i < S * KV_MM * 2; i += PX_CH) {      // (tap, instruction, half)
+    for (int i = tid; i < S * KV_MM * 2; i += PX_CH) {      // (tap, piece, half)
         const int hh = i & 1, jj = (i >> 1) % KV_MM, n = (i >> 1) / KV_MM, t = (n % KS) * KS + n / KS;
         u4 o = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             const int sh = kv_shift(jj, hh, x);
             if (sh < 0) continue;
-            uint32_t hi, lo;
-            split2(w[sh * S + t] * up, hi, lo);
-            o[x >> 1] |= (kv_second(jj, x) ? lo : hi) << (16 * (x & 1));
+            const int term = kv_term(jj, hh, x);
+            float e[3];
+            split3(w[sh * S + t], e);
+            o[x >> 1] |= (uint32_t)f32_to_bf16(term == 0 ? e[0] : term == 1 ? e[1] : e[2]) << (16 * (x & 1));
         }
         kv[(n * KV_MM + jj) * 64 + 32 * hh] = o;
     }
-}
-
-// a pixel's record of p[s] (slide_split.h), one half of the lanes' shifts each
-__device__ __forceinline__ void write_record(unsigned char* rec, int h, const float (&p)[13], float other_max, bool live)
-{
-    float mx = other_max;
-    float up, down;
-    scale_for(mx, up, down);
-    uint32_t hi[13], lo[13];
-#pragma unroll
-    for (int i = 0; i < 13; ++i) split2(p[i] * up, hi[i], lo[i]);
-    auto two = [](uint32_t x, uint32_t y) { return x | y << 16; };
-    if (!live) return;
-    *(u4*)(rec + REC_A + 16 * h) = u4{two(hi[0], hi[1]), two(hi[2], hi[3]), two(hi[4], hi[5]), two(hi[6], hi[7])};
-    *(u4*)(rec + REC_B + 16 * h) = u4{two(hi[8], hi[9]), two(hi[10], hi[11]), two(lo[8], lo[9]), two(lo[10], lo[11])};
-    *(u4*)(rec + REC_C + 16 * h) = u4{two(lo[0], lo[1]), two(lo[2], lo[3]), two(lo[4], lo[5]), two(lo[6], lo[7])};
-    if (h == 0) *(u4*)(rec + REC_LAST) = u4{two(hi[12], lo[12]), hi[12], __float_as_uint(down), 0u};
 }
 
 struct PixelArgs {
@@ -82,7 +57,6 @@ struct PixelArgs {
     const float* bias;
     bf16_bits* out;                                         // dq
     float* a_ws; float* dl_ws;                              // [B, heads, S, H, W]
-    unsigned char* rec[2];                                  // records of dl, a: [B, heads, H, W]
     unsigned char* xt[2];                                   // q, dO: [B, heads, H, W, channels in 32s] as kv_place has them
     int H, W, C, d;
     float scale;
@@ -268,7 +242,6 @@ pixel_split_kernel(const PixelArgs a)
             if (k + 1 < steps) put(k + 1);
         }
     };
-    constexpr int N = 13;                                   // sums of a lane: its rows of shifts 4 h + 0..3 (+ 8, + 16), shift 24 (half 0)
     // sum over channels of x[c] * window[c]: the channels of a step first, then the steps, with what an addition rounds away
     // carried on (dwv from 64 bits, 2 x 27x29, one head of 64: 1.72e-7 without, 1.52e-7 with it)
     auto contract = [&](int ph, float (&sum)[2][N]) {
@@ -298,30 +271,20 @@ pixel_split_kernel(const PixelArgs a)
         return __uint_as_float(sw[0]);
     };
 
-    auto record = [&](int which, bool there, long px, const float (&v)[N]) {
-        float mx = 0.0f, hi;
-#pragma unroll
-        for (int i = 0; i < N; ++i) mx = fmaxf(mx, __builtin_fabsf(v[i]));
-        const float lo = both(mx, hi);
-        write_record(a.rec[which] + px * REC_BYTES, h, v, fmaxf(lo, hi), there);
-    };
-    // where group g's column lies in a and dl, and in the records (worked out anew where they are stored: kept, they would cost the
-    // sums registers)
-    auto group_pixel = [&](int g, long& first, long& px) -> bool {
+    // where group g's column lies in a and dl (worked out anew where they are stored: kept, it would cost the sums registers)
+    auto group_pixel = [&](int g, long& first) -> bool {
         int n = wave * 64 + 32 * g + col, db, ti, tj;
         asm volatile("" : "+v"(n));
         const bool there = pixel(n, db, ti, tj);
-        first = ((long)(b0 + db) * (a.C / d) + m) * HW;
-        px = first + (long)ti * W + j0 + tj;
-        first = px + first * (S - 1);
+        first = ((long)(b0 + db) * (a.C / d) + m) * HW * S + (long)ti * W + j0 + tj;
         return there;
     };
     float p[2][N];
     contract(0, p);
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-        long first, px;
-        const bool there = group_pixel(g, first, px);
+        long first;
+        const bool there = group_pixel(g, first);
         float mx = -INFINITY, hi;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
@@ -344,15 +307,14 @@ pixel_split_kernel(const PixelArgs a)
             p[g][i] = fmaf(fmaf(-p[g][i], den, e), inv, p[g][i]);
             if (there && shift_of(i) < S) a.a_ws[first + (long)shift_of(i) * HW] = p[g][i];
         }
-        record(1, there, px, p[g]);
     }
     float da[2][N];
     contract(1, da);
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
         // (p waits in a_ws while da is summed: the sums need the registers)
-        long first, px;
-        const bool there = group_pixel(g, first, px);
+        long first;
+        const bool there = group_pixel(g, first);
         float dsum = 0.0f, hi;
 #pragma unroll
         for (int i = 0; i < N; ++i) p[g][i] = shift_of(i) < S ? a.a_ws[first + (long)min(shift_of(i), S - 1) * HW] : 0.0f;
@@ -365,7 +327,6 @@ pixel_split_kernel(const PixelArgs a)
             da[g][i] = shift_of(i) < S ? p[g][i] * (da[g][i] - dsum) : 0.0f;
             if (there && shift_of(i) < S) a.dl_ws[first + (long)shift_of(i) * HW] = da[g][i];
         }
-        record(0, there, px, da[g]);
     }
     bf16_bits* ob = a.out + head;
     float o[2], ov[4];
@@ -390,8 +351,9 @@ pixel_split_kernel(const PixelArgs a)
 //   dk[c,y] = scale * sum_t q[c, y - off(t)] * sum_s wk[c,s,t] dl[s, y - off(t)]
 //   dv[c,y] =         sum_t dO[c, y - off(t)] * sum_s wv[c,s,t] a[s, y - off(t)]
 struct DkdvArgs {
-    const u4* image; const float* factor;                   // [side][head][ncb][KV_IMG], [side][head][ncb * 32]
-    const unsigned char* rec[2]; const unsigned char* xt[2];
+    const u4* image;                                        // [side][head][ncb][KV_IMG]
+    const float* p[2];                                      // dl, a: [B, heads, S, H, W]
+    const unsigned char* xt[2];
     bf16_bits* out[2];                                      // dk, dv
     float f[2];                                             // logit scale, 1
     int H, W, C, d, heads, ncb;
@@ -402,11 +364,13 @@ constexpr int KV_WAVES = 8, KV_NT = 64 * KV_WAVES;
 
 // A block keeps the left operands of 32 channels of one head and side in LDS (125 KB); its waves are on their own.  A wave walks
 // down a band of rows of 32 columns (a column of any item to a lane: every matrix column is used whatever the map's
-// width).  For each source row and column of the taps it loads the lanes' records and q (or dO) at that column once, from
-// memory or cache, and forms the sums over the shifts for the five rows of the taps, 32 channels by 32 pixels by 80 slots in
-// five instructions each, which are multiplied with q and added to the five target rows that the source row reaches.
-// MI355X, B=64, 28x28, C=128, 4 heads: 330 us with 4x4x1 float32 matrix instructions, 85 like this (matrix cores busy 36 %
-// of the time).
+// width).  For each source row and column of the taps it loads the lanes' dl (or a) and q (or dO) at that column once, from
+// memory or cache, and forms the sums over the shifts for the five rows of the taps, 32 channels by 32 pixels by 160 slots in
+// ten instructions each, which are multiplied with q and added to the five target rows that the source row reaches.
+// MI355X, B=64, 28x28, C=128, 4 heads: 330 us with 4x4x1 float32 matrix instructions, 137 like this; 87 with two halves of
+// scaled numbers, five instructions, and records of them that the per-pixel kernel wrote in 10 us, which lose small numbers
+// beside large ones.  Tried: splitting the next source between the matrix instructions of the present one (165: the source
+// has less time to arrive); the pointers of the shifts worked out for each source (150).
 __global__ void __launch_bounds__(KV_NT, 2)
 dkdv_split_kernel(const DkdvArgs a)
 {
@@ -417,8 +381,6 @@ dkdv_split_kernel(const DkdvArgs a)
     const long HW = (long)H * W;
     const u4* image = a.image + ((long)(side * a.heads + m) * a.ncb + cb) * KV_IMG;
     for (int i = wave; i < S * KV_MM; i += KV_WAVES) load_to_lds(image + i * 64, lane * 16u, lds_offset(smem) + i * 1024u);
-    float* const factor = (float*)(smem + KV_IMG * 16);     // by place
-    if (tid < 32) factor[kv_place(tid)] = a.f[side] * a.factor[((side * a.heads + m) * a.ncb + cb) * 32 + tid];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
@@ -430,18 +392,20 @@ dkdv_split_kernel(const DkdvArgs a)
         const bool live = n_ < a.columns;
         const long n = live ? n_ : a.columns - 1, b = n / W;
         const int x = (int)(n - b * W);
-        const long px = (b * a.heads + m) * HW + x;
-        const unsigned char* const rec = a.rec[side] + px * REC_BYTES + 16 * h;
-        const unsigned char* const xt = a.xt[side] + px * xt_px + cb * 64 + 32 * h;
+        const long plane = b * a.heads + m;
+        const float* const given = a.p[side] + (plane * S + 4 * h) * HW + x;    // of shift 4 h on
+        const unsigned char* const xt = a.xt[side] + (plane * HW + x) * xt_px + cb * 64 + 32 * h;
 
-        // the record and q (or dO) of source row y, tap column cc
-        struct Source { u4 A, B, C, L, x0, x1; };
+        // dl (or a) and q (or dO) of source row y, tap column cc
+        struct Source { float p[N]; u4 x0, x1; };
         auto fetch = [&](int y, int cc) -> Source {
             const int xs = x + R - cc, at = min(max(y, 0), H - 1) * W + min(max(xs, 0), W - 1) - x;
-            const unsigned char *r = rec + (long)at * REC_BYTES, *t = xt + (long)at * xt_px;
+            const float* p = given + at;
+            const unsigned char* t = xt + (long)at * xt_px;
             Source s;
-            s.A = *(const u4*)(r + REC_A); s.B = *(const u4*)(r + REC_B); s.C = *(const u4*)(r + REC_C);
-            s.L = *(const u4*)(r + REC_LAST - 16 * h);
+#pragma unroll
+            for (int i = 0; i < N - 1; ++i) s.p[i] = p[(8 * (i / 4) + i % 4) * HW];
+            s.p[N - 1] = p[(S - 1 - 4 * h) * HW];
             s.x0 = *(const u4*)t; s.x1 = *(const u4*)(t + 16);
             return s;
         };
@@ -451,10 +415,10 @@ dkdv_split_kernel(const DkdvArgs a)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[p][i] = 0.0f;
         Source src[2];
-        h8 A[2][KV_MM];
+        bf8 A[2][KV_MM];
         src[0] = fetch(y0 - R, 0);
 #pragma unroll
-        for (int j = 0; j < KV_MM; ++j) A[0][j] = __builtin_bit_cast(h8, wl[j * 64]);
+        for (int j = 0; j < KV_MM; ++j) A[0][j] = __builtin_bit_cast(bf8, wl[j * 64]);
 #pragma unroll 1
         for (int ys = y0 - R; ys < y1 + R; ++ys) {
             const int lo = ys < 0 || ys >= H ? KS : max(0, y0 - ys + R), hi = min(KS - 1, y1 - 1 - ys + R);      // rows of the taps that reach the band
@@ -464,36 +428,40 @@ dkdv_split_kernel(const DkdvArgs a)
                 const Source& s = src[cc & 1];
                 const int xs = x + R - cc;
                 const bool in = xs >= 0 && xs < W;          // columns outside the map add nothing, whatever the record says
-                u4 rA, rB, rC;
-                u2 rL;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) { rA[w] = in ? s.A[w] : 0u; rB[w] = in ? s.B[w] : 0u; rC[w] = in ? s.C[w] : 0u; }
-                rL[0] = in ? s.L[0] : 0u; rL[1] = in ? s.L[1] : 0u;
-                const float down = __uint_as_float(s.L[2]);
                 float xv[16];
 #pragma unroll
                 for (int w = 0; w < 8; ++w) {
                     const uint32_t v = in ? (w < 4 ? s.x0[w] : s.x1[w - 4]) : 0u;
-                    xv[2 * w] = down * __uint_as_float(v << 16);
-                    xv[2 * w + 1] = down * __uint_as_float(v & 0xffff0000u);
+                    xv[2 * w] = __uint_as_float(v << 16);
+                    xv[2 * w + 1] = __uint_as_float(v & 0xffff0000u);
                 }
-                const u4 t2 = {rB[0], rB[1], rL[0], rL[1]};
-                const h8 BA = __builtin_bit_cast(h8, rA), BB = __builtin_bit_cast(h8, rB), BC = __builtin_bit_cast(h8, rC), B2 = __builtin_bit_cast(h8, t2);
+                float v[N];
+#pragma unroll
+                for (int i = 0; i < N; ++i) v[i] = in ? s.p[i] : 0.0f;
+                uint32_t t[(N + 1) / 2][3];
+#pragma unroll
+                for (int i = 0; i < N / 2; ++i) split3_pair(v[2 * i], v[2 * i + 1], t[i]);
+                split3_pair(v[N - 1], v[N - 1], t[N / 2]);
+                const uint32_t l12 = __builtin_amdgcn_perm(t[6][1], t[6][0], h ? 0x01000504u : 0x05040100u);    // second first, first second
+                const uint32_t l31 = h ? 0u : __builtin_amdgcn_perm(t[6][2], t[6][0], 0x01000504u);             // first third
+                auto quad = [&](int e0, int e1, int e) { return __builtin_bit_cast(bf8, u4{t[e0][e], t[e0 + 1][e], t[e1][e], t[e1 + 1][e]}); };
+                const bf8 A1 = quad(0, 2, 0), A2 = quad(0, 2, 1), A3 = quad(0, 2, 2), B1 = quad(4, 4, 0), B2 = quad(4, 4, 1), B3 = quad(4, 4, 2);
+                const bf8 B1L = __builtin_bit_cast(bf8, u4{t[4][0], t[5][0], l12, l31});
 #pragma unroll
                 for (int p = 0; p < KS; ++p) {
                     constexpr int LAST = S - 1;
                     const int idx = cc * KS + p, next = idx < LAST ? idx + 1 : 0;
 #pragma unroll
-                    for (int j = 0; j < KV_MM; ++j) A[(idx + 1) & 1][j] = __builtin_bit_cast(h8, wl[(next * KV_MM + j) * 64]);
+                    for (int j = 0; j < KV_MM; ++j) A[(idx + 1) & 1][j] = __builtin_bit_cast(bf8, wl[(next * KV_MM + j) * 64]);
                     __builtin_amdgcn_sched_barrier(0);      // (the next chain's operands are on their way, and no others)
                     if (p < lo || p > hi) continue;
-                    const h8 (&Ac)[KV_MM] = A[idx & 1];
+                    // small products first
+                    const bf8 (&w)[KV_MM] = A[idx & 1];
                     f16v c = {};
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[0], BA, c, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[1], BC, c, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[2], B2, c, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[3], BB, c, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ac[4], BA, c, 0, 0, 0);
+                    auto mul = [&](const bf8& kernels, const bf8& given) { c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kernels, given, c, 0, 0, 0); };
+                    mul(w[2], A1); mul(w[0], A3); mul(w[1], A2); mul(w[3], B3);
+                    mul(w[1], A1); mul(w[0], A2); mul(w[3], B2);
+                    mul(w[4], B1L); mul(w[3], B1); mul(w[0], A1);
 #pragma unroll
                     for (int i = 0; i < 16; ++i) acc[p][i] = fmaf(c[i], xv[i], acc[p][i]);
                     __builtin_amdgcn_sched_barrier(0);
@@ -509,7 +477,7 @@ dkdv_split_kernel(const DkdvArgs a)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     const int c = 8 * (i / 4) + i % 4;
-                    if (cb * 32 + 4 * h + c < a.d) o[(long)c * HW] = f32_to_bf16(acc[0][i] * factor[16 * h + i]);
+                    if (cb * 32 + 4 * h + c < a.d) o[(long)c * HW] = f32_to_bf16(acc[0][i] * a.f[side]);
                 }
             }
 #pragma unroll
@@ -525,7 +493,7 @@ dkdv_split_kernel(const DkdvArgs a)
 bool split_supported(const Problem& p) { return p.dtype == 1 && p.ksize == 5; }
 
 // what the kernels keep in the workspace behind a, dl and the partial sums
-struct SplitLayout { size_t px, kv, factor, rec[2], xt[2], bytes; int ncb; };
+struct SplitLayout { size_t px, kv, xt[2], bytes; int ncb; };
 static SplitLayout split_layout(const Problem& p)
 {
     using namespace split;
@@ -536,8 +504,6 @@ static SplitLayout split_layout(const Problem& p)
     auto take = [&](size_t bytes) { const size_t o = at; at += (bytes + 255) & ~(size_t)255; return o; };
     l.px = take((size_t)2 * p.heads * ((p.d() + 3) & ~3) * PX_CH * 16);
     l.kv = take((size_t)2 * p.heads * l.ncb * KV_IMG * 16);
-    l.factor = take((size_t)2 * p.heads * l.ncb * 32 * sizeof(float));
-    for (size_t& r : l.rec) r = take(pixels * REC_BYTES);
     for (size_t& x : l.xt) x = take(pixels * l.ncb * 64);
     l.bytes = at;
     return l;
@@ -550,7 +516,7 @@ hipError_t launch_split_prep(const Problem& p, const float* wk, const float* wv,
     const SplitLayout l = split_layout(p);
     char* base = (char*)ws;
     hipLaunchKernelGGL(prep_split_kernel, dim3((unsigned)(p.heads * l.ncb * 32), 2), dim3(PX_CH), 0, st, wk, wv, (u4*)(base + l.px),
-                       (u4*)(base + l.kv), (float*)(base + l.factor), p.d(), l.ncb, p.two_branch ? 1.0f : 0.0f);
+                       (u4*)(base + l.kv), p.d(), l.ncb, p.two_branch ? 1.0f : 0.0f);
     return hipGetLastError();
 }
 
@@ -564,7 +530,7 @@ hipError_t launch_bwd_pixel_split(const Problem& p, const void* dout, const void
     a.q = (const bf16_bits*)q; a.k = (const bf16_bits*)k; a.v = (const bf16_bits*)v; a.dout = (const bf16_bits*)dout;
     a.wk = (const u4*)(base + l.px); a.wv = a.wk + (size_t)p.heads * ((p.d() + 3) & ~3) * PX_CH;
     a.bias = bias; a.out = (bf16_bits*)dq; a.a_ws = a_ws; a.dl_ws = dl_ws;
-    for (int i = 0; i < 2; ++i) { a.rec[i] = base + l.rec[i]; a.xt[i] = base + l.xt[i]; }
+    for (int i = 0; i < 2; ++i) a.xt[i] = base + l.xt[i];
     a.H = p.H; a.W = p.W; a.C = p.C; a.d = p.d();
     a.scale = p.logit_scale();
     const int planes = stack_planes(p.B, p.H, p.W, p.C);
@@ -578,14 +544,15 @@ hipError_t launch_bwd_pixel_split(const Problem& p, const void* dout, const void
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_dkdv_split(const Problem& p, const void* ws, void* dk, void* dv, hipStream_t st)
+hipError_t launch_bwd_dkdv_split(const Problem& p, const float* a_ws, const float* dl_ws, const void* ws, void* dk, void* dv, hipStream_t st)
 {
     using namespace split;
     const SplitLayout l = split_layout(p);
     const unsigned char* base = (const unsigned char*)ws;
     DkdvArgs a{};
-    a.image = (const u4*)(base + l.kv); a.factor = (const float*)(base + l.factor);
-    for (int i = 0; i < 2; ++i) { a.rec[i] = base + l.rec[i]; a.xt[i] = base + l.xt[i]; }
+    a.image = (const u4*)(base + l.kv);
+    a.p[0] = dl_ws; a.p[1] = a_ws;
+    for (int i = 0; i < 2; ++i) a.xt[i] = base + l.xt[i];
     a.out[0] = (bf16_bits*)dk; a.out[1] = (bf16_bits*)dv;
     a.f[0] = p.logit_scale(); a.f[1] = 1.0f;
     a.H = p.H; a.W = p.W; a.C = p.C; a.d = p.d(); a.heads = p.heads; a.ncb = l.ncb;
@@ -595,7 +562,7 @@ hipError_t launch_bwd_dkdv_split(const Problem& p, const void* ws, void* dk, voi
     static LdsOptIn opt_in;
     hipError_t e = opt_in.ensure({(const void*)dkdv_split_kernel}, (int)CU_LDS_BYTES);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(dkdv_split_kernel, dim3((unsigned)t.blocks, (unsigned)(2 * l.ncb), (unsigned)p.heads), dim3(KV_NT), KV_IMG * 16 + 128, st, a);
+    hipLaunchKernelGGL(dkdv_split_kernel, dim3((unsigned)t.blocks, (unsigned)(2 * l.ncb), (unsigned)p.heads), dim3(KV_NT), KV_IMG * 16, st, a);
     return hipGetLastError();
 }
 

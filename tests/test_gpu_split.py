@@ -4,7 +4,7 @@ column strips, rows of odd length, heads that are no whole quad or block of 32 c
 column groups than waves, activations at odd addresses, activations far from one.
 
 Tolerances: the rounded gradients 2e-2 of max(1, largest entry) as everywhere; kernel and bias gradients 1e-5 of the
-largest entry, what float32 arithmetic gives (the split terms hold 23 or 24 bits)."""
+largest entry, what float32 arithmetic gives (the split terms hold all 24 bits)."""
 import pytest
 import torch
 
@@ -152,3 +152,37 @@ def test_gradients_are_added():
     sa.slide_attn_bwd_two_branch(*acts, *learned, bias, 2, 5, outputs=twice, accumulate=True)
     for name, a, b in list(zip(NAMES, twice, once))[3:]:
         assert torch.equal(a, b + 3.0), name
+
+
+def _rounds_once(name, got, want):
+    """bf16 results: 2^-9 of each entry, and float32 sums before."""
+    got = got.double().cpu().numpy()
+    err = float(np.linalg.norm(got - want) / np.linalg.norm(want))
+    print(name, "%.2e" % err, flush=True)
+    assert err <= 2.0 ** -9 + 1e-5, "%s: %.2e" % (name, err)
+
+
+@pytest.mark.parametrize("power", [20, 40, 80])
+def test_ordinary_weights_beside_large_ones(power):
+    """One tap in every channel's kernels is large, at a shift that the bias masks: its terms are zero, the others ordinary."""
+    acts, wk, wv, bias, _ = _inputs((2, 9, 13, 32, 1), 48)
+    for w in (wk, wv):
+        w.view(32, 25, 25)[:, 7, 11] = 2.0 ** power
+    bias.view(25)[7] = -1e30
+    grads = sa.slide_attn_bwd(*acts, wk, wv, bias, 1, 5)
+    want = oracle.bwd(*[x.double().cpu().numpy() for x in (*acts, wk, wv, bias)], 1, 5)
+    for i in (0, 1, 2):
+        _rounds_once(NAMES[i], grads[i], want[i])
+
+
+@pytest.mark.parametrize("lead", [10.0, 25.0, 60.0])
+def test_small_attention_beside_a_saturated_shift(lead):
+    """One shift takes nearly all attention and has no value kernel: dv is made of the others' attention, e^-lead each."""
+    acts, wk, wv, bias, _ = _inputs((2, 9, 13, 32, 1), 49)
+    for w in (wk, wv):
+        w.view(32, 25, 25)[:, 7] = 0.0
+    bias.view(25)[7] = lead
+    grads = sa.slide_attn_bwd(*acts, wk, wv, bias, 1, 5)
+    want = oracle.bwd(*[x.double().cpu().numpy() for x in (*acts, wk, wv, bias)], 1, 5)
+    for i in (0, 1, 2):
+        _rounds_once(NAMES[i], grads[i], want[i])
