@@ -75,6 +75,11 @@ int slide_reparam(const float* w_learned, float* w_merged, int C, int ksize, voi
  * sums that one launch leaves for the next; copies padded to 32 channels per head: several times the size of an
  * activation tensor).  slide_attn_bwd requires it; a forward call that brings less scratch than
  * this (but enough for the float32 kernels: none) is served by those instead.
+ * For bf16 problems with ksize 5 the figure of the backward includes, beside attention weights and logit gradients in float32
+ * (200 bytes per pixel and head) and partial sums, copies of q and dout with heads widened to whole 32s of channels (128 bytes per
+ * pixel, head and 32 channels) and the kernels' terms (18 KB per channel).  A call that brings less, but what the same
+ * sizes need as SLIDE_F32 (more, where there are few pixels), is served by the float32 matrix-core kernels: slide_attn_bwd and
+ * slide_attn_bwd_two_branch; slide_attn_bwd_nhwc with that, rounded up to 256 bytes, and seven activation tensors, rounded likewise.
  */
 size_t slide_attn_workspace_bytes(int B, int H, int W, int C, int heads, int ksize,
                                   int dtype, int backward);

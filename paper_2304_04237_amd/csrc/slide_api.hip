@@ -318,13 +318,15 @@ static int backward(const void* dout, const void* q, const void* k, const void* 
     Problem p{B, H, W, C, heads, ksize, dtype};
     p.two_branch = two_branch;
     p.accumulate = accumulate != 0;
+    auto needed = [&] { return nhwc ? slide::bwd_nhwc_workspace_bytes(p) : slide::bwd_generic_workspace_bytes(p); };
+    // bf16, 5x5: the split kernels need more than the float32 matrix-core ones, which serve a call that brings room for those alone
+    if (workspace_bytes < needed()) p.no_split = slide::split_supported(p);
+    if (!workspace || workspace_bytes < needed()) return SLIDE_ERR_WORKSPACE;
     if (nhwc) {
-        if (!workspace || workspace_bytes < slide::bwd_nhwc_workspace_bytes(p)) return SLIDE_ERR_WORKSPACE;
         hipError_t en = slide::launch_bwd_nhwc(p, dout, q, k, v, wk, wv, bias, dq, dk, dv, dwk, dwv,
                                                dbias, workspace, (hipStream_t)stream);
         return en == hipSuccess ? SLIDE_OK : SLIDE_ERR_HIP;
     }
-    if (!workspace || workspace_bytes < slide::bwd_generic_workspace_bytes(p)) return SLIDE_ERR_WORKSPACE;
     hipError_t e = slide::launch_bwd_generic(p, dout, q, k, v, wk, wv, bias, dq, dk, dv, dwk, dwv,
                                              dbias, workspace, (hipStream_t)stream);
     return e == hipSuccess ? SLIDE_OK : SLIDE_ERR_HIP;

@@ -674,7 +674,7 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
         const bool streaming = half_ws && fwd_ring_enabled() && bwd_pixel_ring_supported(p, aligned16({dq}));
         e = launch_bwd_pixel_mfma(p, dout, q, k, v, wk, wv, bias, dq, attn_ws, dl_ws, half_ws, image_ws,
                                   dkdv_image_ws, streaming, st);
-    } else if constexpr (SPLIT) {
+    } else if (SPLIT && split_supported(p)) {
         e = launch_split_prep(p, wk, wv, split_ws, st);
         if (e != hipSuccess) return e;
         e = launch_bwd_pixel_split(p, dout, q, k, v, bias, dq, attn_ws, dl_ws, split_ws, st);
@@ -700,7 +700,7 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
             e = launch_bwd_dkdv_ring(p, dout, q, attn_ws, dl_ws, dk, dv, image_ws, st);
         else
             e = launch_bwd_dkdv_mfma(p, dout, q, wk, wv, attn_ws, dl_ws, half_ws, dk, dv, image_ws, st);
-    } else if constexpr (SPLIT) {
+    } else if (SPLIT && split_supported(p)) {
         e = launch_bwd_dkdv_split(p, attn_ws, dl_ws, split_ws, dk, dv, st);
     } else if constexpr (M32) {
         e = launch_bwd_dkdv_m32(p, dout, q, wk, wv, attn_ws, dl_ws, dk, dv, st);
@@ -721,9 +721,8 @@ static hipError_t launch_bwd_t(const Problem& p, const void* dout, const void* q
         // kernel and bias gradients on the matrix cores
         return launch_bwd_dw_mfma(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
     }
-    if constexpr (SPLIT) {
-        return launch_bwd_dw_split(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
-    } else if constexpr (M32) {
+    if (SPLIT && split_supported(p)) return launch_bwd_dw_split(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
+    if constexpr (M32) {
         return launch_bwd_dw_m32(p, dout, q, k, v, attn_ws, dl_ws, partial, dwk, dwv, dbias, st);
     } else {
         const int n_chunks = dw_chunks(p);

@@ -20,6 +20,8 @@ struct Problem {
     int accumulate = 0;
     // activations are stored [B, H, W, C] (channels last) instead of [B, C, H, W]; backward: the streaming kernels only
     int nhwc = 0;
+    // backward, bf16, ksize 5: the workspace has room for the float32 matrix-core kernels, not for the split ones
+    int no_split = 0;
     // channels per head that the logit scale 1/sqrt(d) is taken from when the tensors handed to
     // the kernels carry heads padded to more channels (backward of heads narrower than 32); 0: d()
     int scale_dim = 0;

@@ -426,7 +426,7 @@ hipError_t launch_bwd_pixel_m32(const Problem& p, const void* dout, const void* 
     a.dout = dout; a.a_ws = a_ws; a.dl_ws = dl_ws;
     if (p.dtype == 0)
         return p.ksize == 3 ? m32::launch_pixel_t<float, 3, true>(p, a, st) : m32::launch_pixel_t<float, 5, true>(p, a, st);
-    return m32::launch_pixel_t<bf16_bits, 3, true>(p, a, st);           // (5x5: slide_split.hip)
+    return p.ksize == 3 ? m32::launch_pixel_t<bf16_bits, 3, true>(p, a, st) : m32::launch_pixel_t<bf16_bits, 5, true>(p, a, st);
 }
 
 }  // namespace slide

@@ -671,7 +671,7 @@ hipError_t launch_bwd_dkdv_m32(const Problem& p, const void* dout, const void* q
     a.idw = p.two_branch ? 1.0f : 0.0f;
     if (p.dtype == 0)
         return p.ksize == 3 ? m32::launch_dkdv_t<float, 3>(p, a, st) : m32::launch_dkdv_t<float, 5>(p, a, st);
-    return m32::launch_dkdv_t<bf16_bits, 3>(p, a, st);                  // (5x5: slide_split.hip)
+    return p.ksize == 3 ? m32::launch_dkdv_t<bf16_bits, 3>(p, a, st) : m32::launch_dkdv_t<bf16_bits, 5>(p, a, st);
 }
 
 hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, const void* k, const void* v,
@@ -692,7 +692,7 @@ hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, 
     hipError_t e;
 #define SLIDE_DW(T, KS) (vec ? m32::launch_dw<T, KS, true>(p, a, t, st) : m32::launch_dw<T, KS, false>(p, a, t, st))
     if (p.dtype == 0) e = p.ksize == 3 ? SLIDE_DW(float, 3) : SLIDE_DW(float, 5);
-    else              e = SLIDE_DW(bf16_bits, 3);               // (5x5: slide_split_dw.hip)
+    else              e = p.ksize == 3 ? SLIDE_DW(bf16_bits, 3) : SLIDE_DW(bf16_bits, 5);
 #undef SLIDE_DW
     if (e != hipSuccess) return e;
     return launch_bwd_dw_reduce(partial, dwk, dwv, side, t.chunks, a.bias_partial, dbias, p.heads * p.S(), p.accumulate, st);

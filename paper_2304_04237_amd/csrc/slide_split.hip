@@ -490,7 +490,7 @@ dkdv_split_kernel(const DkdvArgs a)
 
 }  // namespace split
 
-bool split_supported(const Problem& p) { return p.dtype == 1 && p.ksize == 5; }
+bool split_supported(const Problem& p) { return p.dtype == 1 && p.ksize == 5 && !p.no_split; }
 
 // what the kernels keep in the workspace behind a, dl and the partial sums
 struct SplitLayout { size_t px, kv, xt[2], bytes; int ncb; };

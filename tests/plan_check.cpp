@@ -42,6 +42,8 @@ static void gradients(int B, int H, int W, int C, int heads)
         for (int esz : {2, 4}) {
             const m32::DwPlan t = m32::plan_dw(B, H, W, C, heads, ks, esz);
             const m32::DwLoads most = m32::dw_loads(ks, esz, W % 4 == 0);
+            // (bf16 5x5 calls that bring the float32 kernels' workspace bring what those need for bf16)
+            CHECK(ks == 3 || t.chunks == m32::plan_dw(B, H, W, C, heads, ks, 4).chunks, "chunks of %dx%dx%d differ by type", B, H, W);
             const int R = ks / 2, S = ks * ks, NT = m32::dw_threads(ks), lanes = NT / m32::DW_CH;
             CHECK(t.TR >= 1 && t.TR <= m32::DW_MAX_ROWS && t.TC >= 4 && t.TC <= 32 && t.TC % 4 == 0 && (long)t.ntr * t.TR >= H && (t.ntr - 1) * t.TR < H &&
                   (long)t.ntc * t.TC >= W && (t.ntc - 1) * t.TC < W, "tiles of %dx%d, window %d", H, W, ks);

@@ -186,3 +186,27 @@ def test_small_attention_beside_a_saturated_shift(lead):
     want = oracle.bwd(*[x.double().cpu().numpy() for x in (*acts, wk, wv, bias)], 1, 5)
     for i in (0, 1, 2):
         _rounds_once(NAMES[i], grads[i], want[i])
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1, 3, 1), (40, 28, 28, 8, 1), (8, 45, 45, 8, 1), (30, 30, 37, 40, 2)])
+def test_smaller_workspace_runs_on_float32_kernels(shape):
+    """What the same sizes need in float32 is enough, as it was before the split kernels; a byte less is refused."""
+    B, H, W, C, heads = shape
+    acts, wk, wv, bias, _ = _inputs(shape, 50)
+    need = sa.slide_attn_workspace_bytes(B, H, W, C, heads, 5, torch.float32, True)
+    assert need < sa.slide_attn_workspace_bytes(B, H, W, C, heads, 5, torch.bfloat16, True)
+    workspace = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    grads = sa.slide_attn_bwd(*acts, wk, wv, bias, heads, 5, workspace=workspace)
+    _compare(grads, acts, wk, wv, bias, heads)
+    split = sa.slide_attn_bwd(*acts, wk, wv, bias, heads, 5)
+    assert shape[:3] == (1, 1, 1) or not torch.equal(grads[3], split[3])        # (other kernels, other roundings)
+    with pytest.raises(sa.SlideAttnError):
+        sa.slide_attn_bwd(*acts, wk, wv, bias, heads, 5, workspace=workspace[:-1])
+    tokens = [a.permute(0, 2, 3, 1).contiguous() for a in acts]
+    need = -need // 256 * -256 + 7 * (-2 * B * C * H * W // 256 * -256)
+    workspace = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    again = sa.slide_attn_bwd_nhwc(*tokens, wk, wv, bias, heads, 5, workspace=workspace)
+    for name, a, b in zip(NAMES, grads, again):
+        assert torch.equal(a, b if b.dim() != 4 or name in ("dwk", "dwv") else b.permute(0, 3, 1, 2)), name
+    with pytest.raises(sa.SlideAttnError):
+        sa.slide_attn_bwd_nhwc(*tokens, wk, wv, bias, heads, 5, workspace=workspace[:-1])
