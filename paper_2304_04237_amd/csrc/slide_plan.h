@@ -302,9 +302,8 @@ inline Bands plan_bands(int B, int H, int W, int sets)
     t.groups = ((long)B * W + 31) / 32;
     const long most = MAX_CU_PLANNED / sets > 1 ? MAX_CU_PLANNED / sets : 1;
     double best = 0;
-    for (int rows = 1; rows <= H && rows <= 512; ++rows) {
-        const int bands = (H + rows - 1) / rows;
-        if (rows > 1 && (H + rows - 2) / (rows - 1) == bands) continue;     // (as many bands as with fewer rows)
+    for (int rows = 1, bands; rows <= H && rows <= 512; rows = bands > 1 ? (H - 1) / (bands - 1) + 1 : H + 1) {     // (the lowest of each number of bands)
+        bands = (H + rows - 1) / rows;
         const long jobs = t.groups * bands, blocks = (jobs + 7) / 8 < most ? (jobs + 7) / 8 : most;
         const double cost = ((jobs + 8 * blocks - 1) / (8 * blocks)) * (rows + 1.5) * (blocks * sets > MAX_CU_PLANNED ? (double)(blocks * sets) / MAX_CU_PLANNED : 1.0);
         if (best == 0 || cost < best) { best = cost; t.rows = rows; t.blocks = (int)blocks; t.jobs = jobs; }

@@ -150,6 +150,33 @@ static void tiles(int B, int H, int W, int heads, int ks, int budget, int waves)
     CHECK(now <= best + 1e-6, "tiles of %dx%dx%d, %d heads: %g, there are some of %g", B, H, W, heads, now, best);
 }
 
+// bands: those that trying every height finds
+static void every_band(int B, int H, int W, int sets)
+{
+    const split::Bands t = split::plan_bands(B, H, W, sets);
+    const long most = std::max(MAX_CU_PLANNED / sets, 1);
+    double best = 0;
+    int low = 0;
+    for (int rows = 1; rows <= H && rows <= 512; ++rows) {
+        const long jobs = t.groups * ((H + rows - 1) / rows), blocks = std::min((jobs + 7) / 8, most);
+        const double cost = ((jobs + 8 * blocks - 1) / (8 * blocks)) * (rows + 1.5) * (blocks * sets > MAX_CU_PLANNED ? (double)(blocks * sets) / MAX_CU_PLANNED : 1.0);
+        if (best == 0 || cost < best) { best = cost; low = rows; }
+    }
+    CHECK(t.rows == low, "bands of %dx%dx%d, %d sets: %d rows, %d are best", B, H, W, sets, t.rows, low);
+}
+
+// microseconds of one call, at its fastest of several rounds
+template <typename F> static double microseconds(F&& plan)
+{
+    double best = 1e300;
+    for (int round = 0; round < 5; ++round) {
+        const auto t0 = std::chrono::steady_clock::now();
+        for (int i = 0; i < 20000; ++i) plan(i);
+        best = std::min(best, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() * 1e6 / 20000);
+    }
+    return best;
+}
+
 int main()
 {
     const long plane = 0x7fffffffL / 64;                    // the largest map the library accepts
@@ -182,6 +209,16 @@ int main()
     for (int i = 0; i < 100000; ++i) sum += t16::plan_tiles(1, 64, 9 + (i & 1), 2, 3, MAX_CU_PLANNED, 77000, 64, 64, 0, 0).th;
     const double us = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() * 10;
     CHECK(us < 4, "planning 64x9 takes %.2f us (%ld)", us, sum);
+    for (int H : {1, 2, 3, 5, 14, 28, 56, 97, 200, 513, 600, 1000})
+        for (int W : {1, 14, 28, 333})
+            for (int B : {1, 3, 64})
+                for (int sets : {2, 8, 66, 600}) every_band(B, H, W, sets);
+    for (int H : {28, 200, 600}) {
+        const double split_us = microseconds([&](int i) {
+            sum += split::plan_bands(64, H, 28 + (i & 1), 8).rows + split::plan_stack(64, H, 28 + (i & 1)).npx + split::plan_dw_split(64, H, 28 + (i & 1), 8).chunks;
+        });
+        CHECK(split_us < 1, "planning the split kernels for %d rows takes %.2f us (%ld)", H, split_us, sum);
+    }
     printf("%d wrong\n", wrong);
     return wrong != 0;
 }
