@@ -175,16 +175,6 @@ __device__ __forceinline__ void build_image(const float* __restrict__ wk, const 
 // ------------------------------------------------------------------ data movement of the streaming kernels
 typedef short short4_t __attribute__((ext_vector_type(4)));
 
-// 16 bytes per active lane from global memory (uniform base + per-lane byte offset) straight
-// into LDS: lane l's bytes land at lds_base + 16 l.  Counts as one vector-memory operation.
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %0"
-                 :: "s"(base), "v"(voff), "s"(lds_base) : "memory");
-}
-
 // the same with a full 64-bit address per lane
 __device__ __forceinline__ void load_to_lds_addr(const void* vaddr, uint32_t lds_base)
 {

@@ -82,14 +82,6 @@ __device__ __forceinline__ void split3_pair(float x, float y, uint32_t (&t)[3])
     t[2] = __builtin_amdgcn_perm(__float_as_uint(y2), __float_as_uint(x2), 0x07060302u);
 }
 
-// 16 bytes per lane from base + voff to LDS at lds_base + 16 * lane, without registers in flight; the wave waits for it by vmcnt
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %1, %0"
-                 :: "s"(base), "v"(voff), "s"(__builtin_amdgcn_readfirstlane(lds_base)) : "memory");
-}
 __device__ __forceinline__ uint32_t lds_offset(const void* p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p; }
 
 }  // namespace split
