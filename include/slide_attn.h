@@ -236,7 +236,8 @@ int slide_attn_fwd_variant(int B, int H, int W, int C, int heads, int ksize, int
 /*
  * The kernels slide_attn_bwd would run, for tests that must know which code ran: 0 = invalid
  * arguments, 10 = general kernels (float32 vector arithmetic; ksize 1 and 7), 11 = float32 matrix-core kernels
- * (ksize 3 and 5; bf16 with ksize 5: the same float32 work on the 16-bit matrix cores with split operands), 20 = tiled matrix-core kernels (bf16, d = 32, ksize 3; the kernel-gradient kernel also needs
+ * (ksize 3 and 5; bf16 with ksize 5: the same float32 work on the 16-bit matrix cores with split operands, where the
+ * workspace is what slide_attn_workspace_bytes says), 20 = tiled matrix-core kernels (bf16, d = 32, ksize 3; the kernel-gradient kernel also needs
  * W % 8 == 0, else the float32 matrix-core one takes that part); 1 is added where the key and value gradients run in the streaming
  * kernel (maps 32..56 columns wide, W % 8 == 0, bands and rings that fit the LDS), 2 where the
  * per-pixel part (attention recompute, logit and query gradients) does (maps 32..64 columns

@@ -88,7 +88,8 @@ hipError_t launch_bwd_dw_m32(const Problem& p, const void* dout, const void* q, 
                              const float* attn_ws, const float* dl_ws, float* partial, float* dwk, float* dwv,
                              float* dbias, hipStream_t st);
 
-// ---- float32 work on the 16-bit matrix cores by splitting (slide_split.hip): bf16, ksize 5, any head size and map.  ws: what the
+// ---- float32 work on the 16-bit matrix cores by splitting (slide_split.hip): bf16, ksize 5, any head size and map (the float32
+// matrix-core kernels serve these where the caller's workspace has no room for more: Problem::no_split).  ws: what the
 // kernels keep between them, split_workspace_bytes, 16-byte aligned; launch_split_prep comes first
 bool split_supported(const Problem& p);
 size_t split_workspace_bytes(const Problem& p);

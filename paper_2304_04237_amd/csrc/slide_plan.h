@@ -169,10 +169,10 @@ inline bool pixel_few(int B, int heads, int H, int W, int d, int ks)
     return sets * eights * (16 + 2.2 * (quads < 8 ? quads : 8)) < (3.5 + 8.7 * quads) * (large > MAX_CU_PLANNED ? 1.6 : 1.0);
 }
 // dk/dv kernel: blocks of 256 pixels where those give every compute unit two and two fit its LDS (maps of a few columns
-// have tall runs with much halo), else 64 pixels whose channels four waves share.  5x5, B=32, 2 heads (measured with bf16
-// activations, which are on slide_split.hip now; the arithmetic is that of float32): 28x28 90 us, 40x40 163; from 41 columns
-// on two quads per step leave no room for a second block, and the small form takes 489 us at 45x45 and 721 at 56x56.  (One
-// quad per step would fit up to 60 columns; it costs 116 us at 28x28.)
+// have tall runs with much halo), else 64 pixels whose channels four waves share.  5x5, float32, B=32,
+// 2 heads, large and small form: 28x28 125 and 220 us, 40x40 224 and 398.  From 41 columns on a second large block does not fit
+// (bf16 has twice the quads of half the size, the same bytes), and the small form runs although one large block per compute
+// unit is the faster one there too: 45x45 239 and 492, 56x56 388 and 730.  Maps of a few columns have not been compared.
 inline bool dkdv_few(int B, int heads, int H, int W, int ks, int element_bytes)
 {
     if (((long)H * W + 255) / 256 * heads * 2 * B < 512) return true;
@@ -226,8 +226,8 @@ inline DwPlan plan_dw(int B, int H, int W, int C, int heads, int ks, int element
                 S * TR * quads > dw_threads(ks) * most.p) continue;
             const int ntr = (H + TR - 1) / TR, ntc = (W + TC - 1) / TC, lr = H - (ntr - 1) * TR, lc = W - (ntc - 1) * TC;
             // a tile costs its rounds, the rows it stages and its barriers; a chunk has whole tiles, so the block with the most of
-            // them has up to one more than the average (5x5, 30 x 54x40, 3 heads, measured with bf16 while it ran here: 395 us with tiles of
-            // the fewest rounds and two blocks more than there is room for, 223 like this; 3x3, 1 x 200x333, 3 heads 73 and 66)
+            // them has up to one more than the average (bf16, 5x5, 30 x 54x40, 3 heads: 395 us with tiles of the fewest rounds and
+            // two blocks more than there is room for, 223 like this, and the same plan for float32; 3x3, 1 x 200x333, 3 heads 73 and 66)
             auto tile = [&](int th, int tw) { return rounds(th, tw) + 1.5 + 0.1 * (th + 2 * R); };
             const double plane = (ntr - 1.0) * ((ntc - 1.0) * tile(TR, TC) + tile(TR, lc)) + (ntc - 1.0) * tile(lr, TC) + tile(lr, lc);
             const long tiles = (long)B * ntr * ntc, chunks = n < tiles ? n : tiles;

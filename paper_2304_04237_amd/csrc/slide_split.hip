@@ -73,11 +73,12 @@ constexpr int PG = SPLIT_PX / 64, NT = SPLIT_PX;            // a wave has 64 pix
 // row are the dwords of every other pixel, one 16-byte read for four channels, and neighbouring lanes read neighbouring
 // places.  A step is fetched while the one before it is multiplied and goes to the other of two LDS buffers, the operand
 // image by loads that write LDS.
-// Bound by what is not overlapped: the matrix cores are busy for 38 % of the time, the vector unit for 45 %, LDS reads (36
-// of 16 bytes per step and wave) for 26 %, and two waves per SIMD do not hide each other's.  MI355X, B=64, 28x28, C=128, 4
-// heads: 386 us with 4x4x1 float32 matrix instructions, 137 like this.  Tried: a tile of 8 bytes per pixel, whose reads need no
-// moves (152 us: 4-byte reads at 8-byte steps meet in the banks), a wave per channel with its operands and eight groups' sums in
-// registers (191 us: spills), the vector work dealt between the matrix instructions by hand (176 us: spills).
+// Bound by what is not overlapped: the matrix cores are busy for 37 % of the time, the vector unit for 50 %, LDS reads (36
+// of 16 bytes per step and wave) for 25 %, and two waves per SIMD do not hide each other's.  MI355X, B=64, 28x28, C=128, 4
+// heads: 386 us with 4x4x1 float32 matrix instructions, 155 like this, 11 of them for the compensated sums.  Tried, without
+// those: a tile of 8 bytes per pixel, whose reads need no moves (137 -> 152 us: 4-byte reads at 8-byte steps meet in the
+// banks), a wave per channel with its operands and eight groups' sums in registers (191 us: spills), the vector work dealt between
+// the matrix instructions by hand (176 us: spills).
 // ONE: planes of one element, which have no dword to load.
 template <bool ONE>
 __global__ void __launch_bounds__(NT, 2)
@@ -369,8 +370,9 @@ constexpr int KV_WAVES = 8, KV_NT = 64 * KV_WAVES;
 // ten instructions each, which are multiplied with q and added to the five target rows that the source row reaches.
 // MI355X, B=64, 28x28, C=128, 4 heads: 330 us with 4x4x1 float32 matrix instructions, 137 like this; 87 with two halves of
 // scaled numbers, five instructions, and records of them that the per-pixel kernel wrote in 10 us, which lose small numbers
-// beside large ones.  Tried: splitting the next source between the matrix instructions of the present one (165: the source
-// has less time to arrive); the pointers of the shifts worked out for each source (150).
+// beside large ones.  The matrix cores are busy for 45 % of the time, the vector unit for 50 %, and the two hardly overlap: a wave's
+// ten instructions are a chain.  Tried: splitting the next source between the matrix instructions of the last two chains
+// (159 us: copies and spills), of the last chain (118 spills).
 __global__ void __launch_bounds__(KV_NT, 2)
 dkdv_split_kernel(const DkdvArgs a)
 {

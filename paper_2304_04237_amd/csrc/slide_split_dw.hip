@@ -1,5 +1,4 @@
-// Kernel and bias gradients of the 5x5 window for bf16 activations, float32 sums on the half-precision matrix cores with
-// split operands.
+// Kernel and bias gradients of the 5x5 window for bf16 activations, float32 sums on the bf16 matrix cores with split operands.
 //   dwk[c,s,t] = scale * sum over items and pixels y of dl[s,y] * q[c,y] * k[c, y + off(t)]
 //   dwv[c,s,t] =                                        a[s,y] * dO[c,y] * v[c, y + off(t)]
 //   dbias[s]   =                                       dl[s,y]
